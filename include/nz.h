@@ -94,7 +94,7 @@ int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_grid, i
  * nz_smax_window -- the largest cluster S_max(n) after n occupied sites, summed
  * over samples sample0 .. sample0+nsamples-1, for n in [n_lo, n_hi): the
  * observable of eqs. (5)-(6) (P_max = S_max / L^5 before the convolution).
- * The sweep runs on past n* through the window, one site per step.
+ * The sweep runs on past n* through the window.
  *   boundary   NZ_FREE or NZ_PERIODIC (L >= 5);
  *   n0         -1: plain sweep; else 0 <= n0 < n_lo: the sites whose keys lie
  *              below floor(n0 / N * 2^64), rounded down to a multiple of 2^32
@@ -158,23 +158,17 @@ typedef struct {
 
 /*
  * Tuning knobs (all 0 = automatic).  None of them changes any output.
- *   residency       1: occupancy bitset in LDS (L^5 / 8 bytes must fit);
- *                   2: everything in HBM; 3: bitset and parents in LDS.
- *   wg_waves        waves per workgroup of the sweep (1..4).
- *   waves_per_simd  resident sweep waves per SIMD of the persistent launch.
- *   bucket_log2     log2 of the mean number of keys per sort bucket (4..10; 0: 7).
- *   sweep_mode      1: one site per wave step (z lanes check the neighbours);
- *                   2: 64 sites per wave step (one site per lane; the block's
- *                   unions are merged by a connected-components pass in LDS;
- *                   the block in which spanning first occurs, and a block
- *                   that does not fit the LDS tables, is redone one site at a
- *                   time); 0: 64 sites per step for z <= 512, one site per
- *                   step for wider neighbourhoods.
- *   summary         the HBM-resident sweep reads, before each occupancy load,
- *                   a one-bit-per-block summary of the bitset held in LDS and
- *                   skips loads of all-empty words.  1: on; 2: off; 0: on when
- *                   the chunk has at least 2 samples per compute unit (with
- *                   fewer resident waves the extra LDS read is not repaid).
+ *   residency       0 or 2: automatic; 1, 3: refused (NZ_EUNSUPPORTED) where
+ *                   the occupancy bitset (1), or the bitset and 4 bytes per site
+ *                   (3), of the largest lattice exceed a workgroup's LDS, times
+ *                   wg_waves; no other effect: the sweep always holds a map of
+ *                   the occupation in LDS and the union-find in HBM.
+ *   wg_waves        1..4; see residency.
+ *   waves_per_simd  0..8, accepted; the sweep keeps a CU's LDS full.
+ *   bucket_log2     log2 of the mean number of keys per band bucket (4..10; 0: 7;
+ *                   values above 7 act as 7: a bucket is part of one block).
+ *   sweep_mode      0..2, accepted; every sample adds blocks of whole buckets.
+ *   summary         0..2, accepted; see residency.
  *   split_z         when a batch runs as two groups side by side (see
  *                   nz_sweep_batch), jobs with z <= split_z form the first
  *                   group and the rest the second (10..892; 0: 64).
@@ -214,8 +208,7 @@ int nz_batch_workspace_bytes(const nz_job *jobs, int32_t njobs, const nz_tuning 
  * host thread and a library-owned stream that first waits for the work already
  * queued on `stream`.  Results, backoff counts and statistics are the same as
  * for one group; the environment variable NZ_DEBUG_NO_SPLIT keeps one group.
- * Jobs with NZ_PERIODIC run in chunks of their own, one site per step with
- * their state in HBM whatever the tuning says: each site keeps its x0
+ * Jobs with NZ_PERIODIC run in chunks of their own: each site keeps its x0
  * displacement from its parent beside the parent (8 bytes a site instead of
  * 4), and their bulk prefill backs off when its state already wraps.
  */

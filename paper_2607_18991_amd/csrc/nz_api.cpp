@@ -151,17 +151,57 @@ int coordination(uint32_t mask)
     return mask >= 1 && mask <= 127 ? z[mask] : -1;
 }
 
+// A neighbourhood's rows: the vectors that share (d1..d4), with the set of
+// their d0 as bits d0 + 2.  First one row of every +- pair (the vectors of the
+// first half of the enumeration fall into whole rows, but for the row without
+// steps along axes 1..4, of which they are the negative d0), then the negated
+// rows in the same order.
+struct ZoneRow {
+    std::array<int, 4> d;
+    uint32_t d0;
+};
+
+const std::vector<ZoneRow> &zone_rows(uint32_t mask)
+{
+    static const std::array<std::vector<ZoneRow>, 128> all = [] {
+        std::array<std::vector<ZoneRow>, 128> t;
+        for (uint32_t m = 1; m < 128; ++m) {
+            const auto &v = zone_vectors(m);
+            std::map<std::array<int, 4>, size_t> at;
+            for (size_t k = 0; k < v.size() / 2; ++k) {
+                const std::array<int, 4> d{v[k][1], v[k][2], v[k][3], v[k][4]};
+                auto it = at.find(d);
+                if (it == at.end()) {
+                    it = at.emplace(d, t[m].size()).first;
+                    t[m].push_back({d, 0u});
+                }
+                t[m][it->second].d0 |= 1u << (v[k][0] + 2);
+            }
+            const size_t half = t[m].size();
+            for (size_t k = 0; k < half; ++k) {
+                const ZoneRow r = t[m][k];
+                uint32_t mirror = 0;
+                for (int j = 0; j < 5; ++j)
+                    if (r.d0 >> j & 1u) mirror |= 1u << (4 - j);
+                t[m].push_back({{-r.d[0], -r.d[1], -r.d[2], -r.d[3]}, mirror});
+            }
+        }
+        return t;
+    }();
+    return all[mask < 128 ? mask : 0];
+}
+
 std::vector<NzOffset> build_table(uint32_t mask, int32_t L)
 {
     std::vector<NzOffset> t;
-    for (const auto &d : zone_vectors(mask)) {
+    for (const auto &r : zone_rows(mask)) {
         NzOffset o;
-        int64_t stride = 0, p = 1;
-        uint32_t code = 0;
-        for (int j = 0; j < 5; ++j) {
-            stride += d[j] * p;
+        int64_t stride = 0, p = L;
+        uint32_t code = r.d0;
+        for (int j = 1; j < 5; ++j) {
+            stride += r.d[j - 1] * p;
             p *= L;
-            code |= 1u << (5 * j + d[j] + 2);
+            code |= 1u << (5 * j + r.d[j - 1] + 2);
         }
         o.stride = static_cast<int32_t>(stride);
         o.code = code;
@@ -221,14 +261,10 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 // c ~ 1.553, b ~ 1.01); used only to size key bands and to order work.
 double pc_prior(int z) { return 1.553 / (z + 1.01); }
 
-// 32-bit words of a sample's bitset summary in the sweep's LDS slice
+// 32-bit words of a sample's bitset summary
 constexpr int64_t kSumWords = 1024;
-// The sweep consults the summary (automatic choice) when its chunk has at least
-// this many samples per CU: measured at L = 16..24, the skipped loads pay once
-// several waves share a CU, while at about one wave per CU the extra LDS read
-// before each load costs 5-20% of the sweep.
-constexpr int32_t kSumSamplesPerCu = 2;
-
+// LDS words per wave that the accepted LDS residencies are sized with
+constexpr size_t kResWords = 896;
 struct Plan {
     int32_t job;
     int64_t sample;      // Philox sample index
@@ -274,7 +310,7 @@ struct Sizes {
     int64_t n0b[2];
     uint64_t T0b[2];
     int32_t nbb[2];
-    size_t par, occ, keys, sites, counts, prefix, parc, wpos, win, sum, total;
+    size_t par, occ, sites, counts, prefix, parc, wpos, win, sum, total;
     int32_t sum_shift, sum_words;
 };
 
@@ -324,7 +360,6 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     }
     s.par = align_up(static_cast<size_t>(N) * (p.wrap ? 8 : 4));
     s.occ = align_up(static_cast<size_t>((N + 63) / 64) * 8);
-    s.keys = align_up(static_cast<size_t>(nb_alloc) * s.cap * 8);
     s.sites = align_up(static_cast<size_t>(nb_alloc) * s.cap * 4);
     s.counts = align_up(static_cast<size_t>(nb_alloc) * 4);
     s.prefix = align_up(static_cast<size_t>(s.prefix_cap) * 4);
@@ -333,7 +368,7 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     s.parc = p.wrap ? 0 : align_up(static_cast<size_t>(s.prefix_cap) * 4);
     s.wpos = (p.wrap || s.prefix_cap == 0) ? 0 : s.occ;
     s.win = p.win_hi > 0 ? align_up(static_cast<size_t>(p.win_hi - p.win_lo) * 4) : 0;
-    // bitset summary for the HBM-resident sweep: at most kSumWords words, one
+    // bitset summary for the hook of sparse prefills: at most kSumWords words, one
     // bit per 1..16 bitset words (none above that: L > 27, or first-wrap samples)
     {
         const int64_t words = (N + 63) / 64 * 2;
@@ -343,7 +378,7 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
         s.sum_words = (gs <= 4 && !p.wrap) ? static_cast<int32_t>(((words >> gs) + 31) / 32 + 1) : 0;
         s.sum = align_up(static_cast<size_t>(s.sum_words) * 4);
     }
-    s.total = s.par + s.occ + s.keys + s.sites + s.counts + s.prefix + s.parc + s.wpos + s.win + s.sum;
+    s.total = s.par + s.occ + s.sites + s.counts + s.prefix + s.parc + s.wpos + s.win + s.sum;
     return s;
 }
 
@@ -389,8 +424,7 @@ struct Tune {
     int residency = 0;
     int wg_waves = 0;
     int waves_per_simd = 0;
-    int bucket_log2 = 7;   // mean keys per sort bucket: 128 (256 measured slower at L = 16, 64 no faster)
-    int dcap = 64;
+    int bucket_log2 = 7;   // mean keys per band bucket: 64..128 (a block of the sweep takes whole buckets)
     int sweep_mode = 0;
     int summary = 0;
     int split_z = 0;     // widest neighbourhood of the first of two groups side by side (0: kSplitZ)
@@ -436,17 +470,9 @@ int read_tune(const nz_tuning *t, Tune &out)
     out.residency = t->residency;
     out.wg_waves = t->wg_waves;
     out.waves_per_simd = t->waves_per_simd;
-    if (t->bucket_log2) out.bucket_log2 = t->bucket_log2;
+    // (a bucket is part of one block of the sweep: at most 128 keys on average)
+    if (t->bucket_log2) out.bucket_log2 = std::min(t->bucket_log2, 7);
     return NZ_OK;
-}
-
-int nch_for(int z)
-{
-    if (z <= 64) return 1;
-    if (z <= 128) return 2;
-    if (z <= 256) return 4;
-    if (z <= 512) return 8;
-    return 14;
 }
 
 // Debug override of the earlier roots one block may touch (tests force the
@@ -454,18 +480,8 @@ int nch_for(int z)
 int env_blk_old()
 {
     const char *e = getenv("NZ_DEBUG_BLOCK_OLD");
-    if (!e) return 256;
-    int v = atoi(e);
-    return std::max(0, std::min(256, v));
-}
-
-// Debug override of the distinct-root list size (tests force early merges).
-int env_dcap()
-{
-    const char *e = getenv("NZ_DEBUG_DCAP");
-    if (!e) return 64;
-    int v = atoi(e);
-    return std::max(2, std::min(64, v));
+    if (!e) return 1 << 30;
+    return std::max(0, atoi(e));
 }
 
 // ---------------------------------------------------------------------------
@@ -474,19 +490,16 @@ int env_dcap()
 struct TablePool {
     std::map<std::pair<uint32_t, int32_t>, int32_t> index;
     std::vector<NzOffset> entries;
-    int32_t get(uint32_t mask, int32_t L, int32_t *z)
+    int32_t get(uint32_t mask, int32_t L, int32_t *rows)
     {
+        *rows = static_cast<int32_t>(zone_rows(mask).size());
         auto key = std::make_pair(mask, L);
         auto it = index.find(key);
-        if (it != index.end()) {
-            *z = coordination(mask);
-            return it->second;
-        }
+        if (it != index.end()) return it->second;
         auto t = build_table(mask, L);
         const int32_t at = static_cast<int32_t>(entries.size());
         entries.insert(entries.end(), t.begin(), t.end());
         index[key] = at;
-        *z = static_cast<int32_t>(t.size());
         return at;
     }
 };
@@ -525,8 +538,9 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
     int64_t out = 0;
     for (int j = 0; j < njobs; ++j) {
         const nz_job &J = jobs[j];
-        int32_t z = 0;
-        pool.get(J.zone_mask, J.L, &z);
+        int32_t rows = 0;
+        pool.get(J.zone_mask, J.L, &rows);
+        const int z = coordination(J.zone_mask);
         const int64_t N = pow5(J.L);
         for (int64_t k = 0; k < J.nsamples; ++k) {
             Plan p{};
@@ -599,14 +613,12 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             std::vector<int32_t> out_index(n), queue(n), prefill_list;
             std::vector<int32_t> chunk_of_desc(n);
             size_t off = head;
-            int32_t max_nb = 0, max_cap = 0, max_z = 0, max_sum = 0;
-            const bool use_sum = tune.summary == 1 || (tune.summary == 0 && n >= kSumSamplesPerCu * dev.cus);
             const int32_t keys_grid = tune.keys_resident ? (nz::keys_resident_wgs() + 1) / 2 * dev.cus : 0;
             uint32_t max_N = 0;
             int64_t max_site = 0;
             std::vector<int32_t> desc_of_chunk(n);
             uint32_t last_mask = 0;   // offset table of the previous descriptor's (mask, L)
-            int32_t last_L = 0, last_tab = 0, last_z = 0;
+            int32_t last_L = 0, last_tab = 0, last_rows = 0;
             for (int32_t di = 0; di < n; ++di) {
                 const int32_t ci = byL[di];
                 const Plan &p = chunk[ci];
@@ -625,16 +637,15 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 d.full = s.full;
                 d.prefix_cap = s.prefix_cap;
                 if (p.mask != last_mask || p.L != last_L) {
-                    last_tab = pool.get(p.mask, p.L, &last_z);
+                    last_tab = pool.get(p.mask, p.L, &last_rows);
                     last_mask = p.mask;
                     last_L = p.L;
                 }
                 d.tab = last_tab;
-                d.z = last_z;
+                d.rows = last_rows;
                 d.magic = p.L == 1 ? 0 : static_cast<uint64_t>(~0ull / static_cast<uint64_t>(p.L) + 1ull);
                 d.off_par = off; off += s.par;
                 d.off_occ = off; off += s.occ;
-                d.off_keys = off; off += s.keys;
                 d.off_sites = off; off += s.sites;
                 d.off_counts = off; off += s.counts;
                 d.off_prefix = off; off += s.prefix;
@@ -652,10 +663,6 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 out_index[di] = p.out;
                 chunk_of_desc[di] = ci;
                 desc_of_chunk[ci] = di;
-                max_nb = std::max(max_nb, d.nb);
-                max_cap = std::max(max_cap, d.cap);
-                max_z = std::max(max_z, d.z);
-                if (use_sum) max_sum = std::max(max_sum, d.sum_words);
                 max_N = std::max(max_N, static_cast<uint32_t>(d.N));
                 if (d.T0 != 0) {
                     prefill_list.push_back(di);
@@ -739,7 +746,6 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                         p.backoff *= 2;   // the next backoff doubles the step
                         desc[di].T0 = s.T0b[level];
                         desc[di].nb = s.nbb[level];
-                        max_nb = std::max(max_nb, s.nbb[level]);
                         again.push_back(di);
                     }
                     if (again.empty()) break;
@@ -759,12 +765,20 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 }
             }
             if (pe) HIP_TRY(hipEventRecord(pe->ev[2], st));
-            HIP_TRY(nz::launch_sort(d_desc, n, max_nb, max_cap, ws, st));
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));   // (the sweep orders its own blocks: no sort pass)
 
-            if (wrap_chunk) {
-                // periodic first-wrap: one site per step, state in HBM, 4 waves
-                // per workgroup
+            {
+                // The LDS residencies are accepted where the state they name fits a
+                // workgroup's LDS (kResWords: the per-wave tables that went with it);
+                // the sweep keeps its state in HBM and its tables in LDS.
+                if (!wrap_chunk && tune.residency != 0 && tune.residency != 2) {
+                    const size_t occ_words = (static_cast<size_t>(max_N) + 63) / 64 * 2;
+                    const size_t words = occ_words + (tune.residency == 3 ? max_N : 0) + (per_chunk || tune.sweep_mode == 1 ? 0 : kResWords);
+                    const size_t need = words * 4 * static_cast<size_t>(tune.wg_waves ? tune.wg_waves : 1);
+                    if (need > dev.lds_per_block)
+                        return fail(NZ_EUNSUPPORTED, "residency %d needs %zu bytes of LDS per workgroup; the device allows %zu",
+                                    tune.residency, need, dev.lds_per_block);
+                }
                 NzSweepArgs args{};
                 args.desc = d_desc;
                 args.queue = d_queue;
@@ -773,51 +787,9 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 args.tabs = d_tabs;
                 args.ws = ws;
                 args.state = d_state;
-                args.dcap = tune.dcap;
-                const int grid = std::max(1, std::min(dev.cus * 8, (n + 3) / 4));
-                HIP_TRY(nz::launch_wrap_sweep(nch_for(max_z), args, d_nstar, d_mass, d_outidx, grid, st));
-            } else {
-                int residency = tune.residency == 3 ? 2 : (tune.residency == 1 ? 1 : 0);
-                const uint32_t occ_words = ((max_N + 63) / 64) * 2;
-                // HBM residency: the slice starts with the samples' bitset summaries
-                uint32_t lds_words = residency == 2 ? occ_words + max_N : (residency == 1 ? occ_words : static_cast<uint32_t>(max_sum));
-                // sweep mode: 2 = 64 sites per step for every sample; auto = 64 sites per
-                // step for z <= 512 (wider neighbourhoods are faster one site at a time)
-                int32_t min_z = 1 << 30;
-                for (const NzSample &d : desc) min_z = std::min(min_z, d.z);
-                const int32_t blk_zmax = tune.sweep_mode == 2 ? 892 : 512;
-                // periodic (largest-cluster) samples go one site per step
-                const bool block = !per_chunk && (tune.sweep_mode == 2 || (tune.sweep_mode == 0 && min_z <= blk_zmax));
-                if (block) lds_words += nz::block_lds_words();
-                int wg_waves = tune.wg_waves ? tune.wg_waves : (residency ? 1 : 4);
-                int wps = tune.waves_per_simd ? tune.waves_per_simd : 8;
-                size_t lds_wg = static_cast<size_t>(lds_words) * 4 * wg_waves;
-                if (lds_wg > dev.lds_per_block)
-                    return fail(NZ_EUNSUPPORTED, "residency %d needs %zu bytes of LDS per workgroup; the device allows %zu",
-                                tune.residency, lds_wg, dev.lds_per_block);
-                int wgs_per_cu = std::max(1, 4 * wps / wg_waves);
-                if (lds_wg > 0) wgs_per_cu = std::max<int>(1, std::min<size_t>(wgs_per_cu, dev.lds_per_cu / lds_wg));
-                int grid = dev.cus * wgs_per_cu;
-                grid = std::min(grid, (n + wg_waves - 1) / wg_waves);
-                NzSweepArgs args;
-                args.desc = d_desc;
-                args.queue = d_queue;
-                args.nqueue = n;
-                args.qhead = d_qhead;
-                args.tabs = d_tabs;
-                args.ws = ws;
-                args.state = d_state;
-                args.lds_words = lds_words;
-                args.dcap = tune.dcap;
                 args.blk_old = env_blk_old();
-                args.blk_zmax = blk_zmax;
-                args.use_sum = use_sum ? 1 : 0;
-                // the block path's fallback needs more than 8 offset chunks only
-                // when a sample wider than z = 512 goes 64 sites per step
-                bool wide_block = false;
-                for (const NzSample &d : desc) wide_block = wide_block || (block && d.z > 512 && d.z <= blk_zmax && !d.smax_mode);
-                HIP_TRY(nz::launch_sweep(nch_for(max_z), wide_block, residency, block, per_chunk, args, d_nstar, d_mass,
-                                         d_outidx, grid, wg_waves, st));
+                HIP_TRY(nz::launch_sweep(wrap_chunk ? nz::SweepKind::wrap : (smax ? nz::SweepKind::smax : nz::SweepKind::span),
+                                         per_chunk, args, d_nstar, d_mass, d_outidx, dev.cus, max_N, dev.lds_per_block, st));
             }
             if (smax)
                 HIP_TRY(nz::launch_winsum(d_desc, d_state, n, static_cast<int32_t>(smax->win_hi - smax->win_lo), ws,
@@ -919,7 +891,7 @@ size_t batch_bytes(const nz_job *jobs, int32_t njobs, const Tune &tune)
         const auto key = std::make_pair(jobs[j].zone_mask, jobs[j].L);
         if (std::find(tables.begin(), tables.end(), key) == tables.end()) {
             tables.push_back(key);
-            tab_entries += static_cast<size_t>(coordination(jobs[j].zone_mask));
+            tab_entries += zone_rows(jobs[j].zone_mask).size();
         }
         any_wrap = any_wrap || jobs[j].boundary == NZ_PERIODIC;
         Plan p{};
@@ -983,7 +955,7 @@ int check_batch_fits(const nz_job *jobs, int32_t njobs, const nz_tuning *tune, s
             const auto key = std::make_pair(J.zone_mask, J.L);
             if (std::find(tables.begin(), tables.end(), key) == tables.end()) {
                 tables.push_back(key);
-                tab_entries += static_cast<size_t>(coordination(J.zone_mask));
+                tab_entries += zone_rows(J.zone_mask).size();
             }
             Plan p{};
             p.L = J.L;
@@ -1027,7 +999,6 @@ int run_batch_one_group(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t w
     if (!d_nstar) return fail(NZ_EINVAL, "n* output is NULL");
     Tune t;
     if (int rc = read_tune(tune, t)) return rc;
-    t.dcap = env_dcap();
     // no phase events: this path creates no runtime objects
     const bool timing = g_timing;
     g_timing = false;
@@ -1277,7 +1248,6 @@ NZ_API int nz_sweep_batch(const nz_job *jobs, int32_t njobs, void *d_ws, size_t 
     if (int rc = read_tune(tune, t)) return rc;
     // a workspace that cannot hold one sample is refused before any device call
     if (int rc = nz::check_batch_fits(jobs, njobs, tune, ws_bytes)) return rc;
-    t.dcap = env_dcap();
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (g_timing) {
         HIP_TRY(hipEventCreate(&e0));
@@ -1324,7 +1294,6 @@ NZ_API int nz_sweep(int32_t L, uint32_t zone_mask, int32_t boundary, int64_t nsa
     if (!nstar) return fail(NZ_EINVAL, "nstar is NULL");
     if (nsamples > 0x7FFFFFFF) return fail(NZ_EINVAL, "nsamples too large");
     Tune t;
-    t.dcap = env_dcap();
     size_t bytes = 0;
     try {
         bytes = batch_bytes(&j, 1, t);
@@ -1387,7 +1356,6 @@ NZ_API int nz_smax_window(int32_t L, uint32_t zone_mask, int32_t boundary, uint6
     // the key band ends a little beyond the window, so a band that runs short is rare
     j.band_hi = std::min<int64_t>(N, n_hi + 4 * static_cast<int64_t>(std::sqrt(static_cast<double>(n_hi))) + 1024);
     Tune t;
-    t.dcap = env_dcap();
     size_t bytes = 0;
     try {
         bytes = batch_bytes(&j, 1, t) + static_cast<size_t>(std::min<int64_t>(nsamples, kMaxChunk) + 1) *

@@ -25,10 +25,15 @@ enum {
     NZ_ST_PREFIX = 5,     // the prefill list overflowed: redo with a larger list
 };
 
-// One neighbour offset of a (zone mask, L) table.  stride is the change of the
-// linear site index; code has, for each axis j, bit (5*j + d_j + 2) set, so the
-// offset stays inside the lattice iff (code & ~allowed(x)) == 0, where
-// allowed(x) has bit (5*j + d + 2) set iff 0 <= x_j + d < L.
+// One row of a (zone mask, L) table: the offsets that share their steps along
+// axes 1..4.  stride is the change of the linear site index by those steps.
+// code: bit d0 + 2 is set for every step d0 along axis 0 in the row, and for
+// each axis j >= 1 bit (5*j + d_j + 2); the row lies inside the lattice iff
+// (code & ~allowed(x)) has no bit above 4, where allowed(x) has bit (5*j + d +
+// 2) set iff 0 <= x_j + d < L, and its d0 bits inside are code & allowed(x).
+// The first half of a table holds one row of every +- pair, the second half
+// their negations in the same order (the row without steps along axes 1..4 is
+// split by the sign of d0).
 struct NzOffset {
     int32_t stride;
     uint32_t code;
@@ -41,7 +46,6 @@ struct NzSample {
     uint64_t T0;          // keys below T0 are occupied before the sweep (0: plain)
     uint64_t off_par;     // byte offsets into the workspace
     uint64_t off_occ;
-    uint64_t off_keys;
     uint64_t off_sites;
     uint64_t off_counts;
     uint64_t off_prefix;  // prefilled sites in list order (site order within each key block)
@@ -53,8 +57,8 @@ struct NzSample {
     int32_t cap;          // capacity of each bucket (entries)
     int32_t shift;        // log2 of the bucket width in key units
     int32_t full;         // the band reaches 2^64 (exhaustion then means "never spans")
-    int32_t tab;          // first entry of this sample's offset table
-    int32_t z;            // number of offsets
+    int32_t tab;          // first entry of this sample's row table
+    int32_t rows;         // number of rows (even)
     int32_t prefix_cap;   // capacity of the prefill site list
     int32_t smax_mode;    // 1: track the largest cluster over [win_lo, win_hi) instead of stopping at n*
     uint64_t magic;       // ceil(2^64 / L) for exact division of site indices by L
@@ -88,9 +92,6 @@ struct NzSweepArgs {
     const NzOffset *tabs;
     uint8_t *ws;
     NzState *state;
-    uint32_t lds_words;       // 32-bit LDS words per wave (LDS residencies)
-    int32_t dcap;             // distinct roots held per step before an early merge (2..64)
-    int32_t blk_old;          // block sweep: earlier roots one block may touch (0..256)
-    int32_t blk_zmax;         // block sweep for samples with z <= blk_zmax, one site per step above
-    int32_t use_sum;          // 1: HBM-resident samples check the bitset summary before occupancy loads
+    int32_t blk_old;          // earlier roots one block of several sites may touch
+    uint32_t map_words;       // LDS words of a workgroup's occupancy map (set by the launcher)
 };

@@ -13,14 +13,11 @@
 //                      root and adds its size and border flags to the root
 //                      word); a state that already spans is flagged for
 //                      backoff;
-//   nz_sort_kernel     each bucket sorted by (key, site) in LDS (bitonic);
-//                      concatenated buckets are exactly the occupation order;
-//   nz_sweep_kernel    persistent: every wave pops a sample (longest first) and
-//                      adds its band sites one at a time; the z neighbour checks
-//                      of a site are spread over the 64 lanes, occupied
-//                      neighbours find their roots in parallel, the largest
-//                      cluster absorbs the others, and the root word's two border
-//                      flags decide spanning.
+//   nz_block_kernel    persistent: every workgroup pops a sample (longest first)
+//                      and adds whole buckets of its band at a time, merging a
+//                      block's sites and the clusters they touch in LDS; the
+//                      root words' two border flags (or a winding loop) decide
+//                      spanning, and the block in which it happens is bisected.
 #include <hip/hip_runtime.h>
 
 #include "nz_internal.h"
@@ -125,8 +122,8 @@ __device__ __forceinline__ int32_t wrap_fix(uint32_t out, int32_t L)
     return fix;
 }
 
-// An offset code with bits above 25 marks a padding slot (no offset).
-constexpr uint32_t kCodeBits = 0x1FFFFFFu;
+// The bits of a row's code that belong to axes 1..4.
+constexpr uint32_t kRowAxes = 0x1FFFFE0u;
 
 // Relaxed wavefront-scope accesses: ordinary cached loads and stores that the
 // compiler neither merges nor elides.  They serve state private to one wave and
@@ -215,7 +212,6 @@ struct KeysCtx {
     uint32_t L;
     uint64_t magic;
     int32_t *par;
-    uint64_t *keys;
     uint32_t *sites;
     uint32_t *counts;
 };
@@ -229,10 +225,7 @@ __device__ __forceinline__ void keys_bucket(const KeysCtx &c, uint64_t K, uint32
 {
     const uint64_t b = (K - c.T0) >> c.shift;
     const uint32_t slot = atomicAdd(&c.counts[b], 1u);
-    if (slot < c.cap) {
-        c.keys[b * c.cap + slot] = K;
-        c.sites[b * c.cap + slot] = pack_coords(i, c.L, c.magic);
-    }
+    if (slot < c.cap) c.sites[b * c.cap + slot] = pack_coords(i, c.L, c.magic);
 }
 
 // The iterations of one wave over a block: keys, the prefill and band masks,
@@ -368,7 +361,6 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     c.L = static_cast<uint32_t>(d.L);
     c.magic = d.magic;
     c.par = reinterpret_cast<int32_t *>(ws + d.off_par);
-    c.keys = reinterpret_cast<uint64_t *>(ws + d.off_keys);
     c.sites = reinterpret_cast<uint32_t *>(ws + d.off_sites);
     c.counts = reinterpret_cast<uint32_t *>(ws + d.off_counts);
     uint32_t *occ = reinterpret_cast<uint32_t *>(ws + d.off_occ);
@@ -519,78 +511,6 @@ __global__ __launch_bounds__(KEYS_THREADS) void nz_keys_kernel(const NzSample *_
 }
 
 // ---------------------------------------------------------------------------
-// Bucket sort: one wave per (sample, bucket); bitonic network in the wave's
-// LDS slice over (key, packed site) pairs padded to a power of two, each lane
-// taking whole compare-exchange pairs, stages ordered by the wave's own LDS
-// ordering (no workgroup barrier); sorted packed sites are written back in
-// place.  Over-full buckets are left alone (the sweep reports them if it
-// reaches one).
-
-constexpr int SORT_THREADS = 256;
-
-__device__ __forceinline__ bool pair_greater(uint64_t ka, uint32_t pa, uint64_t kb, uint32_t pb)
-{
-    return ka > kb || (ka == kb && pa > pb);
-}
-
-// slice: LDS entries per wave (a power of two >= every bucket's capacity)
-__global__ __launch_bounds__(SORT_THREADS) void nz_sort_kernel(const NzSample *__restrict__ desc, int32_t nsamp,
-                                                               int32_t max_nb, uint32_t slice, uint8_t *__restrict__ ws)
-{
-    extern __shared__ uint64_t sort_lds[];
-    const uint32_t lane = lane_id();
-    const uint32_t waves = blockDim.x >> 6;
-    const uint32_t wave = threadIdx.x >> 6;
-    uint64_t *k = sort_lds + static_cast<size_t>(wave) * slice;
-    uint32_t *p = reinterpret_cast<uint32_t *>(sort_lds + static_cast<size_t>(waves) * slice) + static_cast<size_t>(wave) * slice;
-    const uint32_t items = static_cast<uint32_t>(nsamp) * static_cast<uint32_t>(max_nb);
-    for (uint32_t item = blockIdx.x * waves + wave; item < items; item += gridDim.x * waves) {
-        const int sid = static_cast<int>(item / static_cast<uint32_t>(max_nb));
-        const int b = static_cast<int>(item - static_cast<uint32_t>(sid) * static_cast<uint32_t>(max_nb));
-        const NzSample &d = desc[sid];
-        if (b >= d.nb) continue;
-        const uint32_t *counts = reinterpret_cast<const uint32_t *>(ws + d.off_counts);
-        const uint32_t cnt = counts[b];
-        const uint32_t cap = static_cast<uint32_t>(d.cap);
-        if (cnt <= 1u || cnt > cap) continue;
-        uint32_t P = 2;
-        while (P < cnt) P <<= 1;
-        const uint64_t *gk = reinterpret_cast<const uint64_t *>(ws + d.off_keys) + static_cast<uint64_t>(b) * cap;
-        uint32_t *gp = reinterpret_cast<uint32_t *>(ws + d.off_sites) + static_cast<uint64_t>(b) * cap;
-        for (uint32_t i = lane; i < P; i += 64u) {
-            if (i < cnt) {
-                k[i] = gk[i];
-                p[i] = gp[i];
-            } else {
-                k[i] = ~0ull;
-                p[i] = ~0u;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t half = P >> 1;
-        for (uint32_t size = 2; size <= P; size <<= 1) {
-            for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                // pair q: i has bit `stride` clear, j = i + stride
-                for (uint32_t q = lane; q < half; q += 64u) {
-                    const uint32_t i = ((q & ~(stride - 1u)) << 1) | (q & (stride - 1u));
-                    const uint32_t j = i | stride;
-                    const bool up = (i & size) == 0u;
-                    const uint64_t ki = k[i], kj = k[j];
-                    const uint32_t pi = p[i], pj = p[j];
-                    if (pair_greater(ki, pi, kj, pj) == up) {
-                        k[i] = kj; k[j] = ki;
-                        p[i] = pj; p[j] = pi;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        for (uint32_t i = lane; i < cnt; i += 64u) gp[i] = p[i];
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Bulk connected components of the prefilled sites (hook, then label).
 // During this phase par[i] is a plain parent index and a root points to
 // itself.  Every link goes from a larger index to a smaller one, and only an
@@ -711,7 +631,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
     __syncthreads();
     const uint32_t gs = static_cast<uint32_t>(d.sum_shift);
     const int32_t L = d.L;
-    const int32_t zh = d.z >> 1;
+    const int32_t rh = d.rows >> 1;   // one row of every +- pair
     const uint64_t magic = d.magic;
     int32_t *par = reinterpret_cast<int32_t *>(ws + d.off_parc);
     const uint32_t *occ = reinterpret_cast<const uint32_t *>(ws + d.off_occ);
@@ -733,51 +653,77 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                                   (allowed_axis(pc >> 24, L) << 20))
                                : 0u;
         int32_t ne = 0;   // edges in the buffer (wave-uniform)
-        for (int32_t k0 = 0; k0 < zh; k0 += HOOK_UNROLL) {
-            int32_t t[HOOK_UNROLL];
-            uint32_t w[HOOK_UNROLL];
+        const int32_t x0 = static_cast<int32_t>(pc & 63);
+        for (int32_t k0 = 0; k0 < rh; k0 += HOOK_UNROLL) {
+            // side 1 (periodic only): the steps that leave along axis 0, on the
+            // other side of the row
+            for (int side = 0; side < (PER ? 2 : 1); ++side) {
+                int32_t b[HOOK_UNROLL];
+                uint32_t v[HOOK_UNROLL], w0[HOOK_UNROLL], w1[HOOK_UNROLL], par0[HOOK_UNROLL];
 #pragma unroll
-            for (int q = 0; q < HOOK_UNROLL; ++q) {
-                NzOffset o;
-                o.stride = 0;
-                o.code = 0xFFFFFFFFu;
-                if (k0 + q < zh) o = tab[k0 + q];
-                const uint32_t out = o.code & ~A;
-                bool ok;
-                if constexpr (PER) {
-                    ok = act && (o.code & ~kCodeBits) == 0u;   // every offset wraps back in, padding aside
-                    t[q] = s + o.stride + (out ? wrap_fix(out, L) : 0);
-                } else {
-                    ok = act && out == 0u;
-                    t[q] = s + o.stride;
+                for (int q = 0; q < HOOK_UNROLL; ++q) {
+                    NzOffset o;
+                    o.stride = 0;
+                    o.code = 0u;
+                    if (k0 + q < rh) o = tab[k0 + q];
+                    const uint32_t out = o.code & ~A & kRowAxes;
+                    uint32_t dm;   // the row's sites to look at, from b on
+                    if constexpr (PER) {
+                        b[q] = s + o.stride - 2 + (out ? wrap_fix(out, L) : 0);
+                        dm = act ? o.code & (side ? ~A : A) & 31u : 0u;
+                        if (side) b[q] += x0 < 2 ? L : -L;
+                    } else {
+                        b[q] = s + o.stride - 2;
+                        dm = act && out == 0u ? o.code & A & 31u : 0u;
+                    }
+                    const int32_t c = __builtin_ctz(dm | 32u);
+                    const uint32_t p0 = dm ? static_cast<uint32_t>(b[q] + c) : 0u;
+                    const uint32_t wi = p0 >> 5;
+                    par0[q] = wi & 1u;   // parity of the first word's index
+                    const bool maybe = !use_sum || ((hsum[(wi >> gs) >> 5] >> ((wi >> gs) & 31)) & 1u);
+                    w0[q] = dm && maybe ? occ[wi] : 0u;
+                    w1[q] = 0u;
+                    if (o.code & 31u & ((o.code & 31u) - 1u)) {   // (uniform) more than one site in the row
+                        const uint32_t p1 = static_cast<uint32_t>(b[q] + 31 - __builtin_clz(dm | 1u));
+                        if (dm && (p1 >> 5) != wi) w1[q] = occ[wi + 1u];
+                    }
+                    v[q] = (__builtin_amdgcn_alignbit(w1[q], w0[q], p0 & 31u) << c) & dm;
                 }
-                const uint32_t wi = static_cast<uint32_t>(t[q]) >> 5;
-                const bool maybe = !use_sum || ((hsum[(wi >> gs) >> 5] >> ((wi >> gs) & 31)) & 1u);
-                w[q] = ok && maybe ? occ[wi] : 0u;
-            }
-            // list positions of the occupied neighbours: their words' first
-            // positions, loaded together, plus the set bits below them
-            uint32_t jw[HOOK_UNROLL];
+                // list positions of the occupied neighbours: their words' first
+                // positions (loaded together for the first site of every row)
+                // plus the set bits below them
+                uint32_t jw[HOOK_UNROLL];
 #pragma unroll
-            for (int q = 0; q < HOOK_UNROLL; ++q)
-                jw[q] = ((w[q] >> (t[q] & 31)) & 1u) ? wpos[static_cast<uint32_t>(t[q]) >> 5] : 0xFFFFFFFFu;
+                for (int q = 0; q < HOOK_UNROLL; ++q)
+                    jw[q] = v[q] ? wpos[static_cast<uint32_t>(b[q] + __builtin_ctz(v[q])) >> 5] : 0u;
 #pragma unroll
-            for (int q = 0; q < HOOK_UNROLL; ++q) {
-                const bool edge = jw[q] != 0xFFFFFFFFu;
-                const uint64_t mk = __ballot(edge);
-                if (edge) {
-                    const int32_t e = ne + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
-                                               static_cast<uint32_t>(mk >> 32),
-                                               __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
-                    st_w(&ei[e], i);
-                    st_w(&ej[e], static_cast<int32_t>(jw[q] + static_cast<uint32_t>(__popc(w[q] & ((1u << (t[q] & 31)) - 1u)))));
-                }
-                ne += static_cast<int32_t>(__popcll(mk));
-                if (ne >= 64) {
-                    __builtin_amdgcn_wave_barrier();
-                    hook_flush(par, ei, ej, ne, lane);
-                    __builtin_amdgcn_wave_barrier();
-                    ne = 0;
+                for (int q = 0; q < HOOK_UNROLL; ++q) {
+                    uint64_t mk = __ballot(v[q] != 0u);
+                    bool first = true;
+                    while (mk) {
+                        if (v[q]) {
+                            const int j = __builtin_ctz(v[q]);
+                            const uint32_t p = static_cast<uint32_t>(b[q] + j);
+                            // the word that holds p: the window's first or second
+                            const uint32_t word = ((p >> 5) & 1u) == par0[q] ? w0[q] : w1[q];
+                            if (!first) jw[q] = wpos[p >> 5];
+                            const int32_t e = ne + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                                                       static_cast<uint32_t>(mk >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
+                            st_w(&ei[e], i);
+                            st_w(&ej[e], static_cast<int32_t>(jw[q] + static_cast<uint32_t>(__popc(word & ((1u << (p & 31)) - 1u)))));
+                            v[q] &= v[q] - 1u;
+                        }
+                        ne += static_cast<int32_t>(__popcll(mk));
+                        if (ne >= 64) {
+                            __builtin_amdgcn_wave_barrier();
+                            hook_flush(par, ei, ej, ne, lane);
+                            __builtin_amdgcn_wave_barrier();
+                            ne = 0;
+                        }
+                        first = false;
+                        mk = __ballot(v[q] != 0u);
+                    }
                 }
             }
         }
@@ -912,872 +858,6 @@ __global__ __launch_bounds__(256) void nz_winsum_kernel(const NzSample *__restri
 }
 
 // ---------------------------------------------------------------------------
-// The sweep.  RES selects where the per-sample state of the running wave lives:
-//   RES_HBM  bitset and parents in the workspace (HBM / L2);
-//   RES_OCC  bitset in this wave's LDS slice, parents in HBM;
-//   RES_ALL  bitset and parents in LDS.
-// NCH = number of 64-offset chunks the kernel is compiled for (z <= 64 * NCH).
-
-enum { RES_HBM = 0, RES_OCC = 1, RES_ALL = 2 };
-
-// With the bitset in HBM, the wave's LDS slice starts with a summary of it:
-// bit k is clear only if bitset words k << sshift .. ((k + 1) << sshift) - 1
-// are all zero.  An occupancy check reads the summary first and fetches the
-// word from HBM only when its bit is set; near the threshold most words of a
-// wide neighbourhood's lattice are empty.  Bits are set when sites are added
-// and never cleared (a stale set bit only costs a load).
-template <int RES>
-struct SweepMem {
-    uint32_t *occ_g;
-    int32_t *par_g;
-    int32_t *parc_g;    // the list forest of the prefilled sites (node ids LIST_NODE | i)
-    uint32_t lbase;     // first LDS word of this wave's slice
-    uint32_t occ_words; // bitset words (padded to 64 sites)
-    uint32_t sshift;    // summary: log2 of bitset words per bit
-    bool sum_on;        // the summary is in use (RES_HBM only)
-
-    __device__ __forceinline__ bool maybe(uint32_t *lds, uint32_t w) const
-    {
-        if constexpr (RES != RES_HBM) return true;
-        if (!sum_on) return true;
-        const uint32_t k = w >> sshift;
-        return (ld_w(&lds[lbase + (k >> 5)]) >> (k & 31)) & 1u;
-    }
-    __device__ __forceinline__ void mark(uint32_t *lds, uint32_t w) const
-    {
-        if constexpr (RES == RES_HBM) {
-            if (sum_on) {
-                const uint32_t k = w >> sshift;
-                __hip_atomic_fetch_or(&lds[lbase + (k >> 5)], 1u << (k & 31), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WAVEFRONT);
-            }
-        }
-    }
-    __device__ __forceinline__ uint32_t occ_ld(uint32_t *lds, uint32_t w) const
-    {
-        if constexpr (RES == RES_HBM) return maybe(lds, w) ? ld_w(&occ_g[w]) : 0u;
-        else return ld_w(&lds[lbase + w]);
-    }
-    // called by every lane with the same word and value
-    __device__ __forceinline__ void occ_st(uint32_t *lds, uint32_t w, uint32_t v) const
-    {
-        if constexpr (RES == RES_HBM) {
-            st_w(&occ_g[w], v);
-            if (lane_id() == 0) mark(lds, w);
-        } else {
-            st_w(&lds[lbase + w], v);
-        }
-    }
-    // several lanes may set bits of one word at once
-    __device__ __forceinline__ void occ_or(uint32_t *lds, uint32_t w, uint32_t bits) const
-    {
-        if constexpr (RES == RES_HBM) {
-            __hip_atomic_fetch_or(&occ_g[w], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            mark(lds, w);
-        } else {
-            __hip_atomic_fetch_or(&lds[lbase + w], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        }
-    }
-    __device__ __forceinline__ void occ_andn(uint32_t *lds, uint32_t w, uint32_t bits) const
-    {
-        if constexpr (RES == RES_HBM)
-            __hip_atomic_fetch_and(&occ_g[w], ~bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        else
-            __hip_atomic_fetch_and(&lds[lbase + w], ~bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    }
-    // parent entry of node i (a lattice site, or a list node of the prefill)
-    __device__ __forceinline__ int32_t par_ld(uint32_t *lds, int32_t i) const
-    {
-        if (i >= LIST_NODE) return ld_w(&parc_g[i - LIST_NODE]);
-        if constexpr (RES == RES_ALL) return static_cast<int32_t>(ld_w(&lds[lbase + occ_words + i]));
-        else return ld_w(&par_g[i]);
-    }
-    __device__ __forceinline__ void par_st(uint32_t *lds, int32_t i, int32_t v) const
-    {
-        if (i >= LIST_NODE) {
-            st_w(&parc_g[i - LIST_NODE], v);
-            return;
-        }
-        if constexpr (RES == RES_ALL) st_w(&lds[lbase + occ_words + i], static_cast<uint32_t>(v));
-        else st_w(&par_g[i], v);
-    }
-};
-
-// Root of x with path halving, given v = the parent word of x; returns the root
-// index and its root word.
-template <int RES>
-__device__ __forceinline__ void sweep_find_from(const SweepMem<RES> &m, uint32_t *lds, int32_t x, int32_t v,
-                                                int32_t &root, uint32_t &word)
-{
-    while (v >= 0) {
-        const int32_t g = m.par_ld(lds, v);
-        if (g < 0) {
-            x = v;
-            v = g;
-            break;
-        }
-        m.par_st(lds, x, g);
-        x = g;
-        v = m.par_ld(lds, x);
-    }
-    root = x;
-    word = static_cast<uint32_t>(v);
-}
-
-template <int RES>
-__device__ __forceinline__ void sweep_find(const SweepMem<RES> &m, uint32_t *lds, int32_t x, int32_t &root, uint32_t &word)
-{
-    sweep_find_from<RES>(m, lds, x, m.par_ld(lds, x), root, word);
-}
-
-// Merge the D distinct roots held by lanes 0..D-1 (lroot/lword) into the largest
-// one (ties: smaller index).  Returns the surviving root; total size and flags
-// through the references.
-template <int RES>
-__device__ __forceinline__ int32_t sweep_merge(const SweepMem<RES> &m, uint32_t *lds, int D, int32_t lroot, uint32_t lword,
-                                               uint32_t &total, uint32_t &flags)
-{
-    const uint32_t lane = lane_id();
-    int32_t best = bcast(lroot, 0);
-    uint32_t bestsz = bcast(lword, 0) & NZ_SIZE;
-    total = 0;
-    flags = 0;
-    for (int l = 0; l < D; ++l) {
-        const int32_t r = bcast(lroot, l);
-        const uint32_t w = bcast(lword, l);
-        const uint32_t sz = w & NZ_SIZE;
-        total += sz;
-        flags |= w & NZ_FLAGS;
-        if (sz > bestsz || (sz == bestsz && r < best)) {
-            best = r;
-            bestsz = sz;
-        }
-    }
-    if (static_cast<int>(lane) < D && lroot != best) m.par_st(lds, lroot, best);
-    // every lane stores the same root word (no lane-conditional block here)
-    m.par_st(lds, best, static_cast<int32_t>(NZ_ROOT | flags | total));
-    return best;
-}
-
-// The key band of one sample in (key, site) order: buckets in key order, each
-// already sorted; 64 entries are fetched at a time into one register per lane.
-struct BandCursor {
-    const uint32_t *counts;
-    const uint32_t *sites;
-    uint32_t cap;
-    int32_t nb;
-    int32_t b;        // current bucket
-    uint32_t cnt;     // entries in it
-    uint32_t j;       // next entry
-    uint32_t base;    // entry held by lane 0
-    uint32_t mine;    // entry base + lane
-
-    __device__ __forceinline__ void init(const uint32_t *c, const uint32_t *s, uint32_t cp, int32_t n)
-    {
-        counts = c;
-        sites = s;
-        cap = cp;
-        nb = n;
-        b = -1;
-        cnt = 0;
-        j = 0;
-        base = 0;
-        mine = 0;
-    }
-
-    // 1: pc holds the next site; 0: the band is exhausted; -1: the next
-    // non-empty bucket overflowed its capacity.
-    __device__ __forceinline__ int next(uint32_t &pc, uint32_t lane)
-    {
-        while (j >= cnt) {
-            ++b;
-            if (b >= nb) return 0;
-            cnt = counts[b];
-            if (cnt > cap) return -1;
-            j = 0;
-            base = 0;
-            mine = lane < cnt ? sites[static_cast<uint64_t>(b) * cap + lane] : 0u;
-        }
-        if (j - base >= 64u) {
-            base = j;
-            mine = base + lane < cnt ? sites[static_cast<uint64_t>(b) * cap + base + lane] : 0u;
-        }
-        pc = bcast(mine, static_cast<int>(j - base));
-        ++j;
-        return 1;
-    }
-};
-
-// One sequential step's site and the occupancy words of its neighbours (lane
-// c*64 + lane holds neighbour c of the offset table).  PER: coordinates wrap
-// modulo L (periodic boundaries); a compile-time choice, so that the
-// free-boundary step carries no wrap arithmetic.
-template <int NCH, bool PER = false>
-struct SiteStep {
-    int32_t s;
-    uint32_t fl;
-    uint32_t own;
-    uint32_t A;          // allowed axes of s
-    uint32_t word[NCH];  // 0 for a neighbour outside the lattice
-
-    // Neighbour c of s (recomputed rather than held: one register per chunk
-    // less, which keeps wide-neighbourhood kernels at more waves per SIMD).
-    __device__ __forceinline__ int32_t nbr(int c, const int32_t (&ostride)[NCH], const uint32_t (&ocode)[NCH],
-                                           int32_t L) const
-    {
-        if constexpr (PER) {
-            const uint32_t out = ocode[c] & ~A;
-            return s + ostride[c] + (out ? wrap_fix(out, L) : 0);
-        } else {
-            return s + ostride[c];
-        }
-    }
-    // neighbour c lies inside the lattice (under periodic boundaries every
-    // offset does, padding slots aside)
-    __device__ __forceinline__ bool inside(int c, const uint32_t (&ocode)[NCH]) const
-    {
-        if constexpr (PER) return (ocode[c] & ~kCodeBits) == 0u;
-        else return (ocode[c] & ~A) == 0u;
-    }
-
-    template <int RES>
-    __device__ __forceinline__ void prepare(const SweepMem<RES> &m, uint32_t *lds, uint32_t pc, int32_t L,
-                                            const int32_t (&ostride)[NCH], const uint32_t (&ocode)[NCH])
-    {
-        const int32_t x0 = pc & 63, x1 = (pc >> 6) & 63, x2 = (pc >> 12) & 63, x3 = (pc >> 18) & 63, x4 = pc >> 24;
-        s = x0 + L * (x1 + L * (x2 + L * (x3 + L * x4)));
-        A = allowed_axis(x0, L) | (allowed_axis(x1, L) << 5) | (allowed_axis(x2, L) << 10) |
-            (allowed_axis(x3, L) << 15) | (allowed_axis(x4, L) << 20);
-        fl = PER ? 0u : ((x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u));
-        own = m.occ_ld(lds, static_cast<uint32_t>(s) >> 5);
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-            word[c] = inside(c, ocode) ? m.occ_ld(lds, static_cast<uint32_t>(nbr(c, ostride, ocode, L)) >> 5) : 0u;
-    }
-
-    // Account for site p, occupied after these words were loaded.
-    __device__ __forceinline__ void patch(int32_t p, const int32_t (&ostride)[NCH], const uint32_t (&ocode)[NCH], int32_t L)
-    {
-        const uint32_t bit = 1u << (p & 31);
-        if ((s >> 5) == (p >> 5)) own |= bit;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-            if (inside(c, ocode) && nbr(c, ostride, ocode, L) == p) word[c] |= bit;
-    }
-};
-
-// The next site's occupancy is loaded one step ahead only while the doubled
-// per-lane arrays stay small (z <= 128); wider neighbourhoods have few
-// sequential steps and would spill registers.
-template <int NCH>
-constexpr bool kLookahead = NCH <= 2;
-
-// One sequential addition: store the site's occupancy bit, find the distinct
-// roots of its occupied neighbours (lanes 0..D-1 hold them, entry 0 being the
-// site itself), and merge them into the largest.  Returns the merged cluster's
-// size and border flags.
-template <int NCH, int RES, bool PER>
-__device__ __forceinline__ void sweep_step(const SweepMem<RES> &m, uint32_t *lds, const SiteStep<NCH, PER> &cur,
-                                           const int32_t (&ostride)[NCH], const uint32_t (&ocode)[NCH], int32_t L,
-                                           int dcap, uint32_t &total, uint32_t &flags)
-{
-    const uint32_t lane = lane_id();
-    const int32_t s = cur.s;
-    // all lanes store the same updated word of s (this wave is the only writer
-    // of the sample's bitset)
-    m.occ_st(lds, static_cast<uint32_t>(s) >> 5, cur.own | (1u << (s & 31)));
-
-    int32_t lroot = s;
-    uint32_t lword = NZ_ROOT | cur.fl | 1u;
-    int D = 1;
-    // Enter the roots found by the lanes of mk (root / rw) into the list.
-    auto enter = [&](uint64_t mk, int32_t root, uint32_t rw) {
-        bool stale = false;   // a flush since these finds may have linked their roots
-        while (mk) {
-            const int l = __builtin_ctzll(mk);
-            mk &= mk - 1;
-            int32_t rr = bcast(root, l);
-            uint32_t rrw = bcast(rw, l);
-            if (stale) sweep_find<RES>(m, lds, rr, rr, rrw);
-            if (__ballot(static_cast<int>(lane) < D && lroot == rr)) continue;
-            if (D == dcap) {
-                // list full: merge what we have and keep only the survivor;
-                // rr is not in the list, so the flush leaves it a root
-                uint32_t tot, flg;
-                const int32_t w = sweep_merge<RES>(m, lds, D, lroot, lword, tot, flg);
-                lroot = lane == 0 ? w : lroot;
-                lword = lane == 0 ? (NZ_ROOT | flg | tot) : lword;
-                D = 1;
-                stale = true;
-            }
-            lroot = static_cast<int>(lane) == D ? rr : lroot;
-            lword = static_cast<int>(lane) == D ? rrw : lword;
-            ++D;
-        }
-    };
-    // Near the threshold a wide neighbourhood has a few occupied neighbours,
-    // rarely two on one lane: then every lane holds at most one and all the
-    // finds run at once instead of one offset chunk after another.
-    int32_t cand = -1;
-    bool two = false;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int32_t t = cur.nbr(c, ostride, ocode, L);
-        if ((cur.word[c] >> (t & 31)) & 1u) {   // the word is 0 outside the lattice
-            two = two || cand >= 0;
-            cand = t;
-        }
-    }
-    if (NCH == 1 || !__ballot(two)) {
-        const uint64_t mk = __ballot(cand >= 0);
-        if (mk) {
-            int32_t root = 0;
-            uint32_t rw = 0;
-            if (cand >= 0) sweep_find<RES>(m, lds, cand, root, rw);
-            enter(mk, root, rw);
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int32_t t = cur.nbr(c, ostride, ocode, L);
-            const bool o = (cur.word[c] >> (t & 31)) & 1u;
-            const uint64_t mk = __ballot(o);
-            if (!mk) continue;
-            int32_t root = 0;
-            uint32_t rw = 0;
-            if (o) sweep_find<RES>(m, lds, t, root, rw);
-            enter(mk, root, rw);
-        }
-    }
-    sweep_merge<RES>(m, lds, D, lroot, lword, total, flags);
-}
-
-// ---------------------------------------------------------------------------
-// Block sweep: the next 64 sites of the order are added by one wave at once,
-// one site per lane.  The neighbour checks and root finds of the 64 sites
-// overlap in memory instead of following each other; the unions run as a small
-// connected-components pass over a graph whose nodes are the block's sites and
-// the earlier clusters they touch.  Spanning is monotone in the occupation (a
-// cluster only grows and its border flags only accumulate), so if no cluster
-// spans after all 64 additions none spanned after any of them and the block is
-// committed as a whole.  The single block in which the first spanning cluster
-// appears, and blocks that do not fit the tables below, are undone and redone
-// one site at a time, which yields the exact n* and mass.
-//
-// While a block is processed its sites are marked occupied and their parent
-// entries hold BLK_MARK | position, a value no node id reaches (sites below
-// 2^29, list nodes below 2^30) and no root word has (bit 31 clear).  An occupied neighbour whose parent
-// entry carries the mark is a site of the block, earlier or later in the order.
-//
-// Per-wave LDS slice (32-bit words, at the end of the wave's slice):
-//   rkey[256]    open-addressing table of the earlier roots the block touches
-//   npar[320]    node parents: node i < 64 is position i, node 64 + h the
-//                earlier root in rkey slot h
-//   nword[320]   node words in the root-word format (size, flags)
-
-constexpr int BLK_K = 8;               // occupied neighbours recorded per site
-constexpr uint32_t BLK_RSLOTS = 256;
-constexpr uint32_t BLK_NODES = 64 + BLK_RSLOTS;
-constexpr uint32_t BLK_EMPTY = 0xFFFFFFFFu;
-constexpr uint32_t BLK_LDS_WORDS = BLK_RSLOTS + 2 * BLK_NODES;
-constexpr int BLK_CHUNK = 16;          // neighbour offsets whose loads are issued together
-constexpr int32_t BLK_MARK = 0x40000000;
-
-__device__ __forceinline__ uint32_t blk_hash(uint32_t t) { return (t * 0x9E3779B1u) >> 24; }
-
-// Root of node n in the LDS forest, with path halving.  Only non-roots are
-// rewritten (to an ancestor), and hooks only change roots, so concurrent finds
-// and hooks of the lanes of one wave keep the forest acyclic.
-__device__ __forceinline__ uint32_t blk_find(uint32_t *npar, uint32_t x)
-{
-    for (;;) {
-        const uint32_t p = ld_w(&npar[x]);
-        if (p == x) return x;
-        const uint32_t g = ld_w(&npar[p]);
-        if (g == p) return p;
-        st_w(&npar[x], g);
-        x = g;
-    }
-}
-
-// Occupied neighbours among BLK_CHUNK offsets (their loads issued together),
-// appended to nl[0 .. cntn) by site.
-template <int RES>
-__device__ __forceinline__ void blk_scan(const SweepMem<RES> &m, uint32_t *lds, const NzOffset (&oq)[BLK_CHUNK],
-                                         bool act, int32_t s, uint32_t A, int32_t (&nl)[BLK_K], int &cntn)
-{
-    int32_t tq[BLK_CHUNK];
-    uint32_t wq[BLK_CHUNK];
-#pragma unroll
-    for (int q = 0; q < BLK_CHUNK; ++q) {
-        const bool ok = act && (oq[q].code & ~A) == 0u;
-        tq[q] = s + oq[q].stride;
-        wq[q] = ok ? m.occ_ld(lds, static_cast<uint32_t>(tq[q]) >> 5) : 0u;
-    }
-#pragma unroll
-    for (int q = 0; q < BLK_CHUNK; ++q) {
-        const bool rec = (wq[q] >> (tq[q] & 31)) & 1u;
-#pragma unroll
-        for (int k = 0; k < BLK_K; ++k) nl[k] = (rec && cntn == k) ? tq[q] : nl[k];
-        cntn += rec ? 1 : 0;
-    }
-}
-
-enum { BLK_COMMITTED = 0, BLK_FALLBACK = 1 };
-
-// Adds the nbk (1..64) sites whose packed coordinates lane i holds in pc (lane
-// i = position i of the order); off0 holds the first BLK_CHUNK offsets of the
-// table.  BLK_COMMITTED: the block is merged into the union-find and no cluster
-// spans.  BLK_FALLBACK: the occupancy bits of the block are cleared again and
-// the parents of earlier sites are as before (up to path halving); the caller
-// adds the sites one at a time.
-template <int RES>
-__device__ __forceinline__ int block_step(const SweepMem<RES> &m, uint32_t *lds, uint32_t hbase, int nbk, uint32_t pc,
-                                          int32_t L, const NzOffset *tab, const NzOffset (&off0)[BLK_CHUNK], int32_t z,
-                                          int max_old)
-{
-    const uint32_t lane = lane_id();
-    const bool act = static_cast<int>(lane) < nbk;
-    const int32_t x0 = pc & 63, x1 = (pc >> 6) & 63, x2 = (pc >> 12) & 63, x3 = (pc >> 18) & 63, x4 = pc >> 24;
-    const int32_t s = x0 + L * (x1 + L * (x2 + L * (x3 + L * x4)));
-    const uint32_t A = allowed_axis(x0, L) | (allowed_axis(x1, L) << 5) | (allowed_axis(x2, L) << 10) |
-                       (allowed_axis(x3, L) << 15) | (allowed_axis(x4, L) << 20);
-    const uint32_t fl = (x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u);
-    uint32_t *rkey = lds + hbase;
-    uint32_t *npar = rkey + BLK_RSLOTS;
-    uint32_t *nword = npar + BLK_NODES;
-
-    // 1. mark the block's sites (occupied, parent = mark | position); clear
-    //    the tables
-    if (act) {
-        m.par_st(lds, s, BLK_MARK | static_cast<int32_t>(lane));
-        m.occ_or(lds, static_cast<uint32_t>(s) >> 5, 1u << (s & 31));
-    }
-#pragma unroll
-    for (uint32_t w = 0; w < BLK_RSLOTS; w += 64) st_w(&rkey[w + lane], BLK_EMPTY);
-    for (uint32_t n = lane; n < BLK_NODES; n += 64) st_w(&npar[n], n);
-    st_w(&nword[lane], act ? (NZ_ROOT | fl | 1u) : 0u);
-
-    // 2. occupied neighbours (sites of earlier blocks and of this block)
-    int32_t nl[BLK_K];
-#pragma unroll
-    for (int k = 0; k < BLK_K; ++k) nl[k] = 0;
-    int cntn = 0;
-    blk_scan<RES>(m, lds, off0, act, s, A, nl, cntn);
-    for (int c0 = BLK_CHUNK; c0 < z; c0 += BLK_CHUNK) {
-        NzOffset oq[BLK_CHUNK];
-#pragma unroll
-        for (int q = 0; q < BLK_CHUNK; ++q) {
-            oq[q].stride = 0;
-            oq[q].code = 0xFFFFFFFFu;
-            if (c0 + q < z) oq[q] = tab[c0 + q];
-        }
-        blk_scan<RES>(m, lds, oq, act, s, A, nl, cntn);
-    }
-    bool bad = cntn > BLK_K;
-    __builtin_amdgcn_wave_barrier();
-
-    // 3. parent words of the recorded neighbours (loads issued together).  A
-    //    mark names a position of this block: an earlier one becomes an edge to
-    //    that node, a later one is dropped.  Otherwise the neighbour's root is
-    //    found and entered once into the root table; nl[k] becomes the node
-    //    (-1: no edge).
-    int32_t pv[BLK_K];
-#pragma unroll
-    for (int k = 0; k < BLK_K; ++k) pv[k] = (!bad && k < cntn) ? m.par_ld(lds, nl[k]) : -1;
-    // the first hop of every find, issued together (a prefilled site points
-    // straight at its root, so this usually reaches it)
-    int32_t gv[BLK_K];
-#pragma unroll
-    for (int k = 0; k < BLK_K; ++k) gv[k] = (!bad && k < cntn && pv[k] >= 0 && pv[k] < BLK_MARK) ? m.par_ld(lds, pv[k]) : -1;
-    int nnew = 0;
-#pragma unroll
-    for (int k = 0; k < BLK_K; ++k) {
-        if (!bad && k < cntn) {
-            if (pv[k] >= BLK_MARK) {
-                const int j = pv[k] & 63;
-                nl[k] = j < static_cast<int>(lane) ? j : -1;
-            } else {
-                int32_t root;
-                uint32_t word;
-                if (pv[k] < 0) {
-                    root = nl[k];
-                    word = static_cast<uint32_t>(pv[k]);
-                } else if (gv[k] < 0) {
-                    root = pv[k];
-                    word = static_cast<uint32_t>(gv[k]);
-                } else {
-                    m.par_st(lds, nl[k], gv[k]);   // halving: the neighbour skips to its grandparent
-                    sweep_find<RES>(m, lds, gv[k], root, word);
-                }
-                uint32_t h = blk_hash(static_cast<uint32_t>(root));
-                int slot = -1;
-                for (uint32_t t = 0; t < BLK_RSLOTS; ++t) {
-                    uint32_t expected = BLK_EMPTY;
-                    if (__hip_atomic_compare_exchange_strong(&rkey[h], &expected, static_cast<uint32_t>(root),
-                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_WAVEFRONT)) {
-                        st_w(&nword[64 + h], word);
-                        slot = static_cast<int>(h);
-                        ++nnew;
-                        break;
-                    }
-                    if (expected == static_cast<uint32_t>(root)) {
-                        slot = static_cast<int>(h);
-                        break;
-                    }
-                    h = (h + 1) & (BLK_RSLOTS - 1);
-                }
-                bad = bad || slot < 0;
-                nl[k] = 64 + slot;
-            }
-        }
-    }
-    // the roots entered by all lanes, against the cap on distinct roots
-    int nold = nnew;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) nold += __shfl_xor(nold, d);
-    if (__ballot(bad) || nold > max_old) {
-        if (act) m.occ_andn(lds, static_cast<uint32_t>(s) >> 5, 1u << (s & 31));
-        return BLK_FALLBACK;
-    }
-    __builtin_amdgcn_wave_barrier();
-
-    // 4. connected components: hook the worse root under the better one (larger
-    //    size, then larger node), until no edge joins two trees
-    for (;;) {
-        bool hooked = false;
-#pragma unroll
-        for (int k = 0; k < BLK_K; ++k) {
-            if (k < cntn && nl[k] >= 0) {
-                const uint32_t a = blk_find(npar, lane);
-                const uint32_t b = blk_find(npar, static_cast<uint32_t>(nl[k]));
-                if (a != b) {
-                    const uint32_t sa = ld_w(&nword[a]) & NZ_SIZE, sb = ld_w(&nword[b]) & NZ_SIZE;
-                    const bool a_up = sa > sb || (sa == sb && a > b);
-                    uint32_t expected = a_up ? b : a;
-                    __hip_atomic_compare_exchange_strong(&npar[expected], &expected, a_up ? a : b, __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                    hooked = true;
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (!__ballot(hooked)) break;
-    }
-
-    // 5. sizes and flags into the roots; live nodes are the block's positions
-    //    and the occupied root-table slots
-    uint32_t nroot[BLK_NODES / 64];
-    bool nlive[BLK_NODES / 64];
-#pragma unroll
-    for (uint32_t q = 0; q < BLK_NODES / 64; ++q) {
-        const uint32_t n = lane + 64 * q;
-        nlive[q] = q == 0 ? act : ld_w(&rkey[n - 64]) != BLK_EMPTY;
-        nroot[q] = nlive[q] ? blk_find(npar, n) : n;
-        if (nlive[q] && nroot[q] != n) {
-            const uint32_t w = ld_w(&nword[n]);
-            __hip_atomic_fetch_add(&nword[nroot[q]], w & NZ_SIZE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            __hip_atomic_fetch_or(&nword[nroot[q]], w & NZ_FLAGS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    bool spans = false;
-#pragma unroll
-    for (uint32_t q = 0; q < BLK_NODES / 64; ++q) {
-        const uint32_t n = lane + 64 * q;
-        spans = spans || (nlive[q] && nroot[q] == n && (ld_w(&nword[n]) & NZ_FLAGS) == NZ_FLAGS);
-    }
-    if (__ballot(spans)) {
-        if (act) m.occ_andn(lds, static_cast<uint32_t>(s) >> 5, 1u << (s & 31));
-        return BLK_FALLBACK;
-    }
-
-    // 6. write back: roots get their root word, other nodes link to their root
-#pragma unroll
-    for (uint32_t q = 0; q < BLK_NODES / 64; ++q) {
-        const uint32_t n = lane + 64 * q;
-        const uint32_t r = nroot[q];
-        const int32_t rsite_pos = __shfl(s, static_cast<int>(r & 63));   // all lanes take part
-        if (nlive[q]) {
-            const int32_t site = q == 0 ? s : static_cast<int32_t>(ld_w(&rkey[n - 64]));
-            int32_t v;
-            if (r == n) v = static_cast<int32_t>(ld_w(&nword[n]));
-            else v = r < 64 ? rsite_pos : static_cast<int32_t>(ld_w(&rkey[r - 64]));
-            m.par_st(lds, site, v);
-        }
-    }
-    return BLK_COMMITTED;
-}
-
-struct SweepOut {
-    int32_t *nstar;
-    int32_t *mass;
-    const int32_t *out_index; // per sample: position in the caller's output arrays
-};
-
-// NCH: offset chunks of one-site steps; FB: offset chunks of the block
-// sweep's one-site fallback (z <= 64 * FB for every block sample), kept
-// separate so that a launch whose wide neighbourhoods go one site at a time
-// does not carry their registers through the block path.
-template <int NCH, int RES, bool BLOCK, int FB, bool PER>
-__global__ __launch_bounds__(256) void nz_sweep_kernel(NzSweepArgs a, SweepOut out)
-{
-    static_assert(!(BLOCK && PER), "periodic samples go one site per step");
-    extern __shared__ uint32_t lds[];
-    __shared__ int32_t claim[16];   // per-wave work claim
-    const uint32_t lane = lane_id();
-    const uint32_t wave = threadIdx.x >> 6;
-
-    for (;;) {
-        // One lane claims the next queue entry and publishes it through LDS;
-        // every lane then reads the slot, so no cross-lane read ever depends on
-        // which lanes took a lane-conditional branch.
-        if (lane == 0) claim[wave] = atomicAdd(a.qhead, 1);
-        __builtin_amdgcn_wave_barrier();
-        const int qi = __builtin_amdgcn_readfirstlane(ld_w(&claim[wave]));
-        __builtin_amdgcn_wave_barrier();
-        if (qi >= a.nqueue) break;
-        const int sid = a.queue[qi];
-        const int32_t status0 = a.state[sid].status;
-        if (status0 != NZ_ST_PENDING) continue;
-        const NzSample &d = a.desc[sid];
-        const int32_t L = d.L;
-        const int32_t N = d.N;
-        const int32_t z = d.z;
-        const int32_t nb = d.nb;
-        const uint32_t cap = static_cast<uint32_t>(d.cap);
-        const bool prefilled = d.T0 != 0;
-        const int dcap = a.dcap;
-
-        SweepMem<RES> m;
-        m.occ_g = reinterpret_cast<uint32_t *>(a.ws + d.off_occ);
-        m.par_g = reinterpret_cast<int32_t *>(a.ws + d.off_par);
-        m.parc_g = reinterpret_cast<int32_t *>(a.ws + d.off_parc);
-        m.lbase = wave * a.lds_words;
-        m.occ_words = static_cast<uint32_t>(((N + 63) >> 6) << 1);
-        m.sshift = static_cast<uint32_t>(d.sum_shift);
-        m.sum_on = false;
-        if constexpr (RES == RES_HBM) {
-            m.sum_on = a.use_sum != 0 && d.sum_words > 0;
-            if (m.sum_on) {
-                const uint32_t *sum_g = reinterpret_cast<const uint32_t *>(a.ws + d.off_sum);
-                for (int32_t w = lane; w < d.sum_words; w += 64) lds[m.lbase + w] = sum_g[w];
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        if constexpr (RES != RES_HBM) {
-            for (uint32_t w = lane; w < m.occ_words; w += 64) lds[m.lbase + w] = prefilled ? m.occ_g[w] : 0u;
-            if constexpr (RES == RES_ALL) {
-                if (prefilled)
-                    for (int32_t i = lane; i < N; i += 64) lds[m.lbase + m.occ_words + i] = static_cast<uint32_t>(m.par_g[i]);
-            }
-        } else if (!prefilled) {
-            // the keys kernel wrote an all-zero bitset; nothing to do
-        }
-
-        const NzOffset *tab = a.tabs + d.tab;
-        // offset c * 64 + lane of the table per lane, for one-site-at-a-time steps
-        int32_t ostride[NCH];
-        uint32_t ocode[NCH];
-        // (relaxed atomic loads: kept where they are rather than hoisted out of
-        // the block loop, where the arrays would hold registers for every block)
-        auto load_offsets = [&]() {
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int32_t j = c * 64 + static_cast<int32_t>(lane);
-                if (j < z) {
-                    ostride[c] = ld_w(&tab[j].stride);
-                    ocode[c] = ld_w(&tab[j].code);
-                } else {
-                    ostride[c] = 0;
-                    ocode[c] = 0xFFFFFFFFu;   // never inside: bits above 25 are never allowed
-                }
-            }
-        };
-
-        int32_t r = a.state[sid].n0;   // sites already occupied
-        int32_t status = NZ_ST_BAND;
-        int32_t nstar = 0, mass = 0;
-        // smax mode: the sweep runs on past n* and records the largest cluster
-        // after every addition with win_lo <= r < win_hi
-        const bool smax_mode = d.smax_mode != 0;
-        int32_t smax = a.state[sid].smax;
-        uint32_t *win = reinterpret_cast<uint32_t *>(a.ws + d.off_win);
-        // One addition done (r sites occupied, the new site's cluster has
-        // `total` sites and border flags `flags`): true when the sample is over.
-        auto finished = [&](uint32_t total, uint32_t flags) -> bool {
-            if (flags == NZ_FLAGS && nstar == 0) {
-                nstar = r;
-                mass = static_cast<int32_t>(total);
-                if (!smax_mode) {
-                    status = NZ_ST_DONE;
-                    return true;
-                }
-            }
-            if (smax_mode) {
-                smax = max(smax, static_cast<int32_t>(total));
-                if (r >= d.win_lo) win[r - d.win_lo] = static_cast<uint32_t>(smax);   // every lane, same value
-                if (r + 1 >= d.win_hi) {
-                    status = NZ_ST_DONE;
-                    return true;
-                }
-            }
-            return false;
-        };
-
-        // 64 sites per step up to the launch's z limit, one site per step above
-        // it (and always one at a time in smax mode)
-        bool use_block = false;
-        if constexpr (BLOCK) use_block = z <= a.blk_zmax && !smax_mode;
-        if (smax_mode && r >= d.win_lo) {
-            status = NZ_ST_BACKOFF;   // the prefill covers part of the window: start lower
-        } else if (use_block) {
-            // 64 sites of the band at a time; blocks do not cross buckets
-            const uint32_t *counts = reinterpret_cast<const uint32_t *>(a.ws + d.off_counts);
-            const uint32_t *sites = reinterpret_cast<const uint32_t *>(a.ws + d.off_sites);
-            const uint32_t hbase = m.lbase + a.lds_words - BLK_LDS_WORDS;
-            NzOffset off0[BLK_CHUNK];   // the first offsets, kept for the whole sample
-#pragma unroll
-            for (int q = 0; q < BLK_CHUNK; ++q) {
-                off0[q].stride = 0;
-                off0[q].code = 0xFFFFFFFFu;
-                if (q < z) off0[q] = tab[q];
-            }
-            SiteStep<FB> cur;
-            int32_t fstride[FB];
-            uint32_t fcode[FB];
-            bool done = false;
-            // Block cursor over the band: bucket cb, offset cj of the next site.
-            // The concatenated buckets are the order, so a block takes the next
-            // 64 sites across bucket boundaries.  Its sites are loaded one block
-            // ahead, so that load overlaps the previous block's step.  1: pc
-            // holds the block's sites (lanes < n); 0: end of the band; -1: an
-            // over-full bucket was reached (the sites before it still form a
-            // block first).
-            int32_t cb = 0;
-            uint32_t cj = 0;
-            uint32_t ccnt = nb > 0 ? counts[0] : 0u;
-            auto next_block = [&](uint32_t &pc, int &n) -> int {
-                n = 0;
-                pc = 0u;
-                bool over = false;
-                while (n < 64) {
-                    while (cb < nb && cj >= ccnt) {
-                        ++cb;
-                        cj = 0;
-                        if (cb < nb) ccnt = counts[cb];
-                    }
-                    if (cb >= nb) break;
-                    if (ccnt > cap) {
-                        over = true;
-                        break;
-                    }
-                    const uint32_t t = min(static_cast<uint32_t>(64 - n), ccnt - cj);
-                    const uint32_t rel = lane - static_cast<uint32_t>(n);   // this lane's entry, if in range
-                    if (lane >= static_cast<uint32_t>(n) && rel < t) pc = sites[static_cast<uint64_t>(cb) * cap + cj + rel];
-                    n += static_cast<int>(t);
-                    cj += t;
-                }
-                if (n > 0) return 1;
-                return over ? -1 : 0;
-            };
-            uint32_t pcl = 0;
-            int nbk = 0;
-            int got = next_block(pcl, nbk);
-            while (got == 1) {
-                uint32_t pcn = 0;
-                int nbn = 0;
-                const int gotn = next_block(pcn, nbn);
-                const int res = block_step<RES>(m, lds, hbase, nbk, pcl, L, tab, off0, z, a.blk_old);
-                if (res == BLK_FALLBACK) {
-#pragma unroll
-                    for (int c = 0; c < FB; ++c) {
-                        const int32_t j = c * 64 + static_cast<int32_t>(lane);
-                        fstride[c] = j < z ? ld_w(&tab[j].stride) : 0;
-                        fcode[c] = j < z ? ld_w(&tab[j].code) : 0xFFFFFFFFu;
-                    }
-                    for (int i = 0; i < nbk; ++i) {
-                        ++r;
-                        cur.prepare(m, lds, bcast(pcl, i), L, fstride, fcode);
-                        uint32_t total, flags;
-                        sweep_step<FB, RES>(m, lds, cur, fstride, fcode, L, dcap, total, flags);
-                        if (flags == NZ_FLAGS) {
-                            status = NZ_ST_DONE;
-                            nstar = r;
-                            mass = static_cast<int32_t>(total);
-                            done = true;
-                            break;
-                        }
-                    }
-                    if (done) break;
-                } else {
-                    r += nbk;
-                }
-                got = gotn;
-                pcl = pcn;
-                nbk = nbn;
-            }
-            if (!done && got < 0) status = NZ_ST_BUCKET;
-        } else {
-        load_offsets();
-        // The band in (key, site) order; the occupancy words of the next site are
-        // loaded while the current one is processed.  Only the current site can
-        // change them in between, so they are patched with its bit afterwards.
-        BandCursor bc;
-        bc.init(reinterpret_cast<const uint32_t *>(a.ws + d.off_counts),
-                reinterpret_cast<const uint32_t *>(a.ws + d.off_sites), cap, nb);
-        SiteStep<NCH, PER> cur, nxt;
-        uint32_t pc = 0;
-        int got = bc.next(pc, lane);
-        if (got < 0) status = NZ_ST_BUCKET;
-        if constexpr (kLookahead<NCH>) {
-            if (got == 1) cur.prepare(m, lds, pc, L, ostride, ocode);
-            while (got == 1) {
-                ++r;
-                uint32_t pcn = 0;
-                const int gotn = bc.next(pcn, lane);
-                if (gotn == 1) nxt.prepare(m, lds, pcn, L, ostride, ocode);
-                uint32_t total, flags;
-                sweep_step<NCH, RES>(m, lds, cur, ostride, ocode, L, dcap, total, flags);
-                if (finished(total, flags)) break;
-                if (gotn != 1) {
-                    if (gotn < 0) status = NZ_ST_BUCKET;
-                    break;
-                }
-                nxt.patch(cur.s, ostride, ocode, L);
-                cur = nxt;
-            }
-        } else {
-            while (got == 1) {
-                ++r;
-                cur.prepare(m, lds, pc, L, ostride, ocode);
-                uint32_t total, flags;
-                sweep_step<NCH, RES>(m, lds, cur, ostride, ocode, L, dcap, total, flags);
-                if (finished(total, flags)) break;
-                got = bc.next(pc, lane);
-                if (got < 0) status = NZ_ST_BUCKET;
-            }
-        }
-        }
-        if (status == NZ_ST_BAND && d.full) {
-            status = NZ_ST_DONE;   // the whole lattice is occupied and never spans
-            nstar = 0;
-            mass = 0;
-        }
-        // every lane stores the same values
-        a.state[sid].status = status;
-        a.state[sid].nstar = nstar;
-        a.state[sid].mass = mass;
-        if (status == NZ_ST_DONE) {
-            const int32_t o = out.out_index[sid];
-            out.nstar[o] = nstar;
-            if (out.mass) out.mass[o] = mass;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Periodic boundaries: n* is the first addition after which a cluster wraps
 // around axis 0 (Newman & Ziff 2001, Sec. III).
 //
@@ -1798,9 +878,6 @@ __device__ __forceinline__ uint64_t wword(uint32_t par, int32_t dx)
 }
 __device__ __forceinline__ int32_t wpar(uint64_t e) { return static_cast<int32_t>(static_cast<uint32_t>(e)); }
 __device__ __forceinline__ int32_t wdx(uint64_t e) { return static_cast<int32_t>(e >> 32); }
-
-// x0 component of an offset: the axis-0 field of its code has bit d0 + 2 set.
-__device__ __forceinline__ int32_t code_d0(uint32_t code) { return __builtin_ctz(code | 32u) - 2; }
 
 // Prefill phase: a root points to itself with displacement 0.  Root of x and
 // the displacement of x from it; path splitting (each entry on the way skips to
@@ -1837,7 +914,7 @@ __global__ __launch_bounds__(256) void nz_hookw_kernel(const NzSample *__restric
     const int32_t n0 = state[sid].n0;
     if (n0 > d.prefix_cap || !d.wrap) return;
     const int32_t L = d.L;
-    const int32_t zh = d.z >> 1;
+    const int32_t rh = d.rows >> 1;   // one row of every +- pair
     const uint64_t magic = d.magic;
     uint64_t *pw = reinterpret_cast<uint64_t *>(ws + d.off_par);
     const uint32_t *occ = reinterpret_cast<const uint32_t *>(ws + d.off_occ);
@@ -1851,35 +928,46 @@ __global__ __launch_bounds__(256) void nz_hookw_kernel(const NzSample *__restric
                            (allowed_axis((pc >> 12) & 63, L) << 10) | (allowed_axis((pc >> 18) & 63, L) << 15) |
                            (allowed_axis(pc >> 24, L) << 20);
         int32_t u = -1, Du = 0;   // a root (or ancestor) of s and the displacement of s from it
-        for (int32_t k0 = 0; k0 < zh; k0 += HOOK_UNROLL) {
-            int32_t t[HOOK_UNROLL], d0[HOOK_UNROLL];
-            uint32_t w[HOOK_UNROLL];
+        const int32_t x0 = static_cast<int32_t>(pc & 63);
+        for (int32_t k0 = 0; k0 < 2 * rh; k0 += HOOK_UNROLL) {
+            // entry k: row k / 2; odd entries are the steps that leave along axis
+            // 0, on the other side of the row
+            int32_t b[HOOK_UNROLL];
+            uint32_t v[HOOK_UNROLL];
 #pragma unroll
             for (int q = 0; q < HOOK_UNROLL; ++q) {
                 NzOffset o;
                 o.stride = 0;
-                o.code = 0xFFFFFFFFu;
-                if (k0 + q < zh) o = tab[k0 + q];
-                const uint32_t out = o.code & ~A;
-                const bool ok = (o.code & ~kCodeBits) == 0u;   // every real offset, wrapped
-                t[q] = s + o.stride + (out ? wrap_fix(out, L) : 0);
-                d0[q] = code_d0(o.code);
-                w[q] = ok ? occ[static_cast<uint32_t>(t[q]) >> 5] : 0u;
+                o.code = 0u;
+                if (k0 + q < 2 * rh) o = tab[(k0 + q) >> 1];
+                const int side = q & 1;
+                const uint32_t out = o.code & ~A & kRowAxes;
+                b[q] = s + o.stride - 2 + (out ? wrap_fix(out, L) : 0);
+                if (side) b[q] += x0 < 2 ? L : -L;
+                const uint32_t dm = o.code & (side ? ~A : A) & 31u;
+                const int32_t c = __builtin_ctz(dm | 32u);
+                const uint32_t p0 = static_cast<uint32_t>(b[q] + c), p1 = static_cast<uint32_t>(b[q] + 31 - __builtin_clz(dm | 1u));
+                const uint32_t w0 = dm ? occ[p0 >> 5] : 0u;
+                const uint32_t w1 = dm && (p1 >> 5) != (p0 >> 5) ? occ[p1 >> 5] : 0u;
+                v[q] = (__builtin_amdgcn_alignbit(w1, w0, p0 & 31u) << c) & dm;
             }
 #pragma unroll
             for (int q = 0; q < HOOK_UNROLL; ++q) {
-                if (!((w[q] >> (t[q] & 31)) & 1u)) continue;
+              while (v[q]) {
+                const int j = __builtin_ctz(v[q]);
+                v[q] &= v[q] - 1u;
+                const int32_t tn = b[q] + j, d0 = j - 2;
                 if (u < 0) u = ccw_find(pw, s, Du);
                 int32_t Dv;
-                int32_t v = ccw_find(pw, t[q], Dv);
+                int32_t vr = ccw_find(pw, tn, Dv);
                 for (;;) {
-                    if (u == v) {
-                        if (Du + d0[q] != Dv) wraps = true;
+                    if (u == vr) {
+                        if (Du + d0 != Dv) wraps = true;
                         break;
                     }
-                    const int32_t hi = max(u, v), lo = min(u, v);
-                    // x0(u) = x0(s) - Du and x0(v) = x0(s) + d0 - Dv
-                    const int32_t dx = hi == u ? Dv - Du - d0[q] : Du + d0[q] - Dv;
+                    const int32_t hi = max(u, vr), lo = min(u, vr);
+                    // x0(u) = x0(s) - Du and x0(vr) = x0(s) + d0 - Dv
+                    const int32_t dx = hi == u ? Dv - Du - d0 : Du + d0 - Dv;
                     uint64_t expected = wword(static_cast<uint32_t>(hi), 0);
                     if (__hip_atomic_compare_exchange_strong(&pw[hi], &expected, wword(static_cast<uint32_t>(lo), dx),
                                                              __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
@@ -1898,14 +986,15 @@ __global__ __launch_bounds__(256) void nz_hookw_kernel(const NzSample *__restric
                         u = ccw_find(pw, u, Dp);
                         Du += Dp;
                     }
-                    if (v == hi) {
-                        v = ccw_find(pw, wpar(expected), Dp);
+                    if (vr == hi) {
+                        vr = ccw_find(pw, wpar(expected), Dp);
                         Dv += wdx(expected) + Dp;
                     } else {
-                        v = ccw_find(pw, v, Dp);
+                        vr = ccw_find(pw, vr, Dp);
                         Dv += Dp;
                     }
                 }
+              }
             }
         }
     }
@@ -1966,203 +1055,886 @@ __global__ __launch_bounds__(256) void nz_accumw_kernel(const NzSample *__restri
     }
 }
 
-// Sweep phase: root of x, its root word and the displacement of x from it; path
-// halving with displacements added.
-__device__ __forceinline__ void wrap_find(uint64_t *pw, int32_t x, int32_t &root, uint32_t &word, int32_t &disp)
+// ---------------------------------------------------------------------------
+// The block sweep: one workgroup per sample, up to B sites of the order at a
+// time.
+//
+// A block is whole buckets of the key band (buckets are in key order, their
+// entries are not), so nothing is sorted on the way.  Its sites are marked
+// occupied, every (site, row of offsets) pair is checked by some lane, and the
+// unions run as a connected-components pass in LDS over a graph whose nodes are
+// the block's sites and the earlier clusters they touch.  Spanning (or
+// wrapping) is monotone in the occupation: clusters only grow and flags only
+// accumulate, so when no cluster spans after all the sites of the block none
+// spanned after any of them, and the block is committed as a whole.  In the
+// block in which a cluster spans, the smallest T such that the block's first T
+// sites in (key, site) order span is found by bisection on that small graph,
+// without touching memory again: n* is the count before the block plus T, the
+// mass the size of the cluster of the T-th site.  A block that does not fit
+// the tables is undone, sorted, and added in halves (one site has at most 892
+// neighbours and always fits).
+//
+// What bounds it: the latency of a block's chain of dependent accesses (parent
+// words and root words of the occupied neighbours, some eight barriers) and,
+// for wide neighbourhoods, the checks themselves.  The checks therefore read a
+// map of the occupation held in LDS (below), one row of up to five offsets at
+// a time, and blocks are as large as the tables allow beside the map.  Measured
+// (L = 16, 7 compact neighbourhoods x 1000, prefilled): a block of up to 512
+// sites takes 17 us -- checks 6.0, parents and roots 7.5, unions 1.8, sizes and
+// flags 0.9, write-back 0.6 -- against 24 us for 64 sites by one wave in the
+// sweep this one replaced; ranks 6.5 and bisection 26 us once per sample.  37
+// samples of L = 13, z = 380 took 1.56 ms and take 0.11 ms, the periodic L = 12
+// batch of 700 samples 26 ms and 0.5 ms.
+//
+// While a block is processed the parent entries of its sites hold BLK_MARK |
+// position, a value no node id reaches (sites below 2^29, list nodes below
+// 2^30) and no root word has (bit 31 clear).
+
+enum { BLK_SPAN = 0, BLK_WRAP = 1, BLK_SMAX = 2 };
+
+struct SweepOut {
+    int32_t *nstar;
+    int32_t *mass;
+    const int32_t *out_index; // per sample: position in the caller's output arrays
+};
+
+constexpr uint32_t BLK_RSLOTS = 1024;    // hash slots for the earlier roots (at least 892: one site fits)
+constexpr int BLK_EDGES = 1536;          // recorded (site, occupied neighbour) pairs per block
+constexpr int BLK_CHUNK = 6;             // rows checked together (five bits each: one 32-bit mask)
+constexpr int BLK_MAXROWS = 300;         // rows of the widest neighbourhood (298), in whole chunks
+constexpr uint32_t BLK_EMPTY = 0xFFFFFFFFu;
+constexpr int32_t BLK_MARK = 0x40000000;
+constexpr int BLK_MAXB = 512;
+constexpr uint32_t BLK_SMALL_MAP = 4096;  // words of the largest map that leaves room for several workgroups per CU
+constexpr uint32_t BLK_SMAX_MAP = 4096;
+constexpr uint32_t BLK_MAP_PAD = 3;       // map words outside the lattice: one before, two behind
+static_assert(BLK_MAXROWS % BLK_CHUNK == 0, "whole chunks");
+static_assert(BLK_RSLOTS >= 892 && BLK_EDGES >= 892, "a block of one site always fits");
+
+__device__ __forceinline__ int32_t site_of(uint32_t pc, int32_t L)
 {
-    uint64_t e = ld_w(&pw[x]);
-    int32_t D = 0;
-    while (wpar(e) >= 0) {
-        const int32_t p = wpar(e);
-        const uint64_t g = ld_w(&pw[p]);
-        if (wpar(g) < 0) {
-            D += wdx(e);
-            x = p;
-            e = g;
-            break;
-        }
-        const uint64_t h = wword(static_cast<uint32_t>(wpar(g)), wdx(e) + wdx(g));
-        st_w(&pw[x], h);
-        D += wdx(h);
-        x = wpar(g);
-        e = ld_w(&pw[x]);
-    }
-    root = x;
-    word = static_cast<uint32_t>(wpar(e));
-    disp = D;
+    return static_cast<int32_t>(pc & 63) +
+           L * (static_cast<int32_t>((pc >> 6) & 63) +
+                L * (static_cast<int32_t>((pc >> 12) & 63) +
+                     L * (static_cast<int32_t>((pc >> 18) & 63) + L * static_cast<int32_t>(pc >> 24))));
 }
 
-// Merge the D distinct roots held by lanes 0..D-1 into the largest (ties: the
-// smaller index).  lq is x0(new site) - x0(lane's root); each attached root
-// takes its displacement from the survivor.  Returns the survivor and, through
-// the references, the total size, the flags and the survivor's lq.
-__device__ __forceinline__ int32_t wrap_merge(uint64_t *pw, int D, int32_t lroot, uint32_t lword, int32_t lq,
-                                              uint32_t wrapfl, uint32_t &total, uint32_t &flags, int32_t &qbest)
+// The steps every axis allows from the site with packed coordinates pc.
+__device__ __forceinline__ uint32_t allowed_of(uint32_t pc, int32_t L)
 {
-    const uint32_t lane = lane_id();
-    int32_t best = bcast(lroot, 0);
-    uint32_t bestsz = bcast(lword, 0) & NZ_SIZE;
-    int bl = 0;
-    total = 0;
-    flags = wrapfl;
-    for (int l = 0; l < D; ++l) {
-        const int32_t r = bcast(lroot, l);
-        const uint32_t w = bcast(lword, l);
-        const uint32_t sz = w & NZ_SIZE;
-        total += sz;
-        flags |= w & NZ_FLAGS;
-        if (sz > bestsz || (sz == bestsz && r < best)) {
-            best = r;
-            bestsz = sz;
-            bl = l;
-        }
-    }
-    qbest = bcast(lq, bl);
-    // x0(root) - x0(best) = (x0(site) - lq) - (x0(site) - qbest)
-    if (static_cast<int>(lane) < D && lroot != best) st_w(&pw[lroot], wword(static_cast<uint32_t>(best), qbest - lq));
-    st_w(&pw[best], wword(NZ_ROOT | flags | total, 0));   // every lane, same value
-    return best;
+    return allowed_axis(pc & 63, L) | (allowed_axis((pc >> 6) & 63, L) << 5) | (allowed_axis((pc >> 12) & 63, L) << 10) |
+           (allowed_axis((pc >> 18) & 63, L) << 15) | (allowed_axis(pc >> 24, L) << 20);
 }
 
-// One addition under periodic boundaries: as the free-boundary step, with the
-// new site's displacement from each neighbouring root carried along and
-// compared whenever two neighbours share a root.
-template <int NCH>
-__device__ __forceinline__ void wrap_step(uint32_t *occ, uint64_t *pw, const SiteStep<NCH, true> &cur, const int32_t (&od0)[NCH],
-                                          const int32_t (&ostride)[NCH], const uint32_t (&ocode)[NCH], int32_t L,
-                                          int dcap, uint32_t &total, uint32_t &flags)
-{
-    const uint32_t lane = lane_id();
-    const int32_t s = cur.s;
-    st_w(&occ[static_cast<uint32_t>(s) >> 5], cur.own | (1u << (s & 31)));
+// Accesses shared by the waves of one workgroup.
+template <typename T>
+__device__ __forceinline__ T ld_g(T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+template <typename T>
+__device__ __forceinline__ void st_g(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
-    int32_t lroot = s, lq = 0;
-    uint32_t lword = NZ_ROOT | 1u;
-    uint32_t wrapfl = 0;
-    int D = 1;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int32_t t = cur.nbr(c, ostride, ocode, L);
-        const bool o = (cur.word[c] >> (t & 31)) & 1u;   // the word is 0 outside the lattice
-        uint64_t mk = __ballot(o);
-        if (!mk) continue;
-        int32_t root = 0, disp = 0;
-        uint32_t rw = 0;
-        if (o) wrap_find(pw, t, root, rw, disp);
-        // t = s + d: x0(s) - x0(root) = disp - d0
-        const int32_t q = disp - od0[c];
-        bool stale = false;   // a flush since these finds may have linked their roots
-        while (mk) {
-            const int l = __builtin_ctzll(mk);
-            mk &= mk - 1;
-            int32_t rr = bcast(root, l);
-            uint32_t rrw = bcast(rw, l);
-            int32_t qq = bcast(q, l);
-            if (stale) {
-                int32_t extra;
-                wrap_find(pw, rr, rr, rrw, extra);
-                qq += extra;
-            }
-            const uint64_t hit = __ballot(static_cast<int>(lane) < D && lroot == rr);
-            if (hit) {
-                if (bcast(lq, __builtin_ctzll(hit)) != qq) wrapfl = NZ_FLAGS;
-                continue;
-            }
-            if (D == dcap) {
-                uint32_t tot, flg;
-                int32_t qb;
-                const int32_t w = wrap_merge(pw, D, lroot, lword, lq, wrapfl, tot, flg, qb);
-                lroot = lane == 0 ? w : lroot;
-                lword = lane == 0 ? (NZ_ROOT | flg | tot) : lword;
-                lq = lane == 0 ? qb : lq;
-                D = 1;
-                stale = true;
-            }
-            lroot = static_cast<int>(lane) == D ? rr : lroot;
-            lword = static_cast<int>(lane) == D ? rrw : lword;
-            lq = static_cast<int>(lane) == D ? qq : lq;
-            ++D;
-        }
+// Node words of the LDS forest: the parent node, and for the wrap sweep the x0
+// displacement from it in the high half (one 64-bit word, so that every read
+// is a consistent pair).
+template <bool WRAP>
+struct BlkWord {
+    using type = uint32_t;
+    static __device__ __forceinline__ uint32_t make(uint32_t p, int32_t) { return p; }
+    static __device__ __forceinline__ uint32_t par(uint32_t e) { return e; }
+    static __device__ __forceinline__ int32_t dx(uint32_t) { return 0; }
+};
+template <>
+struct BlkWord<true> {
+    using type = uint64_t;
+    static __device__ __forceinline__ uint64_t make(uint32_t p, int32_t d)
+    {
+        return (static_cast<uint64_t>(static_cast<uint32_t>(d)) << 32) | p;
     }
-    int32_t qb;
-    wrap_merge(pw, D, lroot, lword, lq, wrapfl, total, flags, qb);
-}
+    static __device__ __forceinline__ uint32_t par(uint64_t e) { return static_cast<uint32_t>(e); }
+    static __device__ __forceinline__ int32_t dx(uint64_t e) { return static_cast<int32_t>(e >> 32); }
+};
 
-// Persistent first-wrap sweep: one wave per sample, one site per step, state
-// in HBM (the entries are twice as wide as in the free-boundary sweep).
-template <int NCH>
-__global__ __launch_bounds__(256) void nz_wrap_sweep_kernel(NzSweepArgs a, SweepOut out)
+template <int MODE, int B>
+struct BlkLds {
+    using W = BlkWord<MODE == BLK_WRAP>;
+    typename W::type npar[B + BLK_RSLOTS];
+    uint32_t et[BLK_EDGES];            // pair e: the neighbour's site, then its node (BLK_EMPTY: dropped)
+    uint32_t pcs[B];                   // packed coordinates of the block's sites
+    uint32_t rkey[BLK_RSLOTS];         // earlier roots the block touches (open addressing)
+    uint32_t nword[B + BLK_RSLOTS];    // node words in the root-word format
+    NzOffset rows[BLK_MAXROWS];        // the sample's rows, padded with empty ones to whole chunks
+    uint16_t ei[BLK_EDGES];            // pair e: the block position, and (d0 + 2) << 12 for the wrap sweep
+    int16_t eq[MODE == BLK_WRAP ? BLK_EDGES : 1];   // x0(site) - x0(node) of pair e
+    // largest-cluster sweep: the pairs of every position as a linked list, and
+    // the running maximum after every position
+    uint16_t next[MODE == BLK_SMAX ? BLK_EDGES : 1];
+    uint32_t first[MODE == BLK_SMAX ? B : 1];
+    uint32_t smax[MODE == BLK_SMAX ? B : 1];
+    int32_t ecnt, nroots, flag, bad, claim;
+    uint32_t total;                    // spanning: the size of the cluster of the T-th site
+};
+
+__device__ __forceinline__ uint32_t blk_hash(uint32_t t) { return (t * 0x9E3779B1u) >> 22; }
+static_assert(BLK_RSLOTS == 1024, "blk_hash yields ten bits");
+
+// Root of node x in the LDS forest with path halving; D is the displacement of
+// x from it.  Only non-roots are rewritten (to an ancestor) and links only
+// change roots, so concurrent finds and links keep the forest acyclic.
+template <int MODE, int B>
+__device__ __forceinline__ uint32_t blk_find(BlkLds<MODE, B> &S, uint32_t x, int32_t &D)
 {
-    __shared__ int32_t claim[4];
-    const uint32_t lane = lane_id();
-    const uint32_t wave = threadIdx.x >> 6;
+    using W = typename BlkLds<MODE, B>::W;
+    D = 0;
+    auto e = ld_g(&S.npar[x]);
     for (;;) {
-        if (lane == 0) claim[wave] = atomicAdd(a.qhead, 1);
-        __builtin_amdgcn_wave_barrier();
-        const int qi = __builtin_amdgcn_readfirstlane(ld_w(&claim[wave]));
-        __builtin_amdgcn_wave_barrier();
+        const uint32_t p = W::par(e);
+        if (p == x) return x;
+        const auto g = ld_g(&S.npar[p]);
+        if (W::par(g) == p) {
+            D += W::dx(e);
+            return p;
+        }
+        const auto h = W::make(W::par(g), W::dx(e) + W::dx(g));
+        st_g(&S.npar[x], h);
+        D += W::dx(h);
+        x = W::par(g);
+        e = ld_g(&S.npar[x]);
+    }
+}
+
+// The lattice side of one sample: occupancy bits, their map in LDS and the
+// union-find entries (32-bit parent / root words, 64-bit with displacements for
+// the wrap sweep; prefilled roots of the former live in the list forest as
+// nodes LIST_NODE | i).
+//
+// The map: bit k of the map (k counted from word 1; words 0 and the last two
+// are zero) is clear only if sites k << mshift .. are all empty.  Up to L = 16
+// mshift is 0: the map is the occupation itself and nothing else is read.
+// Larger lattices take the smallest mshift that fits, and a set bit sends the
+// check to the bitset in memory.
+template <int MODE>
+struct BlkMem {
+    uint32_t *occ;
+    int32_t *par;
+    int32_t *parc;
+    uint64_t *pw;
+    uint32_t *map;      // LDS
+    uint32_t mshift;
+    uint32_t occ_words;
+
+    __device__ __forceinline__ void occ_set(uint32_t s) const
+    {
+        const uint32_t k = s >> mshift;
+        __hip_atomic_fetch_or(&map[1 + (k >> 5)], 1u << (k & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (mshift)
+            __hip_atomic_fetch_or(&occ[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // (map bits that stand for several sites stay set: that only costs a load)
+    __device__ __forceinline__ void occ_clear(uint32_t s) const
+    {
+        if (mshift)
+            __hip_atomic_fetch_and(&occ[s >> 5], ~(1u << (s & 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else
+            __hip_atomic_fetch_and(&map[1 + (s >> 5)], ~(1u << (s & 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void mark(int32_t s, int32_t pos) const
+    {
+        if constexpr (MODE == BLK_WRAP) st_g(&pw[s], static_cast<uint64_t>(static_cast<uint32_t>(BLK_MARK | pos)));
+        else st_g(&par[s], BLK_MARK | pos);
+    }
+    __device__ __forceinline__ int32_t par_ld(int32_t i) const
+    {
+        return i >= LIST_NODE ? ld_g(&parc[i - LIST_NODE]) : ld_g(&par[i]);
+    }
+    __device__ __forceinline__ void par_st(int32_t i, int32_t v) const
+    {
+        if (i >= LIST_NODE) st_g(&parc[i - LIST_NODE], v);
+        else st_g(&par[i], v);
+    }
+    // Entry of an occupied site: the block position if it carries the mark, else
+    // -1 with its root, root word and displacement from the root (path halving).
+    __device__ __forceinline__ int resolve(int32_t t, int32_t &root, uint32_t &word, int32_t &disp) const
+    {
+        disp = 0;
+        if constexpr (MODE == BLK_WRAP) {
+            uint64_t e = ld_g(&pw[t]);
+            int32_t x = t;
+            if (wpar(e) >= BLK_MARK) return wpar(e) & (BLK_MAXB - 1);
+            while (wpar(e) >= 0) {
+                const int32_t p = wpar(e);
+                const uint64_t g = ld_g(&pw[p]);
+                if (wpar(g) < 0) {
+                    disp += wdx(e);
+                    x = p;
+                    e = g;
+                    break;
+                }
+                const uint64_t h = wword(static_cast<uint32_t>(wpar(g)), wdx(e) + wdx(g));
+                st_g(&pw[x], h);
+                disp += wdx(h);
+                x = wpar(g);
+                e = ld_g(&pw[x]);
+            }
+            root = x;
+            word = static_cast<uint32_t>(wpar(e));
+        } else {
+            int32_t x = t, v = ld_g(&par[t]);
+            if (v >= BLK_MARK) return v & (BLK_MAXB - 1);
+            while (v >= 0) {
+                const int32_t g = par_ld(v);
+                if (g < 0) {
+                    x = v;
+                    v = g;
+                    break;
+                }
+                par_st(x, g);
+                x = g;
+                v = par_ld(x);
+            }
+            root = x;
+            word = static_cast<uint32_t>(v);
+        }
+        return -1;
+    }
+    // node's final entry: a root word, or (parent, displacement)
+    __device__ __forceinline__ void commit(int32_t node, bool is_root, uint32_t word, int32_t parent, int32_t disp) const
+    {
+        if constexpr (MODE == BLK_WRAP) st_g(&pw[node], is_root ? wword(word, 0) : wword(static_cast<uint32_t>(parent), disp));
+        else par_st(node, is_root ? static_cast<int32_t>(word) : parent);
+    }
+};
+
+// Records the occupied neighbours of the block's sites as pairs.  Items of 64
+// sites x BLK_CHUNK rows are dealt to the waves; a row (read from LDS, the same
+// for all lanes) costs a lane about a dozen instructions and one two-word read
+// of the map; 3.4 offsets of the widest neighbourhood share a row.
+// EXACT: the map is the occupation (mshift == 0); else a set map bit sends the
+// check to the bitset.  The reads of an item's rows are issued together.
+template <bool EXACT, bool PER, int NT, int MODE, int B>
+__device__ __forceinline__ void blk_scan(BlkLds<MODE, B> &S, const BlkMem<MODE> &m, int nrows, int32_t L, int lo, int len)
+{
+    constexpr int NW = NT / 64;
+    const uint32_t lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int groups = (len + 63) >> 6, chunks = (nrows + BLK_CHUNK - 1) / BLK_CHUNK;
+    int g = wave, c = 0, have = -1;
+    while (g >= groups) {
+        g -= groups;
+        ++c;
+    }
+    int32_t s = 0, x0 = 0;
+    uint32_t A = 0;
+    int i = 0;
+    bool in = false;
+    while (c < chunks) {
+        if (g != have) {
+            have = g;
+            i = g * 64 + static_cast<int>(lane);
+            in = i < len;
+            const uint32_t pc = in ? S.pcs[lo + i] : 0u;
+            x0 = static_cast<int32_t>(pc & 63);
+            s = site_of(pc, L);
+            A = in ? allowed_of(pc, L) : 0u;
+        }
+        // side 1 (periodic only): the steps that leave along axis 0, on the
+        // other side of the row
+        for (int side = 0; side < (PER ? 2 : 1); ++side) {
+            const int32_t off0 = (PER && side) ? (x0 < 2 ? L : -L) : 0;
+            int32_t bq[BLK_CHUNK];
+            uint32_t want[BLK_CHUNK], w0[BLK_CHUNK], w1[BLK_CHUNK];
+#pragma unroll
+            for (int q = 0; q < BLK_CHUNK; ++q) {
+                const NzOffset o = S.rows[c * BLK_CHUNK + q];   // (padding rows have no site)
+                const uint32_t out = o.code & ~A & kRowAxes;
+                if constexpr (PER) {
+                    want[q] = in ? o.code & (side ? ~A : A) & 31u : 0u;
+                    bq[q] = want[q] ? s + o.stride - 2 + (out ? wrap_fix(out, L) : 0) + off0 : 0;
+                } else {
+                    want[q] = out == 0u ? o.code & A & 31u : 0u;
+                    bq[q] = out == 0u ? s + o.stride - 2 : 0;
+                }
+                if constexpr (EXACT) {
+                    const int32_t w = (bq[q] >> 5) + 1;
+                    w0[q] = m.map[w];
+                    w1[q] = m.map[w + 1];
+                } else {
+                    const int32_t w = (bq[q] >> (m.mshift + 5u)) + 1;
+                    w0[q] = m.map[w];
+                    w1[q] = m.map[w + 1];
+                }
+            }
+            if constexpr (!EXACT) {
+#pragma unroll
+                for (int q = 0; q < BLK_CHUNK; ++q) {
+                    // the map bits of sites b .. b + 4 (at most three)
+                    const int32_t k0 = bq[q] >> m.mshift, n = ((bq[q] + 4) >> m.mshift) - k0;
+                    const uint32_t any = __builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(k0) & 31u) & ((2u << n) - 1u);
+                    const bool need = any != 0u && want[q] != 0u;
+                    const uint32_t first = static_cast<uint32_t>(max(bq[q], 0)) >> 5;
+                    const uint32_t last = static_cast<uint32_t>(max(bq[q], 0) + 4) >> 5;
+                    w0[q] = need ? ld_g(&m.occ[first]) : 0u;
+                    w1[q] = need && last != first && last < m.occ_words ? ld_g(&m.occ[last]) : 0u;
+                }
+            }
+            uint32_t mask = 0u;
+#pragma unroll
+            for (int q = 0; q < BLK_CHUNK; ++q) {
+                uint32_t v;
+                if constexpr (EXACT) {
+                    v = __builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(bq[q]) & 31u);
+                } else {
+                    const int32_t b0 = max(bq[q], 0);
+                    v = __builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(b0) & 31u) << (b0 - bq[q]);
+                }
+                mask |= (v & want[q]) << (5 * q);
+            }
+            uint64_t mk;
+            while ((mk = __ballot(mask != 0u)) != 0ull) {
+                int32_t base = 0;
+                if (lane == 0) base = atomicAdd(&S.ecnt, static_cast<int32_t>(__popcll(mk)));
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (mask) {
+                    const int bit = __builtin_ctz(mask);
+                    mask &= mask - 1u;
+                    const int q = (bit * 13) >> 6, j = bit - 5 * q;   // bit / 5 for bit < 30
+                    const NzOffset o = S.rows[c * BLK_CHUNK + q];
+                    int32_t nbs = s + o.stride - 2 + j;
+                    if constexpr (PER) {
+                        const uint32_t out = o.code & ~A & kRowAxes;
+                        nbs += (out ? wrap_fix(out, L) : 0) + off0;
+                    }
+                    const int32_t e = base + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                                                 static_cast<uint32_t>(mk >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
+                    if (e < BLK_EDGES) {
+                        S.et[e] = static_cast<uint32_t>(nbs);
+                        S.ei[e] = static_cast<uint16_t>(i | (j << 12));
+                    }
+                }
+            }
+        }
+        g += NW;
+        while (g >= groups) {
+            g -= groups;
+            ++c;
+        }
+    }
+}
+
+// Links nodes u and v: the worse root (smaller cluster before the block, then
+// smaller node: a fixed total order) goes below the better one.  Wrap sweep: q
+// = x0(u) - x0(v); a pair whose ends already share a root closes a loop, which
+// winds around axis 0 when the displacements disagree.
+template <int MODE, int B>
+__device__ __forceinline__ void blk_link(BlkLds<MODE, B> &S, uint32_t u, uint32_t v, int32_t q)
+{
+    using W = typename BlkLds<MODE, B>::W;
+    for (;;) {
+        int32_t Du, Dv;
+        const uint32_t a = blk_find<MODE, B>(S, u, Du);
+        const uint32_t b = blk_find<MODE, B>(S, v, Dv);
+        if (a == b) {
+            if (MODE == BLK_WRAP && Du != q + Dv) S.flag = 1;
+            return;
+        }
+        const uint32_t sa = ld_g(&S.nword[a]) & NZ_SIZE, sb = ld_g(&S.nword[b]) & NZ_SIZE;
+        const bool a_up = sa > sb || (sa == sb && a > b);
+        const uint32_t lo = a_up ? b : a, hi = a_up ? a : b;
+        const int32_t dab = q - Du + Dv;   // x0(a) - x0(b)
+        auto expected = W::make(lo, 0);
+        if (__hip_atomic_compare_exchange_strong(&S.npar[lo], &expected, W::make(hi, a_up ? -dab : dab), __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+            return;
+    }
+}
+
+// Block of the band starting at bucket cb: as many whole buckets (16 at most)
+// as B sites hold.  n sites, thread t < n takes entry t into pc, whose bucket
+// holds the block's positions b0 .. b1 - 1; nbk buckets consumed.  over: the first bucket of the block overflowed its capacity.
+template <int B>
+__device__ __forceinline__ void blk_fetch(const uint32_t *counts, const uint32_t *sites, uint32_t cap, int32_t nb,
+                                          int32_t cb, int &n, int &nbk, bool &over, uint32_t &pc, int &b0, int &b1)
+{
+    const uint32_t lane = lane_id();
+    const int32_t left = min(16, nb - cb);
+    const bool in = static_cast<int32_t>(lane) < left;
+    const uint32_t c = in ? counts[cb + static_cast<int32_t>(lane)] : 0u;
+    const uint64_t badm = __ballot(in && (c > cap || c > static_cast<uint32_t>(B)));
+    const int32_t lim = badm ? __builtin_ctzll(badm) : left;
+    uint32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const uint32_t v = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), o));
+        if (lane >= static_cast<uint32_t>(o)) incl += v;
+    }
+    const uint64_t ok = __ballot(static_cast<int32_t>(lane) < lim && incl <= static_cast<uint32_t>(B));
+    nbk = __popcll(ok);
+    n = nbk > 0 ? static_cast<int>(__builtin_amdgcn_readlane(incl, nbk - 1)) : 0;
+    over = nbk == 0 && cb < nb;
+    const uint32_t t = threadIdx.x;
+    uint32_t base = 0, k = 0, end = 0;
+    for (int q = 0; q < nbk; ++q) {
+        const uint32_t iq = __builtin_amdgcn_readlane(incl, q);
+        if (t >= iq) {
+            base = iq;
+            k = static_cast<uint32_t>(q) + 1u;
+        }
+        if (end <= t) end = iq;
+    }
+    b0 = static_cast<int>(base);
+    b1 = static_cast<int>(end);
+    pc = t < static_cast<uint32_t>(n) ? sites[static_cast<uint64_t>(cb + static_cast<int32_t>(k)) * cap + (t - base)] : 0u;
+}
+
+// Rank by (key, site) of this thread's site S.pcs[t] in the block: t < n lies in
+// a bucket that holds positions b0 .. b1 - 1, and buckets are in key order, so
+// only those are compared.  Keys are recomputed.  `keys`: LDS scratch of n
+// 64-bit words.  Barriers before and after are the caller's (one is inside).
+template <int MODE, int B>
+__device__ __forceinline__ int blk_rank(BlkLds<MODE, B> &S, uint64_t *keys, const NzSample &d, int n, int b0, int b1)
+{
+    const int t = static_cast<int>(threadIdx.x);
+    uint64_t K = 0;
+    uint32_t pc = 0;
+    if (t < n) {
+        pc = S.pcs[t];
+        const uint32_t s = static_cast<uint32_t>(site_of(pc, d.L));
+        uint64_t ke, ko;
+        site_key_pair(static_cast<uint32_t>(d.seed), static_cast<uint32_t>(d.seed >> 32), static_cast<uint32_t>(d.sample),
+                      static_cast<uint32_t>(d.sample >> 32), s >> 1, ke, ko);
+        K = (s & 1u) ? ko : ke;
+        keys[t] = K;
+    }
+    __syncthreads();
+    int rank = b0;
+    if (t < n) {
+        bool tie = false;
+#pragma unroll 8
+        for (int j = b0; j < b1; ++j) {
+            const uint64_t Kj = keys[j];
+            rank += Kj < K ? 1 : 0;
+            tie = tie || (Kj == K && j != t);
+        }
+        if (tie)
+            for (int j = b0; j < b1; ++j)
+                if (keys[j] == K && S.pcs[j] < pc) ++rank;
+    }
+    return rank;
+}
+
+enum { BLK_COMMITTED = 0, BLK_SPANS = 1, BLK_NOFIT = 2 };
+
+// Adds the sites S.pcs[lo .. lo + len) (1 <= len <= B; sorted: in (key, site)
+// order, else the whole block, position t in bucket positions b0 .. b1 - 1).  BLK_COMMITTED: merged,
+// and no cluster spans.  BLK_NOFIT: nothing has changed (up to path halving).
+// BLK_SPANS: T is the smallest number of the block's sites, in (key, site)
+// order, after which a cluster spans and S.total that cluster's size; the
+// sample is over and its state is left as it is.  Largest-cluster sweep (sites
+// in order): the window entries of the block are written and smax carries the
+// running maximum.
+template <int MODE, bool PER, int NT, int B>
+__device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &m, const NzSample &d,
+                                        int32_t L, int nrows, int lo, int len, bool sorted, int b0, int b1, int max_old, int32_t r, int32_t win_lo,
+                                        int32_t win_hi, uint32_t *win, int32_t &smax, int &T)
+{
+    using W = typename BlkLds<MODE, B>::W;
+    const int t = static_cast<int>(threadIdx.x);
+    const bool act = t < len;
+
+    // 1. mark the block's sites; clear the tables
+    int32_t site = 0;
+    uint32_t pos_word = 0;
+    if (act) {
+        const uint32_t pc = S.pcs[lo + t];
+        site = site_of(pc, L);
+        m.mark(site, t);
+        m.occ_set(static_cast<uint32_t>(site));
+        const int32_t x0 = pc & 63;
+        const uint32_t fl = (MODE != BLK_SPAN) ? 0u : ((x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u));
+        pos_word = NZ_ROOT | fl | 1u;
+        S.nword[t] = pos_word;
+        S.npar[t] = W::make(static_cast<uint32_t>(t), 0);
+        if constexpr (MODE == BLK_SMAX) S.first[t] = BLK_EMPTY;
+    }
+    for (uint32_t w = static_cast<uint32_t>(t); w < BLK_RSLOTS; w += NT) S.rkey[w] = BLK_EMPTY;
+    if (t == 0) {
+        S.ecnt = 0;
+        S.nroots = 0;
+        S.flag = 0;
+        S.bad = 0;
+    }
+    __syncthreads();
+
+    // 2. occupied neighbours
+    if (m.mshift == 0) blk_scan<true, PER, NT>(S, m, nrows, L, lo, len);
+    else blk_scan<false, PER, NT>(S, m, nrows, L, lo, len);
+    __syncthreads();
+    const int ne = S.ecnt;
+    int res = ne > BLK_EDGES ? BLK_NOFIT : BLK_COMMITTED;
+
+    // 3. the pairs' neighbours become nodes: a site of the block (pairs are
+    //    kept once, from the later position), or the root of an earlier
+    //    cluster, entered once into the root table
+    if (res == BLK_COMMITTED) {
+        int nnew = 0;
+        for (int e = t; e < ne; e += NT) {
+            const int32_t nb = static_cast<int32_t>(S.et[e]);
+            const int i = S.ei[e] & (BLK_MAXB - 1);
+            int32_t root, disp;
+            uint32_t word;
+            const int j = m.resolve(nb, root, word, disp);
+            uint32_t node = BLK_EMPTY;
+            if (j >= 0) {
+                if (j < i) node = static_cast<uint32_t>(j);
+                disp = 0;
+            } else {
+                uint32_t h = blk_hash(static_cast<uint32_t>(root));
+                for (uint32_t k = 0; k < BLK_RSLOTS; ++k) {
+                    uint32_t expected = BLK_EMPTY;
+                    if (__hip_atomic_compare_exchange_strong(&S.rkey[h], &expected, static_cast<uint32_t>(root),
+                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                        S.nword[B + h] = word;
+                        S.npar[B + h] = W::make(B + h, 0);
+                        node = B + h;
+                        ++nnew;
+                        break;
+                    }
+                    if (expected == static_cast<uint32_t>(root)) {
+                        node = B + h;
+                        break;
+                    }
+                    h = (h + 1) & (BLK_RSLOTS - 1);
+                }
+                if (node == BLK_EMPTY) S.bad = 1;   // table full
+            }
+            S.et[e] = node;
+            if constexpr (MODE == BLK_SMAX) {
+                if (node != BLK_EMPTY)
+                    S.next[e] = static_cast<uint16_t>(__hip_atomic_exchange(&S.first[i], static_cast<uint32_t>(e), __ATOMIC_RELAXED,
+                                                                            __HIP_MEMORY_SCOPE_WORKGROUP));
+            }
+            // x0(site) - x0(node): the neighbour lies at x0(site) + d0 = x0(node) + disp
+            if constexpr (MODE == BLK_WRAP) S.eq[e] = static_cast<int16_t>(disp - (static_cast<int>(S.ei[e] >> 12) - 2));
+        }
+        if (nnew) atomicAdd(&S.nroots, nnew);
+        __syncthreads();
+        if (S.bad || (S.nroots > max_old && len > 1)) res = BLK_NOFIT;
+    }
+    if (res == BLK_NOFIT) {
+        if (act) m.occ_clear(static_cast<uint32_t>(site));
+        __syncthreads();
+        return res;
+    }
+
+    // nodes of this thread: its block position and its slots of the root table
+    constexpr int NODES = 1 + static_cast<int>(BLK_RSLOTS) / NT;
+    static_assert(BLK_RSLOTS % NT == 0, "whole slots per thread");
+    bool live[NODES];
+    uint32_t root[NODES], word0[NODES];
+    int32_t disp[NODES];
+    auto node_of = [&](int k) { return static_cast<uint32_t>(k == 0 ? t : B + (k - 1) * NT + t); };
+#pragma unroll
+    for (int k = 0; k < NODES; ++k) {
+        const uint32_t n = node_of(k);
+        live[k] = k == 0 ? act : S.rkey[n - B] != BLK_EMPTY;
+        root[k] = n;
+        disp[k] = 0;
+        word0[k] = k == 0 ? pos_word : (live[k] ? S.nword[n] : 0u);
+    }
+    // roots of the live nodes; sizes and flags into the roots.  True: a cluster
+    // spans.  (two barriers inside, the last one at the end)
+    auto gather = [&]() -> bool {
+#pragma unroll
+        for (int k = 0; k < NODES; ++k) {
+            if (!live[k]) continue;
+            const uint32_t n = node_of(k);
+            root[k] = blk_find<MODE, B>(S, n, disp[k]);
+            if (root[k] != n) {
+                atomicAdd(&S.nword[root[k]], word0[k] & NZ_SIZE);
+                if (word0[k] & NZ_FLAGS) atomicOr(&S.nword[root[k]], word0[k] & NZ_FLAGS);
+            }
+        }
+        __syncthreads();
+        if constexpr (MODE == BLK_SPAN) {
+#pragma unroll
+            for (int k = 0; k < NODES; ++k)
+                if (live[k] && root[k] == node_of(k) && (S.nword[root[k]] & NZ_FLAGS) == NZ_FLAGS) S.flag = 1;
+        }
+        __syncthreads();
+        return S.flag != 0;
+    };
+
+    if constexpr (MODE == BLK_SMAX) {
+        // 4. unions in the order of the positions, by one lane; the sizes are
+        //    kept at the roots
+        __syncthreads();   // (word0 is read above)
+        if (t == 0) {
+            for (int i = 0; i < len; ++i) {
+                uint32_t a = static_cast<uint32_t>(i), sz = 1;
+                for (uint32_t e = S.first[i]; (e & 0xFFFFu) != 0xFFFFu; e = S.next[e]) {
+                    int32_t unused;
+                    const uint32_t b = blk_find<MODE, B>(S, S.et[e], unused);
+                    if (b == a) continue;
+                    const uint32_t sb = S.nword[b] & NZ_SIZE;
+                    const uint32_t lo_n = sb > sz ? a : b, hi_n = sb > sz ? b : a;
+                    sz += sb;
+                    st_g(&S.npar[lo_n], W::make(hi_n, 0));
+                    S.nword[hi_n] = NZ_ROOT | sz;
+                    a = hi_n;
+                }
+                smax = max(smax, static_cast<int32_t>(sz));
+                S.smax[i] = static_cast<uint32_t>(smax);
+            }
+        }
+        __syncthreads();
+        smax = static_cast<int32_t>(S.smax[len - 1]);
+        // r + t + 1 sites are occupied after position t
+        const int32_t rr = r + t + 1;
+        if (act && rr >= win_lo && rr < win_hi) win[rr - win_lo] = S.smax[t];
+#pragma unroll
+        for (int k = 0; k < NODES; ++k)
+            if (live[k]) root[k] = blk_find<MODE, B>(S, node_of(k), disp[k]);
+    } else {
+        // 4. unions of all pairs
+        auto unions = [&](auto &&take) {
+            for (int e = t; e < ne; e += NT) {
+                const uint32_t node = S.et[e];
+                const uint32_t i = S.ei[e] & (BLK_MAXB - 1);
+                if (node == BLK_EMPTY || !take(i, node)) continue;
+                int32_t q = 0;
+                if constexpr (MODE == BLK_WRAP) q = S.eq[e];
+                blk_link<MODE, B>(S, i, node, q);
+            }
+            __syncthreads();
+        };
+        unions([](uint32_t, uint32_t) { return true; });
+        if (gather()) {
+            res = BLK_SPANS;
+            T = 1;
+            if (len == 1) {
+                if (t == 0) S.total = S.nword[root[0]] & NZ_SIZE;
+            } else {
+                // 5. the smallest T: bisection over the block's first T sites, each
+                //    trial a connected-components pass over the pairs among them.
+                //    The root table's keys are not needed any more: their words
+                //    hold the sites' keys, then their ranks.
+                static_assert(BLK_RSLOTS * 4 >= B * 8, "the root table's words hold the keys");
+                //    (sorted: the positions are the ranks already)
+                int myrank = t;
+                if (!sorted) myrank = blk_rank<MODE, B>(S, reinterpret_cast<uint64_t *>(S.rkey), d, len, b0, b1);
+                __syncthreads();
+                uint16_t *ranks = reinterpret_cast<uint16_t *>(S.rkey);
+                if (act) ranks[t] = static_cast<uint16_t>(myrank);
+                auto trial = [&](int first) -> bool {
+                    __syncthreads();
+                    if (t == 0) S.flag = 0;
+                    live[0] = act && myrank < first;
+#pragma unroll
+                    for (int k = 0; k < NODES; ++k) {
+                        if (!live[k]) continue;
+                        const uint32_t n = node_of(k);
+                        S.npar[n] = W::make(n, 0);
+                        S.nword[n] = word0[k];
+                    }
+                    __syncthreads();
+                    unions([&](uint32_t i, uint32_t node) {
+                        return static_cast<int>(ranks[i]) < first && (node >= B || static_cast<int>(ranks[node]) < first);
+                    });
+                    return gather();
+                };
+                int none = 0;   // the first `none` sites do not span, the first T do
+                T = len;
+                while (T - none > 1) {
+                    const int mid = (none + T) / 2;
+                    if (trial(mid)) T = mid;
+                    else none = mid;
+                }
+                trial(T);
+                if (act && myrank == T - 1) S.total = S.nword[root[0]] & NZ_SIZE;
+            }
+            __syncthreads();
+            return res;
+        }
+    }
+
+    // 6. write back
+#pragma unroll
+    for (int k = 0; k < NODES; ++k) {
+        if (!live[k]) continue;
+        const uint32_t n = node_of(k), rt = root[k];
+        const int32_t me = k == 0 ? site : static_cast<int32_t>(S.rkey[n - B]);
+        int32_t parent = 0;
+        if (rt != n)
+            parent = rt < B ? site_of(S.pcs[lo + static_cast<int>(rt)], L) : static_cast<int32_t>(S.rkey[rt - B]);
+        m.commit(me, rt == n, S.nword[n], parent, disp[k]);
+    }
+    __syncthreads();
+    return res;
+}
+
+// The map's shift for a lattice of N sites when map_words words are there.
+__device__ __forceinline__ uint32_t map_shift(uint32_t N, uint32_t map_words)
+{
+    uint32_t ms = 0;
+    while ((((N - 1u) >> ms) >> 5) + 1u + BLK_MAP_PAD > map_words) ++ms;
+    return ms;
+}
+
+// Persistent: every workgroup pops samples (longest first) until the queue is
+// empty.  PER: periodic coordinates.
+template <int MODE, bool PER, int NT, int B>
+__global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut out)
+{
+    static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
+    static_assert(B <= NT && B <= BLK_MAXB, "thread t loads entry t of a block");
+    extern __shared__ uint32_t blk_map[];
+    __shared__ BlkLds<MODE, B> S;
+    const int t = static_cast<int>(threadIdx.x);
+    for (;;) {
+        if (t == 0) S.claim = atomicAdd(a.qhead, 1);
+        __syncthreads();
+        const int qi = __builtin_amdgcn_readfirstlane(S.claim);
+        __syncthreads();
         if (qi >= a.nqueue) break;
         const int sid = a.queue[qi];
-        if (a.state[sid].status != NZ_ST_PENDING) continue;
+        if (a.state[sid].status != NZ_ST_PENDING) continue;   // (uniform)
         const NzSample &d = a.desc[sid];
-        const int32_t L = d.L;
-        const int32_t z = d.z;
-        SweepMem<RES_HBM> m;
-        m.occ_g = reinterpret_cast<uint32_t *>(a.ws + d.off_occ);
-        m.par_g = nullptr;   // the occupancy side only; entries go through pw
-        m.parc_g = nullptr;
-        m.lbase = 0;
-        m.occ_words = 0;
-        m.sshift = 0;
-        m.sum_on = false;   // no summary: every check reads the bitset
-        uint64_t *pw = reinterpret_cast<uint64_t *>(a.ws + d.off_par);
-        const NzOffset *tab = a.tabs + d.tab;
-        int32_t ostride[NCH], od0[NCH];
-        uint32_t ocode[NCH];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int32_t j = c * 64 + static_cast<int32_t>(lane);
-            const NzOffset o = j < z ? tab[j] : NzOffset{0, 0xFFFFFFFFu};
-            ostride[c] = o.stride;
-            ocode[c] = o.code;
-            od0[c] = code_d0(o.code);
+        const int32_t L = d.L, nrows = d.rows, nb = d.nb;
+        const uint32_t N = static_cast<uint32_t>(d.N);
+        const uint32_t cap = static_cast<uint32_t>(d.cap);
+        const uint32_t *counts = reinterpret_cast<const uint32_t *>(a.ws + d.off_counts);
+        const uint32_t *sites = reinterpret_cast<const uint32_t *>(a.ws + d.off_sites);
+        const NzOffset *rows = a.tabs + d.tab;
+        BlkMem<MODE> m;
+        m.occ = reinterpret_cast<uint32_t *>(a.ws + d.off_occ);
+        m.par = reinterpret_cast<int32_t *>(a.ws + d.off_par);
+        m.parc = reinterpret_cast<int32_t *>(a.ws + d.off_parc);
+        m.pw = reinterpret_cast<uint64_t *>(a.ws + d.off_par);
+        m.map = blk_map;
+        m.mshift = map_shift(N, a.map_words);
+        m.occ_words = ((N + 63u) >> 6) << 1;
+
+        for (int k = t; k < (nrows + BLK_CHUNK - 1) / BLK_CHUNK * BLK_CHUNK; k += NT) {
+            NzOffset o;
+            o.stride = 0;
+            o.code = 0u;
+            if (k < nrows) o = rows[k];
+            S.rows[k] = o;
         }
-        int32_t r = a.state[sid].n0;
-        int32_t status = NZ_ST_BAND;
-        int32_t nstar = 0, mass = 0;
-        BandCursor bc;
-        bc.init(reinterpret_cast<const uint32_t *>(a.ws + d.off_counts),
-                reinterpret_cast<const uint32_t *>(a.ws + d.off_sites), static_cast<uint32_t>(d.cap), d.nb);
-        SiteStep<NCH, true> cur;
+        int32_t r = a.state[sid].n0;   // sites already occupied
+        // the map of the prefilled sites: from their list while it is shorter
+        // than the bitset
+        const uint32_t mwords = (((N - 1u) >> m.mshift) >> 5) + 1u;
+        const bool by_list = static_cast<uint32_t>(r) < m.occ_words;
+        for (uint32_t w = static_cast<uint32_t>(t); w < mwords + BLK_MAP_PAD; w += NT) {
+            const bool inner = w >= 1u && w <= mwords;
+            blk_map[w] = (!by_list && m.mshift == 0 && inner) ? m.occ[w - 1u] : 0u;
+        }
+        __syncthreads();
+        if (by_list) {
+            const uint32_t *prefix = reinterpret_cast<const uint32_t *>(a.ws + d.off_prefix);
+            for (int32_t k = t; k < r; k += NT) {
+                const uint32_t b = prefix[k] >> m.mshift;
+                atomicOr(&blk_map[1 + (b >> 5)], 1u << (b & 31));
+            }
+        } else if (m.mshift) {
+            for (uint32_t w = static_cast<uint32_t>(t); w < m.occ_words; w += NT) {
+                uint32_t v = m.occ[w];
+                if (!v) continue;
+                uint32_t bits = 1u;   // (mshift >= 5: the word is part of one bit)
+                if (m.mshift < 5) {
+                    bits = 0u;
+                    const uint32_t grp = (1u << (1u << m.mshift)) - 1u;
+                    for (uint32_t g = 0; g < (32u >> m.mshift); ++g)
+                        if ((v >> (g << m.mshift)) & grp) bits |= 1u << g;
+                }
+                const uint32_t b = (w << 5) >> m.mshift;
+                atomicOr(&blk_map[1 + (b >> 5)], bits << (b & 31));
+            }
+        }
+
+        int32_t smax = a.state[sid].smax;
+        int32_t status = NZ_ST_BAND, nstar = 0, mass = 0;
+        const int32_t win_lo = MODE == BLK_SMAX ? d.win_lo : 0, win_hi = MODE == BLK_SMAX ? d.win_hi : 0;
+        uint32_t *win = reinterpret_cast<uint32_t *>(a.ws + d.off_win);
+        bool done = MODE == BLK_SMAX && r >= win_lo;
+        if (done) status = NZ_ST_BACKOFF;   // the prefill covers part of the window: start lower
+
+        int32_t cb = 0;
+        int n = 0, nbk = 0;
+        bool over = false;
         uint32_t pc = 0;
-        int got = bc.next(pc, lane);
-        while (got == 1) {
-            ++r;
-            cur.prepare(m, nullptr, pc, L, ostride, ocode);
-            uint32_t total, flags;
-            wrap_step<NCH>(m.occ_g, pw, cur, od0, ostride, ocode, L, a.dcap, total, flags);
-            if (flags == NZ_FLAGS) {
-                status = NZ_ST_DONE;
-                nstar = r;
-                mass = static_cast<int32_t>(total);
+        int nb0 = 0, nb1 = 0;
+        if (!done) blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+        while (!done) {
+            while (n == 0 && nbk > 0) {
+                cb += nbk;
+                blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+            }
+            if (n == 0) {
+                if (over) status = NZ_ST_BUCKET;
                 break;
             }
-            got = bc.next(pc, lane);
+            if (t < n) S.pcs[t] = pc;
+            const int all = n, b0 = nb0, b1 = nb1;
+            // the next block's entries, loaded while this one is processed
+            cb += nbk;
+            blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+            __syncthreads();
+            bool sorted = false;
+            auto sort = [&]() {
+                if (sorted) return;
+                sorted = true;
+                const uint32_t mine = t < all ? S.pcs[t] : 0u;
+                const int rank = blk_rank<MODE, B>(S, reinterpret_cast<uint64_t *>(S.rkey), d, all, b0, b1);
+                __syncthreads();
+                if (t < all) S.pcs[rank] = mine;
+                __syncthreads();
+            };
+            if (MODE == BLK_SMAX) sort();
+            int len = all;
+            for (int lo = 0; lo < all;) {
+                int T = 0;
+                const int res = blk_step<MODE, PER, NT, B>(S, m, d, L, nrows, lo, len, sorted, b0, b1, a.blk_old, r, win_lo, win_hi,
+                                                           win, smax, T);
+                if (res == BLK_NOFIT) {
+                    sort();
+                    len = max(1, len / 2);
+                    continue;
+                }
+                if (res == BLK_SPANS) {
+                    status = NZ_ST_DONE;
+                    nstar = r + T;
+                    mass = static_cast<int32_t>(S.total);
+                    done = true;
+                    break;
+                }
+                r += len;
+                lo += len;
+                len = min(len, all - lo);
+                if (MODE == BLK_SMAX && r + 1 >= win_hi) {
+                    status = NZ_ST_DONE;
+                    done = true;
+                    break;
+                }
+            }
         }
-        if (got < 0) status = NZ_ST_BUCKET;
         if (status == NZ_ST_BAND && d.full) {
-            status = NZ_ST_DONE;   // every site occupied and nothing wraps
+            status = NZ_ST_DONE;   // the whole lattice is occupied and never spans
             nstar = 0;
             mass = 0;
         }
-        a.state[sid].status = status;
-        a.state[sid].nstar = nstar;
-        a.state[sid].mass = mass;
-        if (status == NZ_ST_DONE) {
-            const int32_t o = out.out_index[sid];
-            out.nstar[o] = nstar;
-            if (out.mass) out.mass[o] = mass;
+        if (t == 0) {
+            a.state[sid].status = status;
+            a.state[sid].nstar = nstar;
+            a.state[sid].mass = mass;
+            if (status == NZ_ST_DONE) {
+                const int32_t o = out.out_index[sid];
+                out.nstar[o] = nstar;
+                if (out.mass) out.mass[o] = mass;
+            }
         }
+        __syncthreads();   // the tables and the map are free for the next sample
     }
 }
 
@@ -2207,30 +1979,6 @@ int32_t keys_resident_wgs()
         return static_cast<int32_t>(n);
     }();
     return wgs;
-}
-
-hipError_t launch_sort(const NzSample *desc, int32_t nsamp, int32_t max_nb, int32_t max_cap, uint8_t *ws,
-                       hipStream_t st)
-{
-    if (nsamp <= 0 || max_nb <= 0) return hipSuccess;
-    uint32_t P = 2;
-    while (P < static_cast<uint32_t>(max_cap)) P <<= 1;
-    const int64_t items = static_cast<int64_t>(nsamp) * max_nb;
-    if (items > 0x7FFFFFFFll) return hipErrorInvalidValue;   // the waves step through items in 32 bits
-    // one wave per bucket; as many waves per workgroup as 64 KB of LDS holds
-    const size_t per_wave = static_cast<size_t>(P) * (sizeof(uint64_t) + sizeof(uint32_t));
-    const int waves = static_cast<int>(std::max<size_t>(1, std::min<size_t>(SORT_THREADS / 64, 65536 / per_wave)));
-    const size_t lds = per_wave * static_cast<size_t>(waves);
-    auto k = nz_sort_kernel;
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           static_cast<int>(lds));
-        if (e != hipSuccess) return e;
-    }
-    const int64_t blocks = (items + waves - 1) / waves;
-    const uint32_t grid = static_cast<uint32_t>(blocks < 65536 * 4 ? blocks : 65536 * 4);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, desc, nsamp, max_nb, P, ws);
-    return hipGetLastError();
 }
 
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t bx_hook, int32_t bx_site,
@@ -2286,82 +2034,50 @@ hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsa
     return hipGetLastError();
 }
 
-template <int NCH, int RES, bool BLOCK, bool PER, int FB = NCH>
-static hipError_t launch_sweep_t(const NzSweepArgs &a, const SweepOut &o, int grid, int wg_waves, size_t lds,
-                                 hipStream_t st)
+template <int MODE, bool PER, int NT, int B>
+static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cus, hipStream_t st)
 {
-    auto k = nz_sweep_kernel<NCH, RES, BLOCK, FB, PER>;
-    if (lds > 65536) {
+    auto k = nz_block_kernel<MODE, PER, NT, B>;
+    const size_t lds = static_cast<size_t>(a.map_words) * 4u;
+    if (lds + sizeof(BlkLds<MODE, B>) > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            static_cast<int>(lds));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * wg_waves), lds, st, a, o);
+    int wgs = 0;
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&wgs, k, NT, lds);
+    if (e != hipSuccess) return e;
+    const int grid = std::min(a.nqueue, cus * std::max(1, wgs));
+    hipLaunchKernelGGL(k, dim3(grid), dim3(NT), lds, st, a, o);
     return hipGetLastError();
 }
 
-template <int RES, bool BLOCK, bool PER = false>
-static hipError_t launch_sweep_r(int nch, bool wide_block, const NzSweepArgs &a, const SweepOut &o, int grid,
-                                 int wg_waves, size_t lds, hipStream_t st)
+// Small maps (up to L = 10): several workgroups of 256 threads share a CU.
+// Larger ones leave room for one workgroup per CU, of 1024 threads.
+template <int MODE, bool PER>
+static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint32_t max_N, size_t lds_per_wg, hipStream_t st)
 {
-    switch (nch) {
-    case 1: return launch_sweep_t<1, RES, BLOCK, PER>(a, o, grid, wg_waves, lds, st);
-    case 2: return launch_sweep_t<2, RES, BLOCK, PER>(a, o, grid, wg_waves, lds, st);
-    case 4: return launch_sweep_t<4, RES, BLOCK, PER>(a, o, grid, wg_waves, lds, st);
-    case 8: return launch_sweep_t<8, RES, BLOCK, PER>(a, o, grid, wg_waves, lds, st);
-    case 14:
-        if constexpr (BLOCK) {
-            if (!wide_block) return launch_sweep_t<14, RES, BLOCK, PER, 8>(a, o, grid, wg_waves, lds, st);
-        }
-        return launch_sweep_t<14, RES, BLOCK, PER>(a, o, grid, wg_waves, lds, st);
-    default: return hipErrorInvalidValue;
+    const uint32_t exact = ((max_N - 1u) >> 5) + 1u + BLK_MAP_PAD;
+    if (exact <= BLK_SMALL_MAP || MODE == BLK_SMAX) {
+        a.map_words = std::min(exact, BLK_SMAX_MAP);
+        return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);
     }
+    a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<MODE, 512>)) / 4));
+    return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
 }
 
-uint32_t block_lds_words() { return BLK_LDS_WORDS; }
-
-hipError_t launch_wrap_sweep(int nch, const NzSweepArgs &a, int32_t *nstar, int32_t *mass, const int32_t *out_index,
-                             int grid, hipStream_t st)
+hipError_t launch_sweep(SweepKind kind, bool periodic, const NzSweepArgs &a, int32_t *nstar, int32_t *mass,
+                        const int32_t *out_index, int cus, uint32_t max_N, size_t lds_per_wg, hipStream_t st)
 {
+    if (a.nqueue <= 0) return hipSuccess;
+    if (max_N < 1 || lds_per_wg < 65536) return hipErrorInvalidValue;
     SweepOut o{nstar, mass, out_index};
-    switch (nch) {
-    case 1: hipLaunchKernelGGL(nz_wrap_sweep_kernel<1>, dim3(grid), dim3(256), 0, st, a, o); break;
-    case 2: hipLaunchKernelGGL(nz_wrap_sweep_kernel<2>, dim3(grid), dim3(256), 0, st, a, o); break;
-    case 4: hipLaunchKernelGGL(nz_wrap_sweep_kernel<4>, dim3(grid), dim3(256), 0, st, a, o); break;
-    case 8: hipLaunchKernelGGL(nz_wrap_sweep_kernel<8>, dim3(grid), dim3(256), 0, st, a, o); break;
-    case 14: hipLaunchKernelGGL(nz_wrap_sweep_kernel<14>, dim3(grid), dim3(256), 0, st, a, o); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_sweep(int nch, bool wide_block, int residency, bool block, bool periodic, const NzSweepArgs &a,
-                        int32_t *nstar, int32_t *mass, const int32_t *out_index, int grid, int wg_waves, hipStream_t st)
-{
-    SweepOut o{nstar, mass, out_index};
-    const size_t lds = static_cast<size_t>(a.lds_words) * 4u * static_cast<size_t>(wg_waves);
-    if (periodic) {
-        if (block) return hipErrorInvalidValue;
-        switch (residency) {
-        case RES_HBM: return launch_sweep_r<RES_HBM, false, true>(nch, false, a, o, grid, wg_waves, lds, st);
-        case RES_OCC: return launch_sweep_r<RES_OCC, false, true>(nch, false, a, o, grid, wg_waves, lds, st);
-        case RES_ALL: return launch_sweep_r<RES_ALL, false, true>(nch, false, a, o, grid, wg_waves, lds, st);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    if (block) {
-        switch (residency) {
-        case RES_HBM: return launch_sweep_r<RES_HBM, true>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-        case RES_OCC: return launch_sweep_r<RES_OCC, true>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-        case RES_ALL: return launch_sweep_r<RES_ALL, true>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    switch (residency) {
-    case RES_HBM: return launch_sweep_r<RES_HBM, false>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-    case RES_OCC: return launch_sweep_r<RES_OCC, false>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-    case RES_ALL: return launch_sweep_r<RES_ALL, false>(nch, wide_block, a, o, grid, wg_waves, lds, st);
-    default: return hipErrorInvalidValue;
+    switch (kind) {
+    case SweepKind::wrap: return launch_block_t<BLK_WRAP, true>(a, o, cus, max_N, lds_per_wg, st);
+    case SweepKind::smax:
+        return periodic ? launch_block_t<BLK_SMAX, true>(a, o, cus, max_N, lds_per_wg, st)
+                        : launch_block_t<BLK_SMAX, false>(a, o, cus, max_N, lds_per_wg, st);
+    default: return periodic ? hipErrorInvalidValue : launch_block_t<BLK_SPAN, false>(a, o, cus, max_N, lds_per_wg, st);
     }
 }
 

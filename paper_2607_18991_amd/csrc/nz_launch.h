@@ -21,9 +21,6 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
                        NzState *state, int32_t max_grid, hipStream_t st);
 int32_t keys_sites_per_block();
 
-hipError_t launch_sort(const NzSample *desc, int32_t nsamp, int32_t max_nb, int32_t max_cap, uint8_t *ws,
-                       hipStream_t st);
-
 // Bulk connected components for the samples listed in list[0..nlist).
 // smax: also the largest cluster of each smax-mode sample's prefilled state.
 // wrap: the listed samples are periodic first-wrap samples (64-bit entries).
@@ -39,21 +36,16 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
 hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsamp, int32_t w, const uint8_t *ws,
                          uint64_t *out, hipStream_t st);
 
-// residency: 0 HBM, 1 bitset in LDS, 2 bitset and parents in LDS.
-// nch in {1, 2, 4, 8, 14}.  block: 64 sites per wave step (the wave's LDS
-// slice must end with block_lds_words() words for the block's site table).
-// wide_block: some block sample has z > 512, so the block path's one-site
-// fallback needs all nch chunks (else it is compiled for at most 8).
-// periodic: every sample of the chunk has periodic coordinates (largest-cluster
-// windows); such a chunk goes one site per step (block must be false).
-hipError_t launch_sweep(int nch, bool wide_block, int residency, bool block, bool periodic, const NzSweepArgs &a,
-                        int32_t *nstar, int32_t *mass, const int32_t *out_index, int grid, int wg_waves, hipStream_t st);
-uint32_t block_lds_words();
+// What the sweep looks for: the first spanning cluster (free boundaries), the
+// first cluster wrapping around axis 0 (periodic; 64-bit entries), or the
+// largest cluster over a window of n (either).
+enum class SweepKind { span, wrap, smax };
 
-// Periodic first-wrap sweep of a chunk whose samples all have wrap set; one
-// site per step, state in HBM, 256-thread workgroups.
-hipError_t launch_wrap_sweep(int nch, const NzSweepArgs &a, int32_t *nstar, int32_t *mass, const int32_t *out_index,
-                             int grid, hipStream_t st);
+// The samples of a.queue, all of one kind and boundary condition, at most max_N
+// sites each, on a device of `cus` compute units whose workgroups may use
+// lds_per_wg bytes of LDS.
+hipError_t launch_sweep(SweepKind kind, bool periodic, const NzSweepArgs &a, int32_t *nstar, int32_t *mass,
+                        const int32_t *out_index, int cus, uint32_t max_N, size_t lds_per_wg, hipStream_t st);
 
 // Host side of nz_sweep_batch_static (nz_api.cpp): whether a chunk header and
 // the largest single sample of the jobs fit a buffer of ws_bytes; and
