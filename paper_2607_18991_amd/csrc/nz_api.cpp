@@ -37,10 +37,11 @@ thread_local std::vector<int64_t> g_job_serial, g_job_pre;
 // number of dispatches
 thread_local double g_cc_ms[5] = {0, 0, 0, 0, 0};
 
-// Events around each kernel of the bulk labelling; a chunk launches it up to
-// three times (the first pass and two in-chunk backoffs).
+// Events around each kernel of the bulk labelling; a chunk launches it once per
+// group of samples and for its two in-chunk backoffs.
 struct PrefillEvents {
-    hipEvent_t ev[3][5] = {};
+    static constexpr int kSets = 24;
+    hipEvent_t ev[kSets][5] = {};
     int used = 0;
     bool ok = false;
     PrefillEvents()
@@ -382,6 +383,32 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     return s;
 }
 
+// A band that holds more than 8% of the sites (of a sample's Sizes or
+// descriptor): its keys launch keeps each sample on one XCD, from kXcdSamples
+// samples on (fewer would leave XCDs idle).  Both sides are measured at the keys
+// kernel.
+constexpr int32_t kXcdSamples = 32;
+template <typename T>
+bool wide_band(const T &s) { return std::ldexp(static_cast<double>(s.nb), s.shift - 64) > 0.08; }
+
+// Samples whose prefill lists hold like numbers of sites (within a factor of
+// four) are labelled by one launch: its grid has as many workgroups per sample
+// as the largest needs, and in one launch over lists of 2000 and 150000 sites
+// most workgroups would find nothing to do.  An empty workgroup costs some 4 ns,
+// a group's three launches some 20 us (the L = 12 periodic batch of 700 samples:
+// 2.03 ms in groups, 1.75 in one launch), so a class joins the group before it
+// unless that adds more than kEmptyWgs empty workgroups.
+constexpr int64_t kEmptyWgs = 4096;
+int prefill_group(int32_t prefix_cap)
+{
+    int g = 0;
+    while (prefix_cap > 1024) {
+        prefix_cap >>= 2;
+        ++g;
+    }
+    return g;
+}
+
 // plan_sizes of consecutive plans that share its inputs (the samples of one
 // job do) is computed once.
 struct SizesMemo {
@@ -605,17 +632,19 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             const bool wrap_chunk = chunk.front().wrap;
             const bool per_chunk = chunk.front().per;
 
-            // ---- descriptors, grouped by L for the keys launches
+            // ---- descriptors, grouped by L and band width for the keys launches
             std::vector<int32_t> byL(n);
             for (int32_t i = 0; i < n; ++i) byL[i] = i;
-            std::stable_sort(byL.begin(), byL.end(), [&](int32_t a, int32_t b) { return chunk[a].L < chunk[b].L; });
+            std::stable_sort(byL.begin(), byL.end(), [&](int32_t a, int32_t b) {
+                if (chunk[a].L != chunk[b].L) return chunk[a].L < chunk[b].L;
+                return wide_band(sizes[a]) > wide_band(sizes[b]);
+            });
             std::vector<NzSample> desc(n);
             std::vector<int32_t> out_index(n), queue(n), prefill_list;
             std::vector<int32_t> chunk_of_desc(n);
             size_t off = head;
             const int32_t keys_grid = tune.keys_resident ? (nz::keys_resident_wgs() + 1) / 2 * dev.cus : 0;
             uint32_t max_N = 0;
-            int64_t max_site = 0;
             std::vector<int32_t> desc_of_chunk(n);
             uint32_t last_mask = 0;   // offset table of the previous descriptor's (mask, L)
             int32_t last_L = 0, last_tab = 0, last_rows = 0;
@@ -666,9 +695,12 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 max_N = std::max(max_N, static_cast<uint32_t>(d.N));
                 if (d.T0 != 0) {
                     prefill_list.push_back(di);
-                    max_site = std::max<int64_t>(max_site, s.prefix_cap);
                 }
             }
+            // the labelling is launched per group of samples of like prefill sizes
+            std::stable_sort(prefill_list.begin(), prefill_list.end(), [&](int32_t a, int32_t b) {
+                return prefill_group(desc[a].prefix_cap) > prefill_group(desc[b].prefix_cap);
+            });
             for (int32_t q = 0; q < n; ++q) queue[q] = desc_of_chunk[q];   // chunk is in priority order
 
             // ---- header layout
@@ -709,22 +741,38 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 }
             }
             auto prefill_events = [&]() -> hipEvent_t * {
-                return pfe && pfe->used < 3 ? pfe->ev[pfe->used++] : nullptr;
+                return pfe && pfe->used < PrefillEvents::kSets ? pfe->ev[pfe->used++] : nullptr;
             };
             if (pe) HIP_TRY(hipEventRecord(pe->ev[0], st));
             HIP_TRY(nz::launch_clear(d_desc, nullptr, n, ws, d_state, st));
             for (int32_t a = 0; a < n;) {
                 int32_t b = a;
-                while (b < n && desc[b].N == desc[a].N) ++b;
-                HIP_TRY(nz::launch_keys(d_desc, nullptr, a, b - a, desc[a].N, ws, d_state, keys_grid, st));
+                const bool wide = wide_band(desc[a]);
+                while (b < n && desc[b].N == desc[a].N && wide_band(desc[b]) == wide) ++b;
+                HIP_TRY(nz::launch_keys(d_desc, nullptr, a, b - a, desc[a].N, ws, d_state, keys_grid,
+                                        wide && b - a >= kXcdSamples, st));
                 a = b;
             }
             if (pe) HIP_TRY(hipEventRecord(pe->ev[1], st));
             if (!prefill_list.empty()) {
-                const int32_t bx_hook = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(256, (max_site + 1023) / 1024)));
-                const int32_t bx_site = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (max_site + 1023) / 1024)));
-                HIP_TRY(nz::launch_prefill(d_desc, d_list, static_cast<int32_t>(prefill_list.size()), bx_hook, bx_site, d_tabs, ws,
-                                           d_state, smax != nullptr, wrap_chunk, per_chunk, st, prefill_events()));
+                for (size_t g = 0; g < prefill_list.size();) {
+                    const int32_t most = desc[prefill_list[g]].prefix_cap;
+                    size_t e = g;
+                    while (e < prefill_list.size()) {
+                        // the samples of one size class, if a launch of their own saves
+                        // enough empty workgroups
+                        size_t c = e;
+                        const int cls = prefill_group(desc[prefill_list[e]].prefix_cap);
+                        while (c < prefill_list.size() && prefill_group(desc[prefill_list[c]].prefix_cap) == cls) ++c;
+                        const int64_t empty = static_cast<int64_t>(c - e) * (most - desc[prefill_list[e]].prefix_cap) / 1024;
+                        if (e > g && empty > kEmptyWgs) break;
+                        e = c;
+                    }
+                    HIP_TRY(nz::launch_prefill(d_desc, d_list + g, static_cast<int32_t>(e - g),
+                                               desc[prefill_list[g]].prefix_cap, d_tabs, ws, d_state, smax != nullptr,
+                                               wrap_chunk, per_chunk, st, prefill_events()));
+                    g = e;
+                }
                 // Resolve backoffs inside the chunk: samples whose bulk state already
                 // spans are re-keyed and re-labelled from n0 - b, and if that spans
                 // too from n0 - 3b, so they join this chunk's sweep instead of a
@@ -751,16 +799,18 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                     if (again.empty()) break;
                     std::stable_sort(again.begin(), again.end(), [&](int32_t a, int32_t b) { return desc[a].N < desc[b].N; });
                     const int32_t na = static_cast<int32_t>(again.size());
+                    int32_t max_prefix = 0;
+                    for (int32_t di : again) max_prefix = std::max(max_prefix, desc[di].prefix_cap);
                     HIP_TRY(hipMemcpyAsync(d_desc, desc.data(), n * sizeof(NzSample), hipMemcpyHostToDevice, st));
                     HIP_TRY(hipMemcpyAsync(d_list, again.data(), na * sizeof(int32_t), hipMemcpyHostToDevice, st));
                     HIP_TRY(nz::launch_clear(d_desc, d_list, na, ws, d_state, st));
                     for (int32_t a = 0; a < na;) {
                         int32_t b = a;
                         while (b < na && desc[again[b]].N == desc[again[a]].N) ++b;
-                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, b - a, desc[again[a]].N, ws, d_state, keys_grid, st));
+                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, b - a, desc[again[a]].N, ws, d_state, keys_grid, false, st));
                         a = b;
                     }
-                    HIP_TRY(nz::launch_prefill(d_desc, d_list, na, bx_hook, bx_site, d_tabs, ws, d_state, smax != nullptr,
+                    HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, d_tabs, ws, d_state, smax != nullptr,
                                                wrap_chunk, per_chunk, st, prefill_events()));
                 }
             }

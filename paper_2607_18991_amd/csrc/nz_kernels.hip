@@ -191,6 +191,15 @@ constexpr int KEYS_SITES_PER_BLOCK = KEYS_THREADS * 2 * KEYS_ITERS;
 static_assert(KEYS_ITERS % 16 == 0 && KEYS_ITERS <= 64, "whole 64-word groups; lane it keeps iteration it");
 static_assert(KEYS_SITES_PER_BLOCK == (KEYS_THREADS / 64) * KEYS_WAVE_SITES, "waves tile the block");
 
+// by_xcd: the workgroups of one sample share blockIdx mod 8, so that they are
+// dispatched to one XCD: the sample's band buckets and their counters, which
+// every workgroup of the sample appends to, then stay in one L2 and a bucket's
+// lines fill there.  Measured alone (1000 samples, L = 16): zone 1 plain, 16% of
+// the sites in the band, 11.1 -> 7.5 ms (L = 24, 200 samples: 19.5 -> 10.9);
+// with 4% or less in the band the spread over all XCDs is faster (zones 1-2
+// plain 1.50 against 1.88 ms, zone 1 prefilled 1.38 against 1.87), and few
+// samples would leave XCDs idle; the planner draws the line at 8%.
+
 // Predicate code of an unsigned less-than for the lane-mask compare builtins.
 constexpr int kIcmpUlt = 36;
 
@@ -326,8 +335,8 @@ __device__ __forceinline__ void keys_iters(const KeysIter &k, uint32_t &be_lo, u
 }
 
 __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
-                                           int32_t first, int32_t blocks_per_sample, uint8_t *__restrict__ ws,
-                                           NzState *__restrict__ state, int32_t vblock)
+                                           int32_t first, int32_t count, bool by_xcd, int32_t blocks_per_sample,
+                                           uint8_t *__restrict__ ws, NzState *__restrict__ state, int32_t vblock)
 {
     // Every wave works alone on its own KEYS_WAVE_SITES consecutive sites: no
     // workgroup barrier, so a wave that waits for its list atomic or its
@@ -337,9 +346,15 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     // site's list position is that of its word plus the set bits below it.
     __shared__ uint64_t bq_key[KEYS_THREADS / 64][KEYS_BQ];
     __shared__ uint32_t bq_site[KEYS_THREADS / 64][KEYS_BQ];
-    const int which = vblock / blocks_per_sample;
+    int which = vblock / blocks_per_sample;
+    int blk = vblock % blocks_per_sample;
+    if (by_xcd) {
+        const int k = vblock >> 3;
+        which = (k / blocks_per_sample) * 8 + (vblock & 7);
+        blk = k % blocks_per_sample;
+        if (which >= count) return;   // (uniform over the workgroup)
+    }
     const int sid = list ? list[first + which] : first + which;
-    const int blk = vblock % blocks_per_sample;
     const NzSample &d = desc[sid];
     const uint32_t N = static_cast<uint32_t>(d.N);
     const uint32_t lane = lane_id();
@@ -468,11 +483,21 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
         cnt[g] = __builtin_amdgcn_readlane(incl, 63);
         total += cnt[g];
     }
-    if (total == 0u) return;   // wave-uniform
+    uint32_t *wpos = reinterpret_cast<uint32_t *>(ws + d.off_wpos);
+    if (total == 0u) {   // wave-uniform
+        // no prefilled site: the words' positions are stored all the same (any
+        // position will do: the sweep checks the entry it finds there)
+        if (!d.wrap)
+#pragma unroll
+            for (int g = 0; g < KEYS_GROUPS; ++g) {
+                const uint32_t w = w0 + 64u * static_cast<uint32_t>(g) + lane;
+                if (mine[g] && w < occ_words) wpos[w] = 0u;
+            }
+        return;
+    }
     uint32_t got = 0u;
     if (lane == 0u) got = atomicAdd(reinterpret_cast<uint32_t *>(&state[sid].n0), total);
     uint32_t base = __builtin_amdgcn_readlane(got, 0);
-    uint32_t *wpos = reinterpret_cast<uint32_t *>(ws + d.off_wpos);
     const uint32_t cap = static_cast<uint32_t>(d.prefix_cap);
     int32_t *parc = reinterpret_cast<int32_t *>(ws + d.off_parc);
 #pragma unroll
@@ -501,12 +526,12 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
 // Workgroup g takes the blocks g, g + gridDim.x, ... of the launch (one pass
 // when the grid has a workgroup per block).
 __global__ __launch_bounds__(KEYS_THREADS) void nz_keys_kernel(const NzSample *__restrict__ desc,
-                                                               const int32_t *__restrict__ list, int32_t first,
-                                                               int32_t blocks_per_sample, int32_t nblocks,
+                                                               const int32_t *__restrict__ list, int32_t first, int32_t count,
+                                                               bool by_xcd, int32_t blocks_per_sample, int32_t nblocks,
                                                                uint8_t *__restrict__ ws, NzState *__restrict__ state)
 {
     for (int32_t vb = static_cast<int32_t>(blockIdx.x); vb < nblocks; vb += static_cast<int32_t>(gridDim.x)) {
-        keys_block(desc, list, first, blocks_per_sample, ws, state, vb);
+        keys_block(desc, list, first, count, by_xcd, blocks_per_sample, ws, state, vb);
     }
 }
 
@@ -519,18 +544,6 @@ __global__ __launch_bounds__(KEYS_THREADS) void nz_keys_kernel(const NzSample *_
 // (wavefront-scope accesses): a stale entry is still an ancestor (or a former
 // root), which can only make a CAS fail and retry from the value it returns,
 // one true step further up; path-halving writes store an ancestor.
-
-__device__ __forceinline__ int32_t cc_find(int32_t *par, int32_t x)
-{
-    int32_t p = ld_w(&par[x]);
-    while (p != x) {
-        const int32_t g = ld_w(&par[p]);
-        if (g != p) st_w(&par[x], g);   // halving: x skips to its grandparent
-        x = p;
-        p = g;
-    }
-    return x;
-}
 
 // Workgroup l of a prefill launch covers block x of sample slot y.  The
 // workgroups of one sample share l mod 8, so they are dispatched to the same
@@ -549,9 +562,9 @@ __device__ __forceinline__ bool xcd_slot(int32_t nlist, int32_t bx, int32_t &y, 
 // of a sample is 4 bytes per prefilled site and stays in the L2 of the XCD that
 // holds the sample.  The list position of an occupied neighbour t is the
 // position of its bitset word (wpos) plus the set bits below t in that word.
-// The size pass points the lattice entry of every prefilled site at the list
-// node of its cluster's root; the prefilled roots keep their root words in the
-// list forest, where the sweep reads and updates them.
+// The forest stays what it is through the sweep: prefilled sites have no lattice
+// entries, their roots keep their root words in it, and band sites link to its
+// nodes.
 
 // A union-find node id: a lattice site s (< 2^29) or LIST_NODE | i, list entry
 // i of the sample's prefilled sites.  Parent entries hold node ids or root
@@ -565,7 +578,8 @@ constexpr int32_t LIST_NODE = 0x20000000;
 // slot by slot would run one round of dependent finds per slot with most lanes
 // idle.  They are appended to a per-wave edge buffer in LDS instead, and the
 // buffer is linked 64 edges at a time, every lane with an edge of its own.
-constexpr int HOOK_UNROLL = 8;
+constexpr int HOOK_UNROLL = 6;   // rows checked together
+constexpr int HOOKW_UNROLL = 8;  // half as many rows (each has an entry per side)
 // edges buffered per wave: one offset slot adds at most 64, and the buffer is
 // emptied whenever it holds 64 or more (a small buffer leaves LDS for more
 // resident workgroups: this kernel is bound by the latency of its dependent
@@ -581,17 +595,29 @@ constexpr int32_t HOOK_SUM_MAX = 1025;
 // CAS returns.
 __device__ __forceinline__ void cc_link(int32_t *par, int32_t a, int32_t b)
 {
-    int32_t u = cc_find(par, a);
-    int32_t v = cc_find(par, b);
-    while (u != v) {
+    for (;;) {
+        // both finds in step, so that their loads overlap; path splitting: every
+        // entry on the way skips to its grandparent
+        int32_t u = a, v = b;
+        int32_t pu = ld_w(&par[u]), pv = ld_w(&par[v]);
+        while (pu != u || pv != v) {
+            const int32_t gu = ld_w(&par[pu]), gv = ld_w(&par[pv]);
+            if (gu != pu) st_w(&par[u], gu);
+            if (gv != pv) st_w(&par[v], gv);
+            u = pu;
+            v = pv;
+            pu = gu;
+            pv = gv;
+        }
+        if (u == v) return;
         const int32_t hi = max(u, v), lo = min(u, v);
         int32_t expected = hi;
         if (__hip_atomic_compare_exchange_strong(&par[hi], &expected, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
-            break;
+            return;
         // hi is no longer a root: go on from the parent the CAS returned
-        u = cc_find(par, u == hi ? expected : u);
-        v = cc_find(par, v == hi ? expected : v);
+        a = expected;
+        b = lo;
     }
 }
 
@@ -642,6 +668,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
     const uint32_t wave = threadIdx.x >> 6;
     int32_t *ei = ebuf_i[wave];
     int32_t *ej = ebuf_j[wave];
+    int32_t ne = 0;   // edges in the buffer (wave-uniform), carried from pass to pass
     // the wave's 64 sites per pass (wave-uniform loop; lanes past n0 idle)
     for (int32_t ib = x * 256 + static_cast<int32_t>(wave) * 64; ib < n0; ib += bx * 256) {
         const int32_t i = ib + static_cast<int32_t>(lane);
@@ -652,14 +679,34 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                                   (allowed_axis((pc >> 12) & 63, L) << 10) | (allowed_axis((pc >> 18) & 63, L) << 15) |
                                   (allowed_axis(pc >> 24, L) << 20))
                                : 0u;
-        int32_t ne = 0;   // edges in the buffer (wave-uniform)
+        int32_t below = -1;   // the first neighbour found with a smaller list position
+        // appends the lanes' edges (i, j) and links the buffer when it is full
+        auto push = [&](bool edge, int32_t j) {
+            const uint64_t mk = __ballot(edge);
+            if (edge) {
+                const int32_t e = ne + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                                           static_cast<uint32_t>(mk >> 32),
+                                           __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
+                st_w(&ei[e], i);
+                st_w(&ej[e], j);
+            }
+            ne += static_cast<int32_t>(__popcll(mk));
+            if (ne >= 64) {
+                // link the last 64; the rest stays for a later round
+                __builtin_amdgcn_wave_barrier();
+                ne -= 64;
+                hook_flush(par, ei + ne, ej + ne, 64, lane);
+                __builtin_amdgcn_wave_barrier();
+            }
+        };
         const int32_t x0 = static_cast<int32_t>(pc & 63);
         for (int32_t k0 = 0; k0 < rh; k0 += HOOK_UNROLL) {
             // side 1 (periodic only): the steps that leave along axis 0, on the
             // other side of the row
             for (int side = 0; side < (PER ? 2 : 1); ++side) {
                 int32_t b[HOOK_UNROLL];
-                uint32_t v[HOOK_UNROLL], w0[HOOK_UNROLL], w1[HOOK_UNROLL], par0[HOOK_UNROLL];
+                uint32_t v[HOOK_UNROLL], w0[HOOK_UNROLL], w1[HOOK_UNROLL];
+                uint32_t par0 = 0u;   // parities of the first words' indexes
 #pragma unroll
                 for (int q = 0; q < HOOK_UNROLL; ++q) {
                     NzOffset o;
@@ -679,7 +726,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                     const int32_t c = __builtin_ctz(dm | 32u);
                     const uint32_t p0 = dm ? static_cast<uint32_t>(b[q] + c) : 0u;
                     const uint32_t wi = p0 >> 5;
-                    par0[q] = wi & 1u;   // parity of the first word's index
+                    par0 |= (wi & 1u) << q;
                     const bool maybe = !use_sum || ((hsum[(wi >> gs) >> 5] >> ((wi >> gs) & 31)) & 1u);
                     w0[q] = dm && maybe ? occ[wi] : 0u;
                     w1[q] = 0u;
@@ -698,39 +745,42 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                     jw[q] = v[q] ? wpos[static_cast<uint32_t>(b[q] + __builtin_ctz(v[q])) >> 5] : 0u;
 #pragma unroll
                 for (int q = 0; q < HOOK_UNROLL; ++q) {
-                    uint64_t mk = __ballot(v[q] != 0u);
                     bool first = true;
-                    while (mk) {
+                    while (__ballot(v[q] != 0u)) {
+                        bool edge = false;
+                        int32_t j = 0;
                         if (v[q]) {
-                            const int j = __builtin_ctz(v[q]);
-                            const uint32_t p = static_cast<uint32_t>(b[q] + j);
-                            // the word that holds p: the window's first or second
-                            const uint32_t word = ((p >> 5) & 1u) == par0[q] ? w0[q] : w1[q];
-                            if (!first) jw[q] = wpos[p >> 5];
-                            const int32_t e = ne + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
-                                                       static_cast<uint32_t>(mk >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
-                            st_w(&ei[e], i);
-                            st_w(&ej[e], static_cast<int32_t>(jw[q] + static_cast<uint32_t>(__popc(word & ((1u << (p & 31)) - 1u)))));
+                            const int c = __builtin_ctz(v[q]);
                             v[q] &= v[q] - 1u;
+                            const uint32_t p = static_cast<uint32_t>(b[q] + c);
+                            if (!first) jw[q] = wpos[p >> 5];
+                            // the word that holds p: the window's first or second
+                            const uint32_t word = ((p >> 5) & 1u) == ((par0 >> q) & 1u) ? w0[q] : w1[q];
+                            j = static_cast<int32_t>(jw[q] + static_cast<uint32_t>(__popc(word & ((1u << (p & 31)) - 1u))));
+                            // the first neighbour below is linked without finds (at the end)
+                            edge = below >= 0 || j > i;
+                            if (!edge) below = j;
                         }
-                        ne += static_cast<int32_t>(__popcll(mk));
-                        if (ne >= 64) {
-                            __builtin_amdgcn_wave_barrier();
-                            hook_flush(par, ei, ej, ne, lane);
-                            __builtin_amdgcn_wave_barrier();
-                            ne = 0;
-                        }
+                        push(edge, j);
                         first = false;
-                        mk = __ballot(v[q] != 0u);
                     }
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        hook_flush(par, ei, ej, ne, lane);
-        __builtin_amdgcn_wave_barrier();
+        // Links go from larger to smaller positions, so every entry's root is at
+        // or below it: i may point at any smaller member of a neighbour's tree
+        // as long as it is a root itself.  One CAS, no finds; an entry that
+        // another wave has already linked takes the ordinary way.
+        bool left = false;
+        if (below >= 0) {
+            int32_t expected = i;
+            left = !__hip_atomic_compare_exchange_strong(&par[i], &expected, below, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+        }
+        push(left, below);
     }
+    __builtin_amdgcn_wave_barrier();
+    hook_flush(par, ei, ej, ne, lane);
 }
 
 __device__ __forceinline__ uint32_t border_flags(uint32_t s, uint32_t L, uint64_t magic)
@@ -739,8 +789,10 @@ __device__ __forceinline__ uint32_t border_flags(uint32_t s, uint32_t L, uint64_
     return (x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u);
 }
 
-// Compress: every member points straight at its root, and every root takes its
-// root word (size 1 plus its own border flags).  Each thread writes only its
+// Compress: every member points straight at its root's node, and every root
+// takes its root word: its own border flags, and size 1 in largest-cluster runs.
+// The other runs keep no sizes of prefilled clusters (size 0): the sweep counts
+// the members of the one cluster whose mass is asked for.  Each thread writes only its
 // own entry and walks the forest read-only: a halving write here could replace
 // an entry another thread has already pointed at its root with a non-root
 // ancestor.  Roots never change in this kernel, so a walk stops at an entry that
@@ -761,28 +813,31 @@ __global__ __launch_bounds__(256) void nz_compress_kernel(const NzSample *__rest
     for (int32_t k = x * 256 + static_cast<int32_t>(threadIdx.x); k < n0; k += bx * 256) {
         int32_t r = k;
         int32_t p = ld_w(&par[r]);
-        while (p >= 0 && p != r) {
-            r = p;
+        while (p >= 0 && (p & (LIST_NODE - 1)) != r) {
+            r = p & (LIST_NODE - 1);   // (an entry already pointed at its root is a node id)
             p = ld_w(&par[r]);
         }
         if (r == k) {
             const uint32_t fl = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
-            st_w(&par[k], static_cast<int32_t>(NZ_ROOT | fl | 1u));
+            st_w(&par[k], static_cast<int32_t>(NZ_ROOT | fl | (d.smax_mode ? 1u : 0u)));
             if (fl == NZ_FLAGS) state[sid].status = NZ_ST_BACKOFF;   // L = 1: one site spans
         } else {
-            st_w(&par[k], r);
+            st_w(&par[k], LIST_NODE | r);
         }
     }
 }
 
-// Sizes, border flags and lattice entries of the prefilled sites, in one pass
-// over the list: a member adds itself to its root's word in the list forest,
-// and the lattice entry of every prefilled site points at the list node of its
-// cluster's root (its own node for a root), where the sweep reads and updates
-// the root word.  The flag OR returns the previous word, so the member that
-// completes a root's pair of border flags sees it: the state already spans and
-// the sample backs off (not in largest-cluster runs, which stop below the
-// window instead).
+// Border flags of the prefilled clusters (and their sizes in largest-cluster
+// runs): a site on a border adds its flag to its root's word in the list forest.
+// The flag OR returns the previous word, so the site that completes a root's
+// pair of flags sees it: the state already spans and the sample backs off (not
+// in largest-cluster runs, which stop below the window instead).
+//
+// A size for every cluster would take an atomic per member, and lattice entries
+// a scattered 4-byte write per site: for 1000 samples of L = 16, zone 1 this
+// pass took 3.9 ms with both, 2.1 with the lattice entries alone, and takes 0.6
+// with the flags alone.  The sweep finds a prefilled site's list entry from its
+// bitset word instead, and counts the members of the spanning cluster.
 __global__ __launch_bounds__(256) void nz_accum_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
                                                        int32_t nlist, int32_t bx, uint8_t *__restrict__ ws,
                                                        NzState *__restrict__ state)
@@ -797,26 +852,25 @@ __global__ __launch_bounds__(256) void nz_accum_kernel(const NzSample *__restric
         if (x == 0 && threadIdx.x == 0) state[sid].status = NZ_ST_PREFIX;
         return;
     }
+    const bool sizes = d.smax_mode != 0;
+    if (d.periodic && !sizes) return;   // nothing to add (uniform)
     const uint32_t L = static_cast<uint32_t>(d.L);
     int32_t *parc = reinterpret_cast<int32_t *>(ws + d.off_parc);
-    int32_t *par = reinterpret_cast<int32_t *>(ws + d.off_par);
     const uint32_t *prefix = reinterpret_cast<const uint32_t *>(ws + d.off_prefix);
     bool spans = false;
     for (int32_t k = x * 256 + static_cast<int32_t>(threadIdx.x); k < n0; k += bx * 256) {
+        const uint32_t fl = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
+        if (!fl && !sizes) continue;
         const int32_t r = parc[k];
-        const uint32_t site = prefix[k];
-        if (r >= 0) {
-            uint32_t *root = reinterpret_cast<uint32_t *>(&parc[r]);
-            atomicAdd(root, 1u);
-            const uint32_t fl = d.periodic ? 0u : border_flags(site, L, d.magic);
-            if (fl) {
-                const uint32_t old = atomicOr(root, fl);
-                spans = spans || ((old | fl) & NZ_FLAGS) == NZ_FLAGS;
-            }
+        if (r < 0) continue;   // a root: its word holds its own flags and size
+        uint32_t *root = reinterpret_cast<uint32_t *>(&parc[r & (LIST_NODE - 1)]);
+        if (sizes) atomicAdd(root, 1u);
+        if (fl) {
+            const uint32_t old = atomicOr(root, fl);
+            spans = spans || ((old | fl) & NZ_FLAGS) == NZ_FLAGS;
         }
-        par[site] = LIST_NODE | (r >= 0 ? r : k);
     }
-    if (spans && !d.smax_mode) state[sid].status = NZ_ST_BACKOFF;
+    if (spans && !sizes) state[sid].status = NZ_ST_BACKOFF;
 }
 
 // Largest cluster of the prefilled state (smax mode): every root word offers
@@ -929,13 +983,13 @@ __global__ __launch_bounds__(256) void nz_hookw_kernel(const NzSample *__restric
                            (allowed_axis(pc >> 24, L) << 20);
         int32_t u = -1, Du = 0;   // a root (or ancestor) of s and the displacement of s from it
         const int32_t x0 = static_cast<int32_t>(pc & 63);
-        for (int32_t k0 = 0; k0 < 2 * rh; k0 += HOOK_UNROLL) {
+        for (int32_t k0 = 0; k0 < 2 * rh; k0 += HOOKW_UNROLL) {
             // entry k: row k / 2; odd entries are the steps that leave along axis
             // 0, on the other side of the row
-            int32_t b[HOOK_UNROLL];
-            uint32_t v[HOOK_UNROLL];
+            int32_t b[HOOKW_UNROLL];
+            uint32_t v[HOOKW_UNROLL];
 #pragma unroll
-            for (int q = 0; q < HOOK_UNROLL; ++q) {
+            for (int q = 0; q < HOOKW_UNROLL; ++q) {
                 NzOffset o;
                 o.stride = 0;
                 o.code = 0u;
@@ -952,7 +1006,7 @@ __global__ __launch_bounds__(256) void nz_hookw_kernel(const NzSample *__restric
                 v[q] = (__builtin_amdgcn_alignbit(w1, w0, p0 & 31u) << c) & dm;
             }
 #pragma unroll
-            for (int q = 0; q < HOOK_UNROLL; ++q) {
+            for (int q = 0; q < HOOKW_UNROLL; ++q) {
               while (v[q]) {
                 const int j = __builtin_ctz(v[q]);
                 v[q] &= v[q] - 1u;
@@ -1171,6 +1225,7 @@ struct BlkLds {
     uint32_t smax[MODE == BLK_SMAX ? B : 1];
     int32_t ecnt, nroots, flag, bad, claim;
     uint32_t total;                    // spanning: the size of the cluster of the T-th site
+    uint32_t croot;                    //           and its root node
 };
 
 __device__ __forceinline__ uint32_t blk_hash(uint32_t t) { return (t * 0x9E3779B1u) >> 22; }
@@ -1217,6 +1272,9 @@ struct BlkMem {
     int32_t *par;
     int32_t *parc;
     uint64_t *pw;
+    const uint32_t *wpos;     // per bitset word: list position of its first prefilled site
+    const uint32_t *prefix;   // prefilled sites in list order
+    int32_t n0;               // how many
     uint32_t *map;      // LDS
     uint32_t mshift;
     uint32_t occ_words;
@@ -1250,6 +1308,25 @@ struct BlkMem {
         if (i >= LIST_NODE) st_g(&parc[i - LIST_NODE], v);
         else st_g(&par[i], v);
     }
+    // List position of an occupied site t, -1 if it is no prefilled one.  With an
+    // exact map the bitset holds the prefilled sites only: the position of t's
+    // word plus the set bits below t.  Else band sites have been added to the
+    // bitset: the entry is looked for from that position down (each band site
+    // below t in its word puts it one too far).
+    __device__ __forceinline__ int32_t list_entry(int32_t t) const
+    {
+        const uint32_t w = static_cast<uint32_t>(t) >> 5, bit = static_cast<uint32_t>(t) & 31u;
+        const uint32_t word = ld_g(&occ[w]);
+        int32_t k = static_cast<int32_t>(wpos[w] + static_cast<uint32_t>(__popc(word & ((1u << bit) - 1u))));
+        if (mshift == 0) return (word >> bit) & 1u ? k : -1;
+        for (const int32_t last = static_cast<int32_t>(wpos[w]); k >= last; --k) {
+            if (k >= n0) continue;
+            const uint32_t p = prefix[k];
+            if (p == static_cast<uint32_t>(t)) return k;
+            if (p < static_cast<uint32_t>(t) && (p >> 5) == w) break;   // (a word's entries ascend)
+        }
+        return -1;
+    }
     // Entry of an occupied site: the block position if it carries the mark, else
     // -1 with its root, root word and displacement from the root (path halving).
     __device__ __forceinline__ int resolve(int32_t t, int32_t &root, uint32_t &word, int32_t &disp) const
@@ -1277,7 +1354,14 @@ struct BlkMem {
             root = x;
             word = static_cast<uint32_t>(wpar(e));
         } else {
-            int32_t x = t, v = ld_g(&par[t]);
+            int32_t x = t, v = ld_g(&par[t]);   // (a prefilled site has no entry: unused then)
+            if (n0 > 0) {
+                const int32_t k = list_entry(t);
+                if (k >= 0) {
+                    x = LIST_NODE | k;
+                    v = ld_g(&parc[k]);
+                }
+            }
             if (v >= BLK_MARK) return v & (BLK_MAXB - 1);
             while (v >= 0) {
                 const int32_t g = par_ld(v);
@@ -1527,8 +1611,8 @@ enum { BLK_COMMITTED = 0, BLK_SPANS = 1, BLK_NOFIT = 2 };
 // order, else the whole block, position t in bucket positions b0 .. b1 - 1).  BLK_COMMITTED: merged,
 // and no cluster spans.  BLK_NOFIT: nothing has changed (up to path halving).
 // BLK_SPANS: T is the smallest number of the block's sites, in (key, site)
-// order, after which a cluster spans and S.total that cluster's size; the
-// sample is over and its state is left as it is.  Largest-cluster sweep (sites
+// order, after which a cluster spans and S.total that cluster's size (of a
+// prefilled sample: its band sites); the sample is over.  Largest-cluster sweep (sites
 // in order): the window entries of the block are written and smax carries the
 // running maximum.
 template <int MODE, bool PER, int NT, int B>
@@ -1631,6 +1715,7 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
     static_assert(BLK_RSLOTS % NT == 0, "whole slots per thread");
     bool live[NODES];
     uint32_t root[NODES], word0[NODES];
+    int32_t key0[NODES];
     int32_t disp[NODES];
     auto node_of = [&](int k) { return static_cast<uint32_t>(k == 0 ? t : B + (k - 1) * NT + t); };
 #pragma unroll
@@ -1640,6 +1725,7 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
         root[k] = n;
         disp[k] = 0;
         word0[k] = k == 0 ? pos_word : (live[k] ? S.nword[n] : 0u);
+        key0[k] = k == 0 ? site : static_cast<int32_t>(S.rkey[n - B]);
     }
     // roots of the live nodes; sizes and flags into the roots.  True: a cluster
     // spans.  (two barriers inside, the last one at the end)
@@ -1712,7 +1798,10 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
             res = BLK_SPANS;
             T = 1;
             if (len == 1) {
-                if (t == 0) S.total = S.nword[root[0]] & NZ_SIZE;
+                if (t == 0) {
+                    S.total = S.nword[root[0]] & NZ_SIZE;
+                    S.croot = root[0];
+                }
             } else {
                 // 5. the smallest T: bisection over the block's first T sites, each
                 //    trial a connected-components pass over the pairs among them.
@@ -1750,9 +1839,20 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
                     else none = mid;
                 }
                 trial(T);
-                if (act && myrank == T - 1) S.total = S.nword[root[0]] & NZ_SIZE;
+                if (act && myrank == T - 1) {
+                    S.total = S.nword[root[0]] & NZ_SIZE;
+                    S.croot = root[0];
+                }
             }
             __syncthreads();
+            // the earlier clusters of the spanning one get both border flags, by
+            // which their prefilled members are counted
+            if (MODE == BLK_SPAN && m.n0 > 0) {
+#pragma unroll
+                for (int k = 1; k < NODES; ++k)
+                    if (live[k] && root[k] == S.croot) m.par_st(key0[k], static_cast<int32_t>(NZ_ROOT | NZ_FLAGS));
+                __syncthreads();
+            }
             return res;
         }
     }
@@ -1762,11 +1862,10 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
     for (int k = 0; k < NODES; ++k) {
         if (!live[k]) continue;
         const uint32_t n = node_of(k), rt = root[k];
-        const int32_t me = k == 0 ? site : static_cast<int32_t>(S.rkey[n - B]);
         int32_t parent = 0;
         if (rt != n)
             parent = rt < B ? site_of(S.pcs[lo + static_cast<int>(rt)], L) : static_cast<int32_t>(S.rkey[rt - B]);
-        m.commit(me, rt == n, S.nword[n], parent, disp[k]);
+        m.commit(key0[k], rt == n, S.nword[n], parent, disp[k]);
     }
     __syncthreads();
     return res;
@@ -1783,7 +1882,7 @@ __device__ __forceinline__ uint32_t map_shift(uint32_t N, uint32_t map_words)
 // Persistent: every workgroup pops samples (longest first) until the queue is
 // empty.  PER: periodic coordinates.
 template <int MODE, bool PER, int NT, int B>
-__global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut out)
+__global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut out)
 {
     static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
     static_assert(B <= NT && B <= BLK_MAXB, "thread t loads entry t of a block");
@@ -1810,6 +1909,8 @@ __global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut ou
         m.par = reinterpret_cast<int32_t *>(a.ws + d.off_par);
         m.parc = reinterpret_cast<int32_t *>(a.ws + d.off_parc);
         m.pw = reinterpret_cast<uint64_t *>(a.ws + d.off_par);
+        m.wpos = reinterpret_cast<const uint32_t *>(a.ws + d.off_wpos);
+        m.prefix = reinterpret_cast<const uint32_t *>(a.ws + d.off_prefix);
         m.map = blk_map;
         m.mshift = map_shift(N, a.map_words);
         m.occ_words = ((N + 63u) >> 6) << 1;
@@ -1821,7 +1922,9 @@ __global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut ou
             if (k < nrows) o = rows[k];
             S.rows[k] = o;
         }
-        int32_t r = a.state[sid].n0;   // sites already occupied
+        const int32_t n0 = a.state[sid].n0;
+        int32_t r = n0;                // sites already occupied
+        m.n0 = n0;
         // the map of the prefilled sites: from their list while it is shorter
         // than the bitset
         const uint32_t mwords = (((N - 1u) >> m.mshift) >> 5) + 1u;
@@ -1832,9 +1935,8 @@ __global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut ou
         }
         __syncthreads();
         if (by_list) {
-            const uint32_t *prefix = reinterpret_cast<const uint32_t *>(a.ws + d.off_prefix);
-            for (int32_t k = t; k < r; k += NT) {
-                const uint32_t b = prefix[k] >> m.mshift;
+            for (int32_t k = t; k < n0; k += NT) {
+                const uint32_t b = m.prefix[k] >> m.mshift;
                 atomicOr(&blk_map[1 + (b >> 5)], 1u << (b & 31));
             }
         } else if (m.mshift) {
@@ -1906,6 +2008,30 @@ __global__ __launch_bounds__(NT) void nz_block_kernel(NzSweepArgs a, SweepOut ou
                     status = NZ_ST_DONE;
                     nstar = r + T;
                     mass = static_cast<int32_t>(S.total);
+                    // S.total counts the band sites alone (prefilled clusters keep no
+                    // sizes): the prefilled members of the cluster, whose roots carry
+                    // both flags now
+                    if (MODE == BLK_SPAN && n0 > 0 && out.mass) {
+                        int32_t members = 0;
+                        for (int32_t k0 = t; k0 < n0; k0 += 4 * NT) {
+                            int32_t v[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) v[q] = k0 + q * NT < n0 ? ld_g(&m.parc[k0 + q * NT]) : -1;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (v[q] >= 0) v[q] = m.par_ld(v[q]);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                while (v[q] >= 0) v[q] = m.par_ld(v[q]);
+                                if (k0 + q * NT < n0 && (static_cast<uint32_t>(v[q]) & NZ_FLAGS) == NZ_FLAGS) ++members;
+                            }
+                        }
+#pragma unroll
+                        for (int o = 1; o < 64; o <<= 1) members += __shfl_xor(members, o);
+                        if ((t & 63) == 0 && members) atomicAdd(&S.total, static_cast<uint32_t>(members));
+                        __syncthreads();
+                        mass = static_cast<int32_t>(S.total);
+                    }
                     done = true;
                     break;
                 }
@@ -1956,15 +2082,17 @@ hipError_t launch_clear(const NzSample *desc, const int32_t *list, int32_t nsamp
 }
 
 hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first, int32_t count, int32_t N, uint8_t *ws,
-                       NzState *state, int32_t max_grid, hipStream_t st)
+                       NzState *state, int32_t max_grid, bool by_xcd, hipStream_t st)
 {
     if (count <= 0) return hipSuccess;
     const int32_t bps = (N + KEYS_SITES_PER_BLOCK - 1) / KEYS_SITES_PER_BLOCK;
-    const int64_t blocks = static_cast<int64_t>(bps) * count;
+    const int32_t slots = by_xcd ? (count + 7) / 8 * 8 : count;
+    const int64_t blocks = static_cast<int64_t>(bps) * slots;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const int64_t grid = max_grid > 0 ? std::min<int64_t>(blocks, max_grid) : blocks;
+    // (a multiple of 8, so that a workgroup's later blocks keep their XCD)
+    const int64_t grid = max_grid > 0 ? std::min<int64_t>(blocks, std::max<int64_t>(8, max_grid / 8 * 8)) : blocks;
     hipLaunchKernelGGL(nz_keys_kernel, dim3(static_cast<uint32_t>(grid)), dim3(KEYS_THREADS), 0, st, desc, list, first,
-                       bps, static_cast<int32_t>(blocks), ws, state);
+                       count, by_xcd, bps, static_cast<int32_t>(blocks), ws, state);
     return hipGetLastError();
 }
 
@@ -1981,11 +2109,18 @@ int32_t keys_resident_wgs()
     return wgs;
 }
 
-hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t bx_hook, int32_t bx_site,
+hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
                           const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
                           hipStream_t st, hipEvent_t *ev)
 {
     if (nlist <= 0) return hipSuccess;
+    // workgroups per sample: a hook workgroup takes 2048 sites of a large list
+    // (few partly filled edge buffers) down to 256 of a small one (more waves in
+    // flight): zone 1 at L = 16 (150000 sites) 3.78 / 3.23 / 3.08 ms for 1000
+    // samples with 256 / 1024 / 2048, zones 1-7 (2000 sites) 0.46 / 0.57 / 0.62
+    const int64_t per_wg = std::max<int64_t>(256, std::min<int64_t>(2048, max_sites / 16 / 256 * 256));
+    const int32_t bx_hook = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (max_sites + per_wg - 1) / per_wg)));
+    const int32_t bx_site = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (max_sites + 1023) / 1024)));
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], st);
     };
@@ -2017,7 +2152,7 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
     hipLaunchKernelGGL(nz_accum_kernel, dim3(static_cast<uint32_t>(bx_site) * slots8), dim3(256), 0, st, desc, list, nlist,
                        bx_site, ws, state);
     mark(3);
-    mark(4);   // (the lattice entries are written by the size pass)
+    mark(4);   // (there is no separate expand pass)
     if (smax)
         hipLaunchKernelGGL(nz_rootmax_kernel, dim3(static_cast<uint32_t>(bx_site) * slots8), dim3(256), 0, st, desc, list,
                            nlist, bx_site, ws, state);

@@ -15,20 +15,22 @@ hipError_t launch_clear(const NzSample *desc, const int32_t *list, int32_t nsamp
 // lattice size N.
 // (list != NULL: samples list[first .. first + count) instead).
 // max_grid > 0: at most that many workgroups, each taking several blocks.
+// by_xcd: all workgroups of a sample on one XCD (for bands that hold many sites).
 // keys_resident_wgs(): workgroups of the keys kernel one CU holds at once.
 int32_t keys_resident_wgs();
 hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first, int32_t count, int32_t N, uint8_t *ws,
-                       NzState *state, int32_t max_grid, hipStream_t st);
+                       NzState *state, int32_t max_grid, bool by_xcd, hipStream_t st);
 int32_t keys_sites_per_block();
 
-// Bulk connected components for the samples listed in list[0..nlist).
+// Bulk connected components for the samples listed in list[0..nlist), whose
+// prefill lists hold max_sites sites at most.
 // smax: also the largest cluster of each smax-mode sample's prefilled state.
 // wrap: the listed samples are periodic first-wrap samples (64-bit entries).
 // periodic: the listed samples have periodic coordinates (all or none of them).
 // ev (may be NULL): five events recorded before the hook, after it, after
-// compress and after the size pass, the fifth with the fourth (the size pass
-// writes the lattice entries; there is no separate expand pass).
-hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t bx_hook, int32_t bx_site,
+// compress and after the flag pass, the fifth with the fourth (there is no
+// separate expand pass).
+hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
                           const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
                           hipStream_t st, hipEvent_t *ev = nullptr);
 
