@@ -64,90 +64,136 @@ __global__ __launch_bounds__(64) void mlp_forward_kernel(const uint16_t *__restr
     }
 }
 
-// One workgroup of 256 threads for the whole batch, rows taken in tiles of 32:
-// the tile's pre-activation gradients are formed in LDS, then every thread adds
-// the tile's contribution to the parameter gradients it owns.  The summation
-// order is fixed, so results are deterministic.
+// Backward: every workgroup owns a slice of the parameters and goes over all
+// rows, ROWS at a time, so nothing is shared between workgroups and no atomics
+// are needed.  It forms the pre-activation gradients its slice needs in LDS
+// (those of the second layer are two multiply-adds each, so every workgroup
+// forms its own), then every thread adds the rows' contributions to its
+// parameter: sums of TILE rows, added up in row order.  The order is fixed, so
+// results are deterministic, and the same for any ROWS.
+//
+// Bound by latency: 170 rows took 105 us in one workgroup of 256 threads; the
+// 25 workgroups here leave the whole training step (four launches) at 30 us, down
+// from 121, so they cost about as much as their launch.
 constexpr int BT = 256;
-constexpr int TILE = 32;
+constexpr int TILE = 32;    // rows summed before they are added to the total
+constexpr int ROWS = 128;   // rows in LDS at a time
+constexpr int LD = H + 1;   // padded: a column's rows lie in different banks
+constexpr int W2_WGS = H * H / BT;     // slices of W2: 4 of its rows each
+constexpr int W1_K = 8;                // hidden units per slice of W1, b1
+constexpr int W1_WGS = H / W1_K;
+constexpr int BACKWARD_WGS = W2_WGS + W1_WGS + 1;   // the last one: b2, W3, b3
+static_assert(ROWS % TILE == 0 && H % W1_K == 0 && BT % H == 0, "whole tiles and slices");
+
+// dz2 = (dy W3^T) * (1 - h2^2) of rows r0 .. r0 + rows - 1, zero behind them.
+__device__ __forceinline__ void backward_dz2(const uint16_t *__restrict__ p, const float *__restrict__ act,
+                                             const float *__restrict__ dy, int r0, int rows, float (*dz2)[LD])
+{
+    const int k = threadIdx.x % H;   // (the same in every step: BT is a multiple of H)
+    float w3[OUT];
+    for (int o = 0; o < OUT; ++o) w3[o] = bf16_to_f32(p[OFF_W3 + k * OUT + o]);
+#pragma unroll 8
+    for (int r = threadIdx.x / H; r < ROWS; r += BT / H) {
+        const int row = r0 + min(r, rows - 1);
+        const float h2 = act[row * NZ_MLP_NACT + H + k];
+        float g = 0.0f;
+        for (int o = 0; o < OUT; ++o) g = fmaf(dy[row * OUT + o], w3[o], g);
+        const float v = g * (1.0f - h2 * h2);
+        dz2[r][k] = r < rows ? v : 0.0f;
+    }
+}
+
+// acc += sums of TILE rows of term(r, g), r < rows; term adds row r to g.
+template <typename F>
+__device__ __forceinline__ void add_tiles(float &acc, int rows, F &&term)
+{
+    int t0 = 0;
+    for (; t0 + TILE <= rows; t0 += TILE) {
+        float g = 0.0f;
+#pragma unroll
+        for (int r = 0; r < TILE; ++r) g = term(t0 + r, g);   // (unrolled: the LDS reads run ahead)
+        acc += g;
+    }
+    if (t0 < rows) {
+        float g = 0.0f;
+        for (int r = t0; r < rows; ++r) g = term(r, g);
+        acc += g;
+    }
+}
 
 __global__ __launch_bounds__(BT) void mlp_backward_kernel(const uint16_t *__restrict__ p, const float *__restrict__ x,
                                                           const float *__restrict__ act, const float *__restrict__ dy,
                                                           float *__restrict__ grad, int32_t B)
 {
-    __shared__ float sx[TILE][IN], sh1[TILE][H], sh2[TILE][H], sdy[TILE][OUT], dz2[TILE][H], dz1[TILE][H];
-    constexpr int PER = (NPARAM + BT - 1) / BT;
-    float acc[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) acc[q] = 0.0f;
-    const int t = threadIdx.x;
+    __shared__ float dz2[ROWS][LD];
+    __shared__ float side[ROWS][W1_K + 1];   // h1 of the slice's units, then dz1 of them
+    __shared__ float xin[ROWS][IN];
+    __shared__ float w2[W1_K][LD];
+    const int t = threadIdx.x, wg = blockIdx.x;
+    float acc = 0.0f;
 
-    for (int r0 = 0; r0 < B; r0 += TILE) {
-        const int rows = min(TILE, B - r0);
-        for (int e = t; e < TILE * H; e += BT) {
-            const int r = e / H, k = e % H;
-            const bool ok = r < rows;
-            sh1[r][k] = ok ? act[(r0 + r) * NZ_MLP_NACT + k] : 0.0f;
-            sh2[r][k] = ok ? act[(r0 + r) * NZ_MLP_NACT + H + k] : 0.0f;
+    if (wg < W2_WGS) {
+        // grad W2[k][j] = sum_r h1[r][k] dz2[r][j]: thread t owns k = 4 wg + t / H, j = t % H
+        constexpr int KS = BT / H;
+        const int kk = t / H, j = t % H, k0 = KS * wg;
+        for (int r0 = 0; r0 < B; r0 += ROWS) {
+            const int rows = min(ROWS, B - r0);
+            backward_dz2(p, act, dy, r0, rows, dz2);
+            for (int e = t; e < rows * KS; e += BT) side[e / KS][e % KS] = act[(r0 + e / KS) * NZ_MLP_NACT + k0 + e % KS];
+            __syncthreads();
+            add_tiles(acc, rows, [&](int r, float g) { return fmaf(side[r][kk], dz2[r][j], g); });
+            __syncthreads();
         }
-        for (int e = t; e < TILE * IN; e += BT) {
-            const int r = e / IN, i = e % IN;
-            sx[r][i] = r < rows ? x[(r0 + r) * IN + i] : 0.0f;
-        }
-        for (int e = t; e < TILE * OUT; e += BT) {
-            const int r = e / OUT, o = e % OUT;
-            sdy[r][o] = r < rows ? dy[(r0 + r) * OUT + o] : 0.0f;
-        }
-        __syncthreads();
-        // dz2 = (dy W3^T) * (1 - h2^2)
-        for (int e = t; e < TILE * H; e += BT) {
-            const int r = e / H, k = e % H;
-            float g = 0.0f;
-            for (int o = 0; o < OUT; ++o) g = fmaf(sdy[r][o], bf16_to_f32(p[OFF_W3 + k * OUT + o]), g);
-            dz2[r][k] = g * (1.0f - sh2[r][k] * sh2[r][k]);
-        }
-        __syncthreads();
-        // dz1 = (dz2 W2^T) * (1 - h1^2)
-        for (int e = t; e < TILE * H; e += BT) {
-            const int r = e / H, k = e % H;
-            float g = 0.0f;
-            for (int j = 0; j < H; ++j) g = fmaf(dz2[r][j], bf16_to_f32(p[OFF_W2 + k * H + j]), g);
-            dz1[r][k] = g * (1.0f - sh1[r][k] * sh1[r][k]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int idx = t + q * BT;
-            if (idx >= NPARAM) break;
-            float g = 0.0f;
-            if (idx < OFF_B1) {
-                const int i = idx / H, j = idx % H;
-                for (int r = 0; r < rows; ++r) g = fmaf(sx[r][i], dz1[r][j], g);
-            } else if (idx < OFF_W2) {
-                const int j = idx - OFF_B1;
-                for (int r = 0; r < rows; ++r) g += dz1[r][j];
-            } else if (idx < OFF_B2) {
-                const int k = (idx - OFF_W2) / H, j = (idx - OFF_W2) % H;
-                for (int r = 0; r < rows; ++r) g = fmaf(sh1[r][k], dz2[r][j], g);
-            } else if (idx < OFF_W3) {
-                const int j = idx - OFF_B2;
-                for (int r = 0; r < rows; ++r) g += dz2[r][j];
-            } else if (idx < OFF_B3) {
-                const int k = (idx - OFF_W3) / OUT, o = (idx - OFF_W3) % OUT;
-                for (int r = 0; r < rows; ++r) g = fmaf(sh2[r][k], sdy[r][o], g);
-            } else {
-                const int o = idx - OFF_B3;
-                for (int r = 0; r < rows; ++r) g += sdy[r][o];
+        grad[OFF_W2 + (k0 + kk) * H + j] = acc;
+        return;
+    }
+    if (wg < W2_WGS + W1_WGS) {
+        // grad W1[i][k] = sum_r x[r][i] dz1[r][k] and b1[k] = sum_r dz1[r][k], with
+        // dz1 = (dz2 W2^T) * (1 - h1^2), for the slice's W1_K units k
+        const int k0 = W1_K * (wg - W2_WGS);
+        for (int e = t; e < W1_K * H; e += BT) w2[e / H][e % H] = bf16_to_f32(p[OFF_W2 + (k0 + e / H) * H + e % H]);
+        const int i = t / W1_K, kk = t % W1_K;   // threads of i < IN own W1, those of i == IN b1
+        for (int r0 = 0; r0 < B; r0 += ROWS) {
+            const int rows = min(ROWS, B - r0);
+            backward_dz2(p, act, dy, r0, rows, dz2);
+            for (int e = t; e < rows * IN; e += BT) xin[e / IN][e % IN] = x[(r0 + e / IN) * IN + e % IN];
+            __syncthreads();
+            for (int e = t; e < rows * W1_K; e += BT) {
+                const int r = e / W1_K, c = e % W1_K;
+                const float h1 = act[(r0 + r) * NZ_MLP_NACT + k0 + c];
+                float g = 0.0f;
+#pragma unroll 16
+                for (int j = 0; j < H; ++j) g = fmaf(dz2[r][j], w2[c][j], g);
+                side[r][c] = g * (1.0f - h1 * h1);
             }
-            acc[q] += g;
+            __syncthreads();
+            if (i < IN) add_tiles(acc, rows, [&](int r, float g) { return fmaf(xin[r][i], side[r][kk], g); });
+            else if (i == IN) add_tiles(acc, rows, [&](int r, float g) { return g + side[r][kk]; });
+            __syncthreads();
         }
+        if (i < IN) grad[OFF_W1 + i * H + k0 + kk] = acc;
+        else if (i == IN) grad[OFF_B1 + k0 + kk] = acc;
+        return;
+    }
+    // b2[j] = sum_r dz2[r][j] (threads 0 .. 63), W3[k][o] = sum_r h2[r][k] dy[r][o]
+    // (64 .. 191), b3[o] = sum_r dy[r][o] (192, 193)
+    for (int r0 = 0; r0 < B; r0 += ROWS) {
+        const int rows = min(ROWS, B - r0);
+        backward_dz2(p, act, dy, r0, rows, dz2);
+        __syncthreads();
+        if (t < H) add_tiles(acc, rows, [&](int r, float g) { return g + dz2[r][t]; });
+        __syncthreads();
+        for (int e = t; e < rows * H; e += BT) dz2[e / H][e % H] = act[(r0 + e / H) * NZ_MLP_NACT + H + e % H];   // h2
+        for (int e = t; e < rows * OUT; e += BT) xin[e / OUT][e % OUT] = dy[(r0 + e / OUT) * OUT + e % OUT];
+        __syncthreads();
+        const int q = t - H;
+        if (q >= 0 && q < H * OUT) add_tiles(acc, rows, [&](int r, float g) { return fmaf(dz2[r][q / OUT], xin[r][q % OUT], g); });
+        else if (q >= H * OUT && q < H * OUT + OUT) add_tiles(acc, rows, [&](int r, float g) { return g + xin[r][q - H * OUT]; });
         __syncthreads();
     }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int idx = t + q * BT;
-        if (idx < NPARAM) grad[idx] = acc[q];
-    }
+    if (t < H) grad[OFF_B2 + t] = acc;
+    else if (t < H + H * OUT) grad[OFF_W3 + t - H] = acc;
+    else if (t < H + H * OUT + OUT) grad[OFF_B3 + t - H - H * OUT] = acc;
 }
 
 // Adam with decoupled weight decay; FP32 master weights, BF16 copy rewritten.
@@ -229,7 +275,7 @@ NZ_API int nz_mlp_backward(const uint16_t *params_bf16, const float *x, const fl
                            int32_t B, void *stream)
 {
     if (!params_bf16 || !x || !act || !dy || !grad || B < 1) return nz::set_error(NZ_EINVAL, "nz_mlp_backward: NULL pointer or B < 1");
-    hipLaunchKernelGGL(nzmlp::mlp_backward_kernel, dim3(1), dim3(nzmlp::BT), 0, static_cast<hipStream_t>(stream),
+    hipLaunchKernelGGL(nzmlp::mlp_backward_kernel, dim3(nzmlp::BACKWARD_WGS), dim3(nzmlp::BT), 0, static_cast<hipStream_t>(stream),
                        params_bf16, x, act, dy, grad, B);
     return mlp_fail(hipGetLastError());
 }
