@@ -73,8 +73,10 @@ int nz_coordination(uint32_t zone_mask);
  *   seed  any 64-bit value;
  *   nstar      HOST array of nsamples int32, written;
  *   mass       HOST array of nsamples int32, written; may be NULL.
- * Synchronous; allocates and frees its own device memory; runs on the current
- * HIP device and its default stream.  Plain sweep (no prefill).
+ * Synchronous; allocates its own device memory and keeps up to 4 GiB of it for
+ * the calling thread's next call (8 GiB over all threads; freed when the thread
+ * ends); runs on the current HIP device and its default stream.  Plain sweep (no
+ * prefill).
  */
 int nz_sweep(int32_t L, uint32_t zone_mask, int32_t boundary, int64_t nsamples, uint64_t seed,
              int32_t *nstar, int32_t *mass);
@@ -104,8 +106,7 @@ int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_grid, i
  *   1 <= n_lo < n_hi <= N;
  *   smax_sum   HOST array of n_hi - n_lo uint64, written (sum over samples of
  *              S_max(n_lo + k) in entry k).
- * Synchronous; allocates and frees its own device memory; current device,
- * default stream.
+ * Synchronous; device memory as for nz_sweep; current device, default stream.
  */
 int nz_smax_window(int32_t L, uint32_t zone_mask, int32_t boundary, uint64_t seed, int64_t sample0,
                    int64_t nsamples, int64_t n0, int64_t n_lo, int64_t n_hi, uint64_t *smax_sum);

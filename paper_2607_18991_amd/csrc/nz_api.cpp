@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cstdlib>
 #include <cmath>
 #include <cstdarg>
@@ -409,27 +410,6 @@ int prefill_group(int32_t prefix_cap)
     return g;
 }
 
-// plan_sizes of consecutive plans that share its inputs (the samples of one
-// job do) is computed once.
-struct SizesMemo {
-    bool have = false;
-    Plan key{};
-    int bucket_log2 = 0;
-    Sizes s{};
-    const Sizes &get(const Plan &p, int bl)
-    {
-        if (!have || bl != bucket_log2 || p.L != key.L || p.n0 != key.n0 || p.backoff != key.backoff ||
-            p.band_hi != key.band_hi || p.shift_adj != key.shift_adj || p.prefix_mul != key.prefix_mul ||
-            p.wrap != key.wrap || p.win_lo != key.win_lo || p.win_hi != key.win_hi) {
-            s = plan_sizes(p, bl);
-            key = p;
-            bucket_log2 = bl;
-            have = true;
-        }
-        return s;
-    }
-};
-
 int64_t default_band_hi(int32_t L, uint32_t mask, int64_t n0)
 {
     const int64_t N = pow5(L);
@@ -538,6 +518,77 @@ struct SmaxReq {
     uint64_t *d_out;
 };
 
+// Consecutive samples of one job with one plan: p is the first sample's.
+struct Run {
+    Plan p;
+    int64_t count;
+};
+
+// The run goes on with a sample of plan p (its successor, planned the same).
+bool follows(const Run &r, const Plan &p)
+{
+    return p.job == r.p.job && p.sample == r.p.sample + r.count && p.out == r.p.out + r.count && p.n0 == r.p.n0 &&
+           p.backoff == r.p.backoff && p.band_hi == r.p.band_hi && p.shift_adj == r.p.shift_adj && p.prefix_mul == r.p.prefix_mul;
+}
+
+// A run's samples in one chunk.
+struct Part {
+    Plan p;
+    Sizes s;
+    int32_t count, desc0, queue0, list0;
+    size_t off;
+};
+
+NzRun make_run(const Part &part, const nz_job *jobs, TablePool &pool)
+{
+    const Plan &p = part.p;
+    const Sizes &s = part.s;
+    NzRun r;
+    std::memset(&r, 0, sizeof r);
+    NzSample &d = r.first;
+    d.seed = jobs[p.job].seed;
+    d.sample = static_cast<uint64_t>(p.sample);
+    d.T0 = s.T0;
+    d.L = p.L;
+    d.N = static_cast<int32_t>(pow5(p.L));
+    d.nb = s.nb;
+    d.cap = s.cap;
+    d.shift = s.shift;
+    d.full = s.full;
+    d.prefix_cap = s.prefix_cap;
+    d.tab = pool.get(p.mask, p.L, &d.rows);
+    d.magic = p.L == 1 ? 0 : static_cast<uint64_t>(~0ull / static_cast<uint64_t>(p.L) + 1ull);
+    size_t off = part.off;
+    d.off_par = off; off += s.par;
+    d.off_occ = off; off += s.occ;
+    d.off_sites = off; off += s.sites;
+    d.off_counts = off; off += s.counts;
+    d.off_prefix = off; off += s.prefix;
+    d.off_parc = off; off += s.parc;
+    d.off_wpos = off; off += s.wpos;
+    d.off_sum = off; off += s.sum;
+    d.sum_shift = s.sum_shift;
+    d.sum_words = s.sum_words;
+    d.off_win = off; off += s.win;
+    d.smax_mode = p.win_hi > 0 ? 1 : 0;
+    d.win_lo = static_cast<int32_t>(p.win_lo);
+    d.win_hi = static_cast<int32_t>(p.win_hi);
+    d.periodic = p.per ? 1 : 0;
+    d.wrap = p.wrap ? 1 : 0;
+    for (int lv = 0; lv < 2; ++lv) {
+        d.T0b[lv] = s.T0b[lv];
+        d.nbb[lv] = s.nbb[lv];
+    }
+    r.stride = s.total;
+    r.count = part.count;
+    r.desc0 = part.desc0;
+    r.queue0 = part.queue0;
+    r.list0 = part.list0;
+    r.out0 = p.out;
+    return r;
+}
+static_assert(sizeof(NzRun) <= 4 * kAlign, "a run fits the region of the smallest sample (par, occ, sites, counts)");
+
 // job_out (may be NULL): first output index of every job (default: the
 // samples of the jobs in order, from 0).
 int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_t *d_nstar, int32_t *d_mass,
@@ -556,152 +607,127 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
 
     // tables for every (mask, L) of the batch live at the start of the workspace
     TablePool pool;
-    std::vector<Plan> todo;
-    {
-        int64_t total = 0;
-        for (int j = 0; j < njobs; ++j) total += std::max<int64_t>(0, jobs[j].nsamples);
-        todo.reserve(static_cast<size_t>(std::min<int64_t>(total, 0x7FFFFFFF)));
-    }
-    int64_t out = 0;
+    std::vector<Run> todo;
+    std::vector<std::vector<int32_t>> lists;   // host lists whose copies may be under way
+    int64_t out = 0, left = 0;   // left: samples in todo
     for (int j = 0; j < njobs; ++j) {
         const nz_job &J = jobs[j];
         int32_t rows = 0;
         pool.get(J.zone_mask, J.L, &rows);
         const int z = coordination(J.zone_mask);
         const int64_t N = pow5(J.L);
-        for (int64_t k = 0; k < J.nsamples; ++k) {
-            Plan p{};
-            p.job = j;
-            p.sample = J.sample0 + k;
-            p.out = static_cast<int32_t>(job_out ? job_out[j] + k : out);
-            ++out;
-            p.L = J.L;
-            p.mask = J.zone_mask;
-            p.n0 = J.n0 > 0 ? J.n0 : 0;
-            p.backoff = J.backoff;
-            p.band_hi = J.band_hi > 0 ? std::min<int64_t>(J.band_hi, N) : default_band_hi(J.L, J.zone_mask, p.n0);
-            if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
-            p.shift_adj = 0;
-            p.prefix_mul = 1;
-            p.prio = J.prio > 0 ? J.prio : static_cast<double>(std::max<int64_t>(1, p.band_hi - p.n0)) * (1.0 + z / 64.0);
-            p.win_lo = smax ? smax->win_lo : 0;
-            p.win_hi = smax ? smax->win_hi : 0;
-            p.per = J.boundary == NZ_PERIODIC;
-            p.wrap = p.per && !smax;
-            todo.push_back(p);
-        }
+        if (J.nsamples <= 0) continue;
+        Run run{};
+        Plan &p = run.p;
+        p.job = j;
+        p.sample = J.sample0;
+        p.out = static_cast<int32_t>(job_out ? job_out[j] : out);
+        p.L = J.L;
+        p.mask = J.zone_mask;
+        p.n0 = J.n0 > 0 ? J.n0 : 0;
+        p.backoff = J.backoff;
+        p.band_hi = J.band_hi > 0 ? std::min<int64_t>(J.band_hi, N) : default_band_hi(J.L, J.zone_mask, p.n0);
+        if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
+        p.shift_adj = 0;
+        p.prefix_mul = 1;
+        p.prio = J.prio > 0 ? J.prio : static_cast<double>(std::max<int64_t>(1, p.band_hi - p.n0)) * (1.0 + z / 64.0);
+        p.win_lo = smax ? smax->win_lo : 0;
+        p.win_hi = smax ? smax->win_hi : 0;
+        p.per = J.boundary == NZ_PERIODIC;
+        p.wrap = p.per && !smax;
+        run.count = J.nsamples;
+        out += J.nsamples;
+        left += J.nsamples;
+        todo.push_back(run);
     }
     if (out > 0x7FFFFFFF || (job_out && njobs > 0 && job_out[njobs - 1] + jobs[njobs - 1].nsamples > 0x7FFFFFFF))
         return fail(NZ_EINVAL, "too many samples in one batch");
     const size_t tab_bytes = align_up(pool.entries.size() * sizeof(NzOffset));
+    bool tabs_there = false;
 
     int rounds = 0;
     while (!todo.empty()) {
         if (++rounds > 64) return fail(NZ_EDEVICE, "samples still unfinished after 64 redo rounds");
         // free-boundary samples first, then the periodic ones: a chunk holds one
         // boundary condition only, since the sweep is compiled for each
-        std::stable_sort(todo.begin(), todo.end(), [](const Plan &a, const Plan &b) {
-            return a.per != b.per ? b.per : a.prio > b.prio;
+        std::stable_sort(todo.begin(), todo.end(), [](const Run &a, const Run &b) {
+            return a.p.per != b.p.per ? b.p.per : a.p.prio > b.p.prio;
         });
-        std::vector<Plan> redo;
-        SizesMemo memo;
+        std::vector<Run> redo;
+        int64_t redo_left = 0;
         size_t pos = 0;
         while (pos < todo.size()) {
             // ---- form a chunk: longest first, as many as the workspace holds
-            const int32_t cmax = static_cast<int32_t>(std::min<size_t>(kMaxChunk, todo.size() - pos));
+            const int32_t cmax = static_cast<int32_t>(std::min<int64_t>(kMaxChunk, left));
             const size_t head = header_bytes(pool.entries.size(), cmax);
             if (head >= ws_bytes) return fail(NZ_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu-byte header", ws_bytes, head);
-            std::vector<Plan> chunk;
-            std::vector<Sizes> sizes;
+            std::vector<Part> parts;   // in queue order
+            int32_t n = 0;
             size_t used = head;
-            while (pos < todo.size() && static_cast<int32_t>(chunk.size()) < cmax) {
-                if (!chunk.empty() && todo[pos].per != chunk.front().per) break;
-                const Sizes &s = memo.get(todo[pos], tune.bucket_log2);
-                if (used + s.total > ws_bytes) break;
-                used += s.total;
-                chunk.push_back(todo[pos]);
-                sizes.push_back(s);
+            while (pos < todo.size() && n < cmax) {
+                Run &run = todo[pos];
+                if (!parts.empty() && run.p.per != parts.front().p.per) break;
+                Part part{};
+                part.p = run.p;
+                part.s = plan_sizes(run.p, tune.bucket_log2);
+                part.count = static_cast<int32_t>(std::min<int64_t>({run.count, cmax - n, static_cast<int64_t>((ws_bytes - used) / part.s.total)}));
+                if (part.count <= 0) break;
+                part.queue0 = n;
+                used += part.s.total * static_cast<size_t>(part.count);
+                n += part.count;
+                run.p.sample += part.count;
+                run.p.out += part.count;
+                run.count -= part.count;
+                parts.push_back(part);
+                if (run.count > 0) break;   // the chunk is full
                 ++pos;
             }
-            if (chunk.empty()) {
-                Sizes s = plan_sizes(todo[pos], tune.bucket_log2);
+            if (parts.empty()) {
+                Sizes s = plan_sizes(todo[pos].p, tune.bucket_log2);
                 return fail(NZ_EWORKSPACE, "workspace of %zu bytes cannot hold one sample (needs %zu)", ws_bytes, head + s.total);
             }
+            left -= n;
             ++g_stats[0];
-            const int32_t n = static_cast<int32_t>(chunk.size());
-            const bool wrap_chunk = chunk.front().wrap;
-            const bool per_chunk = chunk.front().per;
+            const bool wrap_chunk = parts.front().p.wrap;
+            const bool per_chunk = parts.front().p.per;
 
             // ---- descriptors, grouped by L and band width for the keys launches
-            std::vector<int32_t> byL(n);
-            for (int32_t i = 0; i < n; ++i) byL[i] = i;
-            std::stable_sort(byL.begin(), byL.end(), [&](int32_t a, int32_t b) {
-                if (chunk[a].L != chunk[b].L) return chunk[a].L < chunk[b].L;
-                return wide_band(sizes[a]) > wide_band(sizes[b]);
+            const int32_t np = static_cast<int32_t>(parts.size());
+            std::vector<int32_t> order(np);   // parts in descriptor order
+            for (int32_t i = 0; i < np; ++i) order[i] = i;
+            std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+                if (parts[a].p.L != parts[b].p.L) return parts[a].p.L < parts[b].p.L;
+                return wide_band(parts[a].s) > wide_band(parts[b].s);
             });
-            std::vector<NzSample> desc(n);
-            std::vector<int32_t> out_index(n), queue(n), prefill_list;
-            std::vector<int32_t> chunk_of_desc(n);
             size_t off = head;
             const int32_t keys_grid = tune.keys_resident ? (nz::keys_resident_wgs() + 1) / 2 * dev.cus : 0;
             uint32_t max_N = 0;
-            std::vector<int32_t> desc_of_chunk(n);
-            uint32_t last_mask = 0;   // offset table of the previous descriptor's (mask, L)
-            int32_t last_L = 0, last_tab = 0, last_rows = 0;
-            for (int32_t di = 0; di < n; ++di) {
-                const int32_t ci = byL[di];
-                const Plan &p = chunk[ci];
-                const Sizes &s = sizes[ci];
-                const nz_job &J = jobs[p.job];
-                NzSample &d = desc[di];
-                std::memset(&d, 0, sizeof d);
-                d.seed = J.seed;
-                d.sample = static_cast<uint64_t>(p.sample);
-                d.T0 = s.T0;
-                d.L = p.L;
-                d.N = static_cast<int32_t>(pow5(p.L));
-                d.nb = s.nb;
-                d.cap = s.cap;
-                d.shift = s.shift;
-                d.full = s.full;
-                d.prefix_cap = s.prefix_cap;
-                if (p.mask != last_mask || p.L != last_L) {
-                    last_tab = pool.get(p.mask, p.L, &last_rows);
-                    last_mask = p.mask;
-                    last_L = p.L;
-                }
-                d.tab = last_tab;
-                d.rows = last_rows;
-                d.magic = p.L == 1 ? 0 : static_cast<uint64_t>(~0ull / static_cast<uint64_t>(p.L) + 1ull);
-                d.off_par = off; off += s.par;
-                d.off_occ = off; off += s.occ;
-                d.off_sites = off; off += s.sites;
-                d.off_counts = off; off += s.counts;
-                d.off_prefix = off; off += s.prefix;
-                d.off_parc = off; off += s.parc;
-                d.off_wpos = off; off += s.wpos;
-                d.off_sum = off; off += s.sum;
-                d.sum_shift = s.sum_shift;
-                d.sum_words = s.sum_words;
-                d.off_win = off; off += s.win;
-                d.smax_mode = p.win_hi > 0 ? 1 : 0;
-                d.win_lo = static_cast<int32_t>(p.win_lo);
-                d.win_hi = static_cast<int32_t>(p.win_hi);
-                d.periodic = J.boundary == NZ_PERIODIC ? 1 : 0;
-                d.wrap = p.wrap ? 1 : 0;
-                out_index[di] = p.out;
-                chunk_of_desc[di] = ci;
-                desc_of_chunk[ci] = di;
-                max_N = std::max(max_N, static_cast<uint32_t>(d.N));
-                if (d.T0 != 0) {
-                    prefill_list.push_back(di);
-                }
+            int32_t max_count = 0, di = 0;
+            for (int32_t i : order) {
+                Part &part = parts[i];
+                part.desc0 = di;
+                part.off = off;
+                di += part.count;
+                off += part.s.total * static_cast<size_t>(part.count);
+                max_N = std::max(max_N, static_cast<uint32_t>(pow5(part.p.L)));
+                max_count = std::max(max_count, part.count);
             }
-            // the labelling is launched per group of samples of like prefill sizes
-            std::stable_sort(prefill_list.begin(), prefill_list.end(), [&](int32_t a, int32_t b) {
-                return prefill_group(desc[a].prefix_cap) > prefill_group(desc[b].prefix_cap);
+            // the prefilled parts, in groups of like prefill sizes for the labelling
+            std::vector<int32_t> pre;
+            for (int32_t i : order)
+                if (parts[i].s.T0 != 0) pre.push_back(i);
+            std::stable_sort(pre.begin(), pre.end(), [&](int32_t a, int32_t b) {
+                return prefill_group(parts[a].s.prefix_cap) > prefill_group(parts[b].s.prefix_cap);
             });
-            for (int32_t q = 0; q < n; ++q) queue[q] = desc_of_chunk[q];   // chunk is in priority order
+            int32_t nlist = 0;
+            for (Part &part : parts) part.list0 = -1;
+            for (int32_t i : pre) {
+                parts[i].list0 = nlist;
+                nlist += parts[i].count;
+            }
+            std::vector<NzRun> runs;
+            runs.reserve(parts.size());
+            for (int32_t i : order) runs.push_back(make_run(parts[i], jobs, pool));
 
             // ---- header layout
             uint8_t *h = ws;
@@ -718,15 +744,16 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             int32_t *d_list = reinterpret_cast<int32_t *>(h);
             h += align_up(cmax * sizeof(int32_t));
             int32_t *d_qhead = reinterpret_cast<int32_t *>(h);
+            // the runs pass through the samples' own region, which nothing uses
+            // before they are expanded (every sample's is larger than a run)
+            NzRun *d_runs = reinterpret_cast<NzRun *>(ws + head);
 
-            HIP_TRY(hipMemcpyAsync(d_tabs, pool.entries.data(), pool.entries.size() * sizeof(NzOffset), hipMemcpyHostToDevice, st));
-            HIP_TRY(hipMemcpyAsync(d_desc, desc.data(), n * sizeof(NzSample), hipMemcpyHostToDevice, st));
-            HIP_TRY(hipMemcpyAsync(d_queue, queue.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st));
-            HIP_TRY(hipMemcpyAsync(d_outidx, out_index.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st));
-            if (!prefill_list.empty())
-                HIP_TRY(hipMemcpyAsync(d_list, prefill_list.data(), prefill_list.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-            const int32_t zero = 0;
-            HIP_TRY(hipMemcpyAsync(d_qhead, &zero, sizeof zero, hipMemcpyHostToDevice, st));
+            if (!tabs_there) {
+                HIP_TRY(hipMemcpyAsync(d_tabs, pool.entries.data(), pool.entries.size() * sizeof(NzOffset), hipMemcpyHostToDevice, st));
+                tabs_there = true;
+            }
+            HIP_TRY(hipMemcpyAsync(d_runs, runs.data(), runs.size() * sizeof(NzRun), hipMemcpyHostToDevice, st));
+            HIP_TRY(nz::launch_expand(d_runs, np, max_count, d_desc, d_state, d_queue, d_outidx, d_list, d_qhead, st));
 
             // ---- launches
             PhaseEvents *pe = nullptr;
@@ -744,74 +771,79 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 return pfe && pfe->used < PrefillEvents::kSets ? pfe->ev[pfe->used++] : nullptr;
             };
             if (pe) HIP_TRY(hipEventRecord(pe->ev[0], st));
-            HIP_TRY(nz::launch_clear(d_desc, nullptr, n, ws, d_state, st));
-            for (int32_t a = 0; a < n;) {
-                int32_t b = a;
-                const bool wide = wide_band(desc[a]);
-                while (b < n && desc[b].N == desc[a].N && wide_band(desc[b]) == wide) ++b;
-                HIP_TRY(nz::launch_keys(d_desc, nullptr, a, b - a, desc[a].N, ws, d_state, keys_grid,
-                                        wide && b - a >= kXcdSamples, st));
+            HIP_TRY(nz::launch_clear(d_desc, nullptr, n, 0, ws, d_state, st));
+            for (int32_t a = 0; a < np;) {
+                const Part &first = parts[order[a]];
+                const bool wide = wide_band(first.s);
+                int32_t b = a, count = 0;
+                while (b < np && parts[order[b]].p.L == first.p.L && wide_band(parts[order[b]].s) == wide) count += parts[order[b++]].count;
+                HIP_TRY(nz::launch_keys(d_desc, nullptr, first.desc0, count, static_cast<int32_t>(pow5(first.p.L)), ws, d_state,
+                                        keys_grid, wide && count >= kXcdSamples, st));
                 a = b;
             }
             if (pe) HIP_TRY(hipEventRecord(pe->ev[1], st));
-            if (!prefill_list.empty()) {
-                for (size_t g = 0; g < prefill_list.size();) {
-                    const int32_t most = desc[prefill_list[g]].prefix_cap;
+            std::vector<NzState> state(n);
+            std::vector<uint8_t> level(n, 0);   // in-chunk backoffs of every sample
+            if (nlist > 0) {
+                for (size_t g = 0; g < pre.size();) {
+                    const int32_t most = parts[pre[g]].s.prefix_cap;
+                    int32_t count = 0;
                     size_t e = g;
-                    while (e < prefill_list.size()) {
+                    while (e < pre.size()) {
                         // the samples of one size class, if a launch of their own saves
                         // enough empty workgroups
                         size_t c = e;
-                        const int cls = prefill_group(desc[prefill_list[e]].prefix_cap);
-                        while (c < prefill_list.size() && prefill_group(desc[prefill_list[c]].prefix_cap) == cls) ++c;
-                        const int64_t empty = static_cast<int64_t>(c - e) * (most - desc[prefill_list[e]].prefix_cap) / 1024;
+                        int32_t samples = 0;
+                        const int cls = prefill_group(parts[pre[e]].s.prefix_cap);
+                        while (c < pre.size() && prefill_group(parts[pre[c]].s.prefix_cap) == cls) samples += parts[pre[c++]].count;
+                        const int64_t empty = static_cast<int64_t>(samples) * (most - parts[pre[e]].s.prefix_cap) / 1024;
                         if (e > g && empty > kEmptyWgs) break;
+                        count += samples;
                         e = c;
                     }
-                    HIP_TRY(nz::launch_prefill(d_desc, d_list + g, static_cast<int32_t>(e - g),
-                                               desc[prefill_list[g]].prefix_cap, d_tabs, ws, d_state, smax != nullptr,
-                                               wrap_chunk, per_chunk, st, prefill_events()));
+                    HIP_TRY(nz::launch_prefill(d_desc, d_list + parts[pre[g]].list0, count, most, d_tabs, ws, d_state,
+                                               smax != nullptr, wrap_chunk, per_chunk, st, prefill_events()));
                     g = e;
                 }
                 // Resolve backoffs inside the chunk: samples whose bulk state already
                 // spans are re-keyed and re-labelled from n0 - b, and if that spans
                 // too from n0 - 3b, so they join this chunk's sweep instead of a
                 // later redo round.
-                for (int level = 0; level < 2; ++level) {
-                    std::vector<NzState> st0(n);
-                    HIP_TRY(hipMemcpyAsync(st0.data(), d_state, n * sizeof(NzState), hipMemcpyDeviceToHost, st));
+                for (int lv = 0; lv < 2; ++lv) {
+                    HIP_TRY(hipMemcpyAsync(state.data(), d_state, n * sizeof(NzState), hipMemcpyDeviceToHost, st));
                     HIP_TRY(hipStreamSynchronize(st));
-                    std::vector<int32_t> again;
-                    for (int32_t di : prefill_list) {
-                        if (st0[di].status != NZ_ST_BACKOFF) continue;
-                        const int32_t ci = chunk_of_desc[di];
-                        const Sizes &s = sizes[ci];
-                        if (s.n0b[level] <= 0) continue;   // not planned: the redo round takes it
-                        Plan &p = chunk[ci];
-                        ++g_stats[3];
-                        if (h_backoffs) ++h_backoffs[p.job];
-                        p.n0 = s.n0b[level];
-                        p.backoff *= 2;   // the next backoff doubles the step
-                        desc[di].T0 = s.T0b[level];
-                        desc[di].nb = s.nbb[level];
-                        again.push_back(di);
+                    std::vector<int32_t> again;        // descriptors, by L (the order of `order`)
+                    std::vector<std::pair<int32_t, int32_t>> sizes;   // (N, count) of every L among them
+                    int32_t max_prefix = 0;
+                    for (int32_t i : order) {
+                        const Part &part = parts[i];
+                        if (part.s.T0b[lv] == 0) continue;   // not planned: the redo round takes it
+                        const int32_t N = static_cast<int32_t>(pow5(part.p.L));
+                        for (int32_t k = part.desc0; k < part.desc0 + part.count; ++k) {
+                            if (state[k].status != NZ_ST_BACKOFF) continue;
+                            ++g_stats[3];
+                            if (h_backoffs) ++h_backoffs[part.p.job];
+                            level[k] = static_cast<uint8_t>(lv + 1);
+                            again.push_back(k);
+                            if (sizes.empty() || sizes.back().first != N) sizes.emplace_back(N, 0);
+                            ++sizes.back().second;
+                            max_prefix = std::max(max_prefix, part.s.prefix_cap);
+                        }
                     }
                     if (again.empty()) break;
-                    std::stable_sort(again.begin(), again.end(), [&](int32_t a, int32_t b) { return desc[a].N < desc[b].N; });
                     const int32_t na = static_cast<int32_t>(again.size());
-                    int32_t max_prefix = 0;
-                    for (int32_t di : again) max_prefix = std::max(max_prefix, desc[di].prefix_cap);
-                    HIP_TRY(hipMemcpyAsync(d_desc, desc.data(), n * sizeof(NzSample), hipMemcpyHostToDevice, st));
                     HIP_TRY(hipMemcpyAsync(d_list, again.data(), na * sizeof(int32_t), hipMemcpyHostToDevice, st));
-                    HIP_TRY(nz::launch_clear(d_desc, d_list, na, ws, d_state, st));
-                    for (int32_t a = 0; a < na;) {
-                        int32_t b = a;
-                        while (b < na && desc[again[b]].N == desc[again[a]].N) ++b;
-                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, b - a, desc[again[a]].N, ws, d_state, keys_grid, false, st));
-                        a = b;
+                    HIP_TRY(nz::launch_clear(d_desc, d_list, na, lv, ws, d_state, st));
+                    int32_t a = 0;
+                    for (const auto &e : sizes) {
+                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, e.second, e.first, ws, d_state, keys_grid, false, st));
+                        a += e.second;
                     }
                     HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, d_tabs, ws, d_state, smax != nullptr,
                                                wrap_chunk, per_chunk, st, prefill_events()));
+                    // (`again` stays untouched until the copy has been read: the next
+                    // pass synchronises first, and so does the end of the chunk)
+                    lists.push_back(std::move(again));
                 }
             }
             if (pe) HIP_TRY(hipEventRecord(pe->ev[2], st));
@@ -847,9 +879,9 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             if (pe) HIP_TRY(hipEventRecord(pe->ev[4], st));
 
             // ---- read back and schedule the redo of unfinished samples
-            std::vector<NzState> state(n);
             HIP_TRY(hipMemcpyAsync(state.data(), d_state, n * sizeof(NzState), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
+            lists.clear();
             if (pe) {
                 for (int k = 0; k < 4; ++k) {
                     float ms = 0.0f;
@@ -870,65 +902,81 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             }
             if (getenv("NZ_DEBUG_TRACE")) {
                 int cnt[8] = {0};
-                for (int32_t di = 0; di < n; ++di) ++cnt[std::max(0, std::min(7, static_cast<int>(state[di].status)))];
+                for (int32_t k = 0; k < n; ++k) ++cnt[std::max(0, std::min(7, static_cast<int>(state[k].status)))];
                 std::fprintf(stderr, "nz: round %d chunk of %d: done %d band %d bucket %d backoff %d prefix %d other %d\n",
                              rounds, n, cnt[NZ_ST_DONE], cnt[NZ_ST_BAND], cnt[NZ_ST_BUCKET], cnt[NZ_ST_BACKOFF],
                              cnt[NZ_ST_PREFIX], n - cnt[NZ_ST_DONE] - cnt[NZ_ST_BAND] - cnt[NZ_ST_BUCKET] -
                                                     cnt[NZ_ST_BACKOFF] - cnt[NZ_ST_PREFIX]);
             }
-            for (int32_t di = 0; di < n; ++di) {
-                Plan p = chunk[chunk_of_desc[di]];
-                const int64_t N = pow5(p.L);
-                switch (state[di].status) {
-                case NZ_ST_DONE:
-                    g_stats[4] += state[di].n0;
-                    g_stats[5] += (state[di].nstar > 0 ? state[di].nstar : N) - state[di].n0;
-                    g_job_pre[p.job] += state[di].n0;
-                    g_job_serial[p.job] += (state[di].nstar > 0 ? state[di].nstar : N) - state[di].n0;
-                    continue;
-                case NZ_ST_BAND:
-                    ++g_stats[1];
-                    p.band_hi = std::min<int64_t>(N, p.n0 + 2 * std::max<int64_t>(p.band_hi - p.n0, 2048));
-                    break;
-                case NZ_ST_BUCKET:
-                    ++g_stats[2];
-                    p.shift_adj += 1;
-                    break;
-                case NZ_ST_BACKOFF:
-                    ++g_stats[3];
-                    if (h_backoffs) ++h_backoffs[p.job];
-                    // back off by the caller's step, doubling it each time
-                    // (n0 - b, n0 - 3b, n0 - 7b, ...), until the start would
-                    // reach 0; without a step, halve.  A badly predicted lattice
-                    // needs only a few rounds, and n0 reaches 0 after at most
-                    // log2(N) of them.
-                    if (p.backoff > 0) {
-                        if (p.n0 - p.backoff > 0) {
-                            p.n0 -= p.backoff;
-                            p.backoff *= 2;
-                        } else {
-                            p.n0 = 0;
-                            p.backoff = 0;
-                        }
-                    } else {
-                        p.n0 = p.n0 >= 64 ? p.n0 / 2 : 0;
+            for (int32_t i : order) {
+                const Part &part = parts[i];
+                const int64_t N = pow5(part.p.L);
+                for (int32_t k = 0; k < part.count; ++k) {
+                    const NzState &end = state[part.desc0 + k];
+                    if (end.status == NZ_ST_DONE) {
+                        const int64_t serial = (end.nstar > 0 ? end.nstar : N) - end.n0;
+                        g_stats[4] += end.n0;
+                        g_stats[5] += serial;
+                        g_job_pre[part.p.job] += end.n0;
+                        g_job_serial[part.p.job] += serial;
+                        continue;
                     }
-                    break;
-                case NZ_ST_PREFIX:
-                    p.prefix_mul *= 2;
-                    break;
-                default:
-                    return fail(NZ_EDEVICE, "sample %lld finished with status %d", (long long)p.sample, state[di].status);
+                    Plan p = part.p;
+                    p.sample += k;
+                    p.out += k;
+                    for (int lv = 0; lv < level[part.desc0 + k]; ++lv) {
+                        p.n0 = part.s.n0b[lv];
+                        p.backoff *= 2;   // the next backoff doubles the step
+                    }
+                    switch (end.status) {
+                    case NZ_ST_BAND:
+                        ++g_stats[1];
+                        p.band_hi = std::min<int64_t>(N, p.n0 + 2 * std::max<int64_t>(p.band_hi - p.n0, 2048));
+                        break;
+                    case NZ_ST_BUCKET:
+                        ++g_stats[2];
+                        p.shift_adj += 1;
+                        break;
+                    case NZ_ST_BACKOFF:
+                        ++g_stats[3];
+                        if (h_backoffs) ++h_backoffs[p.job];
+                        // back off by the caller's step, doubling it each time
+                        // (n0 - b, n0 - 3b, n0 - 7b, ...), until the start would
+                        // reach 0; without a step, halve.  A badly predicted lattice
+                        // needs only a few rounds, and n0 reaches 0 after at most
+                        // log2(N) of them.
+                        if (p.backoff > 0) {
+                            if (p.n0 - p.backoff > 0) {
+                                p.n0 -= p.backoff;
+                                p.backoff *= 2;
+                            } else {
+                                p.n0 = 0;
+                                p.backoff = 0;
+                            }
+                        } else {
+                            p.n0 = p.n0 >= 64 ? p.n0 / 2 : 0;
+                        }
+                        break;
+                    case NZ_ST_PREFIX:
+                        p.prefix_mul *= 2;
+                        break;
+                    default:
+                        return fail(NZ_EDEVICE, "sample %lld finished with status %d", (long long)p.sample, end.status);
+                    }
+                    ++redo_left;
+                    if (!redo.empty() && follows(redo.back(), p)) ++redo.back().count;
+                    else redo.push_back(Run{p, 1});
                 }
-                redo.push_back(p);
             }
         }
         todo.swap(redo);
+        left = redo_left;
     }
     return NZ_OK;
 }
 
-size_t batch_bytes(const nz_job *jobs, int32_t njobs, const Tune &tune)
+// smax: the jobs run in largest-cluster mode (window entries apart).
+size_t batch_bytes(const nz_job *jobs, int32_t njobs, const Tune &tune, bool smax = false)
 {
     // all samples of the first chunk resident, plus room for one redo of the
     // largest sample with a full band
@@ -943,13 +991,14 @@ size_t batch_bytes(const nz_job *jobs, int32_t njobs, const Tune &tune)
             tables.push_back(key);
             tab_entries += zone_rows(jobs[j].zone_mask).size();
         }
-        any_wrap = any_wrap || jobs[j].boundary == NZ_PERIODIC;
+        const bool wrap = jobs[j].boundary == NZ_PERIODIC && !smax;
+        any_wrap = any_wrap || wrap;
         Plan p{};
         p.L = jobs[j].L;
         p.mask = jobs[j].zone_mask;
         p.n0 = jobs[j].n0 > 0 ? jobs[j].n0 : 0;
         p.backoff = jobs[j].backoff;   // sizes the band of a first backoff too
-        p.wrap = jobs[j].boundary == NZ_PERIODIC;
+        p.wrap = wrap;
         const int64_t N = pow5(p.L);
         p.band_hi = jobs[j].band_hi > 0 ? std::min<int64_t>(jobs[j].band_hi, N) : default_band_hi(p.L, p.mask, p.n0);
         if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
@@ -1328,6 +1377,102 @@ NZ_API int nz_sweep_batch(const nz_job *jobs, int32_t njobs, void *d_ws, size_t 
     return rc;
 }
 
+// Device memory of the host entry points (nz_sweep, nz_smax_window), kept from
+// one call to the next on the same thread: mapping and unmapping it cost more
+// than the sweep itself (L = 12, 1000 samples of zone 1, 2 GB: 9 ms or 60 ms of
+// a call, by the state of the allocator).  Blocks up to kKeepBytes are kept, at
+// most kKeepTotal over all threads; larger ones are freed with the call, and a
+// kept block when its thread ends, when the thread turns to another device or a
+// larger block, or when an allocation fails.
+constexpr size_t kKeepBytes = size_t(4) << 30;
+constexpr size_t kKeepTotal = size_t(8) << 30;
+
+class DeviceBlock {
+public:
+    ~DeviceBlock() { release(); }
+    // `bytes` of memory on `device` (current), NULL if there is none
+    void *get(int device, size_t bytes)
+    {
+        if (p_ && device_ == device && bytes_ >= bytes) return p_;
+        release();
+        void *p = nullptr;
+        if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        p_ = p;
+        device_ = device;
+        bytes_ = bytes;
+        counted_ = false;
+        return p_;
+    }
+    // the call is over: keeps the block if the bounds allow it
+    void done()
+    {
+        if (!p_ || counted_) return;
+        if (bytes_ <= kKeepBytes && kept_.fetch_add(bytes_) + bytes_ <= kKeepTotal) {
+            counted_ = true;
+            return;
+        }
+        if (bytes_ <= kKeepBytes) kept_.fetch_sub(bytes_);
+        release();
+    }
+    void release()
+    {
+        if (!p_) return;
+        (void)hipFree(p_);
+        if (counted_) kept_.fetch_sub(bytes_);
+        p_ = nullptr;
+        counted_ = false;
+    }
+
+private:
+    void *p_ = nullptr;
+    size_t bytes_ = 0;
+    int device_ = -1;
+    bool counted_ = false;
+    static std::atomic<size_t> kept_;
+};
+std::atomic<size_t> DeviceBlock::kept_{0};
+
+DeviceBlock &thread_block()
+{
+    static thread_local DeviceBlock block;
+    return block;
+}
+
+// Workspace of at most `want` bytes (`samples` samples resident at once) followed
+// by `extra` bytes of outputs.  One beyond the kept size is cut to it while it
+// still holds kEnough samples: the chunks then fill the chip all the same, and
+// an extra chunk costs less than the mapping.  Else it is limited to half of the
+// free memory.
+constexpr int64_t kEnough = 512;
+int host_block(size_t want, int64_t samples, size_t extra, uint8_t **ws, size_t *ws_bytes, uint8_t **tail)
+{
+    int device = 0;
+    HIP_TRY(hipGetDevice(&device));
+    want = align_up(want);
+    if (extra < kKeepBytes / 2 && want + extra > kKeepBytes) {
+        const size_t cut = (kKeepBytes - extra) / kAlign * kAlign;
+        if (static_cast<double>(samples) * (static_cast<double>(cut) / static_cast<double>(want)) >= static_cast<double>(kEnough)) want = cut;
+    }
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        if (want + extra > kKeepBytes || attempt > 0) {
+            thread_block().release();   // (it counts as free memory)
+            size_t freeb = 0, totalb = 0;
+            HIP_TRY(hipMemGetInfo(&freeb, &totalb));
+            want = std::min(want, freeb / 2 / kAlign * kAlign);
+        }
+        if (void *p = thread_block().get(device, want + extra)) {
+            *ws = static_cast<uint8_t *>(p);
+            *ws_bytes = want;
+            *tail = *ws + want;
+            return NZ_OK;
+        }
+    }
+    return fail(NZ_ENOMEM, "hipMalloc of %zu workspace bytes failed", want + extra);
+}
+
 NZ_API int nz_sweep(int32_t L, uint32_t zone_mask, int32_t boundary, int64_t nsamples, uint64_t seed, int32_t *nstar,
                     int32_t *mass)
 {
@@ -1350,33 +1495,27 @@ NZ_API int nz_sweep(int32_t L, uint32_t zone_mask, int32_t boundary, int64_t nsa
     } catch (...) {
         return fail(NZ_ENOMEM, "host allocation failed");
     }
-    // stay well inside the device memory
-    size_t freeb = 0, totalb = 0;
-    HIP_TRY(hipMemGetInfo(&freeb, &totalb));
-    bytes = std::min(bytes, freeb / 2);
-    void *ws = nullptr;
-    int32_t *dn = nullptr, *dm = nullptr;
-    if (hipMalloc(&ws, bytes) != hipSuccess) return fail(NZ_ENOMEM, "hipMalloc of %zu workspace bytes failed", bytes);
-    if (hipMalloc(reinterpret_cast<void **>(&dn), nsamples * 4) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&dm), nsamples * 4) != hipSuccess) {
-        (void)hipFree(ws);
-        (void)hipFree(dn);
-        return fail(NZ_ENOMEM, "hipMalloc of outputs failed");
-    }
+    uint8_t *ws = nullptr, *tail = nullptr;
+    const size_t out_bytes = static_cast<size_t>(nsamples) * 4;
+    if (int rc = host_block(bytes, std::min<int64_t>(nsamples, kMaxChunk), 2 * out_bytes, &ws, &bytes, &tail)) return rc;
+    int32_t *dn = reinterpret_cast<int32_t *>(tail), *dm = dn + nsamples;
     int rc;
     try {
-        rc = run_batch(&j, 1, static_cast<uint8_t *>(ws), bytes, dn, dm, nullptr, t, nullptr);
+        rc = run_batch(&j, 1, ws, bytes, dn, mass ? dm : nullptr, nullptr, t, nullptr);
+        if (rc == NZ_OK) {
+            // n* and masses lie one behind the other: one copy
+            std::vector<int32_t> both(static_cast<size_t>(nsamples) * (mass ? 2 : 1));
+            if (hipMemcpy(both.data(), dn, both.size() * 4, hipMemcpyDeviceToHost) != hipSuccess) {
+                rc = fail(NZ_EDEVICE, "copy of results failed");
+            } else {
+                std::memcpy(nstar, both.data(), out_bytes);
+                if (mass) std::memcpy(mass, both.data() + nsamples, out_bytes);
+            }
+        }
     } catch (...) {
         rc = fail(NZ_ENOMEM, "host allocation failed");
     }
-    if (rc == NZ_OK) {
-        if (hipMemcpy(nstar, dn, nsamples * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-            (mass && hipMemcpy(mass, dm, nsamples * 4, hipMemcpyDeviceToHost) != hipSuccess))
-            rc = fail(NZ_EDEVICE, "copy of results failed");
-    }
-    (void)hipFree(ws);
-    (void)hipFree(dn);
-    (void)hipFree(dm);
+    thread_block().done();
     return rc;
 }
 
@@ -1408,41 +1547,71 @@ NZ_API int nz_smax_window(int32_t L, uint32_t zone_mask, int32_t boundary, uint6
     Tune t;
     size_t bytes = 0;
     try {
-        bytes = batch_bytes(&j, 1, t) + static_cast<size_t>(std::min<int64_t>(nsamples, kMaxChunk) + 1) *
-                                            align_up(static_cast<size_t>(W) * 4);
+        bytes = batch_bytes(&j, 1, t, true) + static_cast<size_t>(std::min<int64_t>(nsamples, kMaxChunk) + 1) *
+                                                  align_up(static_cast<size_t>(W) * 4);
     } catch (...) {
         return fail(NZ_ENOMEM, "host allocation failed");
     }
-    size_t freeb = 0, totalb = 0;
-    HIP_TRY(hipMemGetInfo(&freeb, &totalb));
-    bytes = std::min(bytes, freeb / 2);
-    void *ws = nullptr;
-    int32_t *dn = nullptr;
-    uint64_t *dsum = nullptr;
-    if (hipMalloc(&ws, bytes) != hipSuccess) return fail(NZ_ENOMEM, "hipMalloc of %zu workspace bytes failed", bytes);
-    if (hipMalloc(reinterpret_cast<void **>(&dn), nsamples * 4) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&dsum), W * 8) != hipSuccess) {
-        (void)hipFree(ws);
-        (void)hipFree(dn);
-        return fail(NZ_ENOMEM, "hipMalloc of outputs failed");
-    }
+    uint8_t *ws = nullptr, *tail = nullptr;
+    if (int rc = host_block(bytes, std::min<int64_t>(nsamples, kMaxChunk), static_cast<size_t>(W) * 8 + static_cast<size_t>(nsamples) * 4,
+                            &ws, &bytes, &tail)) return rc;
+    uint64_t *dsum = reinterpret_cast<uint64_t *>(tail);
+    int32_t *dn = reinterpret_cast<int32_t *>(tail + W * 8);
     int rc = NZ_OK;
     if (hipMemset(dsum, 0, W * 8) != hipSuccess) rc = fail(NZ_EDEVICE, "clearing the window sums failed");
     SmaxReq req{n_lo, n_hi, dsum};
     if (rc == NZ_OK) {
         try {
-            rc = run_batch(&j, 1, static_cast<uint8_t *>(ws), bytes, dn, nullptr, nullptr, t, nullptr, &req);
+            rc = run_batch(&j, 1, ws, bytes, dn, nullptr, nullptr, t, nullptr, &req);
         } catch (...) {
             rc = fail(NZ_ENOMEM, "host allocation failed");
         }
     }
     if (rc == NZ_OK && hipMemcpy(smax_sum, dsum, W * 8, hipMemcpyDeviceToHost) != hipSuccess)
         rc = fail(NZ_EDEVICE, "copy of the window sums failed");
-    (void)hipFree(ws);
-    (void)hipFree(dn);
-    (void)hipFree(dsum);
+    thread_block().done();
     return rc;
 }
+
+// Walks the binomial weights w(n) = C(N,n) p^n (1-p)^(N-n) / that of the mode
+// (1 at the mode), 0 < p < 1, from the mode outward by their ratio: up first,
+// then down.  term(n, w) adds a term, done(n, w) may end a direction once no
+// later term of it can change a sum.  Terms below 1e-300 are dropped.  The
+// ratios of eight steps are formed together (their divisions overlap); the
+// product runs through them one by one, in the same order as step by step.
+template <typename Term, typename Done>
+void binomial_walk(int64_t N, double p, int64_t mode, Term &&term, Done &&done)
+{
+    const double up = p / (1.0 - p);
+    double r[8];
+    double w = 1.0;
+    for (int64_t n = mode; n < N; n += 8) {
+        const int m = static_cast<int>(std::min<int64_t>(8, N - n));
+        for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(N - n - k) / static_cast<double>(n + k + 1) * up;
+        for (int k = 0; k < m; ++k) {
+            w *= r[k];
+            if (w < 1e-300) goto down;
+            term(n + k + 1, w, true);
+        }
+        if (done(n + m, w, true)) break;
+    }
+down:
+    w = 1.0;
+    for (int64_t n = mode; n > 0; n -= 8) {
+        const int m = static_cast<int>(std::min<int64_t>(8, n));
+        for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(n - k) / static_cast<double>(N - n + k + 1) / up;
+        for (int k = 0; k < m; ++k) {
+            w *= r[k];
+            if (w < 1e-300) return;
+            term(n - k - 1, w, false);
+        }
+        if (done(n - m, w, false)) return;
+    }
+}
+
+// Adding less than this times a sum leaves the sum as it is (half an ulp of it
+// is at least 2^-54 of it), and the weights only fall on the way outward.
+constexpr double kNoChange = 0x1p-55;
 
 // Binomial convolution of an observable on a window (eqs. (5)-(6) need
 // P_max(p) = <S_max(n)>/N convolved with the binomial of (N, p)): the same
@@ -1456,32 +1625,32 @@ NZ_API int nz_convolve_window(const double *Q, int64_t n_lo, int64_t n_hi, int64
     if (np < 0 || (np > 0 && (!p_grid || !out))) return fail(NZ_EINVAL, "bad p grid or output");
     for (int64_t k = 0; k < np; ++k)
         if (!(p_grid[k] >= 0.0 && p_grid[k] <= 1.0)) return fail(NZ_EINVAL, "p_grid[%lld] outside [0, 1]", (long long)k);
+    double most = 0.0;   // largest |Q| (NaN: the walks are not cut short)
+    for (int64_t n = 0; n < n_hi - n_lo; ++n) {
+        const double q = std::fabs(Q[n]);
+        if (!(q <= most)) most = q;
+        if (q != q) break;
+    }
     for (int64_t k = 0; k < np; ++k) {
         const double p = p_grid[k];
         int64_t mode = p == 0.0 ? 0 : (p == 1.0 ? N : static_cast<int64_t>(std::floor((N + 1) * p)));
         if (mode > N) mode = N;
-        auto q = [&](int64_t n) { return n >= n_lo && n < n_hi ? Q[n - n_lo] : 0.0; };
-        auto in = [&](int64_t n) { return n >= n_lo && n < n_hi ? 1.0 : 0.0; };
-        double sw = 1.0, swq = q(mode), swin = in(mode);
-        if (p > 0.0 && p < 1.0) {
-            const double up = p / (1.0 - p);
-            double w = 1.0;
-            for (int64_t n = mode; n < N; ++n) {
-                w *= static_cast<double>(N - n) / static_cast<double>(n + 1) * up;
-                if (w < 1e-300) break;
-                sw += w;
-                swq += w * q(n + 1);
-                swin += w * in(n + 1);
-            }
-            w = 1.0;
-            for (int64_t n = mode; n > 0; --n) {
-                w *= static_cast<double>(n) / static_cast<double>(N - n + 1) / up;
-                if (w < 1e-300) break;
-                sw += w;
-                swq += w * q(n - 1);
-                swin += w * in(n - 1);
-            }
-        }
+        const bool inside = mode >= n_lo && mode < n_hi;
+        double sw = 1.0, swq = inside ? Q[mode - n_lo] : 0.0, swin = inside ? 1.0 : 0.0;
+        if (p > 0.0 && p < 1.0)
+            binomial_walk(
+                N, p, mode,
+                [&](int64_t n, double w, bool) {
+                    sw += w;
+                    const bool in = n >= n_lo && n < n_hi;
+                    swq += w * (in ? Q[n - n_lo] : 0.0);
+                    swin += w * (in ? 1.0 : 0.0);
+                },
+                [&](int64_t n, double w, bool upward) {
+                    if (!(w < kNoChange * sw)) return false;
+                    if (upward ? n >= n_hi - 1 : n <= n_lo) return true;   // past the window
+                    return w < kNoChange * swin && w * most < kNoChange * std::fabs(swq);
+                });
         out[k] = swq / sw;
         if (cover) cover[k] = swin / sw;
     }
@@ -1594,17 +1763,42 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
     for (int64_t k = 0; k < np; ++k)
         if (!(p_grid[k] >= 0.0 && p_grid[k] <= 1.0)) return fail(NZ_EINVAL, "p_grid[%lld] outside [0, 1]", (long long)k);
     const int64_t N = hist_len - 1;
-    std::vector<double> F(N + 1);
+    // F(n) = (samples with 1 <= n* <= n) / total is a step function: its steps
+    // (n, samples up to n), one pass over the histogram
+    std::vector<int64_t> at;
+    std::vector<uint64_t> upto;
     double total = 0.0;
-    for (int64_t n = 0; n <= N; ++n) total += static_cast<double>(hist[n]);
-    if (total <= 0.0) return fail(NZ_EINVAL, "empty histogram");
-    // prefix sums in integers, divided once, so F is exact to rounding
-    uint64_t run = 0;
-    F[0] = 0.0;
-    for (int64_t n = 1; n <= N; ++n) {
-        run += hist[n];
-        F[n] = static_cast<double>(run) / total;
+    uint64_t run = 0, exact = 0;
+    bool whole = true;   // the total is an exact integer below 2^53
+    try {
+        for (int64_t n0 = 0; n0 <= N; n0 += 64) {
+            const int64_t n1 = std::min<int64_t>(n0 + 64, N + 1);
+            uint64_t any = 0;
+            for (int64_t n = n0; n < n1; ++n) any |= hist[n];
+            if (!any) continue;
+            for (int64_t n = n0; n < n1; ++n) {
+                if (!hist[n]) continue;
+                total += static_cast<double>(hist[n]);
+                exact += hist[n];
+                whole = whole && hist[n] < (1ull << 53) && exact < (1ull << 53);
+                if (n == 0) continue;
+                run += hist[n];
+                at.push_back(n);
+                upto.push_back(run);
+            }
+        }
+    } catch (...) {
+        return fail(NZ_ENOMEM, "host allocation failed");
     }
+    if (whole) total = static_cast<double>(exact);
+    if (total <= 0.0) return fail(NZ_EINVAL, "empty histogram");
+    // F at the steps (integers, divided once, so F is exact to rounding)
+    std::vector<double> F(upto.size() + 1);
+    F[0] = 0.0;
+    for (size_t i = 0; i < upto.size(); ++i) F[i + 1] = static_cast<double>(upto[i]) / total;
+    const auto step_of = [&](int64_t n) {   // steps at or below n
+        return static_cast<size_t>(std::upper_bound(at.begin(), at.end(), n) - at.begin());
+    };
     for (int64_t k = 0; k < np; ++k) {
         const double p = p_grid[k];
         if (p == 0.0) {
@@ -1612,27 +1806,35 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
             continue;
         }
         if (p == 1.0) {
-            R[k] = F[N];
+            R[k] = F[step_of(N)];
             continue;
         }
         int64_t mode = static_cast<int64_t>(std::floor((N + 1) * p));
         if (mode > N) mode = N;
-        const double up = p / (1.0 - p);
-        double sw = 1.0, swf = F[mode];
-        double w = 1.0;
-        for (int64_t n = mode; n < N; ++n) {
-            w *= static_cast<double>(N - n) / static_cast<double>(n + 1) * up;
-            if (w < 1e-300) break;
-            sw += w;
-            swf += w * F[n + 1];
-        }
-        w = 1.0;
-        for (int64_t n = mode; n > 0; --n) {
-            w *= static_cast<double>(n) / static_cast<double>(N - n + 1) / up;
-            if (w < 1e-300) break;
-            sw += w;
-            swf += w * F[n - 1];
-        }
+        const size_t mode_step = step_of(mode);
+        double sw = 1.0, swf = F[mode_step];
+        size_t i = mode_step;   // steps at or below the current n
+        bool was_up = true;
+        binomial_walk(
+            N, p, mode,
+            [&](int64_t n, double w, bool upward) {
+                if (upward != was_up) {
+                    was_up = upward;
+                    i = mode_step;
+                }
+                if (upward)
+                    while (i < at.size() && at[i] <= n) ++i;
+                else
+                    while (i > 0 && at[i - 1] > n) --i;
+                sw += w;
+                swf += w * F[i];
+            },
+            [&](int64_t n, double w, bool upward) {
+                if (!(w < kNoChange * sw)) return false;
+                if (w < kNoChange * swf) return true;                       // F <= 1
+                if (!upward) return at.empty() || n <= at.front();          // F = 0 from here down
+                return at.empty();                                          // F = 0 everywhere
+            });
         R[k] = swf / sw;
     }
     return NZ_OK;

@@ -72,6 +72,22 @@ struct NzSample {
     uint64_t off_sum;     // bitset summary: bit k set unless words k << sum_shift .. are all zero
     int32_t sum_shift;
     int32_t sum_words;    // 32-bit summary words (0: no summary)
+    // the in-chunk backoffs: threshold and buckets at n0 - b and at n0 - 3b (T0b =
+    // 0: not planned)
+    uint64_t T0b[2];
+    int32_t nbb[2];
+};
+
+// Consecutive samples of one job in a chunk, as the host plans them; the expand
+// kernel writes a descriptor, a queue entry and an output index for each.
+struct NzRun {
+    NzSample first;       // descriptor of the first sample
+    uint64_t stride;      // workspace bytes from one sample to the next
+    int32_t count;
+    int32_t desc0;        // first descriptor index
+    int32_t queue0;       // first place in the sweep's queue
+    int32_t list0;        // first place in the prefill list (-1: nothing prefilled)
+    int32_t out0;         // first output index
 };
 
 // Per-sample result/state record written by the kernels.

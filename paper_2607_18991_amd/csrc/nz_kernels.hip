@@ -2,7 +2,8 @@
 // sweep on sc(5) (Malarz & Woloszyn, Sec. II.B; neighbourhoods of Sec. II.A.2).
 //
 // Pipeline per chunk of samples (all launched on one stream):
-//   nz_clear_kernel    zero the bucket counters and per-sample state;
+//   nz_expand_kernel   a descriptor per sample from the host's runs of samples;
+//   nz_clear_kernel    zero the bucket counters and bitset summaries;
 //   nz_keys_kernel     Philox4x32-10 key of every site (integer VALU bound);
 //                      sites below the prefill threshold T0 are occupied at once
 //                      (bitset word per 32 sites, parent = self, site list);
@@ -19,6 +20,9 @@
 //                      root words' two border flags (or a winding loop) decide
 //                      spanning, and the block in which it happens is bisected.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
 
 #include "nz_internal.h"
 
@@ -143,26 +147,67 @@ __device__ __forceinline__ T bcast(T v, int lane)
 }
 
 // ---------------------------------------------------------------------------
-// Clearing: bucket counters and per-sample state of a chunk.
+// The samples of a chunk from its runs (the host plans runs of samples, so that
+// a batch of thousands costs it a few dozen records).
 
-__global__ __launch_bounds__(256) void nz_clear_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
-                                                       int32_t nsamp, uint8_t *__restrict__ ws, NzState *__restrict__ state)
+__global__ __launch_bounds__(256) void nz_expand_kernel(const NzRun *__restrict__ runs, NzSample *__restrict__ desc,
+                                                        NzState *__restrict__ state, int32_t *__restrict__ queue,
+                                                        int32_t *__restrict__ out_index, int32_t *__restrict__ list,
+                                                        int32_t *__restrict__ qhead)
 {
-    if (static_cast<int32_t>(blockIdx.x) >= nsamp) return;
-    const int sid = list ? list[blockIdx.x] : static_cast<int>(blockIdx.x);
-    const NzSample &d = desc[sid];
-    uint32_t *counts = reinterpret_cast<uint32_t *>(ws + d.off_counts);
-    for (int b = threadIdx.x; b < d.nb; b += blockDim.x) counts[b] = 0u;
-    uint32_t *sum = reinterpret_cast<uint32_t *>(ws + d.off_sum);
-    for (int w = threadIdx.x; w < d.sum_words; w += blockDim.x) sum[w] = 0u;
-    if (threadIdx.x == 0) {
+    const NzRun &r = runs[blockIdx.y];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *qhead = 0;
+    for (int32_t k = static_cast<int32_t>(blockIdx.x) * 256 + static_cast<int32_t>(threadIdx.x); k < r.count;
+         k += static_cast<int32_t>(gridDim.x) * 256) {
+        const int32_t di = r.desc0 + k;
+        const uint64_t off = static_cast<uint64_t>(k) * r.stride;
+        NzSample d = r.first;
+        d.sample += static_cast<uint64_t>(k);
+        d.off_par += off;
+        d.off_occ += off;
+        d.off_sites += off;
+        d.off_counts += off;
+        d.off_prefix += off;
+        d.off_parc += off;
+        d.off_wpos += off;
+        d.off_sum += off;
+        d.off_win += off;
+        desc[di] = d;
         NzState s;
         s.status = NZ_ST_PENDING;
         s.nstar = 0;
         s.mass = 0;
         s.n0 = 0;
         s.smax = 0;
-        state[sid] = s;
+        state[di] = s;
+        queue[r.queue0 + k] = di;
+        out_index[di] = r.out0 + k;
+        if (r.list0 >= 0) list[r.list0 + k] = di;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Clearing: bucket counters and summaries; samples that back off also take
+// their next threshold and start over.
+
+__global__ __launch_bounds__(256) void nz_clear_kernel(NzSample *__restrict__ desc, const int32_t *__restrict__ list,
+                                                       int32_t nsamp, int32_t level, uint8_t *__restrict__ ws,
+                                                       NzState *__restrict__ state)
+{
+    if (static_cast<int32_t>(blockIdx.x) >= nsamp) return;
+    const int sid = list ? list[blockIdx.x] : static_cast<int>(blockIdx.x);
+    NzSample &d = desc[sid];
+    const int32_t nb = list ? d.nbb[level] : d.nb;
+    uint32_t *counts = reinterpret_cast<uint32_t *>(ws + d.off_counts);
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) counts[b] = 0u;
+    uint32_t *sum = reinterpret_cast<uint32_t *>(ws + d.off_sum);
+    for (int w = threadIdx.x; w < d.sum_words; w += blockDim.x) sum[w] = 0u;
+    if (list && threadIdx.x == 0) {
+        d.T0 = d.T0b[level];
+        d.nb = nb;
+        state[sid].status = NZ_ST_PENDING;
+        state[sid].n0 = 0;
+        state[sid].smax = 0;
     }
 }
 
@@ -2073,11 +2118,21 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
 
 namespace nz {
 
-hipError_t launch_clear(const NzSample *desc, const int32_t *list, int32_t nsamp, uint8_t *ws, NzState *state,
+hipError_t launch_expand(const NzRun *runs, int32_t nruns, int32_t max_count, NzSample *desc, NzState *state,
+                         int32_t *queue, int32_t *out_index, int32_t *list, int32_t *qhead, hipStream_t st)
+{
+    if (nruns <= 0 || nruns > 65535) return nruns <= 0 ? hipSuccess : hipErrorInvalidValue;
+    hipLaunchKernelGGL(nz_expand_kernel, dim3(static_cast<uint32_t>((max_count + 255) / 256), static_cast<uint32_t>(nruns)),
+                       dim3(256), 0, st, runs, desc, state, queue, out_index, list, qhead);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(NzSample *desc, const int32_t *list, int32_t nsamp, int32_t level, uint8_t *ws, NzState *state,
                         hipStream_t st)
 {
     if (nsamp <= 0) return hipSuccess;
-    hipLaunchKernelGGL(nz_clear_kernel, dim3(nsamp), dim3(256), 0, st, desc, list, nsamp, ws, state);
+    if (list && (level < 0 || level > 1)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(nz_clear_kernel, dim3(nsamp), dim3(256), 0, st, desc, list, nsamp, level, ws, state);
     return hipGetLastError();
 }
 
@@ -2179,9 +2234,17 @@ static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cu
                                            static_cast<int>(lds));
         if (e != hipSuccess) return e;
     }
-    int wgs = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&wgs, k, NT, lds);
-    if (e != hipSuccess) return e;
+    // workgroups per CU for this much LDS (one architecture: fixed for the process)
+    static std::atomic<uint64_t> last{0};   // lds << 32 | workgroups of the last shape asked for
+    uint64_t l = last.load(std::memory_order_relaxed);
+    if (l == 0 || (l >> 32) != lds) {
+        int n = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, NT, lds);
+        if (e != hipSuccess) return e;
+        l = (static_cast<uint64_t>(lds) << 32) | static_cast<uint32_t>(n);
+        last.store(l, std::memory_order_relaxed);
+    }
+    const int wgs = static_cast<int>(l & 0xFFFFFFFFu);
     const int grid = std::min(a.nqueue, cus * std::max(1, wgs));
     hipLaunchKernelGGL(k, dim3(grid), dim3(NT), lds, st, a, o);
     return hipGetLastError();

@@ -7,8 +7,14 @@
 
 namespace nz {
 
-// Samples 0..nsamp-1, or list[0..nsamp) when list != NULL.
-hipError_t launch_clear(const NzSample *desc, const int32_t *list, int32_t nsamp, uint8_t *ws, NzState *state,
+// Descriptors, pending states, queue, output indexes and prefill list of a
+// chunk's samples from runs[0..nruns), none longer than max_count; *qhead = 0.
+hipError_t launch_expand(const NzRun *runs, int32_t nruns, int32_t max_count, NzSample *desc, NzState *state,
+                         int32_t *queue, int32_t *out_index, int32_t *list, int32_t *qhead, hipStream_t st);
+
+// Clears the bucket counters and summaries of samples 0..nsamp-1; with a list
+// those of list[0..nsamp), which start over at their backoff `level`.
+hipError_t launch_clear(NzSample *desc, const int32_t *list, int32_t nsamp, int32_t level, uint8_t *ws, NzState *state,
                         hipStream_t st);
 
 // Keys for samples [first, first + count) of the descriptor array, all of

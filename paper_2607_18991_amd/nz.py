@@ -45,6 +45,19 @@ class NzJob(ctypes.Structure):
     ]
 
 
+_JOB_DTYPE = np.dtype([("L", "<i4"), ("zone_mask", "<u4"), ("boundary", "<i4"), ("reserved", "<i4"), ("seed", "<u8"),
+                       ("sample0", "<i8"), ("nsamples", "<i8"), ("n0", "<i8"), ("backoff", "<i8"), ("band_hi", "<i8"),
+                       ("prio", "<f8")])
+assert _JOB_DTYPE.itemsize == ctypes.sizeof(NzJob)
+_JOB_FIELDS = (
+    ("L", lambda j: int(j["L"])), ("zone_mask", lambda j: int(j["zone_mask"])),
+    ("boundary", lambda j: int(j.get("boundary", NZ_FREE))), ("seed", lambda j: int(j["seed"]) & (2**64 - 1)),
+    ("sample0", lambda j: int(j.get("sample0", 0))), ("nsamples", lambda j: int(j["nsamples"])),
+    ("n0", lambda j: int(j.get("n0", -1))), ("backoff", lambda j: int(j.get("backoff", 0))),
+    ("band_hi", lambda j: int(j.get("band_hi", 0))), ("prio", lambda j: float(j.get("prio", 0.0))),
+)
+
+
 class NzTuning(ctypes.Structure):
     _fields_ = [("residency", ctypes.c_int32), ("wg_waves", ctypes.c_int32),
                 ("waves_per_simd", ctypes.c_int32), ("bucket_log2", ctypes.c_int32),
@@ -192,17 +205,18 @@ def make_jobs(jobs) -> ctypes.Array:
     sample0, n0 (-1 plain), backoff, band_hi, prio, boundary."""
     jobs = list(jobs)
     arr = (NzJob * max(len(jobs), 1))()
-    for k, j in enumerate(jobs):
-        arr[k].L = int(j["L"])
-        arr[k].zone_mask = int(j["zone_mask"])
-        arr[k].boundary = int(j.get("boundary", NZ_FREE))
-        arr[k].seed = int(j["seed"]) & (2**64 - 1)
-        arr[k].sample0 = int(j.get("sample0", 0))
-        arr[k].nsamples = int(j["nsamples"])
-        arr[k].n0 = int(j.get("n0", -1))
-        arr[k].backoff = int(j.get("backoff", 0))
-        arr[k].band_hi = int(j.get("band_hi", 0))
-        arr[k].prio = float(j.get("prio", 0.0))
+    try:
+        # column by column through one structured view of the array (a ctypes
+        # attribute access per field costs more than the whole of this)
+        v = np.frombuffer(arr, dtype=_JOB_DTYPE, count=len(jobs))
+        for name, get in _JOB_FIELDS:
+            v[name] = np.array([get(j) for j in jobs], dtype=_JOB_DTYPE[name])
+    except OverflowError:
+        # a value beyond its field: reduced to the field's width, for the library
+        # to judge
+        for k, j in enumerate(jobs):
+            for name, get in _JOB_FIELDS:
+                setattr(arr[k], name, get(j))
     return arr, len(jobs)
 
 
@@ -326,11 +340,13 @@ def nz_prefill_plan(y, jobs, k_sigma: float, band_sigma: float, plain: bool = Fa
     arr, n = make_jobs(jobs)
     _check(lib().nz_prefill_plan(_np_ptr(yy), ctypes.cast(arr, ctypes.c_void_p), n, k_sigma, band_sigma,
                                  int(bool(plain))))
-    for k, j in enumerate(jobs):
-        j["band_hi"] = int(arr[k].band_hi)
-        j["n0"] = int(arr[k].n0)
-        if not plain:
-            j["backoff"] = int(arr[k].backoff)
+    if n:
+        v = np.frombuffer(arr, dtype=_JOB_DTYPE, count=n)
+        for j, band_hi, n0, backoff in zip(jobs, v["band_hi"].tolist(), v["n0"].tolist(), v["backoff"].tolist()):
+            j["band_hi"] = band_hi
+            j["n0"] = n0
+            if not plain:
+                j["backoff"] = backoff
     return jobs
 
 
