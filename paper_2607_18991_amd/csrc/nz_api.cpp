@@ -312,7 +312,7 @@ struct Sizes {
     int64_t n0b[2];
     uint64_t T0b[2];
     int32_t nbb[2];
-    size_t par, occ, sites, counts, prefix, parc, wpos, win, sum, total;
+    size_t par, occ, sites, counts, prefix, parc, wrec, win, sum, total;
     int32_t sum_shift, sum_words;
 };
 
@@ -365,10 +365,10 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     s.sites = align_up(static_cast<size_t>(nb_alloc) * s.cap * 4);
     s.counts = align_up(static_cast<size_t>(nb_alloc) * 4);
     s.prefix = align_up(static_cast<size_t>(s.prefix_cap) * 4);
-    // the bulk labelling's list forest and word positions (not for periodic
+    // the bulk labelling's list forest and word records (not for periodic
     // first-wrap samples, whose labelling runs on the lattice entries)
     s.parc = p.wrap ? 0 : align_up(static_cast<size_t>(s.prefix_cap) * 4);
-    s.wpos = (p.wrap || s.prefix_cap == 0) ? 0 : s.occ;
+    s.wrec = (p.wrap || s.prefix_cap == 0) ? 0 : 2 * s.occ;
     s.win = p.win_hi > 0 ? align_up(static_cast<size_t>(p.win_hi - p.win_lo) * 4) : 0;
     // bitset summary for the hook of sparse prefills: at most kSumWords words, one
     // bit per 1..16 bitset words (none above that: L > 27, or first-wrap samples)
@@ -380,7 +380,7 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
         s.sum_words = (gs <= 4 && !p.wrap) ? static_cast<int32_t>(((words >> gs) + 31) / 32 + 1) : 0;
         s.sum = align_up(static_cast<size_t>(s.sum_words) * 4);
     }
-    s.total = s.par + s.occ + s.sites + s.counts + s.prefix + s.parc + s.wpos + s.win + s.sum;
+    s.total = s.par + s.occ + s.sites + s.counts + s.prefix + s.parc + s.wrec + s.win + s.sum;
     return s;
 }
 
@@ -565,7 +565,7 @@ NzRun make_run(const Part &part, const nz_job *jobs, TablePool &pool)
     d.off_counts = off; off += s.counts;
     d.off_prefix = off; off += s.prefix;
     d.off_parc = off; off += s.parc;
-    d.off_wpos = off; off += s.wpos;
+    d.off_wrec = off; off += s.wrec;
     d.off_sum = off; off += s.sum;
     d.sum_shift = s.sum_shift;
     d.sum_words = s.sum_words;

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void nz_expand_kernel(const NzRun *__restrict_
         d.off_counts += off;
         d.off_prefix += off;
         d.off_parc += off;
-        d.off_wpos += off;
+        d.off_wrec += off;
         d.off_sum += off;
         d.off_win += off;
         desc[di] = d;
@@ -528,15 +528,13 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
         cnt[g] = __builtin_amdgcn_readlane(incl, 63);
         total += cnt[g];
     }
-    uint32_t *wpos = reinterpret_cast<uint32_t *>(ws + d.off_wpos);
-    if (total == 0u) {   // wave-uniform
-        // no prefilled site: the words' positions are stored all the same (any
-        // position will do: the sweep checks the entry it finds there)
+    uint2 *wrec = reinterpret_cast<uint2 *>(ws + d.off_wrec);
+    if (total == 0u) {   // wave-uniform: nothing prefilled in the range
         if (!d.wrap)
 #pragma unroll
             for (int g = 0; g < KEYS_GROUPS; ++g) {
                 const uint32_t w = w0 + 64u * static_cast<uint32_t>(g) + lane;
-                if (mine[g] && w < occ_words) wpos[w] = 0u;
+                if (mine[g] && w < occ_words) wrec[w] = make_uint2(0u, 0u);
             }
         return;
     }
@@ -549,7 +547,7 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     for (int g = 0; g < KEYS_GROUPS; ++g) {
         const uint32_t w = w0 + 64u * static_cast<uint32_t>(g) + lane;
         uint32_t pos = base + excl[g];
-        if (!d.wrap && mine[g] && w < occ_words) wpos[w] = pos;
+        if (!d.wrap && mine[g] && w < occ_words) wrec[w] = make_uint2(pos, word[g]);
         // the word's sites in bit order, one lane per word
         uint32_t bits = word[g];
         const uint32_t site0 = w << 5;
@@ -606,7 +604,8 @@ __device__ __forceinline__ bool xcd_slot(int32_t nlist, int32_t bx, int32_t &y, 
 // lattice indices: parc[i] is the parent of list entry i, so the whole forest
 // of a sample is 4 bytes per prefilled site and stays in the L2 of the XCD that
 // holds the sample.  The list position of an occupied neighbour t is the
-// position of its bitset word (wpos) plus the set bits below t in that word.
+// position of its bitset word plus the set bits below t in that word; both are
+// read as one 8-byte record per word.
 // The forest stays what it is through the sweep: prefilled sites have no lattice
 // entries, their roots keep their root words in it, and band sites link to its
 // nodes.
@@ -706,7 +705,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
     const uint64_t magic = d.magic;
     int32_t *par = reinterpret_cast<int32_t *>(ws + d.off_parc);
     const uint32_t *occ = reinterpret_cast<const uint32_t *>(ws + d.off_occ);
-    const uint32_t *wpos = reinterpret_cast<const uint32_t *>(ws + d.off_wpos);
+    const uint2 *wrec = reinterpret_cast<const uint2 *>(ws + d.off_wrec);
     const uint32_t *prefix = reinterpret_cast<const uint32_t *>(ws + d.off_prefix);
     const NzOffset *tab = tabs + d.tab;
     const uint32_t lane = lane_id();
@@ -750,8 +749,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
             // other side of the row
             for (int side = 0; side < (PER ? 2 : 1); ++side) {
                 int32_t b[HOOK_UNROLL];
-                uint32_t v[HOOK_UNROLL], w0[HOOK_UNROLL], w1[HOOK_UNROLL];
-                uint32_t par0 = 0u;   // parities of the first words' indexes
+                uint32_t v[HOOK_UNROLL];
 #pragma unroll
                 for (int q = 0; q < HOOK_UNROLL; ++q) {
                     NzOffset o;
@@ -771,23 +769,21 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                     const int32_t c = __builtin_ctz(dm | 32u);
                     const uint32_t p0 = dm ? static_cast<uint32_t>(b[q] + c) : 0u;
                     const uint32_t wi = p0 >> 5;
-                    par0 |= (wi & 1u) << q;
                     const bool maybe = !use_sum || ((hsum[(wi >> gs) >> 5] >> ((wi >> gs) & 31)) & 1u);
-                    w0[q] = dm && maybe ? occ[wi] : 0u;
-                    w1[q] = 0u;
+                    const uint32_t w0 = dm && maybe ? occ[wi] : 0u;
+                    uint32_t w1 = 0u;
                     if (o.code & 31u & ((o.code & 31u) - 1u)) {   // (uniform) more than one site in the row
                         const uint32_t p1 = static_cast<uint32_t>(b[q] + 31 - __builtin_clz(dm | 1u));
-                        if (dm && (p1 >> 5) != wi) w1[q] = occ[wi + 1u];
+                        if (dm && (p1 >> 5) != wi) w1 = occ[wi + 1u];
                     }
-                    v[q] = (__builtin_amdgcn_alignbit(w1[q], w0[q], p0 & 31u) << c) & dm;
+                    v[q] = (__builtin_amdgcn_alignbit(w1, w0, p0 & 31u) << c) & dm;
                 }
-                // list positions of the occupied neighbours: their words' first
-                // positions (loaded together for the first site of every row)
-                // plus the set bits below them
-                uint32_t jw[HOOK_UNROLL];
+                // list positions of the occupied neighbours, from their words' records
+                // (loaded together for the first site of every row)
+                uint2 rec[HOOK_UNROLL];
 #pragma unroll
                 for (int q = 0; q < HOOK_UNROLL; ++q)
-                    jw[q] = v[q] ? wpos[static_cast<uint32_t>(b[q] + __builtin_ctz(v[q])) >> 5] : 0u;
+                    rec[q] = v[q] ? wrec[static_cast<uint32_t>(b[q] + __builtin_ctz(v[q])) >> 5] : make_uint2(0u, 0u);
 #pragma unroll
                 for (int q = 0; q < HOOK_UNROLL; ++q) {
                     bool first = true;
@@ -798,10 +794,8 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
                             const int c = __builtin_ctz(v[q]);
                             v[q] &= v[q] - 1u;
                             const uint32_t p = static_cast<uint32_t>(b[q] + c);
-                            if (!first) jw[q] = wpos[p >> 5];
-                            // the word that holds p: the window's first or second
-                            const uint32_t word = ((p >> 5) & 1u) == ((par0 >> q) & 1u) ? w0[q] : w1[q];
-                            j = static_cast<int32_t>(jw[q] + static_cast<uint32_t>(__popc(word & ((1u << (p & 31)) - 1u))));
+                            if (!first) rec[q] = wrec[p >> 5];
+                            j = static_cast<int32_t>(rec[q].x + static_cast<uint32_t>(__popc(rec[q].y & ((1u << (p & 31)) - 1u))));
                             // the first neighbour below is linked without finds (at the end)
                             edge = below >= 0 || j > i;
                             if (!edge) below = j;
@@ -1178,16 +1172,17 @@ __global__ __launch_bounds__(256) void nz_accumw_kernel(const NzSample *__restri
 // for wide neighbourhoods, the checks themselves.  The checks therefore read a
 // map of the occupation held in LDS (below), one row of up to five offsets at
 // a time, and blocks are as large as the tables allow beside the map.  Measured
-// (L = 16, 7 compact neighbourhoods x 1000, prefilled): a block of up to 512
-// sites takes 17 us -- checks 6.0, parents and roots 7.5, unions 1.8, sizes and
-// flags 0.9, write-back 0.6 -- against 24 us for 64 sites by one wave in the
-// sweep this one replaced; ranks 6.5 and bisection 26 us once per sample.  37
+// (L = 16, zone 1 x 1000, prefilled): a block of up to 512 sites takes 16 us --
+// marks 0.7, checks 1.9, parents and roots 9.8, unions 1.4, sizes and flags 0.9,
+// write-back 0.9 -- against 24 us for 64 sites by one wave in the sweep this one
+// replaced; ranks 7 and bisection 20 us once per sample.  With separate tables
+// for a block's sites (marked in memory) and for the earlier roots the kernel
+// took 2.39 ms for this batch and takes 2.13, at L = 24 6.59 and 5.29.  37
 // samples of L = 13, z = 380 took 1.56 ms and take 0.11 ms, the periodic L = 12
 // batch of 700 samples 26 ms and 0.5 ms.
 //
-// While a block is processed the parent entries of its sites hold BLK_MARK |
-// position, a value no node id reaches (sites below 2^29, list nodes below
-// 2^30) and no root word has (bit 31 clear).
+// A block's sites have no entry in memory before it is committed: neighbours
+// among them are found in the node table.
 
 enum { BLK_SPAN = 0, BLK_WRAP = 1, BLK_SMAX = 2 };
 
@@ -1197,18 +1192,16 @@ struct SweepOut {
     const int32_t *out_index; // per sample: position in the caller's output arrays
 };
 
-constexpr uint32_t BLK_RSLOTS = 1024;    // hash slots for the earlier roots (at least 892: one site fits)
 constexpr int BLK_EDGES = 1536;          // recorded (site, occupied neighbour) pairs per block
 constexpr int BLK_CHUNK = 6;             // rows checked together (five bits each: one 32-bit mask)
 constexpr int BLK_MAXROWS = 300;         // rows of the widest neighbourhood (298), in whole chunks
 constexpr uint32_t BLK_EMPTY = 0xFFFFFFFFu;
-constexpr int32_t BLK_MARK = 0x40000000;
-constexpr int BLK_MAXB = 512;
+constexpr int32_t NZ_NONE = static_cast<int32_t>(0x80000000u);   // (a root word of no cluster)
+constexpr int32_t BLK_LINKED = 0x40000000;   // (above every node id: sites < 2^29, list nodes < 2^30)
 constexpr uint32_t BLK_SMALL_MAP = 4096;  // words of the largest map that leaves room for several workgroups per CU
-constexpr uint32_t BLK_SMAX_MAP = 4096;
 constexpr uint32_t BLK_MAP_PAD = 3;       // map words outside the lattice: one before, two behind
 static_assert(BLK_MAXROWS % BLK_CHUNK == 0, "whole chunks");
-static_assert(BLK_RSLOTS >= 892 && BLK_EDGES >= 892, "a block of one site always fits");
+static_assert(BLK_EDGES >= 892, "a block of one site always fits");
 
 __device__ __forceinline__ int32_t site_of(uint32_t pc, int32_t L)
 {
@@ -1231,80 +1224,143 @@ __device__ __forceinline__ T ld_g(T *p) { return __hip_atomic_load(p, __ATOMIC_R
 template <typename T>
 __device__ __forceinline__ void st_g(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
-// Node words of the LDS forest: the parent node, and for the wrap sweep the x0
-// displacement from it in the high half (one 64-bit word, so that every read
-// is a consistent pair).
+// Node words of the LDS forest: a root word (bit 31: cluster size and border
+// flags before the block's unions) or the parent node, and for the wrap sweep
+// the x0 displacement from it in the high half (one 64-bit word, so that every
+// read is a consistent pair).
 template <bool WRAP>
 struct BlkWord {
     using type = uint32_t;
-    static __device__ __forceinline__ uint32_t make(uint32_t p, int32_t) { return p; }
-    static __device__ __forceinline__ uint32_t par(uint32_t e) { return e; }
+    static __device__ __forceinline__ uint32_t make(uint32_t lo, int32_t) { return lo; }
+    static __device__ __forceinline__ uint32_t lo(uint32_t e) { return e; }
     static __device__ __forceinline__ int32_t dx(uint32_t) { return 0; }
 };
 template <>
 struct BlkWord<true> {
     using type = uint64_t;
-    static __device__ __forceinline__ uint64_t make(uint32_t p, int32_t d)
+    static __device__ __forceinline__ uint64_t make(uint32_t lo, int32_t d)
     {
-        return (static_cast<uint64_t>(static_cast<uint32_t>(d)) << 32) | p;
+        return (static_cast<uint64_t>(static_cast<uint32_t>(d)) << 32) | lo;
     }
-    static __device__ __forceinline__ uint32_t par(uint64_t e) { return static_cast<uint32_t>(e); }
+    static __device__ __forceinline__ uint32_t lo(uint64_t e) { return static_cast<uint32_t>(e); }
     static __device__ __forceinline__ int32_t dx(uint64_t e) { return static_cast<int32_t>(e >> 32); }
 };
 
-template <int MODE, int B>
+// One workgroup of NT threads, blocks of up to B sites.  The block's nodes -- its
+// sites and the earlier roots it touches -- are slots of one open-addressing
+// table keyed by node id, so a neighbour that belongs to the block, or is itself
+// an earlier root already there, is found without leaving LDS.
+template <int MODE_, bool PER_, int NT_, int B_>
+struct BlkCfg {
+    static constexpr int MODE = MODE_, NT = NT_, B = B_;
+    static constexpr bool PER = PER_;
+    // slots: a full block, the roots of one site's 892 neighbours
+    static constexpr uint32_t RS = B > 256 ? 2048 : 1024;
+    static constexpr uint32_t SHIFT = B > 256 ? 21 : 22;
+    // the ranks of a bisection go where the map was, if that is large enough
+    static constexpr bool OWN_SCRATCH = NT == 256;
+    static constexpr uint32_t SCRATCH = B + RS / 2;   // words: keys of the sites, 16-bit ranks of the slots
+    static_assert(B <= NT, "thread t loads entry t of a block");
+    static_assert(RS % NT == 0 && RS >= B + 512 && RS >= 893 && RS <= 2048, "whole slots per thread; node numbers of 11 bits");
+    static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
+};
+
+template <typename C>
 struct BlkLds {
-    using W = BlkWord<MODE == BLK_WRAP>;
-    typename W::type npar[B + BLK_RSLOTS];
-    uint32_t et[BLK_EDGES];            // pair e: the neighbour's site, then its node (BLK_EMPTY: dropped)
-    uint32_t pcs[B];                   // packed coordinates of the block's sites
-    uint32_t rkey[BLK_RSLOTS];         // earlier roots the block touches (open addressing)
-    uint32_t nword[B + BLK_RSLOTS];    // node words in the root-word format
+    using W = BlkWord<C::MODE == BLK_WRAP>;
+    typename W::type f[C::RS];         // the forest
+    uint32_t rkey[C::RS];              // node ids (BLK_EMPTY: free)
+    uint32_t et[BLK_EDGES];            // pair e: block position, row and step; then the two nodes, 16 bits each
+    uint32_t pcs[C::B];                // packed coordinates of the block's sites
     NzOffset rows[BLK_MAXROWS];        // the sample's rows, padded with empty ones to whole chunks
-    uint16_t ei[BLK_EDGES];            // pair e: the block position, and (d0 + 2) << 12 for the wrap sweep
-    int16_t eq[MODE == BLK_WRAP ? BLK_EDGES : 1];   // x0(site) - x0(node) of pair e
-    // largest-cluster sweep: the pairs of every position as a linked list, and
-    // the running maximum after every position
-    uint16_t next[MODE == BLK_SMAX ? BLK_EDGES : 1];
-    uint32_t first[MODE == BLK_SMAX ? B : 1];
-    uint32_t smax[MODE == BLK_SMAX ? B : 1];
+    uint16_t spos[C::B];               // the sites' nodes
+    int16_t eq[C::MODE == BLK_WRAP ? BLK_EDGES : 1];   // x0(first node) - x0(second node) of pair e
+    uint32_t scratch[C::OWN_SCRATCH ? C::SCRATCH : 1];
+    // largest-cluster sweep: the block position of every node (0xFFFF: an earlier
+    // root), the pairs of every position as a linked list, and the running
+    // maximum after every position
+    uint16_t pos[C::MODE == BLK_SMAX ? C::RS : 1];
+    uint16_t next[C::MODE == BLK_SMAX ? BLK_EDGES : 1];
+    uint32_t first[C::MODE == BLK_SMAX ? C::B : 1];
+    uint32_t smax[C::MODE == BLK_SMAX ? C::B : 1];
     int32_t ecnt, nroots, flag, bad, claim;
     uint32_t total;                    // spanning: the size of the cluster of the T-th site
     uint32_t croot;                    //           and its root node
 };
 
-__device__ __forceinline__ uint32_t blk_hash(uint32_t t) { return (t * 0x9E3779B1u) >> 22; }
-static_assert(BLK_RSLOTS == 1024, "blk_hash yields ten bits");
+template <typename C>
+__device__ __forceinline__ uint32_t blk_hash(uint32_t id) { return (id * 0x9E3779B1u) >> C::SHIFT; }
 
-// Root of node x in the LDS forest with path halving; D is the displacement of
-// x from it.  Only non-roots are rewritten (to an ancestor) and links only
-// change roots, so concurrent finds and links keep the forest acyclic.
-template <int MODE, int B>
-__device__ __forceinline__ uint32_t blk_find(BlkLds<MODE, B> &S, uint32_t x, int32_t &D)
+// The node of id, entered if it is not there yet (fresh); C::RS if the table is
+// full.
+template <typename C>
+__device__ __forceinline__ uint32_t blk_enter(BlkLds<C> &S, uint32_t id, bool &fresh)
 {
-    using W = typename BlkLds<MODE, B>::W;
-    D = 0;
-    auto e = ld_g(&S.npar[x]);
-    for (;;) {
-        const uint32_t p = W::par(e);
-        if (p == x) return x;
-        const auto g = ld_g(&S.npar[p]);
-        if (W::par(g) == p) {
-            D += W::dx(e);
-            return p;
+    uint32_t h = blk_hash<C>(id);
+    fresh = false;
+    for (uint32_t k = 0; k < C::RS; ++k) {
+        uint32_t expected = BLK_EMPTY;
+        if (__hip_atomic_compare_exchange_strong(&S.rkey[h], &expected, id, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP)) {
+            fresh = true;
+            return h;
         }
-        const auto h = W::make(W::par(g), W::dx(e) + W::dx(g));
-        st_g(&S.npar[x], h);
-        D += W::dx(h);
-        x = W::par(g);
-        e = ld_g(&S.npar[x]);
+        if (expected == id) return h;
+        h = (h + 1) & (C::RS - 1);
     }
+    return C::RS;
+}
+
+// The node of id, C::RS if it is not (yet) there.
+template <typename C>
+__device__ __forceinline__ uint32_t blk_lookup(BlkLds<C> &S, uint32_t id)
+{
+    uint32_t h = blk_hash<C>(id);
+    for (uint32_t k = 0; k < C::RS; ++k) {
+        const uint32_t key = ld_g(&S.rkey[h]);
+        if (key == id) return h;
+        if (key == BLK_EMPTY) break;
+        h = (h + 1) & (C::RS - 1);
+    }
+    return C::RS;
+}
+
+// Root of node x in the LDS forest with path halving, its root word, and the
+// displacement D of x from it.  Only non-roots are rewritten (to an ancestor)
+// and links only change roots, so concurrent finds and links keep the forest
+// acyclic.
+template <typename C>
+__device__ __forceinline__ uint32_t blk_find(BlkLds<C> &S, uint32_t x, uint32_t &word, int32_t &D)
+{
+    using W = typename BlkLds<C>::W;
+    D = 0;
+    auto e = ld_g(&S.f[x]);
+    while (!(W::lo(e) & NZ_ROOT)) {
+        const uint32_t p = W::lo(e);
+        const auto g = ld_g(&S.f[p]);
+        if (W::lo(g) & NZ_ROOT) {
+            D += W::dx(e);
+            x = p;
+            e = g;
+            break;
+        }
+        const auto h = W::make(W::lo(g), W::dx(e) + W::dx(g));
+        st_g(&S.f[x], h);
+        D += W::dx(h);
+        x = W::lo(g);
+        e = ld_g(&S.f[x]);
+    }
+    word = W::lo(e);
+    return x;
 }
 
 // The lattice side of one sample: occupancy bits, their map in LDS and the
 // union-find entries (32-bit parent / root words, 64-bit with displacements for
 // the wrap sweep; prefilled roots of the former live in the list forest as
 // nodes LIST_NODE | i).
+// An entry written by the sweep carries BLK_LINKED, which tells former roots
+// (and members whose path was cut short) from the members that still point at
+// their root of the labelling.
 //
 // The map: bit k of the map (k counted from word 1; words 0 and the last two
 // are zero) is clear only if sites k << mshift .. are all empty.  Up to L = 16
@@ -1317,9 +1373,8 @@ struct BlkMem {
     int32_t *par;
     int32_t *parc;
     uint64_t *pw;
-    const uint32_t *wpos;     // per bitset word: list position of its first prefilled site
-    const uint32_t *prefix;   // prefilled sites in list order
-    int32_t n0;               // how many
+    const uint2 *wrec;        // per bitset word: list position of its first prefilled site, prefilled bits
+    int32_t n0;               // prefilled sites
     uint32_t *map;      // LDS
     uint32_t mshift;
     uint32_t occ_words;
@@ -1339,11 +1394,6 @@ struct BlkMem {
         else
             __hip_atomic_fetch_and(&map[1 + (s >> 5)], ~(1u << (s & 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    __device__ __forceinline__ void mark(int32_t s, int32_t pos) const
-    {
-        if constexpr (MODE == BLK_WRAP) st_g(&pw[s], static_cast<uint64_t>(static_cast<uint32_t>(BLK_MARK | pos)));
-        else st_g(&par[s], BLK_MARK | pos);
-    }
     __device__ __forceinline__ int32_t par_ld(int32_t i) const
     {
         return i >= LIST_NODE ? ld_g(&parc[i - LIST_NODE]) : ld_g(&par[i]);
@@ -1353,34 +1403,17 @@ struct BlkMem {
         if (i >= LIST_NODE) st_g(&parc[i - LIST_NODE], v);
         else st_g(&par[i], v);
     }
-    // List position of an occupied site t, -1 if it is no prefilled one.  With an
-    // exact map the bitset holds the prefilled sites only: the position of t's
-    // word plus the set bits below t.  Else band sites have been added to the
-    // bitset: the entry is looked for from that position down (each band site
-    // below t in its word puts it one too far).
-    __device__ __forceinline__ int32_t list_entry(int32_t t) const
-    {
-        const uint32_t w = static_cast<uint32_t>(t) >> 5, bit = static_cast<uint32_t>(t) & 31u;
-        const uint32_t word = ld_g(&occ[w]);
-        int32_t k = static_cast<int32_t>(wpos[w] + static_cast<uint32_t>(__popc(word & ((1u << bit) - 1u))));
-        if (mshift == 0) return (word >> bit) & 1u ? k : -1;
-        for (const int32_t last = static_cast<int32_t>(wpos[w]); k >= last; --k) {
-            if (k >= n0) continue;
-            const uint32_t p = prefix[k];
-            if (p == static_cast<uint32_t>(t)) return k;
-            if (p < static_cast<uint32_t>(t) && (p >> 5) == w) break;   // (a word's entries ascend)
-        }
-        return -1;
-    }
-    // Entry of an occupied site: the block position if it carries the mark, else
-    // -1 with its root, root word and displacement from the root (path halving).
-    __device__ __forceinline__ int resolve(int32_t t, int32_t &root, uint32_t &word, int32_t &disp) const
+    // Root, root word and displacement from the root of an occupied site t that
+    // is no site of the block.  What the sweep waits for here is the fabric: every
+    // 4-byte read moves a line, and a CU gets some 300 lines a microsecond, so
+    // only what is needed is read (a prefilled site has no lattice entry).  Paths
+    // are split: every entry on the way skips to its grandparent.
+    __device__ __forceinline__ void resolve(int32_t t, int32_t &root, uint32_t &word, int32_t &disp) const
     {
         disp = 0;
         if constexpr (MODE == BLK_WRAP) {
-            uint64_t e = ld_g(&pw[t]);
             int32_t x = t;
-            if (wpar(e) >= BLK_MARK) return wpar(e) & (BLK_MAXB - 1);
+            uint64_t e = ld_g(&pw[t]);
             while (wpar(e) >= 0) {
                 const int32_t p = wpar(e);
                 const uint64_t g = ld_g(&pw[p]);
@@ -1399,36 +1432,30 @@ struct BlkMem {
             root = x;
             word = static_cast<uint32_t>(wpar(e));
         } else {
-            int32_t x = t, v = ld_g(&par[t]);   // (a prefilled site has no entry: unused then)
+            int32_t x = t;
             if (n0 > 0) {
-                const int32_t k = list_entry(t);
-                if (k >= 0) {
-                    x = LIST_NODE | k;
-                    v = ld_g(&parc[k]);
-                }
+                const uint2 rec = wrec[static_cast<uint32_t>(t) >> 5];
+                const uint32_t bit = static_cast<uint32_t>(t) & 31u;
+                if ((rec.y >> bit) & 1u)
+                    x = LIST_NODE | static_cast<int32_t>(rec.x + static_cast<uint32_t>(__popc(rec.y & ((1u << bit) - 1u))));
             }
-            if (v >= BLK_MARK) return v & (BLK_MAXB - 1);
+            int32_t v = par_ld(x);
             while (v >= 0) {
-                const int32_t g = par_ld(v);
-                if (g < 0) {
-                    x = v;
-                    v = g;
-                    break;
-                }
-                par_st(x, g);
-                x = g;
-                v = par_ld(x);
+                const int32_t p = v & ~BLK_LINKED;
+                const int32_t g = par_ld(p);
+                if (g >= 0) par_st(x, BLK_LINKED | g);
+                x = p;
+                v = g;
             }
             root = x;
             word = static_cast<uint32_t>(v);
         }
-        return -1;
     }
     // node's final entry: a root word, or (parent, displacement)
     __device__ __forceinline__ void commit(int32_t node, bool is_root, uint32_t word, int32_t parent, int32_t disp) const
     {
         if constexpr (MODE == BLK_WRAP) st_g(&pw[node], is_root ? wword(word, 0) : wword(static_cast<uint32_t>(parent), disp));
-        else par_st(node, is_root ? static_cast<int32_t>(word) : parent);
+        else par_st(node, is_root ? static_cast<int32_t>(word) : BLK_LINKED | parent);
     }
 };
 
@@ -1438,10 +1465,11 @@ struct BlkMem {
 // of the map; 3.4 offsets of the widest neighbourhood share a row.
 // EXACT: the map is the occupation (mshift == 0); else a set map bit sends the
 // check to the bitset.  The reads of an item's rows are issued together.
-template <bool EXACT, bool PER, int NT, int MODE, int B>
-__device__ __forceinline__ void blk_scan(BlkLds<MODE, B> &S, const BlkMem<MODE> &m, int nrows, int32_t L, int lo, int len)
+template <bool EXACT, typename C>
+__device__ __forceinline__ void blk_scan(BlkLds<C> &S, const BlkMem<C::MODE> &m, int nrows, int32_t L, int lo, int len)
 {
-    constexpr int NW = NT / 64;
+    constexpr bool PER = C::PER;
+    constexpr int NW = C::NT / 64;
     const uint32_t lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int groups = (len + 63) >> 6, chunks = (nrows + BLK_CHUNK - 1) / BLK_CHUNK;
@@ -1525,19 +1553,10 @@ __device__ __forceinline__ void blk_scan(BlkLds<MODE, B> &S, const BlkMem<MODE> 
                     const int bit = __builtin_ctz(mask);
                     mask &= mask - 1u;
                     const int q = (bit * 13) >> 6, j = bit - 5 * q;   // bit / 5 for bit < 30
-                    const NzOffset o = S.rows[c * BLK_CHUNK + q];
-                    int32_t nbs = s + o.stride - 2 + j;
-                    if constexpr (PER) {
-                        const uint32_t out = o.code & ~A & kRowAxes;
-                        nbs += (out ? wrap_fix(out, L) : 0) + off0;
-                    }
                     const int32_t e = base + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
                                                  static_cast<uint32_t>(mk >> 32),
                                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
-                    if (e < BLK_EDGES) {
-                        S.et[e] = static_cast<uint32_t>(nbs);
-                        S.ei[e] = static_cast<uint16_t>(i | (j << 12));
-                    }
+                    if (e < BLK_EDGES) S.et[e] = static_cast<uint32_t>(i | ((c * BLK_CHUNK + q) << 9) | (j << 18));
                 }
             }
         }
@@ -1553,41 +1572,62 @@ __device__ __forceinline__ void blk_scan(BlkLds<MODE, B> &S, const BlkMem<MODE> 
 // smaller node: a fixed total order) goes below the better one.  Wrap sweep: q
 // = x0(u) - x0(v); a pair whose ends already share a root closes a loop, which
 // winds around axis 0 when the displacements disagree.
-template <int MODE, int B>
-__device__ __forceinline__ void blk_link(BlkLds<MODE, B> &S, uint32_t u, uint32_t v, int32_t q)
+template <typename C>
+__device__ __forceinline__ void blk_link(BlkLds<C> &S, uint32_t u, uint32_t v, int32_t q)
 {
-    using W = typename BlkLds<MODE, B>::W;
+    using W = typename BlkLds<C>::W;
     for (;;) {
         int32_t Du, Dv;
-        const uint32_t a = blk_find<MODE, B>(S, u, Du);
-        const uint32_t b = blk_find<MODE, B>(S, v, Dv);
+        uint32_t wa, wb;
+        const uint32_t a = blk_find<C>(S, u, wa, Du);
+        const uint32_t b = blk_find<C>(S, v, wb, Dv);
         if (a == b) {
-            if (MODE == BLK_WRAP && Du != q + Dv) S.flag = 1;
+            if (C::MODE == BLK_WRAP && Du != q + Dv) S.flag = 1;
             return;
         }
-        const uint32_t sa = ld_g(&S.nword[a]) & NZ_SIZE, sb = ld_g(&S.nword[b]) & NZ_SIZE;
+        const uint32_t sa = wa & NZ_SIZE, sb = wb & NZ_SIZE;
         const bool a_up = sa > sb || (sa == sb && a > b);
         const uint32_t lo = a_up ? b : a, hi = a_up ? a : b;
         const int32_t dab = q - Du + Dv;   // x0(a) - x0(b)
-        auto expected = W::make(lo, 0);
-        if (__hip_atomic_compare_exchange_strong(&S.npar[lo], &expected, W::make(hi, a_up ? -dab : dab), __ATOMIC_RELAXED,
+        auto expected = W::make(a_up ? wb : wa, 0);
+        if (__hip_atomic_compare_exchange_strong(&S.f[lo], &expected, W::make(hi, a_up ? -dab : dab), __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
             return;
     }
 }
 
+// Cursor over the buckets of a band.  The counts of 64 buckets are held by the
+// lanes of every wave, so a block costs one read of its entries.
+struct BlkBand {
+    const uint32_t *counts;
+    const uint32_t *sites;
+    uint32_t cap;
+    int32_t nb;
+    int32_t base;    // bucket of lane 0
+    uint32_t mine;   // its count, by lane
+};
+
+__device__ __forceinline__ void blk_counts(BlkBand &bd, int32_t cb)
+{
+    const int32_t k = cb + static_cast<int32_t>(lane_id());
+    bd.base = cb;
+    bd.mine = k < bd.nb ? bd.counts[k] : 0u;
+}
+
 // Block of the band starting at bucket cb: as many whole buckets (16 at most)
 // as B sites hold.  n sites, thread t < n takes entry t into pc, whose bucket
-// holds the block's positions b0 .. b1 - 1; nbk buckets consumed.  over: the first bucket of the block overflowed its capacity.
+// holds the block's positions b0 .. b1 - 1; nbk buckets consumed.  over: the
+// first bucket of the block overflowed its capacity.
 template <int B>
-__device__ __forceinline__ void blk_fetch(const uint32_t *counts, const uint32_t *sites, uint32_t cap, int32_t nb,
-                                          int32_t cb, int &n, int &nbk, bool &over, uint32_t &pc, int &b0, int &b1)
+__device__ __forceinline__ void blk_fetch(BlkBand &bd, int32_t cb, int &n, int &nbk, bool &over, uint32_t &pc, int &b0, int &b1)
 {
     const uint32_t lane = lane_id();
-    const int32_t left = min(16, nb - cb);
+    if (cb + 16 > bd.base + 64 && bd.base + 64 < bd.nb) blk_counts(bd, cb);
+    const int32_t left = min(16, bd.nb - cb);
     const bool in = static_cast<int32_t>(lane) < left;
-    const uint32_t c = in ? counts[cb + static_cast<int32_t>(lane)] : 0u;
-    const uint64_t badm = __ballot(in && (c > cap || c > static_cast<uint32_t>(B)));
+    const uint32_t got = static_cast<uint32_t>(__shfl(static_cast<int>(bd.mine), min(cb - bd.base + static_cast<int>(lane), 63)));
+    const uint32_t c = in ? got : 0u;
+    const uint64_t badm = __ballot(in && (c > bd.cap || c > static_cast<uint32_t>(B)));
     const int32_t lim = badm ? __builtin_ctzll(badm) : left;
     uint32_t incl = c;
 #pragma unroll
@@ -1598,7 +1638,7 @@ __device__ __forceinline__ void blk_fetch(const uint32_t *counts, const uint32_t
     const uint64_t ok = __ballot(static_cast<int32_t>(lane) < lim && incl <= static_cast<uint32_t>(B));
     nbk = __popcll(ok);
     n = nbk > 0 ? static_cast<int>(__builtin_amdgcn_readlane(incl, nbk - 1)) : 0;
-    over = nbk == 0 && cb < nb;
+    over = nbk == 0 && cb < bd.nb;
     const uint32_t t = threadIdx.x;
     uint32_t base = 0, k = 0, end = 0;
     for (int q = 0; q < nbk; ++q) {
@@ -1611,41 +1651,51 @@ __device__ __forceinline__ void blk_fetch(const uint32_t *counts, const uint32_t
     }
     b0 = static_cast<int>(base);
     b1 = static_cast<int>(end);
-    pc = t < static_cast<uint32_t>(n) ? sites[static_cast<uint64_t>(cb + static_cast<int32_t>(k)) * cap + (t - base)] : 0u;
+    pc = t < static_cast<uint32_t>(n) ? bd.sites[static_cast<uint64_t>(cb + static_cast<int32_t>(k)) * bd.cap + (t - base)] : 0u;
+}
+
+__device__ __forceinline__ uint64_t site_key(const NzSample &d, uint32_t pc)
+{
+    const uint32_t s = static_cast<uint32_t>(site_of(pc, d.L));
+    uint64_t ke, ko;
+    site_key_pair(static_cast<uint32_t>(d.seed), static_cast<uint32_t>(d.seed >> 32), static_cast<uint32_t>(d.sample),
+                  static_cast<uint32_t>(d.sample >> 32), s >> 1, ke, ko);
+    return (s & 1u) ? ko : ke;
 }
 
 // Rank by (key, site) of this thread's site S.pcs[t] in the block: t < n lies in
 // a bucket that holds positions b0 .. b1 - 1, and buckets are in key order, so
-// only those are compared.  Keys are recomputed.  `keys`: LDS scratch of n
-// 64-bit words.  Barriers before and after are the caller's (one is inside).
-template <int MODE, int B>
-__device__ __forceinline__ int blk_rank(BlkLds<MODE, B> &S, uint64_t *keys, const NzSample &d, int n, int b0, int b1)
+// only those are compared.  Keys are recomputed; their high words decide, full
+// keys where two are equal.  `keys`: LDS scratch of n words.  Barriers before
+// and after are the caller's (one is inside).
+template <typename C>
+__device__ __forceinline__ int blk_rank(BlkLds<C> &S, uint32_t *keys, const NzSample &d, int n, int b0, int b1)
 {
     const int t = static_cast<int>(threadIdx.x);
     uint64_t K = 0;
     uint32_t pc = 0;
     if (t < n) {
         pc = S.pcs[t];
-        const uint32_t s = static_cast<uint32_t>(site_of(pc, d.L));
-        uint64_t ke, ko;
-        site_key_pair(static_cast<uint32_t>(d.seed), static_cast<uint32_t>(d.seed >> 32), static_cast<uint32_t>(d.sample),
-                      static_cast<uint32_t>(d.sample >> 32), s >> 1, ke, ko);
-        K = (s & 1u) ? ko : ke;
-        keys[t] = K;
+        K = site_key(d, pc);
+        keys[t] = static_cast<uint32_t>(K >> 32);
     }
     __syncthreads();
     int rank = b0;
     if (t < n) {
+        const uint32_t mine = static_cast<uint32_t>(K >> 32);
         bool tie = false;
 #pragma unroll 8
         for (int j = b0; j < b1; ++j) {
-            const uint64_t Kj = keys[j];
-            rank += Kj < K ? 1 : 0;
-            tie = tie || (Kj == K && j != t);
+            const uint32_t kj = keys[j];
+            rank += kj < mine ? 1 : 0;
+            tie = tie || (kj == mine && j != t);
         }
         if (tie)
             for (int j = b0; j < b1; ++j)
-                if (keys[j] == K && S.pcs[j] < pc) ++rank;
+                if (keys[j] == mine && j != t) {
+                    const uint64_t Kj = site_key(d, S.pcs[j]);
+                    if (Kj < K || (Kj == K && S.pcs[j] < pc)) ++rank;
+                }
     }
     return rank;
 }
@@ -1660,31 +1710,21 @@ enum { BLK_COMMITTED = 0, BLK_SPANS = 1, BLK_NOFIT = 2 };
 // prefilled sample: its band sites); the sample is over.  Largest-cluster sweep (sites
 // in order): the window entries of the block are written and smax carries the
 // running maximum.
-template <int MODE, bool PER, int NT, int B>
-__device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &m, const NzSample &d,
-                                        int32_t L, int nrows, int lo, int len, bool sorted, int b0, int b1, int max_old, int32_t r, int32_t win_lo,
-                                        int32_t win_hi, uint32_t *win, int32_t &smax, int &T)
+template <typename C>
+__device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, uint32_t *scratch, const NzSample &d, int32_t L,
+                                        int nrows, int lo, int len, bool sorted, int b0, int b1, int max_old, int32_t r,
+                                        int32_t win_lo, int32_t win_hi, uint32_t *win, int32_t &smax, int &T)
 {
-    using W = typename BlkLds<MODE, B>::W;
+    using W = typename BlkLds<C>::W;
+    constexpr int MODE = C::MODE;
     const int t = static_cast<int>(threadIdx.x);
     const bool act = t < len;
 
-    // 1. mark the block's sites; clear the tables
-    int32_t site = 0;
-    uint32_t pos_word = 0;
-    if (act) {
-        const uint32_t pc = S.pcs[lo + t];
-        site = site_of(pc, L);
-        m.mark(site, t);
-        m.occ_set(static_cast<uint32_t>(site));
-        const int32_t x0 = pc & 63;
-        const uint32_t fl = (MODE != BLK_SPAN) ? 0u : ((x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u));
-        pos_word = NZ_ROOT | fl | 1u;
-        S.nword[t] = pos_word;
-        S.npar[t] = W::make(static_cast<uint32_t>(t), 0);
-        if constexpr (MODE == BLK_SMAX) S.first[t] = BLK_EMPTY;
+    // 1. clear the table; enter the block's sites and set their map bits
+    for (uint32_t w = static_cast<uint32_t>(t); w < C::RS; w += C::NT) {
+        S.rkey[w] = BLK_EMPTY;
+        if constexpr (MODE == BLK_SMAX) S.pos[w] = 0xFFFFu;
     }
-    for (uint32_t w = static_cast<uint32_t>(t); w < BLK_RSLOTS; w += NT) S.rkey[w] = BLK_EMPTY;
     if (t == 0) {
         S.ecnt = 0;
         S.nroots = 0;
@@ -1692,58 +1732,68 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
         S.bad = 0;
     }
     __syncthreads();
+    int32_t site = 0;
+    if (act) {
+        const uint32_t pc = S.pcs[lo + t];
+        site = site_of(pc, L);
+        m.occ_set(static_cast<uint32_t>(site));
+        const int32_t x0 = pc & 63;
+        const uint32_t fl = (MODE != BLK_SPAN) ? 0u : ((x0 == 0 ? NZ_FLO : 0u) | (x0 == L - 1 ? NZ_FHI : 0u));
+        bool fresh;
+        const uint32_t h = blk_enter<C>(S, static_cast<uint32_t>(site), fresh);   // (the table holds B sites)
+        S.f[h] = W::make(NZ_ROOT | fl | 1u, 0);
+        S.spos[t] = static_cast<uint16_t>(h);
+        if constexpr (MODE == BLK_SMAX) {
+            S.first[t] = BLK_EMPTY;
+            S.pos[h] = static_cast<uint16_t>(t);
+        }
+    }
+    __syncthreads();
 
     // 2. occupied neighbours
-    if (m.mshift == 0) blk_scan<true, PER, NT>(S, m, nrows, L, lo, len);
-    else blk_scan<false, PER, NT>(S, m, nrows, L, lo, len);
+    if (m.mshift == 0) blk_scan<true, C>(S, m, nrows, L, lo, len);
+    else blk_scan<false, C>(S, m, nrows, L, lo, len);
     __syncthreads();
     const int ne = S.ecnt;
     int res = ne > BLK_EDGES ? BLK_NOFIT : BLK_COMMITTED;
 
-    // 3. the pairs' neighbours become nodes: a site of the block (pairs are
-    //    kept once, from the later position), or the root of an earlier
-    //    cluster, entered once into the root table
+    // 3. the pairs' neighbours become nodes: a site of the block, or the root of
+    //    an earlier cluster, entered into the table
     if (res == BLK_COMMITTED) {
         int nnew = 0;
-        for (int e = t; e < ne; e += NT) {
-            const int32_t nb = static_cast<int32_t>(S.et[e]);
-            const int i = S.ei[e] & (BLK_MAXB - 1);
-            int32_t root, disp;
-            uint32_t word;
-            const int j = m.resolve(nb, root, word, disp);
-            uint32_t node = BLK_EMPTY;
-            if (j >= 0) {
-                if (j < i) node = static_cast<uint32_t>(j);
-                disp = 0;
-            } else {
-                uint32_t h = blk_hash(static_cast<uint32_t>(root));
-                for (uint32_t k = 0; k < BLK_RSLOTS; ++k) {
-                    uint32_t expected = BLK_EMPTY;
-                    if (__hip_atomic_compare_exchange_strong(&S.rkey[h], &expected, static_cast<uint32_t>(root),
-                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                        S.nword[B + h] = word;
-                        S.npar[B + h] = W::make(B + h, 0);
-                        node = B + h;
-                        ++nnew;
-                        break;
-                    }
-                    if (expected == static_cast<uint32_t>(root)) {
-                        node = B + h;
-                        break;
-                    }
-                    h = (h + 1) & (BLK_RSLOTS - 1);
-                }
-                if (node == BLK_EMPTY) S.bad = 1;   // table full
+        for (int e = t; e < ne; e += C::NT) {
+            const uint32_t code = S.et[e];
+            const int i = static_cast<int>(code & 511u), j = static_cast<int>(code >> 18);
+            const NzOffset o = S.rows[(code >> 9) & 511u];
+            const uint32_t pc = S.pcs[lo + i];
+            int32_t nb = site_of(pc, L) + o.stride - 2 + j;
+            if constexpr (C::PER) {
+                const uint32_t out = o.code & ~allowed_of(pc, L) & (kRowAxes | (1u << j));
+                if (out) nb += wrap_fix(out, L);
             }
-            S.et[e] = node;
+            uint32_t node = blk_lookup<C>(S, static_cast<uint32_t>(nb));
+            int32_t disp = 0;
+            if (node == C::RS) {
+                int32_t root;
+                uint32_t word;
+                m.resolve(nb, root, word, disp);
+                bool fresh;
+                node = blk_enter<C>(S, static_cast<uint32_t>(root), fresh);
+                if (fresh) {
+                    S.f[node] = W::make(word, 0);
+                    ++nnew;
+                }
+                if (node == C::RS) S.bad = 1;   // table full
+            }
             if constexpr (MODE == BLK_SMAX) {
-                if (node != BLK_EMPTY)
+                // kept once, at the later position
+                if (S.pos[node & (C::RS - 1)] == 0xFFFFu || static_cast<int>(S.pos[node & (C::RS - 1)]) < i)
                     S.next[e] = static_cast<uint16_t>(__hip_atomic_exchange(&S.first[i], static_cast<uint32_t>(e), __ATOMIC_RELAXED,
                                                                             __HIP_MEMORY_SCOPE_WORKGROUP));
             }
+            S.et[e] = static_cast<uint32_t>(S.spos[i]) | (node << 16);
             // x0(site) - x0(node): the neighbour lies at x0(site) + d0 = x0(node) + disp
-            if constexpr (MODE == BLK_WRAP) S.eq[e] = static_cast<int16_t>(disp - (static_cast<int>(S.ei[e] >> 12) - 2));
+            if constexpr (MODE == BLK_WRAP) S.eq[e] = static_cast<int16_t>(disp - (j - 2));
         }
         if (nnew) atomicAdd(&S.nroots, nnew);
         __syncthreads();
@@ -1755,41 +1805,40 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
         return res;
     }
 
-    // nodes of this thread: its block position and its slots of the root table
-    constexpr int NODES = 1 + static_cast<int>(BLK_RSLOTS) / NT;
-    static_assert(BLK_RSLOTS % NT == 0, "whole slots per thread");
+    // this thread's slots of the table
+    constexpr int NODES = static_cast<int>(C::RS) / C::NT;
     bool live[NODES];
     uint32_t root[NODES], word0[NODES];
-    int32_t key0[NODES];
     int32_t disp[NODES];
-    auto node_of = [&](int k) { return static_cast<uint32_t>(k == 0 ? t : B + (k - 1) * NT + t); };
+    auto node_of = [&](int k) { return static_cast<uint32_t>(k * C::NT + t); };
 #pragma unroll
     for (int k = 0; k < NODES; ++k) {
         const uint32_t n = node_of(k);
-        live[k] = k == 0 ? act : S.rkey[n - B] != BLK_EMPTY;
+        live[k] = S.rkey[n] != BLK_EMPTY;
         root[k] = n;
         disp[k] = 0;
-        word0[k] = k == 0 ? pos_word : (live[k] ? S.nword[n] : 0u);
-        key0[k] = k == 0 ? site : static_cast<int32_t>(S.rkey[n - B]);
+        word0[k] = live[k] ? W::lo(S.f[n]) : 0u;
     }
+    __syncthreads();   // (the unions rewrite the words)
     // roots of the live nodes; sizes and flags into the roots.  True: a cluster
     // spans.  (two barriers inside, the last one at the end)
     auto gather = [&]() -> bool {
 #pragma unroll
         for (int k = 0; k < NODES; ++k) {
             if (!live[k]) continue;
-            const uint32_t n = node_of(k);
-            root[k] = blk_find<MODE, B>(S, n, disp[k]);
-            if (root[k] != n) {
-                atomicAdd(&S.nword[root[k]], word0[k] & NZ_SIZE);
-                if (word0[k] & NZ_FLAGS) atomicOr(&S.nword[root[k]], word0[k] & NZ_FLAGS);
+            uint32_t unused;
+            root[k] = blk_find<C>(S, node_of(k), unused, disp[k]);
+            if (root[k] != node_of(k)) {
+                uint32_t *w = reinterpret_cast<uint32_t *>(&S.f[root[k]]);   // (low half: the root word)
+                atomicAdd(w, word0[k] & NZ_SIZE);
+                if (word0[k] & NZ_FLAGS) atomicOr(w, word0[k] & NZ_FLAGS);
             }
         }
         __syncthreads();
         if constexpr (MODE == BLK_SPAN) {
 #pragma unroll
             for (int k = 0; k < NODES; ++k)
-                if (live[k] && root[k] == node_of(k) && (S.nword[root[k]] & NZ_FLAGS) == NZ_FLAGS) S.flag = 1;
+                if (live[k] && root[k] == node_of(k) && (W::lo(S.f[root[k]]) & NZ_FLAGS) == NZ_FLAGS) S.flag = 1;
         }
         __syncthreads();
         return S.flag != 0;
@@ -1798,19 +1847,19 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
     if constexpr (MODE == BLK_SMAX) {
         // 4. unions in the order of the positions, by one lane; the sizes are
         //    kept at the roots
-        __syncthreads();   // (word0 is read above)
         if (t == 0) {
             for (int i = 0; i < len; ++i) {
-                uint32_t a = static_cast<uint32_t>(i), sz = 1;
+                uint32_t a = S.spos[i], sz = 1;
                 for (uint32_t e = S.first[i]; (e & 0xFFFFu) != 0xFFFFu; e = S.next[e]) {
                     int32_t unused;
-                    const uint32_t b = blk_find<MODE, B>(S, S.et[e], unused);
+                    uint32_t wb;
+                    const uint32_t b = blk_find<C>(S, S.et[e] >> 16, wb, unused);
                     if (b == a) continue;
-                    const uint32_t sb = S.nword[b] & NZ_SIZE;
+                    const uint32_t sb = wb & NZ_SIZE;
                     const uint32_t lo_n = sb > sz ? a : b, hi_n = sb > sz ? b : a;
                     sz += sb;
-                    st_g(&S.npar[lo_n], W::make(hi_n, 0));
-                    S.nword[hi_n] = NZ_ROOT | sz;
+                    st_g(&S.f[lo_n], W::make(hi_n, 0));
+                    st_g(&S.f[hi_n], W::make(NZ_ROOT | sz, 0));
                     a = hi_n;
                 }
                 smax = max(smax, static_cast<int32_t>(sz));
@@ -1823,18 +1872,19 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
         const int32_t rr = r + t + 1;
         if (act && rr >= win_lo && rr < win_hi) win[rr - win_lo] = S.smax[t];
 #pragma unroll
-        for (int k = 0; k < NODES; ++k)
-            if (live[k]) root[k] = blk_find<MODE, B>(S, node_of(k), disp[k]);
+        for (int k = 0; k < NODES; ++k) {
+            uint32_t unused;
+            if (live[k]) root[k] = blk_find<C>(S, node_of(k), unused, disp[k]);
+        }
     } else {
-        // 4. unions of all pairs
+        // 4. unions of all pairs (that `take` accepts)
         auto unions = [&](auto &&take) {
-            for (int e = t; e < ne; e += NT) {
-                const uint32_t node = S.et[e];
-                const uint32_t i = S.ei[e] & (BLK_MAXB - 1);
-                if (node == BLK_EMPTY || !take(i, node)) continue;
+            for (int e = t; e < ne; e += C::NT) {
+                const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
+                if (!take(u, v)) continue;
                 int32_t q = 0;
                 if constexpr (MODE == BLK_WRAP) q = S.eq[e];
-                blk_link<MODE, B>(S, i, node, q);
+                blk_link<C>(S, u, v, q);
             }
             __syncthreads();
         };
@@ -1842,37 +1892,33 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
         if (gather()) {
             res = BLK_SPANS;
             T = 1;
-            if (len == 1) {
-                if (t == 0) {
-                    S.total = S.nword[root[0]] & NZ_SIZE;
-                    S.croot = root[0];
-                }
-            } else {
+            const uint32_t own = act ? S.spos[t] : 0u;   // this position's node
+            int myrank = t;
+            if (len > 1) {
                 // 5. the smallest T: bisection over the block's first T sites, each
                 //    trial a connected-components pass over the pairs among them.
-                //    The root table's keys are not needed any more: their words
-                //    hold the sites' keys, then their ranks.
-                static_assert(BLK_RSLOTS * 4 >= B * 8, "the root table's words hold the keys");
-                //    (sorted: the positions are the ranks already)
-                int myrank = t;
-                if (!sorted) myrank = blk_rank<MODE, B>(S, reinterpret_cast<uint64_t *>(S.rkey), d, len, b0, b1);
+                //    ranks: of every node, 0 for earlier roots, 1 + rank for sites.
+                uint16_t *ranks = reinterpret_cast<uint16_t *>(scratch + C::B);
+                if (!sorted) myrank = blk_rank<C>(S, scratch, d, len, b0, b1);   // (sorted: positions are ranks)
+#pragma unroll
+                for (int k = 0; k < NODES; ++k) ranks[node_of(k)] = 0;
                 __syncthreads();
-                uint16_t *ranks = reinterpret_cast<uint16_t *>(S.rkey);
-                if (act) ranks[t] = static_cast<uint16_t>(myrank);
+                if (act) ranks[own] = static_cast<uint16_t>(myrank + 1);
+                __syncthreads();
+                uint32_t since[NODES];   // the first T that has this thread's node
+#pragma unroll
+                for (int k = 0; k < NODES; ++k) since[k] = live[k] ? ranks[node_of(k)] : 0xFFFFu;
                 auto trial = [&](int first) -> bool {
                     __syncthreads();
                     if (t == 0) S.flag = 0;
-                    live[0] = act && myrank < first;
 #pragma unroll
                     for (int k = 0; k < NODES; ++k) {
-                        if (!live[k]) continue;
-                        const uint32_t n = node_of(k);
-                        S.npar[n] = W::make(n, 0);
-                        S.nword[n] = word0[k];
+                        live[k] = since[k] <= static_cast<uint32_t>(first);
+                        if (live[k]) S.f[node_of(k)] = W::make(word0[k], 0);
                     }
                     __syncthreads();
-                    unions([&](uint32_t i, uint32_t node) {
-                        return static_cast<int>(ranks[i]) < first && (node >= B || static_cast<int>(ranks[node]) < first);
+                    unions([&](uint32_t u, uint32_t v) {
+                        return static_cast<int>(ranks[u]) <= first && static_cast<int>(ranks[v]) <= first;
                     });
                     return gather();
                 };
@@ -1884,18 +1930,21 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
                     else none = mid;
                 }
                 trial(T);
-                if (act && myrank == T - 1) {
-                    S.total = S.nword[root[0]] & NZ_SIZE;
-                    S.croot = root[0];
-                }
+            }
+            if (act && myrank == T - 1) {
+                uint32_t word;
+                int32_t unused;
+                S.croot = blk_find<C>(S, own, word, unused);
+                S.total = word & NZ_SIZE;
             }
             __syncthreads();
             // the earlier clusters of the spanning one get both border flags, by
             // which their prefilled members are counted
             if (MODE == BLK_SPAN && m.n0 > 0) {
 #pragma unroll
-                for (int k = 1; k < NODES; ++k)
-                    if (live[k] && root[k] == S.croot) m.par_st(key0[k], static_cast<int32_t>(NZ_ROOT | NZ_FLAGS));
+                for (int k = 0; k < NODES; ++k)
+                    if (live[k] && root[k] == S.croot)
+                        m.par_st(static_cast<int32_t>(S.rkey[node_of(k)]), static_cast<int32_t>(NZ_ROOT | NZ_FLAGS));
                 __syncthreads();
             }
             return res;
@@ -1907,12 +1956,9 @@ __device__ __forceinline__ int blk_step(BlkLds<MODE, B> &S, const BlkMem<MODE> &
     for (int k = 0; k < NODES; ++k) {
         if (!live[k]) continue;
         const uint32_t n = node_of(k), rt = root[k];
-        int32_t parent = 0;
-        if (rt != n)
-            parent = rt < B ? site_of(S.pcs[lo + static_cast<int>(rt)], L) : static_cast<int32_t>(S.rkey[rt - B]);
-        m.commit(key0[k], rt == n, S.nword[n], parent, disp[k]);
+        m.commit(static_cast<int32_t>(S.rkey[n]), rt == n, W::lo(S.f[n]), static_cast<int32_t>(S.rkey[rt]), disp[k]);
     }
-    __syncthreads();
+    __syncthreads();   // (the stores drain behind the next block's checks)
     return res;
 }
 
@@ -1926,13 +1972,13 @@ __device__ __forceinline__ uint32_t map_shift(uint32_t N, uint32_t map_words)
 
 // Persistent: every workgroup pops samples (longest first) until the queue is
 // empty.  PER: periodic coordinates.
-template <int MODE, bool PER, int NT, int B>
-__global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut out)
+template <typename C>
+__global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut out)
 {
-    static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
-    static_assert(B <= NT && B <= BLK_MAXB, "thread t loads entry t of a block");
+    constexpr int MODE = C::MODE, NT = C::NT, B = C::B;
     extern __shared__ uint32_t blk_map[];
-    __shared__ BlkLds<MODE, B> S;
+    __shared__ BlkLds<C> S;
+    uint32_t *scratch = C::OWN_SCRATCH ? S.scratch : blk_map;   // (a sample that bisects needs its map no more)
     const int t = static_cast<int>(threadIdx.x);
     for (;;) {
         if (t == 0) S.claim = atomicAdd(a.qhead, 1);
@@ -1945,17 +1991,18 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
         const NzSample &d = a.desc[sid];
         const int32_t L = d.L, nrows = d.rows, nb = d.nb;
         const uint32_t N = static_cast<uint32_t>(d.N);
-        const uint32_t cap = static_cast<uint32_t>(d.cap);
-        const uint32_t *counts = reinterpret_cast<const uint32_t *>(a.ws + d.off_counts);
-        const uint32_t *sites = reinterpret_cast<const uint32_t *>(a.ws + d.off_sites);
+        BlkBand band;
+        band.counts = reinterpret_cast<const uint32_t *>(a.ws + d.off_counts);
+        band.sites = reinterpret_cast<const uint32_t *>(a.ws + d.off_sites);
+        band.cap = static_cast<uint32_t>(d.cap);
+        band.nb = nb;
         const NzOffset *rows = a.tabs + d.tab;
         BlkMem<MODE> m;
         m.occ = reinterpret_cast<uint32_t *>(a.ws + d.off_occ);
         m.par = reinterpret_cast<int32_t *>(a.ws + d.off_par);
         m.parc = reinterpret_cast<int32_t *>(a.ws + d.off_parc);
         m.pw = reinterpret_cast<uint64_t *>(a.ws + d.off_par);
-        m.wpos = reinterpret_cast<const uint32_t *>(a.ws + d.off_wpos);
-        m.prefix = reinterpret_cast<const uint32_t *>(a.ws + d.off_prefix);
+        m.wrec = reinterpret_cast<const uint2 *>(a.ws + d.off_wrec);
         m.map = blk_map;
         m.mshift = map_shift(N, a.map_words);
         m.occ_words = ((N + 63u) >> 6) << 1;
@@ -1980,23 +2027,29 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
         }
         __syncthreads();
         if (by_list) {
+            const uint32_t *prefix = reinterpret_cast<const uint32_t *>(a.ws + d.off_prefix);
             for (int32_t k = t; k < n0; k += NT) {
-                const uint32_t b = m.prefix[k] >> m.mshift;
+                const uint32_t b = prefix[k] >> m.mshift;
                 atomicOr(&blk_map[1 + (b >> 5)], 1u << (b & 31));
             }
         } else if (m.mshift) {
-            for (uint32_t w = static_cast<uint32_t>(t); w < m.occ_words; w += NT) {
-                uint32_t v = m.occ[w];
-                if (!v) continue;
-                uint32_t bits = 1u;   // (mshift >= 5: the word is part of one bit)
-                if (m.mshift < 5) {
-                    bits = 0u;
-                    const uint32_t grp = (1u << (1u << m.mshift)) - 1u;
-                    for (uint32_t g = 0; g < (32u >> m.mshift); ++g)
-                        if ((v >> (g << m.mshift)) & grp) bits |= 1u << g;
+            for (uint32_t w0 = static_cast<uint32_t>(t); w0 < m.occ_words; w0 += 8 * NT) {
+                uint32_t v[8];
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q) v[q] = w0 + q * NT < m.occ_words ? m.occ[w0 + q * NT] : 0u;
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q) {
+                    if (!v[q]) continue;
+                    uint32_t bits = 1u;   // (mshift >= 5: the word is part of one bit)
+                    if (m.mshift < 5) {
+                        bits = 0u;
+                        const uint32_t grp = (1u << (1u << m.mshift)) - 1u;
+                        for (uint32_t g = 0; g < (32u >> m.mshift); ++g)
+                            if ((v[q] >> (g << m.mshift)) & grp) bits |= 1u << g;
+                    }
+                    const uint32_t b = ((w0 + q * NT) << 5) >> m.mshift;
+                    atomicOr(&blk_map[1 + (b >> 5)], bits << (b & 31));
                 }
-                const uint32_t b = (w << 5) >> m.mshift;
-                atomicOr(&blk_map[1 + (b >> 5)], bits << (b & 31));
             }
         }
 
@@ -2012,11 +2065,12 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
         bool over = false;
         uint32_t pc = 0;
         int nb0 = 0, nb1 = 0;
-        if (!done) blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+        blk_counts(band, 0);
+        if (!done) blk_fetch<B>(band, cb, n, nbk, over, pc, nb0, nb1);
         while (!done) {
             while (n == 0 && nbk > 0) {
                 cb += nbk;
-                blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+                blk_fetch<B>(band, cb, n, nbk, over, pc, nb0, nb1);
             }
             if (n == 0) {
                 if (over) status = NZ_ST_BUCKET;
@@ -2026,14 +2080,14 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
             const int all = n, b0 = nb0, b1 = nb1;
             // the next block's entries, loaded while this one is processed
             cb += nbk;
-            blk_fetch<B>(counts, sites, cap, nb, cb, n, nbk, over, pc, nb0, nb1);
+            blk_fetch<B>(band, cb, n, nbk, over, pc, nb0, nb1);
             __syncthreads();
             bool sorted = false;
             auto sort = [&]() {
                 if (sorted) return;
                 sorted = true;
                 const uint32_t mine = t < all ? S.pcs[t] : 0u;
-                const int rank = blk_rank<MODE, B>(S, reinterpret_cast<uint64_t *>(S.rkey), d, all, b0, b1);
+                const int rank = blk_rank<C>(S, S.et, d, all, b0, b1);
                 __syncthreads();
                 if (t < all) S.pcs[rank] = mine;
                 __syncthreads();
@@ -2042,8 +2096,8 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
             int len = all;
             for (int lo = 0; lo < all;) {
                 int T = 0;
-                const int res = blk_step<MODE, PER, NT, B>(S, m, d, L, nrows, lo, len, sorted, b0, b1, a.blk_old, r, win_lo, win_hi,
-                                                           win, smax, T);
+                const int res = blk_step<C>(S, m, scratch, d, L, nrows, lo, len, sorted, b0, b1, a.blk_old, r, win_lo, win_hi, win,
+                                            smax, T);
                 if (res == BLK_NOFIT) {
                     sort();
                     len = max(1, len / 2);
@@ -2057,18 +2111,47 @@ __global__ __launch_bounds__(NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut
                     // sizes): the prefilled members of the cluster, whose roots carry
                     // both flags now
                     if (MODE == BLK_SPAN && n0 > 0 && out.mass) {
+                        // One pass over the list, 4 NT entries at a time.  A cluster's
+                        // root has its smallest position, so the bits of the former
+                        // roots (member of the spanning cluster or not, kept where the
+                        // map was) are known before a member asks for its own root's.
+                        const uint32_t words = min(a.map_words, (static_cast<uint32_t>(n0) + 31u) >> 5);
+                        const int32_t in_bits = static_cast<int32_t>(words << 5);
+                        for (uint32_t w = static_cast<uint32_t>(t); w < words; w += NT) blk_map[w] = 0u;
                         int32_t members = 0;
-                        for (int32_t k0 = t; k0 < n0; k0 += 4 * NT) {
-                            int32_t v[4];
+                        auto chase = [&](int32_t v) -> bool {   // the cluster an entry leads to
+                            while (v >= 0) v = m.par_ld(v & ~BLK_LINKED);
+                            return (static_cast<uint32_t>(v) & NZ_FLAGS) == NZ_FLAGS;
+                        };
+                        int32_t v[4], nv[4];
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) v[q] = k0 + q * NT < n0 ? ld_g(&m.parc[k0 + q * NT]) : -1;
+                        for (int q = 0; q < 4; ++q) nv[q] = t + q * NT < n0 ? ld_g(&m.parc[t + q * NT]) : NZ_NONE;
+                        for (int32_t k0 = t; k0 - t < n0; k0 += 4 * NT) {
 #pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                if (v[q] >= 0) v[q] = m.par_ld(v[q]);
+                            for (int q = 0; q < 4; ++q) v[q] = nv[q];
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
-                                while (v[q] >= 0) v[q] = m.par_ld(v[q]);
-                                if (k0 + q * NT < n0 && (static_cast<uint32_t>(v[q]) & NZ_FLAGS) == NZ_FLAGS) ++members;
+                                const int32_t k = k0 + (4 + q) * NT;   // the next round's
+                                nv[q] = k < n0 ? ld_g(&m.parc[k]) : NZ_NONE;
+                            }
+                            __syncthreads();   // (the zeroed bits; the last round's reads)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const int32_t k = k0 + q * NT;
+                                if (k >= n0 || (v[q] >= 0 && !(v[q] & BLK_LINKED))) continue;
+                                if (chase(v[q])) {   // a former root in the cluster
+                                    ++members;
+                                    if (k < in_bits) atomicOr(&blk_map[k >> 5], 1u << (k & 31));
+                                }
+                                v[q] = NZ_NONE;
+                            }
+                            __syncthreads();
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                if (v[q] < 0) continue;   // (none, or a root)
+                                const int32_t root = v[q] - LIST_NODE;
+                                if (root >= 0 && root < in_bits) members += (blk_map[root >> 5] >> (root & 31)) & 1u;
+                                else members += chase(v[q]) ? 1 : 0;
                             }
                         }
 #pragma unroll
@@ -2227,9 +2310,11 @@ hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsa
 template <int MODE, bool PER, int NT, int B>
 static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cus, hipStream_t st)
 {
-    auto k = nz_block_kernel<MODE, PER, NT, B>;
+    using C = BlkCfg<MODE, PER, NT, B>;
+    if (!C::OWN_SCRATCH && a.map_words < C::SCRATCH) return hipErrorInvalidValue;
+    auto k = nz_block_kernel<C>;
     const size_t lds = static_cast<size_t>(a.map_words) * 4u;
-    if (lds + sizeof(BlkLds<MODE, B>) > 65536) {
+    if (lds + sizeof(BlkLds<C>) > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            static_cast<int>(lds));
         if (e != hipSuccess) return e;
@@ -2257,10 +2342,10 @@ static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint
 {
     const uint32_t exact = ((max_N - 1u) >> 5) + 1u + BLK_MAP_PAD;
     if (exact <= BLK_SMALL_MAP || MODE == BLK_SMAX) {
-        a.map_words = std::min(exact, BLK_SMAX_MAP);
+        a.map_words = std::min(exact, BLK_SMALL_MAP);
         return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);
     }
-    a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<MODE, 512>)) / 4));
+    a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<BlkCfg<MODE, PER, 1024, 512>>)) / 4));
     return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
 }
 
