@@ -1197,7 +1197,11 @@ constexpr int BLK_CHUNK = 6;             // rows checked together (five bits eac
 constexpr int BLK_MAXROWS = 300;         // rows of the widest neighbourhood (298), in whole chunks
 constexpr uint32_t BLK_EMPTY = 0xFFFFFFFFu;
 constexpr int32_t NZ_NONE = static_cast<int32_t>(0x80000000u);   // (a root word of no cluster)
-constexpr int32_t BLK_LINKED = 0x40000000;   // (above every node id: sites < 2^29, list nodes < 2^30)
+// Node ids: band sites, BAND_NODE | k; list nodes, LIST_NODE | index (both below
+// 2^29; a block's own sites go by their lattice index until it is known to
+// fit).  Entries with both bits are list nodes that the sweep wrote.
+constexpr int32_t BAND_NODE = 0x40000000, BLK_LINKED = 0x40000000;
+__device__ __forceinline__ int32_t node_id(int32_t v) { return (v & LIST_NODE) ? v & ~BLK_LINKED : v; }
 constexpr uint32_t BLK_SMALL_MAP = 4096;  // words of the largest map that leaves room for several workgroups per CU
 constexpr uint32_t BLK_MAP_PAD = 3;       // map words outside the lattice: one before, two behind
 static_assert(BLK_MAXROWS % BLK_CHUNK == 0, "whole chunks");
@@ -1355,9 +1359,20 @@ __device__ __forceinline__ uint32_t blk_find(BlkLds<C> &S, uint32_t x, uint32_t 
 }
 
 // The lattice side of one sample: occupancy bits, their map in LDS and the
-// union-find entries (32-bit parent / root words, 64-bit with displacements for
-// the wrap sweep; prefilled roots of the former live in the list forest as
-// nodes LIST_NODE | i).
+// union-find entries.  Wrap sweep: 64-bit parent / root words with displacements,
+// one per lattice site.  Else nodes are those of the labelling's list forest
+// (LIST_NODE | i) and of the band sites (BAND_NODE | k).  A plain sample's band
+// nodes are its lattice entries, k the site.  A prefilled sample's are a dense
+// array, k the position in the band's order, with a node only for the sites that
+// were roots when their block was committed; a lattice entry then names a node.
+// The array lies where the band's buckets were: position k is at most the slot of
+// its own entry, and the slots of a block have been read before it is committed.
+// So of the reads that follow one another from a neighbour to its root only the
+// first goes to the lattice array (32 samples of 4 MB per XCD at L = 16): the
+// batches of 7 compact neighbourhoods take 20.3 ms instead of 20.9 at L = 16 and
+// 33.0 instead of 34.2 at L = 24.  A plain sample starts from single sites, whose
+// lattice entry is their root word itself: there the dense array costs a read more
+// than it saves (zone 1, L = 16, 1000 samples: 17.5 ms against 16.6).
 // An entry written by the sweep carries BLK_LINKED, which tells former roots
 // (and members whose path was cut short) from the members that still point at
 // their root of the labelling.
@@ -1372,6 +1387,8 @@ struct BlkMem {
     uint32_t *occ;
     int32_t *par;
     int32_t *parc;
+    int32_t *band;
+    bool flat;                // the band nodes are the lattice entries
     uint64_t *pw;
     const uint2 *wrec;        // per bitset word: list position of its first prefilled site, prefilled bits
     int32_t n0;               // prefilled sites
@@ -1394,14 +1411,9 @@ struct BlkMem {
         else
             __hip_atomic_fetch_and(&map[1 + (s >> 5)], ~(1u << (s & 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    __device__ __forceinline__ int32_t par_ld(int32_t i) const
+    __device__ __forceinline__ int32_t *entry(int32_t id) const
     {
-        return i >= LIST_NODE ? ld_g(&parc[i - LIST_NODE]) : ld_g(&par[i]);
-    }
-    __device__ __forceinline__ void par_st(int32_t i, int32_t v) const
-    {
-        if (i >= LIST_NODE) st_g(&parc[i - LIST_NODE], v);
-        else st_g(&par[i], v);
+        return &((id & LIST_NODE) ? parc : band)[id & (LIST_NODE - 1)];
     }
     // Root, root word and displacement from the root of an occupied site t that
     // is no site of the block.  What the sweep waits for here is the fabric: every
@@ -1432,19 +1444,23 @@ struct BlkMem {
             root = x;
             word = static_cast<uint32_t>(wpar(e));
         } else {
-            int32_t x = t;
+            int32_t x = BAND_NODE | t;   // (a root only if flat)
+            int32_t *at = &par[t];
             if (n0 > 0) {
                 const uint2 rec = wrec[static_cast<uint32_t>(t) >> 5];
                 const uint32_t bit = static_cast<uint32_t>(t) & 31u;
-                if ((rec.y >> bit) & 1u)
+                if ((rec.y >> bit) & 1u) {
                     x = LIST_NODE | static_cast<int32_t>(rec.x + static_cast<uint32_t>(__popc(rec.y & ((1u << bit) - 1u))));
+                    at = entry(x);
+                }
             }
-            int32_t v = par_ld(x);
+            int32_t v = ld_g(at);
             while (v >= 0) {
-                const int32_t p = v & ~BLK_LINKED;
-                const int32_t g = par_ld(p);
-                if (g >= 0) par_st(x, BLK_LINKED | g);
-                x = p;
+                x = node_id(v);
+                int32_t *up = entry(x);
+                const int32_t g = ld_g(up);
+                if (g >= 0) st_g(at, g | BLK_LINKED);
+                at = up;
                 v = g;
             }
             root = x;
@@ -1455,7 +1471,7 @@ struct BlkMem {
     __device__ __forceinline__ void commit(int32_t node, bool is_root, uint32_t word, int32_t parent, int32_t disp) const
     {
         if constexpr (MODE == BLK_WRAP) st_g(&pw[node], is_root ? wword(word, 0) : wword(static_cast<uint32_t>(parent), disp));
-        else par_st(node, is_root ? static_cast<int32_t>(word) : BLK_LINKED | parent);
+        else st_g(entry(node), is_root ? static_cast<int32_t>(word) : parent | BLK_LINKED);
     }
 };
 
@@ -1805,6 +1821,11 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
         return res;
     }
 
+    // from here on the block's sites go by their band nodes (the barrier below)
+    const int32_t ord0 = BAND_NODE | (r - m.n0);
+    if constexpr (MODE != BLK_WRAP)
+        if (act) S.rkey[S.spos[t]] = static_cast<uint32_t>(m.flat ? BAND_NODE | site : ord0 + t);
+
     // this thread's slots of the table
     constexpr int NODES = static_cast<int>(C::RS) / C::NT;
     bool live[NODES];
@@ -1814,7 +1835,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
 #pragma unroll
     for (int k = 0; k < NODES; ++k) {
         const uint32_t n = node_of(k);
-        live[k] = S.rkey[n] != BLK_EMPTY;
+        live[k] = S.rkey[n] != BLK_EMPTY;   // (a site's key changes from one id to another)
         root[k] = n;
         disp[k] = 0;
         word0[k] = live[k] ? W::lo(S.f[n]) : 0u;
@@ -1944,7 +1965,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
 #pragma unroll
                 for (int k = 0; k < NODES; ++k)
                     if (live[k] && root[k] == S.croot)
-                        m.par_st(static_cast<int32_t>(S.rkey[node_of(k)]), static_cast<int32_t>(NZ_ROOT | NZ_FLAGS));
+                        m.commit(static_cast<int32_t>(S.rkey[node_of(k)]), true, NZ_ROOT | NZ_FLAGS, 0, 0);
                 __syncthreads();
             }
             return res;
@@ -1956,8 +1977,17 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
     for (int k = 0; k < NODES; ++k) {
         if (!live[k]) continue;
         const uint32_t n = node_of(k), rt = root[k];
+        // (dense: nothing points at a site of the block that is no root)
+        if constexpr (MODE != BLK_WRAP)
+            if (!m.flat && rt != n && static_cast<uint32_t>(S.rkey[n] - static_cast<uint32_t>(ord0)) < static_cast<uint32_t>(len)) continue;
         m.commit(static_cast<int32_t>(S.rkey[n]), rt == n, W::lo(S.f[n]), static_cast<int32_t>(S.rkey[rt]), disp[k]);
     }
+    if constexpr (MODE != BLK_WRAP)
+        if (act && !m.flat) {
+            uint32_t unused;
+            int32_t none;
+            st_g(&m.par[site], static_cast<int32_t>(S.rkey[blk_find<C>(S, S.spos[t], unused, none)]) | BLK_LINKED);
+        }
     __syncthreads();   // (the stores drain behind the next block's checks)
     return res;
 }
@@ -2001,6 +2031,8 @@ __global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, Sweep
         m.occ = reinterpret_cast<uint32_t *>(a.ws + d.off_occ);
         m.par = reinterpret_cast<int32_t *>(a.ws + d.off_par);
         m.parc = reinterpret_cast<int32_t *>(a.ws + d.off_parc);
+        m.flat = a.state[sid].n0 == 0;
+        m.band = m.flat ? m.par : reinterpret_cast<int32_t *>(a.ws + d.off_sites);
         m.pw = reinterpret_cast<uint64_t *>(a.ws + d.off_par);
         m.wrec = reinterpret_cast<const uint2 *>(a.ws + d.off_wrec);
         m.map = blk_map;
@@ -2120,7 +2152,7 @@ __global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, Sweep
                         for (uint32_t w = static_cast<uint32_t>(t); w < words; w += NT) blk_map[w] = 0u;
                         int32_t members = 0;
                         auto chase = [&](int32_t v) -> bool {   // the cluster an entry leads to
-                            while (v >= 0) v = m.par_ld(v & ~BLK_LINKED);
+                            while (v >= 0) v = ld_g(m.entry(node_id(v)));
                             return (static_cast<uint32_t>(v) & NZ_FLAGS) == NZ_FLAGS;
                         };
                         int32_t v[4], nv[4];
