@@ -12,6 +12,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <future>
 #include <map>
 #include <mutex>
 #include <string>
@@ -384,13 +385,18 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     return s;
 }
 
-// A band that holds more than 8% of the sites (of a sample's Sizes or
-// descriptor): its keys launch keeps each sample on one XCD, from kXcdSamples
-// samples on (fewer would leave XCDs idle).  Both sides are measured at the keys
-// kernel.
+// How the keys launch of a sample (its Sizes) spreads, by the share of the
+// sites that its band holds: above 3% one workgroup per sample, if there are
+// enough samples (launch_keys); above 8% and with too many buckets for that, each
+// sample's workgroups on one XCD, from kXcdSamples samples on (fewer would leave
+// XCDs idle).  Both sides of each line are measured at the keys kernels.
 constexpr int32_t kXcdSamples = 32;
-template <typename T>
-bool wide_band(const T &s) { return std::ldexp(static_cast<double>(s.nb), s.shift - 64) > 0.08; }
+enum { KEYS_NARROW = 0, KEYS_WIDE = 1, KEYS_WIDEST = 2 };
+int keys_class(const Sizes &s)
+{
+    const double share = std::ldexp(static_cast<double>(s.nb), s.shift - 64);
+    return share > 0.08 ? KEYS_WIDEST : share > 0.03 ? KEYS_WIDE : KEYS_NARROW;
+}
 
 // Samples whose prefill lists hold like numbers of sites (within a factor of
 // four) are labelled by one launch: its grid has as many workgroups per sample
@@ -435,9 +441,6 @@ struct Tune {
     int sweep_mode = 0;
     int summary = 0;
     int split_z = 0;     // widest neighbourhood of the first of two groups side by side (0: kSplitZ)
-    // keys launch: one workgroup per block of sites (false), or half as many
-    // workgroups as the CUs hold at once, each looping over blocks (true)
-    bool keys_resident = false;
 };
 
 int check_job(const nz_job &j, int idx)
@@ -589,11 +592,41 @@ NzRun make_run(const Part &part, const nz_job *jobs, TablePool &pool)
 }
 static_assert(sizeof(NzRun) <= 4 * kAlign, "a run fits the region of the smallest sample (par, occ, sites, counts)");
 
+// The order of the first keys passes of two groups side by side: the second
+// group's stream waits for the first group's event.
+struct KeysTurn {
+    hipEvent_t done = nullptr;
+    bool second = false;
+    std::shared_future<void> recorded;    // second: set once the event is recorded, or never will be
+    std::promise<void> *record = nullptr; // first
+
+    // before / after the stream's first keys pass
+    hipError_t before(hipStream_t st)
+    {
+        if (!second || !recorded.valid()) return hipSuccess;
+        recorded.wait();
+        recorded = {};
+        return hipStreamWaitEvent(st, done, 0);
+    }
+    hipError_t after(hipStream_t st)
+    {
+        if (second || !record) return hipSuccess;
+        const hipError_t e = hipEventRecord(done, st);
+        pass();
+        return e;
+    }
+    void pass()
+    {
+        if (record) record->set_value();
+        record = nullptr;
+    }
+};
+
 // job_out (may be NULL): first output index of every job (default: the
 // samples of the jobs in order, from 0).
 int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_t *d_nstar, int32_t *d_mass,
               int32_t *h_backoffs, const Tune &tune, hipStream_t st, const SmaxReq *smax = nullptr,
-              const int64_t *job_out = nullptr)
+              const int64_t *job_out = nullptr, KeysTurn *turn = nullptr)
 {
     Device dev;
     if (int rc = device_info(dev)) return rc;
@@ -697,10 +730,9 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             for (int32_t i = 0; i < np; ++i) order[i] = i;
             std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
                 if (parts[a].p.L != parts[b].p.L) return parts[a].p.L < parts[b].p.L;
-                return wide_band(parts[a].s) > wide_band(parts[b].s);
+                return keys_class(parts[a].s) > keys_class(parts[b].s);
             });
             size_t off = head;
-            const int32_t keys_grid = tune.keys_resident ? (nz::keys_resident_wgs() + 1) / 2 * dev.cus : 0;
             uint32_t max_N = 0;
             int32_t max_count = 0, di = 0;
             for (int32_t i : order) {
@@ -772,15 +804,20 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             };
             if (pe) HIP_TRY(hipEventRecord(pe->ev[0], st));
             HIP_TRY(nz::launch_clear(d_desc, nullptr, n, 0, ws, d_state, st));
+            if (turn) HIP_TRY(turn->before(st));
             for (int32_t a = 0; a < np;) {
                 const Part &first = parts[order[a]];
-                const bool wide = wide_band(first.s);
-                int32_t b = a, count = 0;
-                while (b < np && parts[order[b]].p.L == first.p.L && wide_band(parts[order[b]].s) == wide) count += parts[order[b++]].count;
+                const int cls = keys_class(first.s);
+                int32_t b = a, count = 0, max_nb = 0;
+                while (b < np && parts[order[b]].p.L == first.p.L && keys_class(parts[order[b]].s) == cls) {
+                    max_nb = std::max(max_nb, parts[order[b]].s.nb);
+                    count += parts[order[b++]].count;
+                }
                 HIP_TRY(nz::launch_keys(d_desc, nullptr, first.desc0, count, static_cast<int32_t>(pow5(first.p.L)), ws, d_state,
-                                        keys_grid, wide && count >= kXcdSamples, st));
+                                        cls == KEYS_WIDEST && count >= kXcdSamples, cls == KEYS_NARROW ? 0 : max_nb, st));
                 a = b;
             }
+            if (turn) HIP_TRY(turn->after(st));
             if (pe) HIP_TRY(hipEventRecord(pe->ev[1], st));
             std::vector<NzState> state(n);
             std::vector<uint8_t> level(n, 0);   // in-chunk backoffs of every sample
@@ -836,7 +873,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                     HIP_TRY(nz::launch_clear(d_desc, d_list, na, lv, ws, d_state, st));
                     int32_t a = 0;
                     for (const auto &e : sizes) {
-                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, e.second, e.first, ws, d_state, keys_grid, false, st));
+                        HIP_TRY(nz::launch_keys(d_desc, d_list, a, e.second, e.first, ws, d_state, false, 0, st));
                         a += e.second;
                     }
                     HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, d_tabs, ws, d_state, smax != nullptr,
@@ -1211,7 +1248,7 @@ bool split_groups(const nz_job *jobs, int32_t njobs, const Tune &tune, SplitPlan
 // thread and device.
 struct SideStream {
     hipStream_t st = nullptr;
-    hipEvent_t start = nullptr;
+    hipEvent_t start = nullptr, keys = nullptr;
     bool ok = false;
 };
 
@@ -1221,7 +1258,8 @@ SideStream *side_stream(int device)
     SideStream &s = per_device[device];
     if (!s.ok && !s.st)
         s.ok = hipStreamCreateWithFlags(&s.st, hipStreamNonBlocking) == hipSuccess &&
-               hipEventCreateWithFlags(&s.start, hipEventDisableTiming) == hipSuccess;
+               hipEventCreateWithFlags(&s.start, hipEventDisableTiming) == hipSuccess &&
+               hipEventCreateWithFlags(&s.keys, hipEventDisableTiming) == hipSuccess;
     return s.ok ? &s : nullptr;
 }
 
@@ -1237,18 +1275,20 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
                                           (sp.bytes[0] + sp.bytes[1])) / kAlign * kAlign;
     std::vector<int32_t> back[2];
     for (int g = 0; g < 2; ++g) back[g].assign(sp.job[g].size(), 0);
-    // Side by side, each group's keys launch keeps the CU slots it is given:
-    // with a workgroup per block of sites, the short keys workgroups would hand
-    // their slots one by one to the other group's long-lived labelling and
-    // sweep workgroups (L = 16 learned step: 46.5 -> 43.0 ms with all the
-    // slots a CU holds, 42.7 ms with half of them, which leaves the other
-    // group's labelling room; a batch that runs as one group is faster with a
-    // workgroup per block).
-    Tune ts = tune;
-    ts.keys_resident = true;
     // the second group starts after the work already queued on the caller's stream
     HIP_TRY(hipEventRecord(side->start, st));
     HIP_TRY(hipStreamWaitEvent(side->st, side->start, 0));
+    // Both groups' keys are bound by the same vector ALUs, so the second group's
+    // first keys pass follows the first group's, whose labelling and sweep are the
+    // longer chain, and runs beside its labelling.  At once, one group's small
+    // workgroups starve the other's large ones (L = 16, 7 compact neighbourhoods
+    // x 1000: prefilled 22.1 ms, in turn 19.9; plain 36.2 and 34.4).
+    std::promise<void> recorded;
+    KeysTurn turn_a, turn_b;
+    turn_a.done = turn_b.done = side->keys;
+    turn_a.record = &recorded;
+    turn_b.second = true;
+    turn_b.recorded = recorded.get_future().share();
     int rc_b = NZ_OK;
     std::string err_b;
     int64_t stats_b[6] = {0, 0, 0, 0, 0, 0};
@@ -1263,7 +1303,7 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
             } else {
                 g_timing = timing;
                 rc_b = run_batch(sp.job[1].data(), static_cast<int32_t>(sp.job[1].size()), ws + wa, ws_bytes - wa,
-                                 d_nstar, d_mass, back[1].data(), ts, side->st, nullptr, sp.out[1].data());
+                                 d_nstar, d_mass, back[1].data(), tune, side->st, nullptr, sp.out[1].data(), &turn_b);
             }
         } catch (...) {
             rc_b = fail(NZ_ENOMEM, "host allocation failed");
@@ -1280,10 +1320,11 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
     int rc_a;
     try {
         rc_a = run_batch(sp.job[0].data(), static_cast<int32_t>(sp.job[0].size()), ws, wa, d_nstar, d_mass,
-                         back[0].data(), ts, st, nullptr, sp.out[0].data());
+                         back[0].data(), tune, st, nullptr, sp.out[0].data(), &turn_a);
     } catch (...) {
         rc_a = fail(NZ_ENOMEM, "host allocation failed");
     }
+    turn_a.pass();   // (whatever happened, the worker does not wait)
     worker.join();
     for (int k = 0; k < 6; ++k) {
         g_stats[k] += stats_b[k];

@@ -226,6 +226,7 @@ __global__ __launch_bounds__(256) void nz_clear_kernel(NzSample *__restrict__ de
 // 2.88 ms for zone 1.
 
 constexpr int KEYS_THREADS = 256;
+constexpr int KEYS_LOCAL_THREADS = 1024;   // at most
 #ifndef NZ_KEYS_ITERS
 #define NZ_KEYS_ITERS 64
 #endif
@@ -270,15 +271,21 @@ struct KeysCtx {
     uint32_t *counts;
 };
 
+// Dynamic LDS of the local kernel: the bucket counters, then the waves' queues.
+extern __shared__ __attribute__((aligned(16))) uint32_t keys_lds[];
+
 // Band sites of a wave are queued in LDS and bucketed 64 at a time, one per
 // lane, so the bucketing work runs on full waves although only a few percent of
 // the sites fall into the band.
 constexpr uint32_t KEYS_BQ = 192;   // queue entries per wave (< 64 left + 128 new)
 
+template <bool LOCAL>
 __device__ __forceinline__ void keys_bucket(const KeysCtx &c, uint64_t K, uint32_t i)
 {
     const uint64_t b = (K - c.T0) >> c.shift;
-    const uint32_t slot = atomicAdd(&c.counts[b], 1u);
+    uint32_t slot;
+    if constexpr (LOCAL) slot = atomicAdd(&keys_lds[b], 1u);
+    else slot = atomicAdd(&c.counts[b], 1u);
     if (slot < c.cap) c.sites[b * c.cap + slot] = pack_coords(i, c.L, c.magic);
 }
 
@@ -298,7 +305,7 @@ struct KeysIter {
     uint32_t seed_lo, seed_hi, smp_lo, smp_hi;
 };
 
-template <bool FULL, bool BALL, bool HI>
+template <bool LOCAL, bool FULL, bool BALL, bool HI>
 __device__ __forceinline__ void keys_iters(const KeysIter &k, uint32_t &be_lo, uint32_t &be_hi, uint32_t &bo_lo,
                                            uint32_t &bo_hi, int &its, uint32_t &nq)
 {
@@ -359,7 +366,7 @@ __device__ __forceinline__ void keys_iters(const KeysIter &k, uint32_t &be_lo, u
         __builtin_amdgcn_wave_barrier();
         if (nq >= 64u) {
             uint32_t base = 0;
-            for (; base + 64u <= nq; base += 64u) keys_bucket(c, qk[base + lane], qs[base + lane]);
+            for (; base + 64u <= nq; base += 64u) keys_bucket<LOCAL>(c, qk[base + lane], qs[base + lane]);
             // move the remainder (< 64 entries) to the front
             const uint32_t rest = nq - base;
             uint64_t rk = 0;
@@ -379,36 +386,18 @@ __device__ __forceinline__ void keys_iters(const KeysIter &k, uint32_t &be_lo, u
     }
 }
 
-__device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
-                                           int32_t first, int32_t count, bool by_xcd, int32_t blocks_per_sample,
-                                           uint8_t *__restrict__ ws, NzState *__restrict__ state, int32_t vblock)
+// One wave's KEYS_WAVE_SITES consecutive sites from wave_base (a multiple of
+// 2048, so that its bitset words start on a 64-word boundary) of sample sid,
+// queue qk / qs.  Waves work alone: no workgroup barrier, so a wave that waits
+// for its list atomic or its sample's descriptor leaves the SIMD to the others.
+// The wave's prefilled sites are appended to the sample's list in site order
+// with one atomic on *n0, and every bitset word's list position is stored, so
+// that a site's list position is that of its word plus the set bits below it.
+template <bool LOCAL>
+__device__ __forceinline__ void keys_wave(const NzSample &d, uint32_t N, uint32_t wave_base, uint64_t *qk, uint32_t *qs,
+                                          uint8_t *__restrict__ ws, uint32_t *n0)
 {
-    // Every wave works alone on its own KEYS_WAVE_SITES consecutive sites: no
-    // workgroup barrier, so a wave that waits for its list atomic or its
-    // sample's descriptor leaves the SIMD to the others.  The wave's prefilled
-    // sites are appended to the sample's list in site order with one global
-    // atomic, and every bitset word's list position is stored, so that a
-    // site's list position is that of its word plus the set bits below it.
-    __shared__ uint64_t bq_key[KEYS_THREADS / 64][KEYS_BQ];
-    __shared__ uint32_t bq_site[KEYS_THREADS / 64][KEYS_BQ];
-    int which = vblock / blocks_per_sample;
-    int blk = vblock % blocks_per_sample;
-    if (by_xcd) {
-        const int k = vblock >> 3;
-        which = (k / blocks_per_sample) * 8 + (vblock & 7);
-        blk = k % blocks_per_sample;
-        if (which >= count) return;   // (uniform over the workgroup)
-    }
-    const int sid = list ? list[first + which] : first + which;
-    const NzSample &d = desc[sid];
-    const uint32_t N = static_cast<uint32_t>(d.N);
     const uint32_t lane = lane_id();
-    const uint32_t wave = threadIdx.x >> 6;
-    // the first site of the wave's range (a multiple of 2048, so its bitset
-    // words start on a 64-word boundary)
-    const uint32_t wave_base =
-        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(blk) * KEYS_SITES_PER_BLOCK + KEYS_WAVE_SITES * wave);
-    if (wave_base >= N) return;   // wave-uniform
     const uint32_t seed_lo = static_cast<uint32_t>(d.seed), seed_hi = static_cast<uint32_t>(d.seed >> 32);
     const uint32_t smp_lo = static_cast<uint32_t>(d.sample), smp_hi = static_cast<uint32_t>(d.sample >> 32);
     const uint32_t occ_words = ((N + 63u) >> 6) << 1;   // padded to whole 64-site words
@@ -430,8 +419,6 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     const bool band_all = c.shift >= 64 || (span >> c.shift) != c.nb || c.T0 + span < c.T0;
     const uint64_t band_end = c.T0 + span;
 
-    uint64_t *qk = bq_key[wave];
-    uint32_t *qs = bq_site[wave];
     uint32_t nq = 0;        // wave-uniform
     // wave-uniform choices held in scalar registers: whether the wave's range
     // lies wholly inside the lattice (then no site needs a range test) and
@@ -449,20 +436,20 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     KeysIter ki{c, qk, qs, N, wave_base, lane, band_end, seed_lo, seed_hi, smp_lo, smp_hi};
     if (hi) {
         if (full) {
-            if (ball) keys_iters<true, true, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
-            else keys_iters<true, false, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+            if (ball) keys_iters<LOCAL, true, true, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+            else keys_iters<LOCAL, true, false, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
         } else {
-            if (ball) keys_iters<false, true, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
-            else keys_iters<false, false, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+            if (ball) keys_iters<LOCAL, false, true, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+            else keys_iters<LOCAL, false, false, true>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
         }
     } else if (full) {
-        if (ball) keys_iters<true, true, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
-        else keys_iters<true, false, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+        if (ball) keys_iters<LOCAL, true, true, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+        else keys_iters<LOCAL, true, false, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
     } else {
-        if (ball) keys_iters<false, true, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
-        else keys_iters<false, false, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+        if (ball) keys_iters<LOCAL, false, true, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
+        else keys_iters<LOCAL, false, false, false>(ki, be_lo, be_hi, bo_lo, bo_hi, its, nq);
     }
-    if (lane < nq) keys_bucket(c, qk[lane], qs[lane]);
+    if (lane < nq) keys_bucket<LOCAL>(c, qk[lane], qs[lane]);
 
     // Word q of iteration it (sites wave_base + 128 it .. + 127) interleaves
     // bits 16q .. 16q + 15 of the even and odd ballots.  The range's words come
@@ -539,7 +526,7 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
         return;
     }
     uint32_t got = 0u;
-    if (lane == 0u) got = atomicAdd(reinterpret_cast<uint32_t *>(&state[sid].n0), total);
+    if (lane == 0u) got = atomicAdd(n0, total);
     uint32_t base = __builtin_amdgcn_readlane(got, 0);
     const uint32_t cap = static_cast<uint32_t>(d.prefix_cap);
     int32_t *parc = reinterpret_cast<int32_t *>(ws + d.off_parc);
@@ -566,16 +553,68 @@ __device__ __forceinline__ void keys_block(const NzSample *__restrict__ desc, co
     }
 }
 
-// Workgroup g takes the blocks g, g + gridDim.x, ... of the launch (one pass
-// when the grid has a workgroup per block).
+// A workgroup per KEYS_SITES_PER_BLOCK sites.
 __global__ __launch_bounds__(KEYS_THREADS) void nz_keys_kernel(const NzSample *__restrict__ desc,
                                                                const int32_t *__restrict__ list, int32_t first, int32_t count,
-                                                               bool by_xcd, int32_t blocks_per_sample, int32_t nblocks,
+                                                               bool by_xcd, int32_t blocks_per_sample,
                                                                uint8_t *__restrict__ ws, NzState *__restrict__ state)
 {
-    for (int32_t vb = static_cast<int32_t>(blockIdx.x); vb < nblocks; vb += static_cast<int32_t>(gridDim.x)) {
-        keys_block(desc, list, first, count, by_xcd, blocks_per_sample, ws, state, vb);
+    __shared__ uint64_t bq_key[KEYS_THREADS / 64][KEYS_BQ];
+    __shared__ uint32_t bq_site[KEYS_THREADS / 64][KEYS_BQ];
+    const uint32_t wave = threadIdx.x >> 6;
+    const int32_t vb = static_cast<int32_t>(blockIdx.x);
+    int which = vb / blocks_per_sample;
+    int blk = vb % blocks_per_sample;
+    if (by_xcd) {
+        const int k = vb >> 3;
+        which = (k / blocks_per_sample) * 8 + (vb & 7);
+        blk = k % blocks_per_sample;
+        if (which >= count) return;   // (uniform over the workgroup)
     }
+    const int sid = list ? list[first + which] : first + which;
+    const NzSample &d = desc[sid];
+    const uint32_t N = static_cast<uint32_t>(d.N);
+    const uint32_t wave_base =
+        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(blk) * KEYS_SITES_PER_BLOCK + KEYS_WAVE_SITES * wave);
+    if (wave_base >= N) return;   // wave-uniform
+    keys_wave<false>(d, N, wave_base, bq_key[wave], bq_site[wave], ws, reinterpret_cast<uint32_t *>(&state[sid].n0));
+}
+
+// One workgroup per sample, for samples whose band holds more than 3% of the
+// sites.  With several workgroups per sample every band site costs a returning
+// atomic on its bucket's counter in the L2, and the chip does 29 G of those a
+// second wherever the counters lie, an eighth of the rate of the stores they
+// order; here the counters and the length of the prefill list are
+// in LDS, and the counters are written out once.  Keys, several workgroups per
+// sample / one: L = 16 zone 1 plain (16% of the sites in the band) 7.6 / 1.7 ms
+// for 1000 samples, 0.93 / 0.36 for 125, L = 24 10.7 / 3.6 for 200; zones 1-2
+// plain (4.4%) 1.43 / 1.05 ms for 1000, L = 24 3.2 / 2.3 for 200; zone 1 prefilled,
+// L = 16 (3.2%) 1.70 / 1.17 for 1000.  With less in the band the atomics are few
+// and the finer spread over the chip wins: zone 1 prefilled, L = 24 (2.2%), 2.3 / 2.7 for
+// 200, zones 1-6 prefilled, L = 16, 0.81 / 0.88 for 1000.  max_nb: words of the
+// counters (an even number; every sample of the launch has at most so many
+// buckets).
+__global__ __launch_bounds__(KEYS_LOCAL_THREADS, 8) void nz_keys_local_kernel(const NzSample *__restrict__ desc, int32_t first,
+                                                                              int32_t max_nb, uint8_t *__restrict__ ws,
+                                                                              NzState *__restrict__ state)
+{
+    __shared__ uint32_t n0;
+    const int sid = first + static_cast<int>(blockIdx.x);
+    const NzSample &d = desc[sid];
+    const uint32_t N = static_cast<uint32_t>(d.N);
+    const int32_t nb = min(d.nb, max_nb);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    for (int32_t b = static_cast<int32_t>(threadIdx.x); b < nb; b += static_cast<int32_t>(blockDim.x)) keys_lds[b] = 0u;
+    if (threadIdx.x == 0) n0 = 0u;
+    __syncthreads();
+    uint64_t *qk = reinterpret_cast<uint64_t *>(keys_lds + max_nb) + wave * KEYS_BQ;
+    uint32_t *qs = keys_lds + max_nb + 2 * waves * KEYS_BQ + wave * KEYS_BQ;
+    for (uint32_t base = wave * KEYS_WAVE_SITES; base < N; base += waves * KEYS_WAVE_SITES)
+        keys_wave<true>(d, N, base, qk, qs, ws, &n0);
+    __syncthreads();
+    uint32_t *counts = reinterpret_cast<uint32_t *>(ws + d.off_counts);
+    for (int32_t b = static_cast<int32_t>(threadIdx.x); b < nb; b += static_cast<int32_t>(blockDim.x)) counts[b] = keys_lds[b];
+    if (threadIdx.x == 0) state[sid].n0 = static_cast<int32_t>(n0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2251,33 +2290,36 @@ hipError_t launch_clear(NzSample *desc, const int32_t *list, int32_t nsamp, int3
     return hipGetLastError();
 }
 
+// The local keys kernel's counters and queues have to fit one CU, and its waves
+// have to reach every CU (fewer samples: several workgroups each).
+constexpr size_t kKeysLds = 150 * 1024;
+constexpr int64_t kKeysLocalWaves = 1024;
+
 hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first, int32_t count, int32_t N, uint8_t *ws,
-                       NzState *state, int32_t max_grid, bool by_xcd, hipStream_t st)
+                       NzState *state, bool by_xcd, int32_t max_nb, hipStream_t st)
 {
     if (count <= 0) return hipSuccess;
+    const int32_t waves = std::min(KEYS_LOCAL_THREADS / 64, (N + KEYS_WAVE_SITES - 1) / KEYS_WAVE_SITES);
+    const size_t words = (static_cast<size_t>(max_nb) + 1) / 2 * 2;
+    const size_t lds = 4 * (words + 3 * static_cast<size_t>(waves) * KEYS_BQ);
+    if (!list && max_nb > 0 && lds <= kKeysLds && static_cast<int64_t>(count) * waves >= kKeysLocalWaves) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(nz_keys_local_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kKeysLds));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(nz_keys_local_kernel, dim3(static_cast<uint32_t>(count)), dim3(static_cast<uint32_t>(64 * waves)), lds,
+                           st, desc, first, static_cast<int32_t>(words), ws, state);
+        return hipGetLastError();
+    }
     const int32_t bps = (N + KEYS_SITES_PER_BLOCK - 1) / KEYS_SITES_PER_BLOCK;
     const int32_t slots = by_xcd ? (count + 7) / 8 * 8 : count;
     const int64_t blocks = static_cast<int64_t>(bps) * slots;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    // (a multiple of 8, so that a workgroup's later blocks keep their XCD)
-    const int64_t grid = max_grid > 0 ? std::min<int64_t>(blocks, std::max<int64_t>(8, max_grid / 8 * 8)) : blocks;
-    hipLaunchKernelGGL(nz_keys_kernel, dim3(static_cast<uint32_t>(grid)), dim3(KEYS_THREADS), 0, st, desc, list, first,
-                       count, by_xcd, bps, static_cast<int32_t>(blocks), ws, state);
+    hipLaunchKernelGGL(nz_keys_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(KEYS_THREADS), 0, st, desc, list,
+                       first, count, by_xcd, bps, ws, state);
     return hipGetLastError();
 }
 
 int32_t keys_sites_per_block() { return KEYS_SITES_PER_BLOCK; }
-
-int32_t keys_resident_wgs()
-{
-    // one kernel, one architecture: the answer is fixed for the process
-    static const int32_t wgs = [] {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, nz_keys_kernel, KEYS_THREADS, 0) != hipSuccess || n < 1) n = 1;
-        return static_cast<int32_t>(n);
-    }();
-    return wgs;
-}
 
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
                           const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,

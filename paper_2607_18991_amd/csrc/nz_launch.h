@@ -20,12 +20,11 @@ hipError_t launch_clear(NzSample *desc, const int32_t *list, int32_t nsamp, int3
 // Keys for samples [first, first + count) of the descriptor array, all of
 // lattice size N.
 // (list != NULL: samples list[first .. first + count) instead).
-// max_grid > 0: at most that many workgroups, each taking several blocks.
 // by_xcd: all workgroups of a sample on one XCD (for bands that hold many sites).
-// keys_resident_wgs(): workgroups of the keys kernel one CU holds at once.
-int32_t keys_resident_wgs();
+// max_nb > 0: no sample has more than max_nb buckets, and one workgroup per sample
+// is preferred where the samples are enough and the counters fit.
 hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first, int32_t count, int32_t N, uint8_t *ws,
-                       NzState *state, int32_t max_grid, bool by_xcd, hipStream_t st);
+                       NzState *state, bool by_xcd, int32_t max_nb, hipStream_t st);
 int32_t keys_sites_per_block();
 
 // Bulk connected components for the samples listed in list[0..nlist), whose
