@@ -973,19 +973,69 @@ __global__ __launch_bounds__(256) void nz_rootmax_kernel(const NzSample *__restr
     if (best > 0) atomicMax(&state[sid].smax, best);
 }
 
+// Largest-cluster samples with lists of up to SIZES_RANGES ranges: the sizes of
+// the clusters whose roots lie in one range of the list, counted in LDS by one
+// workgroup, and their maximum.  `lds_range`: entries of a range.  In place of one
+// atomic per site in the L2 (29 G a second over the chip) a workgroup reads its
+// sample's list once per range: 1000 samples of L = 12, zone 1, 29000 prefilled
+// sites each took 0.88 ms, and 0.11 for the maximum, and take 0.10 together.
+constexpr int32_t SIZES_RANGE = 36864, SIZES_RANGES = 8;
+extern __shared__ uint32_t sizes_lds[];
+
+__global__ __launch_bounds__(1024) void nz_sizes_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
+                                                        int32_t nlist, int32_t ranges, int32_t lds_range,
+                                                        uint8_t *__restrict__ ws, NzState *__restrict__ state)
+{
+    int32_t y, x;
+    if (!xcd_slot(nlist, ranges, y, x)) return;
+    const int sid = list[y];
+    const NzSample &d = desc[sid];
+    const int32_t n0 = state[sid].n0;
+    const int32_t t = static_cast<int32_t>(threadIdx.x), step = static_cast<int32_t>(blockDim.x);
+    if (n0 > d.prefix_cap) {
+        if (x == 0 && t == 0) state[sid].status = NZ_ST_PREFIX;
+        return;
+    }
+    const int32_t base = x * lds_range, cnt = min(lds_range, n0 - base);
+    if (cnt <= 0) return;   // (uniform)
+    int32_t *parc = reinterpret_cast<int32_t *>(ws + d.off_parc);
+    for (int32_t j = t; j < cnt; j += step) sizes_lds[j] = 0u;
+    __syncthreads();
+    for (int32_t k = t; k < n0; k += step) {
+        const int32_t v = parc[k];
+        const int32_t j = (v & (LIST_NODE - 1)) - base;
+        if (v >= 0 && j >= 0 && j < cnt) atomicAdd(&sizes_lds[j], 1u);
+    }
+    __syncthreads();
+    int32_t best = 0;
+    for (int32_t j = t; j < cnt; j += step) {
+        const int32_t v = parc[base + j];
+        if (v >= 0) continue;
+        const uint32_t w = static_cast<uint32_t>(v) + sizes_lds[j];   // (a root's word holds its own 1)
+        if (sizes_lds[j]) parc[base + j] = static_cast<int32_t>(w);
+        best = max(best, static_cast<int32_t>(w & NZ_SIZE));
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) best = max(best, __shfl_xor(best, o));
+    if ((t & 63) == 0 && best > 0) atomicMax(&state[sid].smax, best);
+}
+
 // Sum over the finished samples of a chunk of their S_max(n) windows (all
-// samples of an smax-mode batch share one window of w entries).
+// samples of an smax-mode batch share one window of w entries).  A workgroup
+// takes 256 entries of every gridDim.y-th sample: with all the samples of an entry
+// in one thread, the 15 workgroups of a window of 3800 entries took 0.61 ms for
+// 1000 samples, with the samples spread over the chip 0.01 ms.
 __global__ __launch_bounds__(256) void nz_winsum_kernel(const NzSample *__restrict__ desc,
                                                         const NzState *__restrict__ state, int32_t nsamp, int32_t w,
                                                         const uint8_t *__restrict__ ws, uint64_t *__restrict__ out)
 {
     for (int32_t i = blockIdx.x * 256 + static_cast<int32_t>(threadIdx.x); i < w; i += gridDim.x * 256) {
         uint64_t sum = 0;
-        for (int32_t k = 0; k < nsamp; ++k) {
+        for (int32_t k = static_cast<int32_t>(blockIdx.y); k < nsamp; k += static_cast<int32_t>(gridDim.y)) {
             if (state[k].status != NZ_ST_DONE) continue;
             sum += reinterpret_cast<const uint32_t *>(ws + desc[k].off_win)[i];
         }
-        out[i] += sum;
+        if (sum) atomicAdd(reinterpret_cast<unsigned long long *>(&out[i]), static_cast<unsigned long long>(sum));
     }
 }
 
@@ -1234,6 +1284,7 @@ struct SweepOut {
 constexpr int BLK_EDGES = 1536;          // recorded (site, occupied neighbour) pairs per block
 constexpr int BLK_CHUNK = 6;             // rows checked together (five bits each: one 32-bit mask)
 constexpr int BLK_MAXROWS = 300;         // rows of the widest neighbourhood (298), in whole chunks
+constexpr int BLK_CURVES = 4;            // clusters of a block that may raise the maximum at once
 constexpr uint32_t BLK_EMPTY = 0xFFFFFFFFu;
 constexpr int32_t NZ_NONE = static_cast<int32_t>(0x80000000u);   // (a root word of no cluster)
 // Node ids: band sites, BAND_NODE | k; list nodes, LIST_NODE | index (both below
@@ -1302,10 +1353,12 @@ struct BlkCfg {
     static constexpr uint32_t SHIFT = B > 256 ? 21 : 22;
     // the ranks of a bisection go where the map was, if that is large enough
     static constexpr bool OWN_SCRATCH = NT == 256;
-    static constexpr uint32_t SCRATCH = B + RS / 2;   // words: keys of the sites, 16-bit ranks of the slots
+    // words: keys of the sites, 16-bit ranks of the slots; SMAX: joining times of the slots
+    static constexpr uint32_t SCRATCH = MODE == 2 ? RS : B + RS / 2;
     static_assert(B <= NT, "thread t loads entry t of a block");
     static_assert(RS % NT == 0 && RS >= B + 512 && RS >= 893 && RS <= 2048, "whole slots per thread; node numbers of 11 bits");
     static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
+    static_assert(MODE != BLK_SMAX || OWN_SCRATCH, "the map stays in use");
 };
 
 template <typename C>
@@ -1320,12 +1373,18 @@ struct BlkLds {
     int16_t eq[C::MODE == BLK_WRAP ? BLK_EDGES : 1];   // x0(first node) - x0(second node) of pair e
     uint32_t scratch[C::OWN_SCRATCH ? C::SCRATCH : 1];
     // largest-cluster sweep: the block position of every node (0xFFFF: an earlier
-    // root), the pairs of every position as a linked list, and the running
-    // maximum after every position
+    // root), the clusters that can raise the maximum (`next`: which of them a root
+    // is), their largest members and their growth at every position; one by one:
+    // the pairs of every position as a linked list, and the running maximum after
+    // every position
     uint16_t pos[C::MODE == BLK_SMAX ? C::RS : 1];
     uint16_t next[C::MODE == BLK_SMAX ? BLK_EDGES : 1];
     uint32_t first[C::MODE == BLK_SMAX ? C::B : 1];
-    uint32_t smax[C::MODE == BLK_SMAX ? C::B : 1];
+    uint32_t smax[C::MODE == BLK_SMAX ? BLK_CURVES * C::B : 1];
+    uint64_t member[C::MODE == BLK_SMAX ? BLK_CURVES : 1];   // size before the block << 32 | node
+    uint32_t ends[C::MODE == BLK_SMAX ? BLK_CURVES : 1];
+    uint32_t wsum[C::MODE == BLK_SMAX ? BLK_CURVES * (C::NT / 64) : 1];
+    int32_t nbig;
     int32_t ecnt, nroots, flag, bad, claim;
     uint32_t total;                    // spanning: the size of the cluster of the T-th site
     uint32_t croot;                    //           and its root node
@@ -1764,7 +1823,8 @@ enum { BLK_COMMITTED = 0, BLK_SPANS = 1, BLK_NOFIT = 2 };
 // order, after which a cluster spans and S.total that cluster's size (of a
 // prefilled sample: its band sites); the sample is over.  Largest-cluster sweep (sites
 // in order): the window entries of the block are written and smax carries the
-// running maximum.
+// running maximum; BLK_NOFIT also where its sites have to be added one by one and
+// are many.
 template <typename C>
 __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, uint32_t *scratch, const NzSample &d, int32_t L,
                                         int nrows, int lo, int len, bool sorted, int b0, int b1, int max_old, int32_t r,
@@ -1785,6 +1845,10 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
         S.nroots = 0;
         S.flag = 0;
         S.bad = 0;
+        if constexpr (MODE == BLK_SMAX) {
+            S.nbig = 0;
+            for (int c = 0; c < BLK_CURVES; ++c) S.member[c] = 0;
+        }
     }
     __syncthreads();
     int32_t site = 0;
@@ -1798,10 +1862,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
         const uint32_t h = blk_enter<C>(S, static_cast<uint32_t>(site), fresh);   // (the table holds B sites)
         S.f[h] = W::make(NZ_ROOT | fl | 1u, 0);
         S.spos[t] = static_cast<uint16_t>(h);
-        if constexpr (MODE == BLK_SMAX) {
-            S.first[t] = BLK_EMPTY;
-            S.pos[h] = static_cast<uint16_t>(t);
-        }
+        if constexpr (MODE == BLK_SMAX) S.pos[h] = static_cast<uint16_t>(t);
     }
     __syncthreads();
 
@@ -1839,12 +1900,6 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
                     ++nnew;
                 }
                 if (node == C::RS) S.bad = 1;   // table full
-            }
-            if constexpr (MODE == BLK_SMAX) {
-                // kept once, at the later position
-                if (S.pos[node & (C::RS - 1)] == 0xFFFFu || static_cast<int>(S.pos[node & (C::RS - 1)]) < i)
-                    S.next[e] = static_cast<uint16_t>(__hip_atomic_exchange(&S.first[i], static_cast<uint32_t>(e), __ATOMIC_RELAXED,
-                                                                            __HIP_MEMORY_SCOPE_WORKGROUP));
             }
             S.et[e] = static_cast<uint32_t>(S.spos[i]) | (node << 16);
             // x0(site) - x0(node): the neighbour lies at x0(site) + d0 = x0(node) + disp
@@ -1904,50 +1959,177 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
         return S.flag != 0;
     };
 
-    if constexpr (MODE == BLK_SMAX) {
-        // 4. unions in the order of the positions, by one lane; the sizes are
-        //    kept at the roots
-        if (t == 0) {
-            for (int i = 0; i < len; ++i) {
-                uint32_t a = S.spos[i], sz = 1;
-                for (uint32_t e = S.first[i]; (e & 0xFFFFu) != 0xFFFFu; e = S.next[e]) {
-                    int32_t unused;
-                    uint32_t wb;
-                    const uint32_t b = blk_find<C>(S, S.et[e] >> 16, wb, unused);
-                    if (b == a) continue;
-                    const uint32_t sb = wb & NZ_SIZE;
-                    const uint32_t lo_n = sb > sz ? a : b, hi_n = sb > sz ? b : a;
-                    sz += sb;
-                    st_g(&S.f[lo_n], W::make(hi_n, 0));
-                    st_g(&S.f[hi_n], W::make(NZ_ROOT | sz, 0));
-                    a = hi_n;
-                }
-                smax = max(smax, static_cast<int32_t>(sz));
-                S.smax[i] = static_cast<uint32_t>(smax);
-            }
+    // unions of all pairs (that `take` accepts)
+    auto unions = [&](auto &&take) {
+        for (int e = t; e < ne; e += C::NT) {
+            const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
+            if (!take(u, v)) continue;
+            int32_t q = 0;
+            if constexpr (MODE == BLK_WRAP) q = S.eq[e];
+            blk_link<C>(S, u, v, q);
         }
         __syncthreads();
-        smax = static_cast<int32_t>(S.smax[len - 1]);
-        // r + t + 1 sites are occupied after position t
-        const int32_t rr = r + t + 1;
-        if (act && rr >= win_lo && rr < win_hi) win[rr - win_lo] = S.smax[t];
+    };
+
+    if constexpr (MODE == BLK_SMAX) {
+        // 4. all unions at once.  A cluster that ends the block no larger than the
+        //    maximum before it never counts.  One that ends larger, but in which
+        //    what joins its largest member is no larger than that maximum, counts
+        //    by the cluster of that member alone, and this grows by each node's
+        //    size at the time the node joins: the least time, over all paths of
+        //    pairs, by which the last pair of the path is there.  By one lane, site
+        //    by site, the kernel took 4.1 ms for 1000 samples of L = 12, zone 1
+        //    (windows of 3800 sites around the threshold); with one such cluster per
+        //    block 2.2, with up to four 1.6.
+        unions([](uint32_t, uint32_t) { return true; });
+        gather();
 #pragma unroll
-        for (int k = 0; k < NODES; ++k) {
-            uint32_t unused;
-            if (live[k]) root[k] = blk_find<C>(S, node_of(k), unused, disp[k]);
-        }
-    } else {
-        // 4. unions of all pairs (that `take` accepts)
-        auto unions = [&](auto &&take) {
-            for (int e = t; e < ne; e += C::NT) {
-                const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
-                if (!take(u, v)) continue;
-                int32_t q = 0;
-                if constexpr (MODE == BLK_WRAP) q = S.eq[e];
-                blk_link<C>(S, u, v, q);
+        for (int k = 0; k < NODES; ++k)
+            if (live[k] && root[k] == node_of(k)) {
+                const uint32_t ends = W::lo(S.f[root[k]]) & NZ_SIZE;
+                uint32_t c = BLK_CURVES;
+                if (ends > static_cast<uint32_t>(smax)) {
+                    c = static_cast<uint32_t>(atomicAdd(&S.nbig, 1));
+                    if (c < BLK_CURVES) S.ends[c] = ends;
+                }
+                S.next[root[k]] = static_cast<uint16_t>(min(c, static_cast<uint32_t>(BLK_CURVES)));
+            }
+        __syncthreads();
+        const int nbig = S.nbig;
+        uint32_t curve[NODES];   // of this thread's nodes (BLK_CURVES: none)
+        bool at_once = nbig <= BLK_CURVES;
+        uint32_t ends = static_cast<uint32_t>(smax);
+        if (at_once && nbig > 0) {
+#pragma unroll
+            for (int k = 0; k < NODES; ++k) {
+                curve[k] = live[k] ? S.next[root[k]] : BLK_CURVES;
+                if (curve[k] < BLK_CURVES)
+                    atomicMax(reinterpret_cast<unsigned long long *>(&S.member[curve[k]]),
+                              (static_cast<unsigned long long>(word0[k] & NZ_SIZE) << 32) | node_of(k));
             }
             __syncthreads();
-        };
+            for (int c = 0; c < nbig; ++c) {
+                at_once = at_once && S.ends[c] - static_cast<uint32_t>(S.member[c] >> 32) <= static_cast<uint32_t>(smax);
+                ends = max(ends, S.ends[c]);
+            }
+        }
+        const int32_t rr = r + t + 1;   // r + t + 1 sites are occupied after position t
+        if (at_once) {
+            if (r + len >= win_lo) {
+                auto time_of = [&](uint32_t n) {
+                    const uint32_t p = S.pos[n];
+                    return p == 0xFFFFu ? 0u : p + 1u;
+                };
+                uint32_t *joins = S.scratch;
+                uint32_t best = static_cast<uint32_t>(smax);
+                if (nbig) {
+                    for (int c = 0; c < nbig; ++c)
+                        if (act) S.smax[c * C::B + t] = 0u;
+#pragma unroll
+                    for (int k = 0; k < NODES; ++k) {
+                        const bool first = curve[k] < BLK_CURVES && static_cast<uint32_t>(S.member[curve[k]]) == node_of(k);
+                        joins[node_of(k)] = first ? time_of(node_of(k)) : BLK_EMPTY;
+                    }
+                    for (;;) {
+                        __syncthreads();
+                        if (t == 0) S.flag = 0;
+                        __syncthreads();
+                        bool changed = false;
+                        for (int e = t; e < ne; e += C::NT) {
+                            const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
+                            const uint32_t ju = ld_g(&joins[u]), jv = ld_g(&joins[v]);
+                            const uint32_t there = max(time_of(u), time_of(v));
+                            const uint32_t a = max(ju, there), b = max(jv, there);
+                            if (a < jv) atomicMin(&joins[v], a);
+                            if (b < ju) atomicMin(&joins[u], b);
+                            changed = changed || a < jv || b < ju;
+                        }
+                        if (changed) S.flag = 1;
+                        __syncthreads();
+                        if (!S.flag) break;
+                    }
+#pragma unroll
+                    for (int k = 0; k < NODES; ++k)
+                        if (curve[k] < BLK_CURVES) {
+                            const uint32_t j = joins[node_of(k)];   // (<= len: every node has joined; 0: the member alone)
+                            if (j) atomicAdd(&S.smax[curve[k] * C::B + j - 1u], word0[k] & NZ_SIZE);
+                        }
+                    __syncthreads();
+                    uint32_t grown[BLK_CURVES];
+#pragma unroll
+                    for (int c = 0; c < BLK_CURVES; ++c) {
+                        grown[c] = c < nbig && act ? S.smax[c * C::B + t] : 0u;
+                        if (c >= nbig) continue;   // (uniform)
+#pragma unroll
+                        for (int o = 1; o < 64; o <<= 1) {
+                            const uint32_t v = static_cast<uint32_t>(__shfl_up(static_cast<int>(grown[c]), o));
+                            if ((t & 63) >= o) grown[c] += v;
+                        }
+                        if ((t & 63) == 63) S.wsum[c * (C::NT / 64) + (t >> 6)] = grown[c];
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int c = 0; c < BLK_CURVES; ++c) {
+                        if (c >= nbig) continue;
+                        for (int w = 0; w < (t >> 6); ++w) grown[c] += S.wsum[c * (C::NT / 64) + w];
+                        // (a member that is a site of the block is counted as it joins)
+                        const uint64_t mb = S.member[c];
+                        if (time_of(static_cast<uint32_t>(mb)) == 0u) grown[c] += static_cast<uint32_t>(mb >> 32);
+                        best = max(best, grown[c]);
+                    }
+                }
+                if (act && rr >= win_lo && rr < win_hi) win[rr - win_lo] = best;
+            }
+            smax = static_cast<int32_t>(ends);
+        } else if (len > 32) {
+            // in halves: the condition is soon met
+            if (act) m.occ_clear(static_cast<uint32_t>(site));
+            __syncthreads();
+            return BLK_NOFIT;
+        } else {
+            // one by one, by one lane; the sizes are kept at the roots
+            if (act) S.first[t] = BLK_EMPTY;
+#pragma unroll
+            for (int k = 0; k < NODES; ++k)
+                if (live[k]) S.f[node_of(k)] = W::make(word0[k], 0);
+            __syncthreads();
+            for (int e = t; e < ne; e += C::NT) {
+                // kept once, at the later position
+                const uint32_t i = S.pos[S.et[e] & 0xFFFFu], j = S.pos[S.et[e] >> 16];
+                if (j == 0xFFFFu || j < i)
+                    S.next[e] = static_cast<uint16_t>(__hip_atomic_exchange(&S.first[i], static_cast<uint32_t>(e), __ATOMIC_RELAXED,
+                                                                            __HIP_MEMORY_SCOPE_WORKGROUP));
+            }
+            __syncthreads();
+            if (t == 0) {
+                for (int i = 0; i < len; ++i) {
+                    uint32_t a = S.spos[i], sz = 1;
+                    for (uint32_t e = S.first[i]; (e & 0xFFFFu) != 0xFFFFu; e = S.next[e]) {
+                        int32_t unused;
+                        uint32_t wb;
+                        const uint32_t b = blk_find<C>(S, S.et[e] >> 16, wb, unused);
+                        if (b == a) continue;
+                        const uint32_t sb = wb & NZ_SIZE;
+                        const uint32_t lo_n = sb > sz ? a : b, hi_n = sb > sz ? b : a;
+                        sz += sb;
+                        st_g(&S.f[lo_n], W::make(hi_n, 0));
+                        st_g(&S.f[hi_n], W::make(NZ_ROOT | sz, 0));
+                        a = hi_n;
+                    }
+                    smax = max(smax, static_cast<int32_t>(sz));
+                    S.smax[i] = static_cast<uint32_t>(smax);
+                }
+            }
+            __syncthreads();
+            smax = static_cast<int32_t>(S.smax[len - 1]);
+            if (act && rr >= win_lo && rr < win_hi) win[rr - win_lo] = S.smax[t];
+#pragma unroll
+            for (int k = 0; k < NODES; ++k) {
+                uint32_t unused;
+                if (live[k]) root[k] = blk_find<C>(S, node_of(k), unused, disp[k]);
+            }
+        }
+    } else {
         unions([](uint32_t, uint32_t) { return true; });
         if (gather()) {
             res = BLK_SPANS;
@@ -2361,6 +2543,19 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
     hipLaunchKernelGGL(nz_compress_kernel, dim3(static_cast<uint32_t>(bx_site) * slots8), dim3(256), 0, st, desc, list,
                        nlist, bx_site, ws, state);
     mark(2);
+    if (smax && max_sites <= SIZES_RANGE * SIZES_RANGES) {
+        // (longer lists would be read too often: one atomic per site)
+        const int32_t ranges = std::max(1, (max_sites + SIZES_RANGE - 1) / SIZES_RANGE);
+        const int32_t range = std::max(64, std::min(SIZES_RANGE, max_sites));
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(nz_sizes_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, SIZES_RANGE * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(nz_sizes_kernel, dim3(static_cast<uint32_t>(ranges) * slots8), dim3(range > 8192 ? 1024 : 256),
+                           static_cast<size_t>(range) * 4, st, desc, list, nlist, ranges, range, ws, state);
+        mark(3);
+        mark(4);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(nz_accum_kernel, dim3(static_cast<uint32_t>(bx_site) * slots8), dim3(256), 0, st, desc, list, nlist,
                        bx_site, ws, state);
     mark(3);
@@ -2377,7 +2572,10 @@ hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsa
     if (nsamp <= 0 || w <= 0) return hipSuccess;
     const int32_t blocks = (w + 255) / 256;
     const uint32_t grid = static_cast<uint32_t>(blocks < 4096 ? blocks : 4096);
-    hipLaunchKernelGGL(nz_winsum_kernel, dim3(grid), dim3(256), 0, st, desc, state, nsamp, w, ws, out);
+    // some 2048 workgroups, and at least eight samples each
+    const int32_t spread = std::max(1, std::min((nsamp + 7) / 8, 2048 / static_cast<int32_t>(grid)));
+    hipLaunchKernelGGL(nz_winsum_kernel, dim3(grid, static_cast<uint32_t>(spread)), dim3(256), 0, st, desc, state, nsamp, w, ws,
+                       out);
     return hipGetLastError();
 }
 
@@ -2419,8 +2617,10 @@ static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint
         a.map_words = std::min(exact, BLK_SMALL_MAP);
         return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);
     }
-    a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<BlkCfg<MODE, PER, 1024, 512>>)) / 4));
-    return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
+    if constexpr (MODE != BLK_SMAX) {
+        a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<BlkCfg<MODE, PER, 1024, 512>>)) / 4));
+        return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
+    }
 }
 
 hipError_t launch_sweep(SweepKind kind, bool periodic, const NzSweepArgs &a, int32_t *nstar, int32_t *mass,
