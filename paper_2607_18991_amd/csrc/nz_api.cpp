@@ -622,6 +622,9 @@ struct KeysTurn {
     }
 };
 
+// Whether the labelling takes the hook of sparse lists.
+bool hook_map(const Part &part) { return !part.p.wrap && nz::hook_map_fits(pow5(part.p.L), part.s.prefix_cap); }
+
 // job_out (may be NULL): first output index of every job (default: the
 // samples of the jobs in order, from 0).
 int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_t *d_nstar, int32_t *d_mass,
@@ -749,6 +752,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             for (int32_t i : order)
                 if (parts[i].s.T0 != 0) pre.push_back(i);
             std::stable_sort(pre.begin(), pre.end(), [&](int32_t a, int32_t b) {
+                if (hook_map(parts[a]) != hook_map(parts[b])) return hook_map(parts[b]);
                 return prefill_group(parts[a].s.prefix_cap) > prefill_group(parts[b].s.prefix_cap);
             });
             int32_t nlist = 0;
@@ -824,22 +828,28 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             if (nlist > 0) {
                 for (size_t g = 0; g < pre.size();) {
                     const int32_t most = parts[pre[g]].s.prefix_cap;
-                    int32_t count = 0;
+                    const bool map = hook_map(parts[pre[g]]);
+                    int32_t count = 0, map_N = 0;
                     size_t e = g;
-                    while (e < pre.size()) {
+                    while (e < pre.size() && hook_map(parts[pre[e]]) == map) {
                         // the samples of one size class, if a launch of their own saves
                         // enough empty workgroups
                         size_t c = e;
                         int32_t samples = 0;
                         const int cls = prefill_group(parts[pre[e]].s.prefix_cap);
-                        while (c < pre.size() && prefill_group(parts[pre[c]].s.prefix_cap) == cls) samples += parts[pre[c++]].count;
+                        int32_t N = 0;
+                        while (c < pre.size() && hook_map(parts[pre[c]]) == map && prefill_group(parts[pre[c]].s.prefix_cap) == cls) {
+                            N = std::max(N, static_cast<int32_t>(pow5(parts[pre[c]].p.L)));
+                            samples += parts[pre[c++]].count;
+                        }
                         const int64_t empty = static_cast<int64_t>(samples) * (most - parts[pre[e]].s.prefix_cap) / 1024;
                         if (e > g && empty > kEmptyWgs) break;
                         count += samples;
+                        if (map) map_N = std::max(map_N, N);
                         e = c;
                     }
                     HIP_TRY(nz::launch_prefill(d_desc, d_list + parts[pre[g]].list0, count, most, d_tabs, ws, d_state,
-                                               smax != nullptr, wrap_chunk, per_chunk, st, prefill_events()));
+                                               smax != nullptr, wrap_chunk, per_chunk, map_N, dev.cus, st, prefill_events()));
                     g = e;
                 }
                 // Resolve backoffs inside the chunk: samples whose bulk state already
@@ -851,7 +861,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                     HIP_TRY(hipStreamSynchronize(st));
                     std::vector<int32_t> again;        // descriptors, by L (the order of `order`)
                     std::vector<std::pair<int32_t, int32_t>> sizes;   // (N, count) of every L among them
-                    int32_t max_prefix = 0;
+                    int32_t max_prefix = 0, map_N = 1;
                     for (int32_t i : order) {
                         const Part &part = parts[i];
                         if (part.s.T0b[lv] == 0) continue;   // not planned: the redo round takes it
@@ -865,6 +875,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                             if (sizes.empty() || sizes.back().first != N) sizes.emplace_back(N, 0);
                             ++sizes.back().second;
                             max_prefix = std::max(max_prefix, part.s.prefix_cap);
+                            map_N = map_N > 0 && hook_map(part) ? std::max(map_N, N) : 0;
                         }
                     }
                     if (again.empty()) break;
@@ -877,7 +888,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                         a += e.second;
                     }
                     HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, d_tabs, ws, d_state, smax != nullptr,
-                                               wrap_chunk, per_chunk, st, prefill_events()));
+                                               wrap_chunk, per_chunk, map_N, dev.cus, st, prefill_events()));
                     // (`again` stays untouched until the copy has been read: the next
                     // pass synchronises first, and so does the end of the chunk)
                     lists.push_back(std::move(again));

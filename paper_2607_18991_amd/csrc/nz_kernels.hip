@@ -126,6 +126,13 @@ __device__ __forceinline__ int32_t wrap_fix(uint32_t out, int32_t L)
     return fix;
 }
 
+// The steps every axis allows from the site with packed coordinates pc.
+__device__ __forceinline__ uint32_t allowed_of(uint32_t pc, int32_t L)
+{
+    return allowed_axis(pc & 63, L) | (allowed_axis((pc >> 6) & 63, L) << 5) | (allowed_axis((pc >> 12) & 63, L) << 10) |
+           (allowed_axis((pc >> 18) & 63, L) << 15) | (allowed_axis(pc >> 24, L) << 20);
+}
+
 // The bits of a row's code that belong to axes 1..4.
 constexpr uint32_t kRowAxes = 0x1FFFFE0u;
 
@@ -668,10 +675,22 @@ constexpr int HOOKW_UNROLL = 8;  // half as many rows (each has an entry per sid
 // resident workgroups: this kernel is bound by the latency of its dependent
 // loads and atomics)
 constexpr int HOOK_EBUF = 128;
+constexpr int HOOK_ROWS = 150;   // one row of every +- pair of the widest neighbourhood (149)
 
 // Summary words a hook workgroup stages in LDS (the host sizes summaries to at
 // most 1025 words).
 constexpr int32_t HOOK_SUM_MAX = 1025;
+
+// Words of the occupation map outside the lattice: one before, two behind.
+constexpr uint32_t MAP_PAD = 3;
+
+// The map's shift for a lattice of N sites when map_words words are there.
+__host__ __device__ __forceinline__ uint32_t map_shift(uint32_t N, uint32_t map_words)
+{
+    uint32_t ms = 0;
+    while ((((N - 1u) >> ms) >> 5) + 1u + MAP_PAD > map_words) ++ms;
+    return ms;
+}
 
 // Links list positions a and b: CAS links go from the larger root to the
 // smaller, only onto an entry that is still a root, retried from the parent the
@@ -758,10 +777,7 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
         const bool act = i < n0;
         const int32_t s = act ? static_cast<int32_t>(prefix[i]) : 0;
         const uint32_t pc = pack_coords(static_cast<uint32_t>(s), static_cast<uint32_t>(L), magic);
-        const uint32_t A = act ? (allowed_axis(pc & 63, L) | (allowed_axis((pc >> 6) & 63, L) << 5) |
-                                  (allowed_axis((pc >> 12) & 63, L) << 10) | (allowed_axis((pc >> 18) & 63, L) << 15) |
-                                  (allowed_axis(pc >> 24, L) << 20))
-                               : 0u;
+        const uint32_t A = act ? allowed_of(pc, L) : 0u;
         int32_t below = -1;   // the first neighbour found with a smaller list position
         // appends the lanes' edges (i, j) and links the buffer when it is full
         auto push = [&](bool edge, int32_t j) {
@@ -859,6 +875,193 @@ __global__ __launch_bounds__(256) void nz_hook_kernel(const NzSample *__restrict
     }
     __builtin_amdgcn_wave_barrier();
     hook_flush(par, ei, ej, ne, lane);
+}
+
+// The pairs a wave has found: list position of a site, lattice index of an
+// occupied neighbour.
+struct HookEdges {
+    int32_t *par;
+    const uint2 *wrec;
+    int32_t *ei, *ep;   // LDS, HOOK_EBUF each
+    int32_t ne;         // pairs in the buffer (wave-uniform), carried from pass to pass
+    uint32_t lane;
+
+    // links the pairs e0 .. e0 + n - 1 (n <= 64): neighbours' list positions from
+    // their words' records
+    __device__ __forceinline__ void link(int32_t e0, int32_t n)
+    {
+        __builtin_amdgcn_wave_barrier();
+        if (static_cast<int32_t>(lane) < n) {
+            const int32_t p = ld_w(&ep[e0 + static_cast<int32_t>(lane)]);
+            const uint2 rec = wrec[p >> 5];
+            const int32_t i = ld_w(&ei[e0 + static_cast<int32_t>(lane)]);
+            const int32_t j = static_cast<int32_t>(rec.x + static_cast<uint32_t>(__popc(rec.y & ((1u << (p & 31)) - 1u))));
+            // a root may point at any smaller member of another tree: where the
+            // larger end is still its own root, one CAS without finds does
+            const int32_t low = min(i, j);
+            int32_t top = max(i, j);
+            if (ld_w(&par[top]) != top ||
+                !__hip_atomic_compare_exchange_strong(&par[top], &top, low, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT))
+                cc_link(par, top, low);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // appends the lanes' occupied neighbours: bit 5q + c of mask is the site c of
+    // row k0 + q of site s, entry i; links the buffer when it is full
+    template <bool PER>
+    __device__ __forceinline__ void push(uint32_t mask, const NzOffset *rows, int32_t k0, int32_t i, int32_t s, uint32_t A, int32_t L)
+    {
+        uint64_t mk;
+        while ((mk = __ballot(mask != 0u)) != 0ull) {
+            if (mask) {
+                const int bit = __builtin_ctz(mask);
+                mask &= mask - 1u;
+                const int q = (bit * 13) >> 6, c = bit - 5 * q;   // bit / 5 for bit < 30
+                const NzOffset o = rows[k0 + q];
+                int32_t p = s + o.stride - 2 + c;
+                if constexpr (PER) {
+                    const uint32_t out = o.code & ~A & (kRowAxes | (1u << c));
+                    if (out) p += wrap_fix(out, L);
+                }
+                const int32_t e = ne + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                                           static_cast<uint32_t>(mk >> 32),
+                                           __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u)));
+                st_w(&ei[e], i);
+                st_w(&ep[e], p);
+            }
+            ne += static_cast<int32_t>(__popcll(mk));
+            if (ne >= 64) {
+                ne -= 64;   // the last 64; the rest stays for a later round
+                link(ne, 64);
+            }
+        }
+    }
+};
+
+// The sites ib + lane, ib + bx * blockDim + lane, .. of one wave.  EXACT: the map
+// is the occupation; else a bit stands for 1 << ms sites, and a set one sends the
+// check to the bitset.
+template <bool PER, bool EXACT>
+__device__ __forceinline__ void hook_map_sites(HookEdges &ed, const uint32_t *map, uint32_t ms, const NzOffset *rows, int32_t rh,
+                                               const NzOffset *__restrict__ tab, const uint32_t *__restrict__ occ,
+                                               const uint32_t *__restrict__ prefix, int32_t ib, int32_t step, int32_t n0, int32_t L,
+                                               uint64_t magic, uint32_t words)
+{
+    for (; ib < n0; ib += step) {
+        const int32_t i = ib + static_cast<int32_t>(ed.lane);
+        const bool act = i < n0;
+        const int32_t s = act ? static_cast<int32_t>(prefix[i]) : 0;
+        const uint32_t pc = pack_coords(static_cast<uint32_t>(s), static_cast<uint32_t>(L), magic);
+        const uint32_t A = act ? allowed_of(pc, L) : 0u;
+        const int32_t x0 = static_cast<int32_t>(pc & 63);
+        for (int32_t k0 = 0; k0 < rh; k0 += HOOK_UNROLL) {
+            // side 1 (periodic only): the steps that leave along axis 0, on the
+            // other side of the row
+            for (int side = 0; side < (PER ? 2 : 1); ++side) {
+                int32_t b[HOOK_UNROLL];   // the row's sites start here
+                uint32_t want[HOOK_UNROLL], w0[HOOK_UNROLL], w1[HOOK_UNROLL];
+#pragma unroll
+                for (int q = 0; q < HOOK_UNROLL; ++q) {
+                    NzOffset o;
+                    o.stride = 0;
+                    o.code = 0u;
+                    if (k0 + q < rh) o = tab[k0 + q];   // (uniform: scalar registers)
+                    const uint32_t out = o.code & ~A & kRowAxes;
+                    if constexpr (PER) {
+                        want[q] = act ? o.code & (side ? ~A : A) & 31u : 0u;
+                        b[q] = want[q] ? s + o.stride - 2 + (out ? wrap_fix(out, L) : 0) + (side ? (x0 < 2 ? L : -L) : 0) : 0;
+                    } else {
+                        want[q] = out == 0u ? o.code & A & 31u : 0u;
+                        b[q] = out == 0u ? s + o.stride - 2 : 0;
+                    }
+                    const int32_t w = (EXACT ? b[q] >> 5 : b[q] >> (ms + 5u)) + 1;
+                    w0[q] = map[w];
+                    w1[q] = map[w + 1];
+                }
+                uint32_t mask = 0u;   // of row q: bits 5q ..
+                if constexpr (EXACT) {
+#pragma unroll
+                    for (int q = 0; q < HOOK_UNROLL; ++q)
+                        mask |= (__builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(b[q]) & 31u) & want[q]) << (5 * q);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < HOOK_UNROLL; ++q) {
+                        // the map bits of sites b .. b + 4 (at most three)
+                        const int32_t k = b[q] >> ms, n = ((b[q] + 4) >> ms) - k;
+                        const uint32_t any = __builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(k) & 31u) & ((2u << n) - 1u);
+                        const bool need = any != 0u && want[q] != 0u;
+                        const uint32_t first = static_cast<uint32_t>(max(b[q], 0)) >> 5;
+                        const uint32_t last = static_cast<uint32_t>(max(b[q], 0) + 4) >> 5;
+                        w0[q] = need ? occ[first] : 0u;
+                        w1[q] = need && last != first && last < words ? occ[last] : 0u;
+                    }
+#pragma unroll
+                    for (int q = 0; q < HOOK_UNROLL; ++q) {
+                        const int32_t b0 = max(b[q], 0);
+                        const uint32_t v = __builtin_amdgcn_alignbit(w1[q], w0[q], static_cast<uint32_t>(b0) & 31u) << (b0 - b[q]);
+                        mask |= (v & want[q]) << (5 * q);
+                    }
+                }
+                ed.push<PER>(mask, rows, k0, i, s, A, L);
+            }
+        }
+    }
+    ed.link(0, ed.ne);
+}
+
+// The hook of sparse lists: the workgroup holds a map of the occupation in LDS,
+// as the block sweep does, and a row of offsets costs a dozen instructions and
+// one two-word read of it.  The kernel above takes some 45 with its summary, its
+// two conditional loads and its ballots, and is bound by them (at L = 16, zones
+// 1-4, 88% of its cycles issue vector instructions).  bx workgroups per sample,
+// blockDim sites of the list at a time.  The kernel above / this one, 1000 samples
+// of L = 16: zones 1-3 0.80 / 0.60 ms, 1-4 0.64 / 0.43, 1-7 0.47 / 0.25; L = 24
+// (200, eight sites to a bit, 2% of the bits set), zones 1-7 1.01 / 0.70.  With more
+// bits set it loses: at L = 24 the reads behind them (zones 1-4, 6%, 1.08 / 1.15;
+// zones 1-3, 10%, 1.23 / 1.49), at L = 16 the links, which want the waves that the
+// map's LDS takes away (zones 1-2, 4%, 1.28 / 1.32; zone 1, 15%, 3.1 / 3.4); the
+// line lies at one bit in 32.
+template <bool PER>
+__global__ __launch_bounds__(1024) void nz_hook_map_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
+                                                           int32_t nlist, int32_t bx, uint32_t map_words,
+                                                           const NzOffset *__restrict__ tabs, uint8_t *__restrict__ ws,
+                                                           NzState *__restrict__ state)
+{
+    extern __shared__ uint32_t hook_map[];
+    __shared__ NzOffset rows[HOOK_ROWS];
+    __shared__ int32_t ebuf_i[16][HOOK_EBUF];
+    __shared__ int32_t ebuf_p[16][HOOK_EBUF];
+    int32_t y, x;
+    if (!xcd_slot(nlist, bx, y, x)) return;
+    const int sid = list[y];
+    const NzSample &d = desc[sid];
+    const int32_t n0 = state[sid].n0;
+    const int32_t t = static_cast<int32_t>(threadIdx.x), nt = static_cast<int32_t>(blockDim.x);
+    if (n0 > d.prefix_cap || d.wrap || x * nt >= n0) return;   // (uniform over the workgroup)
+    const int32_t L = d.L;
+    const int32_t rh = d.rows >> 1;   // one row of every +- pair
+    const uint32_t N = static_cast<uint32_t>(d.N);
+    const uint32_t ms = map_shift(N, map_words);
+    const int32_t mwords = static_cast<int32_t>((((N - 1u) >> ms) >> 5) + 1u + MAP_PAD);
+    const uint32_t *occ = reinterpret_cast<const uint32_t *>(ws + d.off_occ);
+    const uint32_t *prefix = reinterpret_cast<const uint32_t *>(ws + d.off_prefix);
+    const NzOffset *tab = tabs + d.tab;
+    for (int32_t w = t; w < mwords; w += nt) hook_map[w] = 0u;
+    for (int32_t k = t; k < rh; k += nt) rows[k] = tab[k];
+    __syncthreads();
+    for (int32_t k = t; k < n0; k += nt) {
+        const uint32_t b = prefix[k] >> ms;
+        atomicOr(&hook_map[1 + (b >> 5)], 1u << (b & 31));
+    }
+    __syncthreads();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    HookEdges ed{reinterpret_cast<int32_t *>(ws + d.off_parc), reinterpret_cast<const uint2 *>(ws + d.off_wrec), ebuf_i[wave],
+                 ebuf_p[wave], 0, lane_id()};
+    const int32_t ib = x * nt + static_cast<int32_t>(wave) * 64;
+    const uint32_t words = ((N + 63u) >> 6) << 1;
+    if (ms == 0) hook_map_sites<PER, true>(ed, hook_map, 0u, rows, rh, tab, occ, prefix, ib, bx * nt, n0, L, d.magic, words);
+    else hook_map_sites<PER, false>(ed, hook_map, ms, rows, rh, tab, occ, prefix, ib, bx * nt, n0, L, d.magic, words);
 }
 
 __device__ __forceinline__ uint32_t border_flags(uint32_t s, uint32_t L, uint64_t magic)
@@ -1293,7 +1496,6 @@ constexpr int32_t NZ_NONE = static_cast<int32_t>(0x80000000u);   // (a root word
 constexpr int32_t BAND_NODE = 0x40000000, BLK_LINKED = 0x40000000;
 __device__ __forceinline__ int32_t node_id(int32_t v) { return (v & LIST_NODE) ? v & ~BLK_LINKED : v; }
 constexpr uint32_t BLK_SMALL_MAP = 4096;  // words of the largest map that leaves room for several workgroups per CU
-constexpr uint32_t BLK_MAP_PAD = 3;       // map words outside the lattice: one before, two behind
 static_assert(BLK_MAXROWS % BLK_CHUNK == 0, "whole chunks");
 static_assert(BLK_EDGES >= 892, "a block of one site always fits");
 
@@ -1303,13 +1505,6 @@ __device__ __forceinline__ int32_t site_of(uint32_t pc, int32_t L)
            L * (static_cast<int32_t>((pc >> 6) & 63) +
                 L * (static_cast<int32_t>((pc >> 12) & 63) +
                      L * (static_cast<int32_t>((pc >> 18) & 63) + L * static_cast<int32_t>(pc >> 24))));
-}
-
-// The steps every axis allows from the site with packed coordinates pc.
-__device__ __forceinline__ uint32_t allowed_of(uint32_t pc, int32_t L)
-{
-    return allowed_axis(pc & 63, L) | (allowed_axis((pc >> 6) & 63, L) << 5) | (allowed_axis((pc >> 12) & 63, L) << 10) |
-           (allowed_axis((pc >> 18) & 63, L) << 15) | (allowed_axis(pc >> 24, L) << 20);
 }
 
 // Accesses shared by the waves of one workgroup.
@@ -2213,14 +2408,6 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
     return res;
 }
 
-// The map's shift for a lattice of N sites when map_words words are there.
-__device__ __forceinline__ uint32_t map_shift(uint32_t N, uint32_t map_words)
-{
-    uint32_t ms = 0;
-    while ((((N - 1u) >> ms) >> 5) + 1u + BLK_MAP_PAD > map_words) ++ms;
-    return ms;
-}
-
 // Persistent: every workgroup pops samples (longest first) until the queue is
 // empty.  PER: periodic coordinates.
 template <typename C>
@@ -2274,7 +2461,7 @@ __global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, Sweep
         // than the bitset
         const uint32_t mwords = (((N - 1u) >> m.mshift) >> 5) + 1u;
         const bool by_list = static_cast<uint32_t>(r) < m.occ_words;
-        for (uint32_t w = static_cast<uint32_t>(t); w < mwords + BLK_MAP_PAD; w += NT) {
+        for (uint32_t w = static_cast<uint32_t>(t); w < mwords + MAP_PAD; w += NT) {
             const bool inner = w >= 1u && w <= mwords;
             blk_map[w] = (!by_list && m.mshift == 0 && inner) ? m.occ[w - 1u] : 0u;
         }
@@ -2503,9 +2690,18 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
 
 int32_t keys_sites_per_block() { return KEYS_SITES_PER_BLOCK; }
 
+// Words of the map of the hook of sparse lists, and whether a list of n0 sites of
+// N counts as one: under one set bit in 32 of the map.
+constexpr uint32_t kHookMapWords = 136 * 256;
+
+bool hook_map_fits(int64_t N, int64_t n0)
+{
+    return (n0 << (5 + map_shift(static_cast<uint32_t>(N), kHookMapWords))) < N;
+}
+
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
                           const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
-                          hipStream_t st, hipEvent_t *ev)
+                          int32_t map_N, int cus, hipStream_t st, hipEvent_t *ev)
 {
     if (nlist <= 0) return hipSuccess;
     // workgroups per sample: a hook workgroup takes 2048 sites of a large list
@@ -2533,7 +2729,19 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
         mark(4);
         return hipGetLastError();
     }
-    if (periodic)
+    if (map_N > 0) {
+        auto k = periodic ? nz_hook_map_kernel<true> : nz_hook_map_kernel<false>;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 static_cast<int>(kHookMapWords * 4));
+        if (e != hipSuccess) return e;
+        const uint32_t words = std::min(kHookMapWords, ((static_cast<uint32_t>(map_N) - 1u) >> 5) + 1u + MAP_PAD);
+        // a few workgroups per CU over all samples, of up to 1024 sites each
+        const int32_t nt = static_cast<int32_t>(std::max(64, std::min(1024, (max_sites + 63) / 64 * 64)));
+        const int32_t most = std::max(1, (max_sites + nt - 1) / nt);
+        const int32_t bx = std::max(1, std::min(most, 4 * cus / nlist));
+        hipLaunchKernelGGL(k, dim3(static_cast<uint32_t>(bx) * slots8), dim3(static_cast<uint32_t>(nt)), words * 4u, st, desc, list,
+                           nlist, bx, words, tabs, ws, state);
+    } else if (periodic)
         hipLaunchKernelGGL(nz_hook_kernel<true>, dim3(static_cast<uint32_t>(bx_hook) * slots8), dim3(256), 0, st, desc, list,
                            nlist, bx_hook, tabs, ws, state);
     else
@@ -2612,7 +2820,7 @@ static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cu
 template <int MODE, bool PER>
 static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint32_t max_N, size_t lds_per_wg, hipStream_t st)
 {
-    const uint32_t exact = ((max_N - 1u) >> 5) + 1u + BLK_MAP_PAD;
+    const uint32_t exact = ((max_N - 1u) >> 5) + 1u + MAP_PAD;
     if (exact <= BLK_SMALL_MAP || MODE == BLK_SMAX) {
         a.map_words = std::min(exact, BLK_SMALL_MAP);
         return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);

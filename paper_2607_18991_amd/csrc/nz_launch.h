@@ -35,9 +35,10 @@ int32_t keys_sites_per_block();
 // ev (may be NULL): five events recorded before the hook, after it, after
 // compress and after the flag pass, the fifth with the fourth (there is no
 // separate expand pass).
+bool hook_map_fits(int64_t N, int64_t n0);
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
                           const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
-                          hipStream_t st, hipEvent_t *ev = nullptr);
+                          int32_t map_N, int cus, hipStream_t st, hipEvent_t *ev = nullptr);
 
 // out[0..w) += sum over the chunk's finished samples 0..nsamp-1 of their S_max windows.
 hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsamp, int32_t w, const uint8_t *ws,
