@@ -1078,6 +1078,13 @@ __device__ __forceinline__ uint32_t border_flags(uint32_t s, uint32_t L, uint64_
 // an entry another thread has already pointed at its root with a non-root
 // ancestor.  Roots never change in this kernel, so a walk stops at an entry that
 // points to itself or already holds a root word.
+//
+// What bounds it is the latency of the walks, so a thread has WALKS of them under
+// way (1000 samples of L = 16, zone 1: one 0.91 ms, two 0.88, four 0.79, eight
+// 0.83), and so in the flag pass below (0.77 without the read before the atomic; with it one
+// at a time 0.66, four 0.57, eight 0.68).
+constexpr int WALKS = 4;
+
 __global__ __launch_bounds__(256) void nz_compress_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
                                                           int32_t nlist, int32_t bx, uint8_t *__restrict__ ws,
                                                           NzState *__restrict__ state)
@@ -1091,19 +1098,35 @@ __global__ __launch_bounds__(256) void nz_compress_kernel(const NzSample *__rest
     const uint32_t L = static_cast<uint32_t>(d.L);
     int32_t *par = reinterpret_cast<int32_t *>(ws + d.off_parc);
     const uint32_t *prefix = reinterpret_cast<const uint32_t *>(ws + d.off_prefix);
-    for (int32_t k = x * 256 + static_cast<int32_t>(threadIdx.x); k < n0; k += bx * 256) {
-        int32_t r = k;
-        int32_t p = ld_w(&par[r]);
-        while (p >= 0 && (p & (LIST_NODE - 1)) != r) {
-            r = p & (LIST_NODE - 1);   // (an entry already pointed at its root is a node id)
-            p = ld_w(&par[r]);
+    const int32_t step = bx * 256;
+    for (int32_t k0 = x * 256 + static_cast<int32_t>(threadIdx.x); k0 < n0; k0 += WALKS * step) {
+        int32_t r[WALKS], p[WALKS];
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q) {
+            r[q] = min(k0 + q * step, n0 - 1);   // (past the end: the last entry, not stored)
+            p[q] = ld_w(&par[r[q]]);
         }
-        if (r == k) {
-            const uint32_t fl = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
-            st_w(&par[k], static_cast<int32_t>(NZ_ROOT | fl | (d.smax_mode ? 1u : 0u)));
-            if (fl == NZ_FLAGS) state[sid].status = NZ_ST_BACKOFF;   // L = 1: one site spans
-        } else {
-            st_w(&par[k], LIST_NODE | r);
+        for (bool more = true; more;) {
+            more = false;
+#pragma unroll
+            for (int q = 0; q < WALKS; ++q)
+                if (p[q] >= 0 && (p[q] & (LIST_NODE - 1)) != r[q]) {
+                    r[q] = p[q] & (LIST_NODE - 1);   // (an entry already pointed at its root is a node id)
+                    p[q] = ld_w(&par[r[q]]);
+                    more = true;
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q) {
+            const int32_t k = k0 + q * step;
+            if (k >= n0) continue;
+            if (r[q] == k) {
+                const uint32_t fl = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
+                st_w(&par[k], static_cast<int32_t>(NZ_ROOT | fl | (d.smax_mode ? 1u : 0u)));
+                if (fl == NZ_FLAGS) state[sid].status = NZ_ST_BACKOFF;   // L = 1: one site spans
+            } else {
+                st_w(&par[k], LIST_NODE | r[q]);
+            }
         }
     }
 }
@@ -1116,7 +1139,7 @@ __global__ __launch_bounds__(256) void nz_compress_kernel(const NzSample *__rest
 //
 // A size for every cluster would take an atomic per member, and lattice entries
 // a scattered 4-byte write per site: for 1000 samples of L = 16, zone 1 this
-// pass took 3.9 ms with both, 2.1 with the lattice entries alone, and takes 0.6
+// pass took 3.9 ms with both, 2.1 with the lattice entries alone, and takes 0.57
 // with the flags alone.  The sweep finds a prefilled site's list entry from its
 // bitset word instead, and counts the members of the spanning cluster.
 __global__ __launch_bounds__(256) void nz_accum_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
@@ -1139,16 +1162,31 @@ __global__ __launch_bounds__(256) void nz_accum_kernel(const NzSample *__restric
     int32_t *parc = reinterpret_cast<int32_t *>(ws + d.off_parc);
     const uint32_t *prefix = reinterpret_cast<const uint32_t *>(ws + d.off_prefix);
     bool spans = false;
-    for (int32_t k = x * 256 + static_cast<int32_t>(threadIdx.x); k < n0; k += bx * 256) {
-        const uint32_t fl = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
-        if (!fl && !sizes) continue;
-        const int32_t r = parc[k];
-        if (r < 0) continue;   // a root: its word holds its own flags and size
-        uint32_t *root = reinterpret_cast<uint32_t *>(&parc[r & (LIST_NODE - 1)]);
-        if (sizes) atomicAdd(root, 1u);
-        if (fl) {
-            const uint32_t old = atomicOr(root, fl);
-            spans = spans || ((old | fl) & NZ_FLAGS) == NZ_FLAGS;
+    const int32_t step = bx * 256;
+    for (int32_t k0 = x * 256 + static_cast<int32_t>(threadIdx.x); k0 < n0; k0 += WALKS * step) {
+        uint32_t fl[WALKS], had[WALKS];
+        int32_t r[WALKS];   // (< 0: nothing to add, or a root, whose word holds its own flags and size)
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q) {
+            const int32_t k = min(k0 + q * step, n0 - 1);
+            fl[q] = d.periodic ? 0u : border_flags(prefix[k], L, d.magic);
+        }
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q) r[q] = k0 + q * step < n0 && (fl[q] || sizes) ? parc[k0 + q * step] : -1;
+        // (most roots have the flag already: a read costs less than an atomic, and a
+        // stale one only costs the atomic)
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q)
+            had[q] = r[q] >= 0 && fl[q] ? static_cast<uint32_t>(ld_w(&parc[r[q] & (LIST_NODE - 1)])) : 0u;
+#pragma unroll
+        for (int q = 0; q < WALKS; ++q) {
+            if (r[q] < 0) continue;
+            uint32_t *root = reinterpret_cast<uint32_t *>(&parc[r[q] & (LIST_NODE - 1)]);
+            if (sizes) atomicAdd(root, 1u);
+            if (fl[q] & ~had[q]) {
+                const uint32_t old = atomicOr(root, fl[q]);
+                spans = spans || ((old | fl[q]) & NZ_FLAGS) == NZ_FLAGS;
+            }
         }
     }
     if (spans && !sizes) state[sid].status = NZ_ST_BACKOFF;
