@@ -18,7 +18,7 @@
 //                      and adds whole buckets of its band at a time, merging a
 //                      block's sites and the clusters they touch in LDS; the
 //                      root words' two border flags (or a winding loop) decide
-//                      spanning, and the block in which it happens is bisected.
+//                      spanning, and n* is found within the block in which it happens.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1491,7 +1491,7 @@ __global__ __launch_bounds__(256) void nz_accumw_kernel(const NzSample *__restri
 // accumulate, so when no cluster spans after all the sites of the block none
 // spanned after any of them, and the block is committed as a whole.  In the
 // block in which a cluster spans, the smallest T such that the block's first T
-// sites in (key, site) order span is found by bisection on that small graph,
+// sites in (key, site) order span is found on that small graph,
 // without touching memory again: n* is the count before the block plus T, the
 // mass the size of the cluster of the T-th site.  A block that does not fit
 // the tables is undone, sorted, and added in halves (one site has at most 892
@@ -1505,7 +1505,7 @@ __global__ __launch_bounds__(256) void nz_accumw_kernel(const NzSample *__restri
 // (L = 16, zone 1 x 1000, prefilled): a block of up to 512 sites takes 16 us --
 // marks 0.7, checks 1.9, parents and roots 9.8, unions 1.4, sizes and flags 0.9,
 // write-back 0.9 -- against 24 us for 64 sites by one wave in the sweep this one
-// replaced; ranks 7 and bisection 20 us once per sample.  With separate tables
+// replaced; ranks 7 and the smallest T 8 us once per sample.  With separate tables
 // for a block's sites (marked in memory) and for the earlier roots the kernel
 // took 2.39 ms for this batch and takes 2.13, at L = 24 6.59 and 5.29.  37
 // samples of L = 13, z = 380 took 1.56 ms and take 0.11 ms, the periodic L = 12
@@ -1584,10 +1584,11 @@ struct BlkCfg {
     // slots: a full block, the roots of one site's 892 neighbours
     static constexpr uint32_t RS = B > 256 ? 2048 : 1024;
     static constexpr uint32_t SHIFT = B > 256 ? 21 : 22;
-    // the ranks of a bisection go where the map was, if that is large enough
+    // the ranks and times within a block go where the map was, if that is large enough
     static constexpr bool OWN_SCRATCH = NT == 256;
-    // words: keys of the sites, 16-bit ranks of the slots; SMAX: joining times of the slots
-    static constexpr uint32_t SCRATCH = MODE == 2 ? RS : B + RS / 2;
+    // words: keys of the sites, 16-bit ranks of the slots, spanning: joining times of
+    // the slots; largest cluster: these alone
+    static constexpr uint32_t SCRATCH = MODE == 2 ? RS : B + RS / 2 + (MODE == 0 ? RS : 0);
     static_assert(B <= NT, "thread t loads entry t of a block");
     static_assert(RS % NT == 0 && RS >= B + 512 && RS >= 893 && RS <= 2048, "whole slots per thread; node numbers of 11 bits");
     static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
@@ -2047,6 +2048,33 @@ __device__ __forceinline__ int blk_rank(BlkLds<C> &S, uint32_t *keys, const NzSa
     return rank;
 }
 
+// joins[n] of every node: the least time, over all paths of pairs from the nodes
+// that start with one, by which the path is there, a node from time_of(n) on.
+// (barriers inside, one at the end)
+template <typename C, typename Time>
+__device__ __forceinline__ void blk_relax(BlkLds<C> &S, uint32_t *joins, int ne, Time &&time_of)
+{
+    const int t = static_cast<int>(threadIdx.x);
+    for (;;) {
+        __syncthreads();
+        if (t == 0) S.flag = 0;
+        __syncthreads();
+        bool changed = false;
+        for (int e = t; e < ne; e += C::NT) {
+            const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
+            const uint32_t ju = ld_g(&joins[u]), jv = ld_g(&joins[v]);
+            const uint32_t there = max(time_of(u), time_of(v));
+            const uint32_t a = max(ju, there), b = max(jv, there);
+            if (a < jv) atomicMin(&joins[v], a);
+            if (b < ju) atomicMin(&joins[u], b);
+            changed = changed || a < jv || b < ju;
+        }
+        if (changed) S.flag = 1;
+        __syncthreads();
+        if (!S.flag) break;
+    }
+}
+
 enum { BLK_COMMITTED = 0, BLK_SPANS = 1, BLK_NOFIT = 2 };
 
 // Adds the sites S.pcs[lo .. lo + len) (1 <= len <= B; sorted: in (key, site)
@@ -2263,24 +2291,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
                         const bool first = curve[k] < BLK_CURVES && static_cast<uint32_t>(S.member[curve[k]]) == node_of(k);
                         joins[node_of(k)] = first ? time_of(node_of(k)) : BLK_EMPTY;
                     }
-                    for (;;) {
-                        __syncthreads();
-                        if (t == 0) S.flag = 0;
-                        __syncthreads();
-                        bool changed = false;
-                        for (int e = t; e < ne; e += C::NT) {
-                            const uint32_t u = S.et[e] & 0xFFFFu, v = S.et[e] >> 16;
-                            const uint32_t ju = ld_g(&joins[u]), jv = ld_g(&joins[v]);
-                            const uint32_t there = max(time_of(u), time_of(v));
-                            const uint32_t a = max(ju, there), b = max(jv, there);
-                            if (a < jv) atomicMin(&joins[v], a);
-                            if (b < ju) atomicMin(&joins[u], b);
-                            changed = changed || a < jv || b < ju;
-                        }
-                        if (changed) S.flag = 1;
-                        __syncthreads();
-                        if (!S.flag) break;
-                    }
+                    blk_relax<C>(S, joins, ne, time_of);
 #pragma unroll
                     for (int k = 0; k < NODES; ++k)
                         if (curve[k] < BLK_CURVES) {
@@ -2370,8 +2381,13 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
             const uint32_t own = act ? S.spos[t] : 0u;   // this position's node
             int myrank = t;
             if (len > 1) {
-                // 5. the smallest T: bisection over the block's first T sites, each
-                //    trial a connected-components pass over the pairs among them.
+                // 5. the smallest T.  Spanning: the least time by which a path joins a
+                //    node on the low border to one on the high border.  Wrapping: by
+                //    bisection over the block's first T sites.  A trial is a connected-
+                //    components pass over the pairs among the first so many sites; the
+                //    last one gives the cluster.  (Nine trials took 20 to 27 us per
+                //    sample: 1000 samples of L = 16, zones 1-7, 0.45 ms, and 0.38
+                //    with the paths.)
                 //    ranks: of every node, 0 for earlier roots, 1 + rank for sites.
                 uint16_t *ranks = reinterpret_cast<uint16_t *>(scratch + C::B);
                 if (!sorted) myrank = blk_rank<C>(S, scratch, d, len, b0, b1);   // (sorted: positions are ranks)
@@ -2397,12 +2413,26 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
                     });
                     return gather();
                 };
-                int none = 0;   // the first `none` sites do not span, the first T do
-                T = len;
-                while (T - none > 1) {
-                    const int mid = (none + T) / 2;
-                    if (trial(mid)) T = mid;
-                    else none = mid;
+                if constexpr (MODE == BLK_SPAN) {
+                    uint32_t *joins = scratch + C::B + C::RS / 2;
+#pragma unroll
+                    for (int k = 0; k < NODES; ++k)
+                        joins[node_of(k)] = live[k] && (word0[k] & NZ_FLO) ? since[k] : BLK_EMPTY;
+                    if (t == 0) S.total = BLK_EMPTY;
+                    blk_relax<C>(S, joins, ne, [&](uint32_t n) { return static_cast<uint32_t>(ranks[n]); });
+#pragma unroll
+                    for (int k = 0; k < NODES; ++k)
+                        if (live[k] && (word0[k] & NZ_FHI)) atomicMin(&S.total, joins[node_of(k)]);
+                    __syncthreads();
+                    T = static_cast<int>(S.total);
+                } else {
+                    int none = 0;   // the first `none` sites do not span, the first T do
+                    T = len;
+                    while (T - none > 1) {
+                        const int mid = (none + T) / 2;
+                        if (trial(mid)) T = mid;
+                        else none = mid;
+                    }
                 }
                 trial(T);
             }
@@ -2454,7 +2484,7 @@ __global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, Sweep
     constexpr int MODE = C::MODE, NT = C::NT, B = C::B;
     extern __shared__ uint32_t blk_map[];
     __shared__ BlkLds<C> S;
-    uint32_t *scratch = C::OWN_SCRATCH ? S.scratch : blk_map;   // (a sample that bisects needs its map no more)
+    uint32_t *scratch = C::OWN_SCRATCH ? S.scratch : blk_map;   // (a sample that spans needs its map no more)
     const int t = static_cast<int>(threadIdx.x);
     for (;;) {
         if (t == 0) S.claim = atomicAdd(a.qhead, 1);
