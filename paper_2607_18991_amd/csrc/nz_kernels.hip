@@ -14,7 +14,7 @@
 //                      root and adds its size and border flags to the root
 //                      word); a state that already spans is flagged for
 //                      backoff;
-//   nz_block_kernel    persistent: every workgroup pops a sample (longest first)
+//   nz_sweep_kernel    persistent: every workgroup pops a sample (longest first)
 //                      and adds whole buckets of its band at a time, merging a
 //                      block's sites and the clusters they touch in LDS; the
 //                      root words' two border flags (or a winding loop) decide
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(KEYS_THREADS) void nz_keys_kernel(const NzSample *_
 // 200, zones 1-6 prefilled, L = 16, 0.81 / 0.88 for 1000.  max_nb: words of the
 // counters (an even number; every sample of the launch has at most so many
 // buckets).
-__global__ __launch_bounds__(KEYS_LOCAL_THREADS, 8) void nz_keys_local_kernel(const NzSample *__restrict__ desc, int32_t first,
+__global__ __launch_bounds__(KEYS_LOCAL_THREADS, 8) void nz_keys_kernel_local(const NzSample *__restrict__ desc, int32_t first,
                                                                               int32_t max_nb, uint8_t *__restrict__ ws,
                                                                               NzState *__restrict__ state)
 {
@@ -1027,7 +1027,7 @@ __device__ __forceinline__ void hook_map_sites(HookEdges &ed, const uint32_t *ma
 // map's LDS takes away (zones 1-2, 4%, 1.28 / 1.32; zone 1, 15%, 3.1 / 3.4); the
 // line lies at one bit in 32.
 template <bool PER>
-__global__ __launch_bounds__(1024) void nz_hook_map_kernel(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
+__global__ __launch_bounds__(1024) void nz_hook_kernel_map(const NzSample *__restrict__ desc, const int32_t *__restrict__ list,
                                                            int32_t nlist, int32_t bx, uint32_t map_words,
                                                            const NzOffset *__restrict__ tabs, uint8_t *__restrict__ ws,
                                                            NzState *__restrict__ state)
@@ -2483,7 +2483,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
 // Persistent: every workgroup pops samples (longest first) until the queue is
 // empty.  PER: periodic coordinates.
 template <typename C>
-__global__ __launch_bounds__(C::NT, 4) void nz_block_kernel(NzSweepArgs a, SweepOut out)
+__global__ __launch_bounds__(C::NT, 4) void nz_sweep_kernel(NzSweepArgs a, SweepOut out)
 {
     constexpr int MODE = C::MODE, NT = C::NT, B = C::B;
     extern __shared__ uint32_t blk_map[];
@@ -2744,10 +2744,10 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
     const size_t words = (static_cast<size_t>(max_nb) + 1) / 2 * 2;
     const size_t lds = 4 * (words + 3 * static_cast<size_t>(waves) * KEYS_BQ);
     if (!list && max_nb > 0 && lds <= kKeysLds && static_cast<int64_t>(count) * waves >= kKeysLocalWaves) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(nz_keys_local_kernel),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(nz_keys_kernel_local),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kKeysLds));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(nz_keys_local_kernel, dim3(static_cast<uint32_t>(count)), dim3(static_cast<uint32_t>(64 * waves)), lds,
+        hipLaunchKernelGGL(nz_keys_kernel_local, dim3(static_cast<uint32_t>(count)), dim3(static_cast<uint32_t>(64 * waves)), lds,
                            st, desc, first, static_cast<int32_t>(words), ws, state);
         return hipGetLastError();
     }
@@ -2802,7 +2802,7 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
         return hipGetLastError();
     }
     if (map_N > 0) {
-        auto k = periodic ? nz_hook_map_kernel<true> : nz_hook_map_kernel<false>;
+        auto k = periodic ? nz_hook_kernel_map<true> : nz_hook_kernel_map<false>;
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  static_cast<int>(kHookMapWords * 4));
         if (e != hipSuccess) return e;
@@ -2864,7 +2864,7 @@ static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cu
 {
     using C = BlkCfg<MODE, PER, NT, B>;
     if (!C::OWN_SCRATCH && a.map_words < C::SCRATCH) return hipErrorInvalidValue;
-    auto k = nz_block_kernel<C>;
+    auto k = nz_sweep_kernel<C>;
     const size_t lds = static_cast<size_t>(a.map_words) * 4u;
     if (lds + sizeof(BlkLds<C>) > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
