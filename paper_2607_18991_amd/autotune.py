@@ -1,13 +1,13 @@
-"""Autotuner of the persistent sweep: for every (L, z-class) it times the
-candidate launch shapes on the GPU -- where the per-sample state lives (HBM,
-occupancy bitset in LDS, bitset and parents in LDS), waves per workgroup,
-resident waves per SIMD, one site or 64 sites per wave step, and whether the
-HBM-resident sweep checks the bitset summary -- and keeps the fastest in a
-JSON table shipped with the package.  Tuning never changes an
-output (the library guarantees it and the tests check it); it only moves time.
+"""Autotuner of the persistent sweep.  For a named batch it times the split into
+two groups side by side (split_z) and the prefill depth k; for every (L,
+z-class) the launch-shape knobs of nz_tuning (state residency, waves per
+workgroup and SIMD, sites per step, bitset summary).  The sweep has one shape
+for all values of the latter, which are accepted as hints, so their times
+differ by noise; the former move time.  The fastest of each goes into a JSON
+table shipped with the package.  Tuning never changes an output (the library
+guarantees it and the tests check it).
 
-z-classes follow the offset chunks the kernels are compiled for: z <= 64, 128,
-256, 512, 892.
+z-classes: z <= 64, 128, 256, 512, 892.
 
     python -m paper_2607_18991_amd.autotune --out tuning_table.json
 
