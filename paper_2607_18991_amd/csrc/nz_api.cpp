@@ -1213,20 +1213,17 @@ NZ_API int nz_last_batch_timing(double ms[6])
 }
 
 // ---------------------------------------------------------------------------
-// Two groups at once.  Narrow neighbourhoods (z <= 64) spend their sweep in
-// long chains of dependent 64-site steps that keep few waves busy; a batch that
-// also holds wider ones runs the two groups side by side (the wide group on a
-// second host thread and stream), so that one group's sweep overlaps the
-// other's keys and labelling.  Each group gets its own share of the workspace.
+// Two groups at once.  Narrow neighbourhoods (z <= 64) spend their time in the
+// latency of labelling and sweep; a batch that also holds wider ones runs the two
+// groups side by side (the wide group on a second host thread and stream), so that
+// one group's sweep and host round trips overlap the other's keys and labelling.
+// Each group gets its own share of the workspace.  7 compact neighbourhoods,
+// prefilled, side by side / as one group: L = 16 x 1000 20.4 / 21.5 ms, L = 24 x 200
+// 33.3 / 34.2, L = 8 1.73 / 1.89; plain L = 16 40.3 / 40.4.
 
-// (256 rather than 512: the L = 24 table of 27 masks x 200 has 400 narrow
-// samples, and split it runs 163-167 ms instead of 170-174 learned, 333 ms
-// instead of 345-404 plain)
-constexpr int64_t kSplitMinSamples = 256;
-// widest neighbourhood of the first group (L = 16, 7 compact masks x 1000,
-// learned: 47.0 ms with z <= 64, 47.5 with z <= 130, 49.9 with z <= 220;
-// with the keys launches keeping their slots: 43.0 ms with z <= 64, 44.1 with
-// z <= 10, 45.7 with z <= 130)
+constexpr int64_t kSplitMinSamples = 256;   // on both sides
+// widest neighbourhood of the first group (L = 16, 7 compact x 1000, prefilled:
+// z <= 10 18.1 ms, 64 17.8, 130 17.8, 242 17.8, 340 18.2)
 constexpr int32_t kSplitZ = 64;
 
 struct SplitPlan {
