@@ -2924,8 +2924,15 @@ static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cu
     return hipGetLastError();
 }
 
-// Small maps (up to L = 10): several workgroups of 256 threads share a CU.
-// Larger ones leave room for one workgroup per CU, of 1024 threads.
+// Small maps (up to L = 10): several workgroups of 256 threads share a CU.  Exact
+// maps of which a CU holds two (L = 11 to 13): two workgroups of 512 threads, if
+// there are samples for both, so that one sample's reads cover the other's
+// barriers.  Larger ones leave room for one workgroup per CU, of 1024 threads.
+// Sweep kernel, 1000 samples, one / two workgroups per CU: zone 1 plain, L = 11
+// 2.42 / 1.71 ms, L = 12 3.74 / 2.64; prefilled, L = 12, zone 1 0.77 / 0.68, zones
+// 1-7 0.27 / 0.24, L = 13, zone 1 1.04 / 0.94.  Two maps that are not exact lose
+// by the reads behind them: L = 16, zones 1-2 prefilled 0.85 / 1.02 ms, 1-7 0.39 /
+// 0.53, L = 24 zones 1-2 2.40 / 3.44 (300 samples).
 template <int MODE, bool PER>
 static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint32_t max_N, size_t lds_per_wg, hipStream_t st)
 {
@@ -2935,6 +2942,10 @@ static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint
         return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);
     }
     if constexpr (MODE != BLK_SMAX) {
+        if (a.nqueue > cus && 2 * (static_cast<size_t>(exact) * 4 + sizeof(BlkLds<BlkCfg<MODE, PER, 512, 512>>)) <= lds_per_wg) {
+            a.map_words = exact;
+            return launch_block_n<MODE, PER, 512, 512>(a, o, cus, st);
+        }
         a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<BlkCfg<MODE, PER, 1024, 512>>)) / 4));
         return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
     }
