@@ -827,23 +827,24 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             std::vector<uint8_t> level(n, 0);   // in-chunk backoffs of every sample
             if (nlist > 0) {
                 for (size_t g = 0; g < pre.size();) {
-                    const int32_t most = parts[pre[g]].s.prefix_cap;
                     const bool map = hook_map(parts[pre[g]]);
-                    int32_t count = 0, map_N = 0;
+                    int32_t count = 0, map_N = 0, most = 0;
                     size_t e = g;
                     while (e < pre.size() && hook_map(parts[pre[e]]) == map) {
-                        // the samples of one size class, if a launch of their own saves
-                        // enough empty workgroups
+                        // the samples of one size class (in no order within it), if a
+                        // launch of their own saves enough empty workgroups
                         size_t c = e;
-                        int32_t samples = 0;
+                        int32_t samples = 0, largest = 0;
                         const int cls = prefill_group(parts[pre[e]].s.prefix_cap);
                         int32_t N = 0;
                         while (c < pre.size() && hook_map(parts[pre[c]]) == map && prefill_group(parts[pre[c]].s.prefix_cap) == cls) {
                             N = std::max(N, static_cast<int32_t>(pow5(parts[pre[c]].p.L)));
+                            largest = std::max(largest, parts[pre[c]].s.prefix_cap);
                             samples += parts[pre[c++]].count;
                         }
-                        const int64_t empty = static_cast<int64_t>(samples) * (most - parts[pre[e]].s.prefix_cap) / 1024;
+                        const int64_t empty = static_cast<int64_t>(samples) * (most - largest) / 1024;
                         if (e > g && empty > kEmptyWgs) break;
+                        most = std::max(most, largest);
                         count += samples;
                         if (map) map_N = std::max(map_N, N);
                         e = c;
