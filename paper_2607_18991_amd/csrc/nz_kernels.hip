@@ -1817,6 +1817,9 @@ struct BlkMem {
 // of the map; 3.4 offsets of the widest neighbourhood share a row.
 // EXACT: the map is the occupation (mshift == 0); else a set map bit sends the
 // check to the bitset.  The reads of an item's rows are issued together.
+// More pairs than the list holds end the scan: a block of a small dense lattice
+// has ten times as many, and finding them all is most of its time (12000 samples
+// of L = 3, zones 1-7: 2.41 ms to the end, 0.78 so; L = 5 periodic 4.17, 2.03).
 template <bool EXACT, typename C>
 __device__ __forceinline__ void blk_scan(BlkLds<C> &S, const BlkMem<C::MODE> &m, int nrows, int32_t L, int lo, int len)
 {
@@ -1901,6 +1904,7 @@ __device__ __forceinline__ void blk_scan(BlkLds<C> &S, const BlkMem<C::MODE> &m,
                 int32_t base = 0;
                 if (lane == 0) base = atomicAdd(&S.ecnt, static_cast<int32_t>(__popcll(mk)));
                 base = __builtin_amdgcn_readfirstlane(base);
+                if (base >= BLK_EDGES) return;   // (uniform) the pairs do not fit: the block is added in halves
                 if (mask) {
                     const int bit = __builtin_ctz(mask);
                     mask &= mask - 1u;
