@@ -2901,15 +2901,18 @@ hipError_t launch_winsum(const NzSample *desc, const NzState *state, int32_t nsa
 }
 
 template <int MODE, bool PER, int NT, int B>
-static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cus, hipStream_t st)
+static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cus, size_t lds_per_wg, hipStream_t st)
 {
     using C = BlkCfg<MODE, PER, NT, B>;
+    static_assert(!C::OWN_SCRATCH || sizeof(BlkLds<C>) + BLK_SMALL_MAP * 4 <= 65536, "small maps need no limit of their own");
     if (!C::OWN_SCRATCH && a.map_words < C::SCRATCH) return hipErrorInvalidValue;
     auto k = nz_sweep_kernel<C>;
     const size_t lds = static_cast<size_t>(a.map_words) * 4u;
-    if (lds + sizeof(BlkLds<C>) > 65536) {
+    if (!C::OWN_SCRATCH) {
+        // the limit is the kernel's, not this launch's: always what a workgroup can
+        // have, so that no other thread's smaller lattice lowers it before the launch
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           static_cast<int>(lds));
+                                           static_cast<int>(lds_per_wg - sizeof(BlkLds<C>)));
         if (e != hipSuccess) return e;
     }
     // workgroups per CU for this much LDS (one architecture: fixed for the process)
@@ -2943,15 +2946,15 @@ static hipError_t launch_block_t(NzSweepArgs a, const SweepOut &o, int cus, uint
     const uint32_t exact = ((max_N - 1u) >> 5) + 1u + MAP_PAD;
     if (exact <= BLK_SMALL_MAP || MODE == BLK_SMAX) {
         a.map_words = std::min(exact, BLK_SMALL_MAP);
-        return launch_block_n<MODE, PER, 256, 256>(a, o, cus, st);
+        return launch_block_n<MODE, PER, 256, 256>(a, o, cus, lds_per_wg, st);
     }
     if constexpr (MODE != BLK_SMAX) {
         if (a.nqueue > cus && 2 * (static_cast<size_t>(exact) * 4 + sizeof(BlkLds<BlkCfg<MODE, PER, 512, 512>>)) <= lds_per_wg) {
             a.map_words = exact;
-            return launch_block_n<MODE, PER, 512, 512>(a, o, cus, st);
+            return launch_block_n<MODE, PER, 512, 512>(a, o, cus, lds_per_wg, st);
         }
         a.map_words = std::min<uint32_t>(exact, static_cast<uint32_t>((lds_per_wg - sizeof(BlkLds<BlkCfg<MODE, PER, 1024, 512>>)) / 4));
-        return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, st);
+        return launch_block_n<MODE, PER, 1024, 512>(a, o, cus, lds_per_wg, st);
     }
 }
 

@@ -1,0 +1,39 @@
+"""The host side of the library with a stand-in for the HIP runtime (not GPU)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import host_lib
+
+pytestmark = pytest.mark.skipif(host_lib.hipcc() is None, reason="hipcc missing")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return host_lib.build(str(tmp_path_factory.mktemp("host")))
+
+
+def _ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+def sweep(lib, L, mask, samples, boundary=0):
+    ns = np.zeros(samples, dtype=np.int32)
+    return lib.nz_sweep(L, mask, boundary, samples, 1, _ptr(ns), None)
+
+
+@pytest.mark.parametrize("boundary", [0, 1])
+def test_lds_limit_is_the_same_for_every_launch_of_a_kernel(lib, boundary):
+    """The limit belongs to the kernel, not to a launch: were it that of the launch at
+    hand, a second thread with a smaller lattice could lower it between another's
+    setting and its launch."""
+    lib.fake_reset()
+    limits = {}
+    for L, samples in ((11, 300), (12, 300), (14, 2), (15, 2), (16, 2), (18, 2), (14, 2)):
+        assert sweep(lib, L, 0x01, samples, boundary) == 0, lib.nz_last_error()
+    for name, lds, limit in host_lib.launches(lib):
+        assert lds <= limit, (name, lds, limit)
+        if lds > 16384 and "nz_sweep_kernel" in name:
+            limits.setdefault(name, set()).add(limit)
+    assert len(limits) == 2 and all(len(v) == 1 for v in limits.values()), limits
