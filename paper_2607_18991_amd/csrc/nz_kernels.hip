@@ -1589,13 +1589,16 @@ struct BlkCfg {
     static constexpr uint32_t RS = B > 256 ? 2048 : 1024;
     static constexpr uint32_t SHIFT = B > 256 ? 21 : 22;
     // the ranks and times within a block go where the map was, if that is large enough
-    static constexpr bool OWN_SCRATCH = NT == 256;
+    // (wrapping: where the node ids were, which a block that wraps needs no more)
+    static constexpr bool OWN_SCRATCH = NT == 256 && MODE != 1;
+    static constexpr bool ID_SCRATCH = NT == 256 && MODE == 1;
     // words: keys of the sites, 16-bit ranks of the slots, spanning: joining times of
     // the slots; largest cluster: these alone
     static constexpr uint32_t SCRATCH = MODE == 2 ? RS : B + RS / 2 + (MODE == 0 ? RS : 0);
     static_assert(B <= NT, "thread t loads entry t of a block");
     static_assert(RS % NT == 0 && RS >= B + 512 && RS >= 893 && RS <= 2048, "whole slots per thread; node numbers of 11 bits");
     static_assert(MODE != BLK_WRAP || PER, "wrapping needs periodic coordinates");
+    static_assert(!ID_SCRATCH || SCRATCH <= RS, "the ids' space is large enough");
     static_assert(MODE != BLK_SMAX || OWN_SCRATCH, "the map stays in use");
 };
 
@@ -1608,7 +1611,9 @@ struct BlkLds {
     uint32_t pcs[C::B];                // packed coordinates of the block's sites
     NzOffset rows[BLK_MAXROWS];        // the sample's rows, padded with empty ones to whole chunks
     uint16_t spos[C::B];               // the sites' nodes
-    int16_t eq[C::MODE == BLK_WRAP ? BLK_EDGES : 1];   // x0(first node) - x0(second node) of pair e
+    // x0(first node) - x0(second node) of pair e: up to two steps for every site of the
+    // lattice, since a cluster that does not wrap around axis 0 may wind around the others
+    int32_t eq[C::MODE == BLK_WRAP ? BLK_EDGES : 1];
     uint32_t scratch[C::OWN_SCRATCH ? C::SCRATCH : 1];
     // largest-cluster sweep: the block position of every node (0xFFFF: an earlier
     // root), the clusters that can raise the maximum (`next`: which of them a root
@@ -2172,7 +2177,7 @@ __device__ __forceinline__ int blk_step(BlkLds<C> &S, const BlkMem<C::MODE> &m, 
             }
             S.et[e] = static_cast<uint32_t>(S.spos[i]) | (node << 16);
             // x0(site) - x0(node): the neighbour lies at x0(site) + d0 = x0(node) + disp
-            if constexpr (MODE == BLK_WRAP) S.eq[e] = static_cast<int16_t>(disp - (j - 2));
+            if constexpr (MODE == BLK_WRAP) S.eq[e] = disp - (j - 2);
         }
         if (nnew) atomicAdd(&S.nroots, nnew);
         __syncthreads();
@@ -2492,7 +2497,8 @@ __global__ __launch_bounds__(C::NT, 4) void nz_sweep_kernel(NzSweepArgs a, Sweep
     constexpr int MODE = C::MODE, NT = C::NT, B = C::B;
     extern __shared__ uint32_t blk_map[];
     __shared__ BlkLds<C> S;
-    uint32_t *scratch = C::OWN_SCRATCH ? S.scratch : blk_map;   // (a sample that spans needs its map no more)
+    // (a sample that spans needs its map no more)
+    uint32_t *scratch = C::OWN_SCRATCH ? S.scratch : C::ID_SCRATCH ? S.rkey : blk_map;
     const int t = static_cast<int>(threadIdx.x);
     for (;;) {
         if (t == 0) S.claim = atomicAdd(a.qhead, 1);
@@ -2904,11 +2910,11 @@ template <int MODE, bool PER, int NT, int B>
 static hipError_t launch_block_n(const NzSweepArgs &a, const SweepOut &o, int cus, size_t lds_per_wg, hipStream_t st)
 {
     using C = BlkCfg<MODE, PER, NT, B>;
-    static_assert(!C::OWN_SCRATCH || sizeof(BlkLds<C>) + BLK_SMALL_MAP * 4 <= 65536, "small maps need no limit of their own");
-    if (!C::OWN_SCRATCH && a.map_words < C::SCRATCH) return hipErrorInvalidValue;
+    static_assert(NT > 256 || sizeof(BlkLds<C>) + BLK_SMALL_MAP * 4 <= 65536, "small maps need no limit of their own");
+    if (NT > 256 && a.map_words < C::SCRATCH) return hipErrorInvalidValue;
     auto k = nz_sweep_kernel<C>;
     const size_t lds = static_cast<size_t>(a.map_words) * 4u;
-    if (!C::OWN_SCRATCH) {
+    if constexpr (NT > 256) {
         // the limit is the kernel's, not this launch's: always what a workgroup can
         // have, so that no other thread's smaller lattice lowers it before the launch
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,5 +1,7 @@
 """The host side of the library with a stand-in for the HIP runtime (not GPU)."""
 import ctypes
+import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -37,3 +39,27 @@ def test_lds_limit_is_the_same_for_every_launch_of_a_kernel(lib, boundary):
         if lds > 16384 and "nz_sweep_kernel" in name:
             limits.setdefault(name, set()).add(limit)
     assert len(limits) == 2 and all(len(v) == 1 for v in limits.values()), limits
+
+
+def test_wrap_displacements_are_not_narrowed(tmp_path):
+    """A displacement is the sum of up to two steps of every site on a path, so the
+    one between a pair's nodes takes any value up to twice the largest lattice."""
+    src = tmp_path / "width.hip"
+    kernels = os.path.join(host_lib.CSRC, "nz_kernels.hip")
+    src.write_text(f'#include "{kernels}"\n' + """
+#include <limits>
+#include <type_traits>
+#include <utility>
+template <int NT, int B>
+constexpr long long widest()
+{
+    using C = nz::BlkCfg<nz::BLK_WRAP, true, NT, B>;
+    using T = std::remove_reference_t<decltype(std::declval<nz::BlkLds<C> &>().eq[0])>;
+    return std::numeric_limits<T>::max();
+}
+constexpr long long bound = 2LL * 55 * 55 * 55 * 55 * 55;
+static_assert(widest<256, 256>() >= bound && widest<512, 512>() >= bound && widest<1024, 512>() >= bound, "too narrow");
+""")
+    run = subprocess.run([host_lib.hipcc(), "--cuda-host-only", "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", str(src)],
+                         capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stderr[-2000:]
