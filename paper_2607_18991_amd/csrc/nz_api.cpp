@@ -15,7 +15,6 @@
 #include <future>
 #include <map>
 #include <mutex>
-#include <string>
 #include <thread>
 #include <vector>
 
@@ -27,7 +26,8 @@
 
 namespace {
 
-thread_local std::string g_err = "no error";
+// (a fixed buffer: describing a failed allocation allocates nothing)
+thread_local char g_err[512] = "no error";
 thread_local int64_t g_stats[6] = {0, 0, 0, 0, 0, 0};
 thread_local bool g_timing = false;
 thread_local double g_ms[6] = {0, 0, 0, 0, 0, 0};
@@ -78,12 +78,12 @@ struct PhaseEvents {
 
 int fail(int code, const char *fmt, ...)
 {
-    char buf[512];
+    char buf[sizeof g_err] = "";
     va_list ap;
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    g_err = buf;
+    std::memcpy(g_err, buf, sizeof buf);
     return code;
 }
 
@@ -1164,7 +1164,7 @@ int run_batch_one_group(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t w
 // ---------------------------------------------------------------------------
 // Public entry points.
 
-NZ_API const char *nz_last_error(void) { return g_err.c_str(); }
+NZ_API const char *nz_last_error(void) { return g_err; }
 
 NZ_API int nz_abi_version(void) { return NZ_ABI_VERSION; }
 
@@ -1299,7 +1299,7 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
     turn_b.second = true;
     turn_b.recorded = recorded.get_future().share();
     int rc_b = NZ_OK;
-    std::string err_b;
+    char err_b[sizeof g_err] = "";
     int64_t stats_b[6] = {0, 0, 0, 0, 0, 0};
     double ms_b[6] = {0, 0, 0, 0, 0, 0};
     double cc_b[5] = {0, 0, 0, 0, 0};
@@ -1317,14 +1317,14 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
         } catch (...) {
             rc_b = fail(NZ_ENOMEM, "host allocation failed");
         }
-        if (rc_b != NZ_OK) err_b = g_err;
+        if (rc_b != NZ_OK) std::memcpy(err_b, g_err, sizeof err_b);
         for (int k = 0; k < 6; ++k) {
             stats_b[k] = g_stats[k];
             ms_b[k] = g_ms[k];
         }
         for (int k = 0; k < 5; ++k) cc_b[k] = g_cc_ms[k];
-        serial_b = g_job_serial;
-        pre_b = g_job_pre;
+        serial_b.swap(g_job_serial);
+        pre_b.swap(g_job_pre);
     });
     int rc_a;
     try {
@@ -1355,7 +1355,7 @@ int run_split(SplitPlan &sp, int32_t njobs, uint8_t *ws, size_t ws_bytes, int32_
         g_job_pre.swap(pre);
     }
     if (rc_a != NZ_OK) return rc_a;
-    if (rc_b != NZ_OK) return fail(rc_b, "%s", err_b.c_str());
+    if (rc_b != NZ_OK) return fail(rc_b, "%s", err_b);
     if (h_backoffs) {
         for (int j = 0; j < njobs; ++j) h_backoffs[j] = 0;
         for (int g = 0; g < 2; ++g)
@@ -1817,6 +1817,7 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
     // (n, samples up to n), one pass over the histogram
     std::vector<int64_t> at;
     std::vector<uint64_t> upto;
+    std::vector<double> F;
     double total = 0.0;
     uint64_t run = 0, exact = 0;
     bool whole = true;   // the total is an exact integer below 2^53
@@ -1837,13 +1838,13 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
                 upto.push_back(run);
             }
         }
+        F.resize(upto.size() + 1);
     } catch (...) {
         return fail(NZ_ENOMEM, "host allocation failed");
     }
     if (whole) total = static_cast<double>(exact);
     if (total <= 0.0) return fail(NZ_EINVAL, "empty histogram");
     // F at the steps (integers, divided once, so F is exact to rounding)
-    std::vector<double> F(upto.size() + 1);
     F[0] = 0.0;
     for (size_t i = 0; i < upto.size(); ++i) F[i + 1] = static_cast<double>(upto[i]) / total;
     const auto step_of = [&](int64_t n) {   // steps at or below n

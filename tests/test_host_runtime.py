@@ -2,6 +2,7 @@
 import ctypes
 import os
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -63,3 +64,30 @@ static_assert(widest<256, 256>() >= bound && widest<512, 512>() >= bound && wide
     run = subprocess.run([host_lib.hipcc(), "--cuda-host-only", "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", str(src)],
                          capture_output=True, text=True, timeout=300)
     assert run.returncode == 0, run.stderr[-2000:]
+
+
+def test_canonical_reports_failed_allocations(lib):
+    """Every host allocation of the call fails in turn: a status, never an exception
+    through the C interface (which would end the process; hence one of its own)."""
+    code = """
+import ctypes, sys
+lib = ctypes.CDLL(sys.argv[1])
+h = (ctypes.c_uint64 * 65)(*range(65))
+p = (ctypes.c_double * 3)(0.1, 0.5, 0.9)
+R = (ctypes.c_double * 3)()
+lib.nz_canonical.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
+lib.fake_fail_new.argtypes = [ctypes.c_int64]
+failed = 0
+while True:
+    lib.fake_fail_new(failed)
+    rc = lib.nz_canonical(h, 65, p, 3, R)
+    lib.fake_fail_new(-1)
+    if rc == 0:
+        break
+    assert rc == -3, rc
+    failed += 1
+print(failed)
+"""
+    run = subprocess.run([sys.executable, "-c", code, lib._name], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0, (run.returncode, run.stderr[-500:])
+    assert int(run.stdout) >= 1
