@@ -1803,9 +1803,32 @@ NZ_API int nz_prefill_plan(const float *y, nz_job *jobs, int32_t njobs, double k
     return NZ_OK;
 }
 
+// Whether more than an eighth of the entries hold counts: all of them up to 4096
+// entries, else 64 blocks of 64 spread over the histogram.
+static bool dense_histogram(const uint64_t *hist, int64_t N)
+{
+    const int64_t stride = N < 4096 ? 64 : N / 64;
+    int64_t seen = 0, held = 0;
+    for (int64_t b = 0; b <= N; b += stride)
+        for (int64_t n = b; n < std::min<int64_t>(b + 64, N + 1); ++n) {
+            ++seen;
+            held += hist[n] != 0 ? 1 : 0;
+        }
+    return 8 * held > seen;
+}
+
 // Binomial convolution (Sec. II.B): weights C(N,n) p^n (1-p)^(N-n) are formed
 // from the mode outward with the ratio w(n+1)/w(n) = (N-n)/(n+1) * p/(1-p) and
 // normalised by their sum.  Terms below 1e-300 of the mode weight are dropped.
+//
+// F(n) = (samples with 1 <= n* <= n) / total is a step function.  The n* of a run
+// lie in a few thousand of the N + 1 entries, and the steps alone are kept, in one
+// pass over the histogram (L = 16, 1000 samples, 101 points, one core: 2.0 ms, and
+// 10.2 with F at every n).  A histogram with counts in more than an eighth of its
+// entries is taken as F at every n: as steps it costs three arrays instead of one
+// and a search per term.  L = 16, steps / every n: all entries held, one point 14.6
+// / 2.2 ms, 101 points 15.5 / 3.7; a seventh of them, 3.4 / 2.2 and 5.9 / 3.7; a
+// tenth, as steps, 2.7 and 4.7.
 NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_grid, int64_t np, double *R)
 {
     if (!hist || hist_len < 2) return fail(NZ_EINVAL, "hist must have at least 2 entries");
@@ -1813,16 +1836,15 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
     for (int64_t k = 0; k < np; ++k)
         if (!(p_grid[k] >= 0.0 && p_grid[k] <= 1.0)) return fail(NZ_EINVAL, "p_grid[%lld] outside [0, 1]", (long long)k);
     const int64_t N = hist_len - 1;
-    // F(n) = (samples with 1 <= n* <= n) / total is a step function: its steps
-    // (n, samples up to n), one pass over the histogram
-    std::vector<int64_t> at;
+    bool dense = dense_histogram(hist, N);
+    std::vector<int64_t> at;      // the steps: n, samples up to n
     std::vector<uint64_t> upto;
-    std::vector<double> F;
+    std::vector<double> F;        // before the first step and at every step; dense: at every n
     double total = 0.0;
-    uint64_t run = 0, exact = 0;
-    bool whole = true;   // the total is an exact integer below 2^53
     try {
-        for (int64_t n0 = 0; n0 <= N; n0 += 64) {
+        uint64_t run = 0, exact = 0;
+        bool whole = true;   // the total is an exact integer below 2^53
+        for (int64_t n0 = 0; n0 <= N && !dense; n0 += 64) {
             const int64_t n1 = std::min<int64_t>(n0 + 64, N + 1);
             uint64_t any = 0;
             for (int64_t n = n0; n < n1; ++n) any |= hist[n];
@@ -1837,38 +1859,71 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
                 at.push_back(n);
                 upto.push_back(run);
             }
+            dense = static_cast<int64_t>(at.size()) > N / 8 + 64;   // (the blocks looked at were not typical)
         }
-        F.resize(upto.size() + 1);
+        if (dense) {
+            total = 0.0;
+            uint64_t any = 0;
+            exact = run = 0;
+            for (int64_t n = 0; n <= N; ++n) {
+                any |= hist[n];
+                exact += hist[n];
+            }
+            if (any < (1ull << 53) / static_cast<uint64_t>(N + 1)) total = static_cast<double>(exact);
+            else
+                for (int64_t n = 0; n <= N; ++n) total += static_cast<double>(hist[n]);
+            F.resize(static_cast<size_t>(N) + 1);
+            for (int64_t n = 1; n <= N; ++n) {
+                run += hist[n];
+                F[n] = static_cast<double>(run) / total;
+            }
+        } else {
+            if (whole) total = static_cast<double>(exact);
+            // (integers, divided once, so F is exact to rounding)
+            F.resize(upto.size() + 1);
+            for (size_t i = 0; i < upto.size(); ++i) F[i + 1] = static_cast<double>(upto[i]) / total;
+        }
     } catch (...) {
         return fail(NZ_ENOMEM, "host allocation failed");
     }
-    if (whole) total = static_cast<double>(exact);
     if (total <= 0.0) return fail(NZ_EINVAL, "empty histogram");
-    // F at the steps (integers, divided once, so F is exact to rounding)
-    F[0] = 0.0;
-    for (size_t i = 0; i < upto.size(); ++i) F[i + 1] = static_cast<double>(upto[i]) / total;
     const auto step_of = [&](int64_t n) {   // steps at or below n
         return static_cast<size_t>(std::upper_bound(at.begin(), at.end(), n) - at.begin());
     };
-    for (int64_t k = 0; k < np; ++k) {
-        const double p = p_grid[k];
-        if (p == 0.0) {
-            R[k] = F[0];
-            continue;
-        }
-        if (p == 1.0) {
-            R[k] = F[step_of(N)];
-            continue;
-        }
-        int64_t mode = static_cast<int64_t>(std::floor((N + 1) * p));
-        if (mode > N) mode = N;
-        const size_t mode_step = step_of(mode);
-        double sw = 1.0, swf = F[mode_step];
-        size_t i = mode_step;   // steps at or below the current n
-        bool was_up = true;
+    // f_mode = F(mode), F_at(n, upward) = F(n), none_below(n): F = 0 below n
+    const auto convolve = [&](double p, int64_t mode, double f_mode, auto &&F_at, auto &&none_below) {
+        double sw = 1.0, swf = f_mode;
         binomial_walk(
             N, p, mode,
             [&](int64_t n, double w, bool upward) {
+                sw += w;
+                swf += w * F_at(n, upward);
+            },
+            [&](int64_t n, double w, bool upward) {
+                if (!(w < kNoChange * sw)) return false;
+                if (w < kNoChange * swf) return true;   // F <= 1
+                return upward ? F.back() == 0.0 : none_below(n);
+            });
+        return swf / sw;
+    };
+    for (int64_t k = 0; k < np; ++k) {
+        const double p = p_grid[k];
+        if (p == 0.0 || p == 1.0) {
+            R[k] = p == 0.0 ? 0.0 : F.back();   // F(0) = 0, F(N)
+            continue;
+        }
+        const int64_t mode = std::min(N, static_cast<int64_t>(std::floor((N + 1) * p)));
+        if (dense) {
+            R[k] = convolve(
+                p, mode, F[mode], [&](int64_t n, bool) { return F[n]; }, [&](int64_t n) { return n == 0 || F[n - 1] == 0.0; });
+            continue;
+        }
+        const size_t mode_step = step_of(mode);
+        size_t i = mode_step;   // steps at or below the current n
+        bool was_up = true;
+        R[k] = convolve(
+            p, mode, F[mode_step],
+            [&](int64_t n, bool upward) {
                 if (upward != was_up) {
                     was_up = upward;
                     i = mode_step;
@@ -1877,16 +1932,9 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
                     while (i < at.size() && at[i] <= n) ++i;
                 else
                     while (i > 0 && at[i - 1] > n) --i;
-                sw += w;
-                swf += w * F[i];
+                return F[i];
             },
-            [&](int64_t n, double w, bool upward) {
-                if (!(w < kNoChange * sw)) return false;
-                if (w < kNoChange * swf) return true;                       // F <= 1
-                if (!upward) return at.empty() || n <= at.front();          // F = 0 from here down
-                return at.empty();                                          // F = 0 everywhere
-            });
-        R[k] = swf / sw;
+            [&](int64_t n) { return at.empty() || n <= at.front(); });
     }
     return NZ_OK;
 }

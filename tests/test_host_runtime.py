@@ -72,22 +72,35 @@ def test_canonical_reports_failed_allocations(lib):
     code = """
 import ctypes, sys
 lib = ctypes.CDLL(sys.argv[1])
-h = (ctypes.c_uint64 * 65)(*range(65))
+every = (ctypes.c_uint64 * 65)(*range(65))
+few = (ctypes.c_uint64 * 65)(*[n == 20 or n == 30 for n in range(65)])
 p = (ctypes.c_double * 3)(0.1, 0.5, 0.9)
 R = (ctypes.c_double * 3)()
 lib.nz_canonical.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
 lib.fake_fail_new.argtypes = [ctypes.c_int64]
-failed = 0
-while True:
-    lib.fake_fail_new(failed)
-    rc = lib.nz_canonical(h, 65, p, 3, R)
-    lib.fake_fail_new(-1)
-    if rc == 0:
-        break
-    assert rc == -3, rc
-    failed += 1
-print(failed)
+for h in (every, few):
+    failed = 0
+    while True:
+        lib.fake_fail_new(failed)
+        rc = lib.nz_canonical(h, 65, p, 3, R)
+        lib.fake_fail_new(-1)
+        if rc == 0:
+            break
+        assert rc == -3, rc
+        failed += 1
+    assert failed >= 1
 """
     run = subprocess.run([sys.executable, "-c", code, lib._name], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0, (run.returncode, run.stderr[-500:])
-    assert int(run.stdout) >= 1
+
+
+def test_canonical_of_a_dense_histogram_keeps_one_array(lib):
+    """A histogram with counts in every entry costs one table of N + 1 values, not
+    three (the steps' places, their counts and their values, grown as they are met),
+    which was most of such a call."""
+    N = 1 << 18
+    h, p, R = np.ones(N + 1, dtype=np.uint64), np.array([0.3]), np.zeros(1)
+    lib.fake_reset_peak()
+    assert lib.nz_canonical(_ptr(h), N + 1, _ptr(p), 1, _ptr(R)) == 0
+    assert 8 * N <= lib.fake_peak() <= 12 * N
+    assert abs(R[0] - 0.3) < 1e-5   # F(n) = n / (N + 1)
