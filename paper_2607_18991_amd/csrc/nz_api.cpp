@@ -1638,7 +1638,9 @@ void binomial_walk(int64_t N, double p, int64_t mode, Term &&term, Done &&done)
     for (int64_t n = mode; n < N; n += 8) {
         const int m = static_cast<int>(std::min<int64_t>(8, N - n));
         for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(N - n - k) / static_cast<double>(n + k + 1) * up;
-        for (int k = 0; k < m; ++k) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (k == m) break;
             w *= r[k];
             if (w < 1e-300) goto down;
             term(n + k + 1, w, true);
@@ -1650,7 +1652,9 @@ down:
     for (int64_t n = mode; n > 0; n -= 8) {
         const int m = static_cast<int>(std::min<int64_t>(8, n));
         for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(n - k) / static_cast<double>(N - n + k + 1) / up;
-        for (int k = 0; k < m; ++k) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (k == m) break;
             w *= r[k];
             if (w < 1e-300) return;
             term(n - k - 1, w, false);
@@ -1675,11 +1679,17 @@ NZ_API int nz_convolve_window(const double *Q, int64_t n_lo, int64_t n_hi, int64
     if (np < 0 || (np > 0 && (!p_grid || !out))) return fail(NZ_EINVAL, "bad p grid or output");
     for (int64_t k = 0; k < np; ++k)
         if (!(p_grid[k] >= 0.0 && p_grid[k] <= 1.0)) return fail(NZ_EINVAL, "p_grid[%lld] outside [0, 1]", (long long)k);
-    double most = 0.0;   // largest |Q| (NaN: the walks are not cut short)
-    for (int64_t n = 0; n < n_hi - n_lo; ++n) {
+    // Largest |Q| (NaN or infinite: the walks are not cut short inside the window).  An
+    // entry costs as much here as a step of a walk, of which a walk cut short saves
+    // some 57 standard deviations' worth, so windows wider than the walks gain
+    // from it are not looked through (N = 16^5, 200000 entries, one p: 0.58 ms with
+    // the look, 0.08 without; 65 p on 4000 entries: 1.5 and 4.3).
+    double reach = 0.0;
+    for (int64_t k = 0; k < np; ++k) reach += 57.0 * std::sqrt(static_cast<double>(N) * p_grid[k] * (1.0 - p_grid[k]));
+    double most = static_cast<double>(n_hi - n_lo) <= reach ? 0.0 : HUGE_VAL;
+    for (int64_t n = 0; n < n_hi - n_lo && most < HUGE_VAL; ++n) {
         const double q = std::fabs(Q[n]);
         if (!(q <= most)) most = q;
-        if (q != q) break;
     }
     for (int64_t k = 0; k < np; ++k) {
         const double p = p_grid[k];

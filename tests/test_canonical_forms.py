@@ -41,3 +41,41 @@ def test_only_samples_that_never_span():
     h = np.zeros(100, dtype=np.uint64)
     h[0] = 7
     assert (nz.nz_canonical(h, np.linspace(0, 1, 5)) == 0).all()
+
+
+def _window(N, W, seed):
+    rng = np.random.default_rng(seed)
+    lo = int(0.14 * N) - W // 2
+    return np.abs(rng.standard_normal(W)) * N, lo
+
+
+@pytest.mark.parametrize("W,points", [(3000, 40), (30000, 3), (30000, 400)])
+def test_windows_on_both_sides_of_the_look_match_the_oracle(nzo, W, points):
+    """Windows narrower than the walks are looked through for their largest value, so
+    that walks can end early; wider ones are not."""
+    N = 10**5
+    Q, lo = _window(N, W, 3) if W < 20000 else (np.abs(np.random.default_rng(4).standard_normal(W)) * N, 0)
+    p = np.linspace(0.12, 0.16, points)
+    a, ca = nz.nz_convolve_window(Q, lo, N, p)
+    b, cb = nzo.convolve_window(Q, lo, N, p)
+    assert np.allclose(a, b, rtol=1e-12, atol=1e-12 * N) and np.allclose(ca, cb, atol=1e-12)
+
+
+def test_wide_window_costs_no_look_through_it():
+    """One p on a window of two million entries walks some 73000 of them: as long as
+    on a window of 80000 that holds them all, not thirty times as long."""
+    import time
+
+    N, p = 24**5, [0.14]
+
+    def best(W):
+        Q, lo = _window(N, W, 6)
+        times = []
+        for _ in range(9):
+            t = time.perf_counter()
+            nz.nz_convolve_window(Q, lo, N, p)
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    wide, narrow = best(2_000_000), best(80_000)
+    assert wide < 8 * narrow, (wide, narrow)
