@@ -74,12 +74,19 @@ int nz_coordination(uint32_t zone_mask);
  *   nstar      HOST array of nsamples int32, written;
  *   mass       HOST array of nsamples int32, written; may be NULL.
  * Synchronous; allocates its own device memory and keeps up to 4 GiB of it for
- * the calling thread's next call (8 GiB over all threads; freed when the thread
- * ends); runs on the current HIP device and its default stream.  Plain sweep (no
- * prefill).
+ * the calling thread's next call (8 GiB over all threads; freed by nz_release or
+ * when the thread ends); runs on the current HIP device and its default stream.
+ * Plain sweep (no prefill).
  */
 int nz_sweep(int32_t L, uint32_t zone_mask, int32_t boundary, int64_t nsamples, uint64_t seed,
              int32_t *nstar, int32_t *mass);
+
+/*
+ * nz_release -- gives back the device memory that nz_sweep and nz_smax_window
+ * keep for the calling thread (none: does nothing).  The next call allocates
+ * anew.
+ */
+int nz_release(void);
 
 /*
  * nz_canonical -- R_L(p) = sum_n C(N,n) p^n (1-p)^(N-n) F_n (Sec. II.B, the

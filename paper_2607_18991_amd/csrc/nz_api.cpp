@@ -1432,8 +1432,8 @@ NZ_API int nz_sweep_batch(const nz_job *jobs, int32_t njobs, void *d_ws, size_t 
 // than the sweep itself (L = 12, 1000 samples of zone 1, 2 GB: 9 ms or 60 ms of
 // a call, by the state of the allocator).  Blocks up to kKeepBytes are kept, at
 // most kKeepTotal over all threads; larger ones are freed with the call, and a
-// kept block when its thread ends, when the thread turns to another device or a
-// larger block, or when an allocation fails.
+// kept block by nz_release, when its thread ends, when the thread turns to
+// another device or a larger block, or when an allocation fails.
 constexpr size_t kKeepBytes = size_t(4) << 30;
 constexpr size_t kKeepTotal = size_t(8) << 30;
 
@@ -1489,6 +1489,12 @@ DeviceBlock &thread_block()
 {
     static thread_local DeviceBlock block;
     return block;
+}
+
+NZ_API int nz_release(void)
+{
+    thread_block().release();
+    return NZ_OK;
 }
 
 // Workspace of at most `want` bytes (`samples` samples resident at once) followed

@@ -32,7 +32,7 @@ EXPORTS = (
     "nz_mlp_forward", "nz_mlp_backward", "nz_mlp_adam", "nz_set_timing", "nz_last_batch_timing",
     "nz_mlp_loss", "nz_smax_window", "nz_convolve_window", "nz_sweep_batch_static", "nz_static_scratch_bytes",
     "nz_last_batch_job_stats", "nz_last_batch_cc_timing",
-    "nz_mlp_size_stats", "nz_mlp_features", "nz_prefill_target", "nz_prefill_plan",
+    "nz_mlp_size_stats", "nz_mlp_features", "nz_prefill_target", "nz_prefill_plan", "nz_release",
 )
 
 
@@ -93,6 +93,8 @@ def lib():
     L.nz_coordination.restype = ctypes.c_int
     L.nz_sweep.argtypes = [i32, u32, i32, i64, u64, P, P]
     L.nz_sweep.restype = ctypes.c_int
+    L.nz_release.argtypes = []
+    L.nz_release.restype = ctypes.c_int
     L.nz_canonical.argtypes = [P, i64, P, i64, P]
     L.nz_canonical.restype = ctypes.c_int
     L.nz_smax_window.argtypes = [i32, u32, i32, u64, i64, i64, i64, i64, i64, P]
@@ -198,6 +200,11 @@ def nz_sweep(L: int, zone_mask: int, nsamples: int, seed: int, boundary: int = N
     ms = np.zeros(max(nsamples, 1), dtype=np.int32)
     _check(lib().nz_sweep(L, zone_mask, boundary, nsamples, seed, _np_ptr(ns), _np_ptr(ms)))
     return ns[:nsamples], ms[:nsamples]
+
+
+def nz_release() -> None:
+    """Gives back the device memory that nz_sweep and nz_smax_window keep for this thread."""
+    _check(lib().nz_release())
 
 
 def make_jobs(jobs) -> ctypes.Array:

@@ -39,6 +39,7 @@ std::vector<Launch> g_launches;
 int64_t g_mallocs = 0, g_frees = 0, g_streams = 0;
 void *g_bad_stream = nullptr;   // copies on it fail
 bool g_bad_copies = false;
+int g_bad_mallocs = 0;          // so many allocations of device memory fail
 // host allocations of the calling thread: bytes held and their peak, and the
 // number of allocations until one fails (< 0: none)
 thread_local int64_t t_held = 0, t_peak = 0, t_left = -1;
@@ -101,6 +102,7 @@ FAKE void fake_fail_copies(void *stream)
     g_bad_stream = stream;
     g_bad_copies = true;
 }
+FAKE void fake_fail_mallocs(int n) { g_bad_mallocs = n; }
 FAKE void fake_fail_new(int64_t after) { t_left = after; }
 FAKE void fake_reset_peak() { t_held = t_peak = 0; }
 FAKE int64_t fake_peak() { return t_peak; }
@@ -180,8 +182,12 @@ FAKE hipError_t hipMemGetInfo(size_t *freeb, size_t *total)
 }
 FAKE hipError_t hipMalloc(void **p, size_t n)
 {
-    *p = std::calloc(1, n);   // (pages come when they are touched)
     std::lock_guard<std::mutex> g(g_lock);
+    if (g_bad_mallocs > 0) {
+        --g_bad_mallocs;
+        return hipErrorOutOfMemory;
+    }
+    *p = std::calloc(1, n);   // (pages come when they are touched)
     g_blocks[*p] = n;
     ++g_mallocs;
     return *p ? hipSuccess : hipErrorOutOfMemory;

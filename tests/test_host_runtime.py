@@ -3,6 +3,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -104,3 +105,75 @@ def test_canonical_of_a_dense_histogram_keeps_one_array(lib):
     assert lib.nz_canonical(_ptr(h), N + 1, _ptr(p), 1, _ptr(R)) == 0
     assert 8 * N <= lib.fake_peak() <= 12 * N
     assert abs(R[0] - 0.3) < 1e-5   # F(n) = n / (N + 1)
+
+
+GIB = 1 << 30
+
+
+def in_thread(f):
+    """f() on a thread of its own, which has ended when this returns."""
+    out = []
+    t = threading.Thread(target=lambda: out.append(f()))
+    t.start()
+    t.join()
+    return out[0]
+
+
+def test_kept_device_memory_is_reused_grown_and_given_back(lib):
+    def work():
+        lib.fake_reset()
+        assert sweep(lib, 8, 0x01, 100) == 0
+        small = lib.fake_device_bytes()
+        assert small > 0 and (lib.fake_mallocs(), lib.fake_frees()) == (1, 0)
+        assert sweep(lib, 8, 0x01, 100) == 0 and sweep(lib, 5, 0x7F, 100) == 0
+        assert (lib.fake_mallocs(), lib.fake_frees()) == (1, 0)
+        assert sweep(lib, 12, 0x01, 100) == 0   # a larger one takes its place
+        assert (lib.fake_mallocs(), lib.fake_frees()) == (2, 1) and lib.fake_device_bytes() > small
+        sums = np.zeros(50, dtype=np.uint64)    # windows use the same block
+        assert lib.nz_smax_window(8, 1, 0, 1, 0, 10, -1, 100, 150, _ptr(sums)) == 0
+        assert lib.fake_mallocs() == 2
+        assert lib.nz_release() == 0
+        assert lib.fake_frees() == 2 and lib.fake_device_bytes() == 0
+        assert lib.nz_release() == 0 and lib.fake_frees() == 2
+        assert sweep(lib, 8, 0x01, 100) == 0
+        return lib.fake_device_bytes()
+
+    lib.nz_release()
+    assert in_thread(work) > 0
+    assert lib.fake_device_bytes() == 0   # the end of the thread gives back what it kept
+
+
+def test_kept_device_memory_is_bounded(lib):
+    """Over all threads no more than 8 GiB stay, and none of a block above 4 GiB."""
+    lib.nz_release()
+    assert lib.fake_device_bytes() == 0
+    barrier = threading.Barrier(4)
+    codes, kept = [], []
+
+    def work():
+        codes.append(sweep(lib, 16, 0x01, 400))   # some 3 GiB
+        barrier.wait()
+        kept.append(lib.fake_device_bytes())
+        barrier.wait()
+
+    ts = [threading.Thread(target=work) for _ in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert codes == [0] * 4
+    assert all(2 * GIB < k <= 8 * GIB for k in kept), kept
+    assert lib.fake_device_bytes() == 0
+    assert in_thread(lambda: (sweep(lib, 30, 0x01, 40), lib.fake_device_bytes())) == (0, 0)
+
+
+def test_a_failed_allocation_is_tried_with_less(lib):
+    def work():
+        lib.fake_fail_mallocs(1)
+        first = sweep(lib, 8, 0x01, 100)
+        lib.fake_fail_mallocs(2)
+        second = sweep(lib, 12, 0x01, 100)
+        lib.fake_fail_mallocs(0)
+        return first, second, sweep(lib, 12, 0x01, 100)
+
+    assert in_thread(work) == (0, -3, 0)   # NZ_ENOMEM
