@@ -88,6 +88,7 @@ FAKE const char *fake_launch(int k, size_t *lds, size_t *limit)
     *limit = g_launches[k].limit;
     return g_launches[k].name.c_str();
 }
+FAKE void *fake_launch_stream(int k) { return g_launches[k].stream; }
 FAKE int64_t fake_mallocs() { return g_mallocs; }
 FAKE int64_t fake_frees() { return g_frees; }
 FAKE int64_t fake_device_bytes()

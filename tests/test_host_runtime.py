@@ -4,6 +4,7 @@ import os
 import subprocess
 import sys
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -110,8 +111,16 @@ def test_canonical_of_a_dense_histogram_keeps_one_array(lib):
 GIB = 1 << 30
 
 
+def all_given_back(lib):
+    """(A thread that has been joined may be about to end.)"""
+    end = time.monotonic() + 10
+    while lib.fake_device_bytes() and time.monotonic() < end:
+        time.sleep(0.01)
+    return lib.fake_device_bytes() == 0
+
+
 def in_thread(f):
-    """f() on a thread of its own, which has ended when this returns."""
+    """f() on a thread of its own."""
     out = []
     t = threading.Thread(target=lambda: out.append(f()))
     t.start()
@@ -139,14 +148,15 @@ def test_kept_device_memory_is_reused_grown_and_given_back(lib):
         return lib.fake_device_bytes()
 
     lib.nz_release()
+    assert all_given_back(lib)
     assert in_thread(work) > 0
-    assert lib.fake_device_bytes() == 0   # the end of the thread gives back what it kept
+    assert all_given_back(lib)   # the end of the thread gives back what it kept
 
 
 def test_kept_device_memory_is_bounded(lib):
     """Over all threads no more than 8 GiB stay, and none of a block above 4 GiB."""
     lib.nz_release()
-    assert lib.fake_device_bytes() == 0
+    assert all_given_back(lib)
     barrier = threading.Barrier(4)
     codes, kept = [], []
 
@@ -163,7 +173,7 @@ def test_kept_device_memory_is_bounded(lib):
         t.join()
     assert codes == [0] * 4
     assert all(2 * GIB < k <= 8 * GIB for k in kept), kept
-    assert lib.fake_device_bytes() == 0
+    assert all_given_back(lib)
     assert in_thread(lambda: (sweep(lib, 30, 0x01, 40), lib.fake_device_bytes())) == (0, 0)
 
 
@@ -177,3 +187,47 @@ def test_a_failed_allocation_is_tried_with_less(lib):
         return first, second, sweep(lib, 12, 0x01, 100)
 
     assert in_thread(work) == (0, -3, 0)   # NZ_ENOMEM
+
+
+@pytest.mark.parametrize("failing", [0, 1])
+def test_one_group_of_a_batch_fails_and_the_other_ends(lib, failing):
+    """Two groups side by side: the second one's keys wait for the first one's, which
+    never come if its first copy fails.  The call ends with that failure all the
+    same, and a later one runs."""
+    from paper_2607_18991_amd import nz
+
+    arr, n = nz.make_jobs([dict(L=6, zone_mask=m, seed=1, nsamples=300) for m in (0x01, 0x7F)])
+    need = ctypes.c_size_t()
+    assert lib.nz_batch_workspace_bytes(arr, n, None, ctypes.byref(need)) == 0
+    space = np.zeros(need.value + 256, dtype=np.uint8)
+    ws = ctypes.c_void_p((space.ctypes.data + 255) // 256 * 256)
+    out = np.zeros(600, dtype=np.int32)
+    stream = ctypes.c_void_p(0x77)
+
+    def call():
+        return lib.nz_sweep_batch(arr, n, ws, need.value, _ptr(out), None, None, None, stream), lib.nz_last_error()
+
+    def work():
+        first = call()
+        lib.fake_reset()
+        assert call()[0] == 0
+        streams = {k for k in lib_streams(lib)}
+        assert len(streams) == 2 and 0x77 in streams   # the two groups
+        lib.fake_fail_copies(ctypes.c_void_p(0x77 if failing == 0 else (streams - {0x77}).pop()))
+        second = call()
+        lib.fake_reset()
+        return first, second, call()
+
+    done = []
+    t = threading.Thread(target=lambda: done.append(work()), daemon=True)
+    t.start()
+    t.join(30)
+    assert done, "the call hangs"
+    first, second, third = done[0]
+    assert first[0] == 0 and third[0] == 0
+    assert second[0] == nz.NZ_EDEVICE and b"hipMemcpyAsync" in second[1]
+
+
+def lib_streams(lib):
+    lib.fake_launch_stream.restype = ctypes.c_void_p
+    return [lib.fake_launch_stream(k) or 0 for k in range(lib.fake_launches())]
