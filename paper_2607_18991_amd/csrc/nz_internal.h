@@ -55,28 +55,30 @@ struct NzSample {
     int32_t N;
     int32_t nb;           // buckets of the key band [T0, T0 + nb << shift)
     int32_t cap;          // capacity of each bucket (entries)
-    int32_t shift;        // log2 of the bucket width in key units
-    int32_t full;         // the band reaches 2^64 (exhaustion then means "never spans")
     int32_t tab;          // first entry of this sample's row table
     int32_t rows;         // number of rows (even)
     int32_t prefix_cap;   // capacity of the prefill site list
-    int32_t smax_mode;    // 1: track the largest cluster over [win_lo, win_hi) instead of stopping at n*
+    uint32_t shift : 8;     // log2 of the bucket width in key units
+    uint32_t sum_shift : 8;
+    uint32_t full : 1;      // the band reaches 2^64 (exhaustion then means "never spans")
+    uint32_t smax_mode : 1; // 1: track the largest cluster over [win_lo, win_hi) instead of stopping at n*
+    uint32_t periodic : 1;  // 1: coordinates wrap mod L (L >= 5); no borders, so no border flags
+    uint32_t wrap : 1;      // 1: periodic first-wrap sweep; entries of off_par are 64-bit
+                            //    (low half the parent word, high half the x0 displacement
+                            //    from the parent)
     uint64_t magic;       // ceil(2^64 / L) for exact division of site indices by L
     uint64_t off_win;     // smax mode: S_max(n) for n in [win_lo, win_hi), uint32 each
     int32_t win_lo;
     int32_t win_hi;
-    int32_t periodic;     // 1: coordinates wrap mod L (L >= 5); no borders, so no border flags
-    int32_t wrap;         // 1: periodic first-wrap sweep; entries of off_par are 64-bit
-                          //    (low half the parent word, high half the x0 displacement
-                          //    from the parent)
     uint64_t off_sum;     // bitset summary: bit k set unless words k << sum_shift .. are all zero
-    int32_t sum_shift;
-    int32_t sum_words;    // 32-bit summary words (0: no summary)
     // the in-chunk backoffs: threshold and buckets at n0 - b and at n0 - 3b (T0b =
     // 0: not planned)
     uint64_t T0b[2];
     int32_t nbb[2];
+    int32_t sum_words;    // 32-bit summary words (0: no summary)
 };
+// (a chunk of 16384 samples needs that many of them beside its smallest sample)
+static_assert(sizeof(NzSample) <= 176, "the chunk header does not grow");
 
 // Consecutive samples of one job in a chunk, as the host plans them; the expand
 // kernel writes a descriptor, a queue entry and an output index for each.

@@ -217,7 +217,7 @@ FAKE hipError_t hipMemset(void *d, int v, size_t n)
 }
 FAKE hipError_t hipGetSymbolAddress(void **p, const void *)
 {
-    static void *block = std::calloc(1, size_t(256) << 20);
+    static void *block = std::aligned_alloc(4096, size_t(256) << 20);   // (the one symbol: the static buffer)
     *p = block;
     return hipSuccess;
 }

@@ -231,3 +231,23 @@ def test_one_group_of_a_batch_fails_and_the_other_ends(lib, failing):
 def lib_streams(lib):
     lib.fake_launch_stream.restype = ctypes.c_void_p
     return [lib.fake_launch_stream(k) or 0 for k in range(lib.fake_launches())]
+
+
+def aligned(nbytes):
+    """(address, owner) of nbytes of memory on a 256-byte boundary."""
+    space = np.zeros(nbytes + 256, dtype=np.uint8)
+    return ctypes.c_void_p((space.ctypes.data + 255) // 256 * 256), space
+
+
+@pytest.mark.parametrize("L,mask,samples,smallest", [(1, 0x01, 20000, 3410176), (2, 0x28, 20000, 3413504)])
+def test_workspaces_of_many_small_samples(lib, L, mask, samples, smallest):
+    """A chunk of 16384 samples needs a header for them beside its smallest sample: a
+    workspace sized for that with descriptors of 176 bytes stays large enough."""
+    from paper_2607_18991_amd import nz
+
+    arr, n = nz.make_jobs([dict(L=L, zone_mask=mask, seed=1, nsamples=samples)])
+    ws, space = aligned(smallest)
+    out = np.zeros(samples, dtype=np.int32)
+    assert lib.nz_sweep_batch(arr, n, ws, smallest, _ptr(out), None, None, None, None) == 0, lib.nz_last_error()
+    assert lib.nz_sweep_batch(arr, n, ws, smallest - 65536, _ptr(out), None, None, None, None) == nz.NZ_EWORKSPACE
+    del space
