@@ -193,7 +193,9 @@ typedef struct {
 
 /* Device workspace bytes that lets nz_sweep_batch run the jobs with all their
  * samples resident at once.  Smaller workspaces (down to the size needed by one
- * sample of the largest L) are accepted and processed in chunks. */
+ * sample of the largest L) are accepted and processed in chunks.  A prefilled
+ * sample that would fit but for up to L^5 / 8 bytes is swept plainly (the same n*
+ * and mass; no backoffs). */
 int nz_batch_workspace_bytes(const nz_job *jobs, int32_t njobs, const nz_tuning *tune,
                              size_t *bytes);
 

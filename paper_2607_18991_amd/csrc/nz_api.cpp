@@ -385,6 +385,24 @@ Sizes plan_sizes(const Plan &p, int bucket_log2)
     return s;
 }
 
+// The plan without its prefill.
+Plan plain_plan(Plan p)
+{
+    p.n0 = p.backoff = 0;
+    return p;
+}
+
+// The smallest workspace region that runs a sample of plan p.  A prefilled sample
+// holds an 8-byte record per bitset word; one that would fit with 4 bytes each is
+// swept plainly where it does not fit with 8 (L = 36 in 256 MiB, for instance).
+// Only the time and the backoff count depend on that.
+size_t smallest_bytes(const Plan &p, int bucket_log2)
+{
+    const Sizes s = plan_sizes(p, bucket_log2);
+    if (s.wrec == 0) return s.total;
+    return std::min(s.total, std::max(s.total - s.wrec / 2, plan_sizes(plain_plan(p), bucket_log2).total));
+}
+
 // How the keys launch of a sample (its Sizes) spreads, by the share of the
 // sites that its band holds: above 3% one workgroup per sample, if there are
 // enough samples (launch_keys); above 8% and with too many buckets for that, each
@@ -707,7 +725,11 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 part.p = run.p;
                 part.s = plan_sizes(run.p, tune.bucket_log2);
                 part.count = static_cast<int32_t>(std::min<int64_t>({run.count, cmax - n, static_cast<int64_t>((ws_bytes - used) / part.s.total)}));
-                if (part.count <= 0) break;
+                if (part.count <= 0) {
+                    if (!parts.empty() || run.p.n0 == 0 || used + smallest_bytes(run.p, tune.bucket_log2) > ws_bytes) break;
+                    run.p = plain_plan(run.p);   // (not one sample fits with its prefill)
+                    continue;
+                }
                 part.queue0 = n;
                 used += part.s.total * static_cast<size_t>(part.count);
                 n += part.count;
@@ -1116,7 +1138,7 @@ int check_batch_fits(const nz_job *jobs, int32_t njobs, const nz_tuning *tune, s
             p.band_hi = J.band_hi > 0 ? std::min<int64_t>(J.band_hi, N) : default_band_hi(J.L, J.zone_mask, p.n0);
             if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
             p.prefix_mul = 1;
-            const size_t b = plan_sizes(p, t.bucket_log2).total;
+            const size_t b = smallest_bytes(p, t.bucket_log2);
             if (b > largest) {
                 largest = b;
                 worst = j;

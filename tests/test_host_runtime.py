@@ -251,3 +251,19 @@ def test_workspaces_of_many_small_samples(lib, L, mask, samples, smallest):
     assert lib.nz_sweep_batch(arr, n, ws, smallest, _ptr(out), None, None, None, None) == 0, lib.nz_last_error()
     assert lib.nz_sweep_batch(arr, n, ws, smallest - 65536, _ptr(out), None, None, None, None) == nz.NZ_EWORKSPACE
     del space
+
+
+@pytest.mark.parametrize("mask", [0x06, 0x07, 0x0C])
+def test_the_static_buffer_holds_one_sample_of_L36(lib, mask):
+    """A prefilled sample of 60 million sites fits the 256 MiB with 4-byte records; with
+    8-byte ones it is swept plainly."""
+    from paper_2607_18991_amd import nz
+
+    N, p = 36**5, 1.553 / (nz.nz_coordination(mask) + 1.01)
+    arr, n = nz.make_jobs([dict(L=36, zone_mask=mask, seed=1, nsamples=1, n0=int(0.97 * p * N), backoff=int(0.03 * p * N),
+                                band_hi=int(1.05 * p * N) + 1024)])
+    out = np.zeros(1, dtype=np.int32)
+    lib.nz_sweep_batch_static.argtypes = [ctypes.c_void_p, ctypes.c_int32] + [ctypes.c_void_p] * 5
+    assert lib.nz_sweep_batch_static(arr, n, _ptr(out), None, None, None, None) == 0, lib.nz_last_error()
+    arr[0].L = 37
+    assert lib.nz_sweep_batch_static(arr, n, _ptr(out), None, None, None, None) == nz.NZ_EWORKSPACE
