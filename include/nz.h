@@ -272,16 +272,15 @@ int nz_last_batch_job_stats(int64_t *serial, int64_t *prefilled, int32_t njobs);
  * stream around each group of launches.  nz_set_timing(1) turns it on for later
  * calls on the calling thread (0 turns it off).  nz_last_batch_timing fills
  * ms[0..5]: milliseconds in keys (with clearing), bulk connected components,
- * bucket sort, sweep, the whole call, and ms[5] = number of sweep launches. */
+ * 0 (there is no separate sort pass), sweep, the whole call, and ms[5] = number of sweep launches. */
 int nz_set_timing(int enable);
 int nz_last_batch_timing(double ms[6]);
 
 /* With timing on, the bulk labelling of free-boundary prefills split by kernel
  * (HIP events on the launch stream around every dispatch, in-chunk backoff
  * passes included): ms[0..3] = milliseconds summed over dispatches in the hook,
- * compress and size kernels (the size pass also writes the prefilled sites'
- * lattice entries) and 0 (no separate expand pass), ms[4] = number of
- * dispatches of each. */
+ * compress and flag kernels (largest-cluster runs: the sizes) and 0 (no separate
+ * expand pass), ms[4] = number of dispatches of each. */
 int nz_last_batch_cc_timing(double ms[5]);
 
 /*

@@ -35,7 +35,7 @@ thread_local double g_ms[6] = {0, 0, 0, 0, 0, 0};
 // sites occupied by the bulk prefill, summed over the final runs of its samples
 thread_local std::vector<int64_t> g_job_serial, g_job_pre;
 // bulk-labelling kernels of the last batch: milliseconds in hook, compress and
-// the size pass (summed over dispatches), 0 (no separate expand pass) and the
+// the flag pass (summed over dispatches), 0 (no separate expand pass) and the
 // number of dispatches
 thread_local double g_cc_ms[5] = {0, 0, 0, 0, 0};
 
@@ -60,9 +60,9 @@ struct PrefillEvents {
     }
 };
 
-// Events bracketing the phases of one chunk (keys, prefill, sort, sweep).
+// Events bracketing the phases of one chunk (keys, prefill, sweep).
 struct PhaseEvents {
-    hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     bool ok = false;
     PhaseEvents()
     {
@@ -220,7 +220,6 @@ struct Device {
     int id = -1;
     int cus = 256;
     size_t lds_per_block = 65536;
-    size_t lds_per_cu = 65536;
 };
 
 int device_info(Device &dev)
@@ -243,7 +242,6 @@ int device_info(Device &dev)
     dev.id = id;
     dev.cus = p.multiProcessorCount;
     dev.lds_per_block = p.sharedMemPerBlock;
-    dev.lds_per_cu = p.maxSharedMemoryPerMultiProcessor ? p.maxSharedMemoryPerMultiProcessor : p.sharedMemPerBlock;
     int optin = 0;
     if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, id) == hipSuccess && optin > 0)
         dev.lds_per_block = std::max(dev.lds_per_block, static_cast<size_t>(optin));
@@ -454,10 +452,8 @@ size_t header_bytes(size_t table_entries, int32_t chunk)
 struct Tune {
     int residency = 0;
     int wg_waves = 0;
-    int waves_per_simd = 0;
     int bucket_log2 = 7;   // mean keys per band bucket: 64..128 (a block of the sweep takes whole buckets)
     int sweep_mode = 0;
-    int summary = 0;
     int split_z = 0;     // widest neighbourhood of the first of two groups side by side (0: kSplitZ)
 };
 
@@ -491,13 +487,11 @@ int read_tune(const nz_tuning *t, Tune &out)
     if (t->sweep_mode < 0 || t->sweep_mode > 2) return fail(NZ_EINVAL, "tuning: sweep_mode %d outside [0, 2]", t->sweep_mode);
     out.sweep_mode = t->sweep_mode;
     if (t->summary < 0 || t->summary > 2) return fail(NZ_EINVAL, "tuning: summary %d outside [0, 2]", t->summary);
-    out.summary = t->summary;
     if (t->split_z != 0 && (t->split_z < 10 || t->split_z > 892))
         return fail(NZ_EINVAL, "tuning: split_z %d outside [10, 892]", t->split_z);
     out.split_z = t->split_z;
     out.residency = t->residency;
     out.wg_waves = t->wg_waves;
-    out.waves_per_simd = t->waves_per_simd;
     // (a bucket is part of one block of the sweep: at most 128 keys on average)
     if (t->bucket_log2) out.bucket_log2 = std::min(t->bucket_log2, 7);
     return NZ_OK;
@@ -918,7 +912,6 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 }
             }
             if (pe) HIP_TRY(hipEventRecord(pe->ev[2], st));
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));   // (the sweep orders its own blocks: no sort pass)
 
             {
                 // The LDS residencies are accepted where the state they name fits a
@@ -947,17 +940,17 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             if (smax)
                 HIP_TRY(nz::launch_winsum(d_desc, d_state, n, static_cast<int32_t>(smax->win_hi - smax->win_lo), ws,
                                           smax->d_out, st));
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[4], st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));
 
             // ---- read back and schedule the redo of unfinished samples
             HIP_TRY(hipMemcpyAsync(state.data(), d_state, n * sizeof(NzState), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
             lists.clear();
             if (pe) {
-                for (int k = 0; k < 4; ++k) {
+                for (int k = 0; k < 3; ++k) {
                     float ms = 0.0f;
                     HIP_TRY(hipEventElapsedTime(&ms, pe->ev[k], pe->ev[k + 1]));
-                    g_ms[k] += ms;
+                    g_ms[k < 2 ? k : 3] += ms;   // ([2]: the sweep orders its own blocks, there is no sort pass)
                 }
                 g_ms[5] += 1.0;
             }

@@ -20,7 +20,7 @@ enum {
     NZ_ST_PENDING = 0,
     NZ_ST_DONE = 1,       // n*, mass final
     NZ_ST_BAND = 2,       // the key band ran out before the sample spanned: redo wider
-    NZ_ST_BUCKET = 3,     // a sort bucket overflowed before the sample spanned: redo finer
+    NZ_ST_BUCKET = 3,     // a band bucket overflowed before the sample spanned: redo finer
     NZ_ST_BACKOFF = 4,    // the prefilled state already spans: redo with a smaller n0
     NZ_ST_PREFIX = 5,     // the prefill list overflowed: redo with a larger list
 };

@@ -6,14 +6,14 @@
 //   nz_clear_kernel    zero the bucket counters and bitset summaries;
 //   nz_keys_kernel     Philox4x32-10 key of every site (integer VALU bound);
 //                      sites below the prefill threshold T0 are occupied at once
-//                      (bitset word per 32 sites, parent = self, site list);
-//                      sites in the key band [T0, T0 + nb << shift) are appended
-//                      to the bucket of their key;
-//   nz_hook/label      bulk connected components of the prefilled sites
-//   kernels            (hooking with CAS links, then every member points at its
-//                      root and adds its size and border flags to the root
-//                      word); a state that already spans is flagged for
-//                      backoff;
+//                      (bitset word per 32 sites, site list, a list entry that is
+//                      its own parent); sites in the key band [T0, T0 + nb <<
+//                      shift) are appended to the bucket of their key;
+//   nz_hook, compress, bulk connected components of the prefilled sites on their
+//   accum kernels      list positions (hooking with CAS links, then every entry
+//                      points at its root and border sites add their flags to the
+//                      root's word; sizes in largest-cluster runs only); a state
+//                      that already spans is flagged for backoff;
 //   nz_sweep_kernel    persistent: every workgroup pops a sample (longest first)
 //                      and adds whole buckets of its band at a time, merging a
 //                      block's sites and the clusters they touch in LDS; the
@@ -662,7 +662,7 @@ __device__ __forceinline__ bool xcd_slot(int32_t nlist, int32_t bx, int32_t &y, 
 constexpr int32_t LIST_NODE = 0x20000000;
 
 // Hook: one lane per prefilled site and its forward half of the offset table
-// (one of each +-d pair), eight neighbour words loaded at a time.  The edges a
+// (one row of each +-d pair), six rows loaded at a time.  The edges a
 // wave finds (site, occupied neighbour) are not linked where they are found:
 // each offset slot has only a few lanes with an occupied neighbour, so linking
 // slot by slot would run one round of dependent finds per slot with most lanes
@@ -2806,8 +2806,6 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
                        first, count, by_xcd, bps, ws, state);
     return hipGetLastError();
 }
-
-int32_t keys_sites_per_block() { return KEYS_SITES_PER_BLOCK; }
 
 // Words of the map of the hook of sparse lists, and whether a list of n0 sites of
 // N counts as one: under one set bit in 32 of the map.

@@ -25,7 +25,6 @@ hipError_t launch_clear(NzSample *desc, const int32_t *list, int32_t nsamp, int3
 // is preferred where the samples are enough and the counters fit.
 hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first, int32_t count, int32_t N, uint8_t *ws,
                        NzState *state, bool by_xcd, int32_t max_nb, hipStream_t st);
-int32_t keys_sites_per_block();
 
 // Bulk connected components for the samples listed in list[0..nlist), whose
 // prefill lists hold max_sites sites at most.
