@@ -1108,9 +1108,8 @@ int check_batch_fits(const nz_job *jobs, int32_t njobs, const nz_tuning *tune, s
         // in one chunk) plus the largest single sample of any job, planned as
         // the engine plans it
         std::vector<std::pair<uint32_t, int32_t>> tables;
-        size_t tab_entries = 0, largest = 0;
+        size_t tab_entries = 0;
         int64_t total = 0;
-        int32_t worst = -1;
         for (int j = 0; j < njobs; ++j) {
             const nz_job &J = jobs[j];
             if (J.nsamples <= 0) continue;
@@ -1120,28 +1119,38 @@ int check_batch_fits(const nz_job *jobs, int32_t njobs, const nz_tuning *tune, s
                 tables.push_back(key);
                 tab_entries += zone_rows(J.zone_mask).size();
             }
-            Plan p{};
-            p.L = J.L;
-            p.mask = J.zone_mask;
-            p.n0 = J.n0 > 0 ? J.n0 : 0;
-            p.backoff = J.backoff;
-            p.per = J.boundary == NZ_PERIODIC;
-            p.wrap = p.per;
-            const int64_t N = pow5(J.L);
-            p.band_hi = J.band_hi > 0 ? std::min<int64_t>(J.band_hi, N) : default_band_hi(J.L, J.zone_mask, p.n0);
-            if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
-            p.prefix_mul = 1;
-            const size_t b = smallest_bytes(p, t.bucket_log2);
-            if (b > largest) {
-                largest = b;
-                worst = j;
-            }
         }
-        if (worst < 0) return NZ_OK;
-        const size_t need = header_bytes(tab_entries, static_cast<int32_t>(std::min<int64_t>(total, kMaxChunk))) + largest;
-        if (need > ws_bytes)
-            return fail(NZ_EWORKSPACE, "job %d (L = %d) needs %zu bytes for one sample; the buffer holds %zu",
-                        worst, jobs[worst].L, need, ws_bytes);
+        if (total == 0) return NZ_OK;
+        const size_t head = header_bytes(tab_entries, static_cast<int32_t>(std::min<int64_t>(total, kMaxChunk)));
+        // with every prefill as it is, and if that does not fit in the smallest form
+        for (bool smallest : {false, true}) {
+            size_t largest = 0;
+            int32_t worst = -1;
+            for (int j = 0; j < njobs; ++j) {
+                const nz_job &J = jobs[j];
+                if (J.nsamples <= 0) continue;
+                Plan p{};
+                p.L = J.L;
+                p.mask = J.zone_mask;
+                p.n0 = J.n0 > 0 ? J.n0 : 0;
+                p.backoff = J.backoff;
+                p.per = J.boundary == NZ_PERIODIC;
+                p.wrap = p.per;
+                const int64_t N = pow5(J.L);
+                p.band_hi = J.band_hi > 0 ? std::min<int64_t>(J.band_hi, N) : default_band_hi(J.L, J.zone_mask, p.n0);
+                if (p.band_hi <= p.n0) p.band_hi = std::min<int64_t>(N, p.n0 + 4096);
+                p.prefix_mul = 1;
+                const size_t b = smallest ? smallest_bytes(p, t.bucket_log2) : plan_sizes(p, t.bucket_log2).total;
+                if (b > largest) {
+                    largest = b;
+                    worst = j;
+                }
+            }
+            if (head + largest <= ws_bytes) return NZ_OK;
+            if (smallest)
+                return fail(NZ_EWORKSPACE, "job %d (L = %d) needs %zu bytes for one sample; the buffer holds %zu",
+                            worst, jobs[worst].L, head + largest, ws_bytes);
+        }
     } catch (...) {
         return fail(NZ_ENOMEM, "host allocation failed while sizing the batch");
     }
