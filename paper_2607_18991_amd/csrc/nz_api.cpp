@@ -1659,37 +1659,50 @@ NZ_API int nz_smax_window(int32_t L, uint32_t zone_mask, int32_t boundary, uint6
 // later term of it can change a sum.  Terms below 1e-300 are dropped.  The
 // ratios of eight steps are formed together (their divisions overlap); the
 // product runs through them one by one, in the same order as step by step.
-template <typename Term, typename Done>
+// UNROLL: so are the products and terms (the window convolution's 7% faster, the
+// canonical one's steps, which search, 7% slower).
+template <bool UNROLL, typename Term, typename Done>
 void binomial_walk(int64_t N, double p, int64_t mode, Term &&term, Done &&done)
 {
     const double up = p / (1.0 - p);
     double r[8];
     double w = 1.0;
+    // step(k) for k = 0 .. m - 1, while it says so
+    const auto steps = [&](int m, auto &&step) {
+        if constexpr (UNROLL) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (k == m) return true;
+                if (!step(k)) return false;
+            }
+        } else {
+            for (int k = 0; k < m; ++k)
+                if (!step(k)) return false;
+        }
+        return true;
+    };
     for (int64_t n = mode; n < N; n += 8) {
         const int m = static_cast<int>(std::min<int64_t>(8, N - n));
         for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(N - n - k) / static_cast<double>(n + k + 1) * up;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (k == m) break;
+        const bool on = steps(m, [&](int k) {
             w *= r[k];
-            if (w < 1e-300) goto down;
+            if (w < 1e-300) return false;
             term(n + k + 1, w, true);
-        }
-        if (done(n + m, w, true)) break;
+            return true;
+        });
+        if (!on || done(n + m, w, true)) break;
     }
-down:
     w = 1.0;
     for (int64_t n = mode; n > 0; n -= 8) {
         const int m = static_cast<int>(std::min<int64_t>(8, n));
         for (int k = 0; k < 8; ++k) r[k] = static_cast<double>(n - k) / static_cast<double>(N - n + k + 1) / up;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (k == m) break;
+        const bool on = steps(m, [&](int k) {
             w *= r[k];
-            if (w < 1e-300) return;
+            if (w < 1e-300) return false;
             term(n - k - 1, w, false);
-        }
-        if (done(n - m, w, false)) return;
+            return true;
+        });
+        if (!on || done(n - m, w, false)) return;
     }
 }
 
@@ -1728,7 +1741,7 @@ NZ_API int nz_convolve_window(const double *Q, int64_t n_lo, int64_t n_hi, int64
         const bool inside = mode >= n_lo && mode < n_hi;
         double sw = 1.0, swq = inside ? Q[mode - n_lo] : 0.0, swin = inside ? 1.0 : 0.0;
         if (p > 0.0 && p < 1.0)
-            binomial_walk(
+            binomial_walk<true>(
                 N, p, mode,
                 [&](int64_t n, double w, bool) {
                     sw += w;
@@ -1933,7 +1946,7 @@ NZ_API int nz_canonical(const uint64_t *hist, int64_t hist_len, const double *p_
     // f_mode = F(mode), F_at(n, upward) = F(n), none_below(n): F = 0 below n
     const auto convolve = [&](double p, int64_t mode, double f_mode, auto &&F_at, auto &&none_below) {
         double sw = 1.0, swf = f_mode;
-        binomial_walk(
+        binomial_walk<false>(
             N, p, mode,
             [&](int64_t n, double w, bool upward) {
                 sw += w;
