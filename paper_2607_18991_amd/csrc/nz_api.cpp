@@ -416,11 +416,13 @@ int keys_class(const Sizes &s)
 
 // Samples whose prefill lists hold like numbers of sites (within a factor of
 // four) are labelled by one launch: its grid has as many workgroups per sample
-// as the largest needs, and in one launch over lists of 2000 and 150000 sites
-// most workgroups would find nothing to do.  An empty workgroup costs some 4 ns,
-// a group's three launches some 20 us (the L = 12 periodic batch of 700 samples:
-// 2.03 ms in groups, 1.75 in one launch), so a class joins the group before it
-// unless that adds more than kEmptyWgs empty workgroups.
+// as the first list needs, that of the samples that come first in the queue
+// (7 compact neighbourhoods x 1000 of L = 8 1.39 ms; as the mean list needs 1.44,
+// as the longest 1.48; longer ones take more passes), and in one launch over lists
+// of 2000 and 150000 sites most workgroups would find nothing to do.  An empty
+// workgroup costs some 4 ns, a group's three launches some 20 us (the L = 12
+// periodic batch of 700 samples: 2.03 ms in groups, 1.75 in one launch), so a class
+// joins the group before it unless that adds more than kEmptyWgs empty workgroups.
 constexpr int64_t kEmptyWgs = 4096;
 int prefill_group(int32_t prefix_cap)
 {
@@ -844,6 +846,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             if (nlist > 0) {
                 for (size_t g = 0; g < pre.size();) {
                     const bool map = hook_map(parts[pre[g]]);
+                    const int32_t grid = parts[pre[g]].s.prefix_cap;
                     int32_t count = 0, map_N = 0, most = 0;
                     size_t e = g;
                     while (e < pre.size() && hook_map(parts[pre[e]]) == map) {
@@ -858,14 +861,14 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                             largest = std::max(largest, parts[pre[c]].s.prefix_cap);
                             samples += parts[pre[c++]].count;
                         }
-                        const int64_t empty = static_cast<int64_t>(samples) * (most - largest) / 1024;
+                        const int64_t empty = static_cast<int64_t>(samples) * (grid - parts[pre[e]].s.prefix_cap) / 1024;
                         if (e > g && empty > kEmptyWgs) break;
                         most = std::max(most, largest);
                         count += samples;
                         if (map) map_N = std::max(map_N, N);
                         e = c;
                     }
-                    HIP_TRY(nz::launch_prefill(d_desc, d_list + parts[pre[g]].list0, count, most, d_tabs, ws, d_state,
+                    HIP_TRY(nz::launch_prefill(d_desc, d_list + parts[pre[g]].list0, count, most, grid, d_tabs, ws, d_state,
                                                smax != nullptr, wrap_chunk, per_chunk, map_N, dev.cus, st, prefill_events()));
                     g = e;
                 }
@@ -904,7 +907,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                         HIP_TRY(nz::launch_keys(d_desc, d_list, a, e.second, e.first, ws, d_state, false, 0, st));
                         a += e.second;
                     }
-                    HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, d_tabs, ws, d_state, smax != nullptr,
+                    HIP_TRY(nz::launch_prefill(d_desc, d_list, na, max_prefix, max_prefix, d_tabs, ws, d_state, smax != nullptr,
                                                wrap_chunk, per_chunk, map_N, dev.cus, st, prefill_events()));
                     // (`again` stays untouched until the copy has been read: the next
                     // pass synchronises first, and so does the end of the chunk)

@@ -2817,7 +2817,7 @@ bool hook_map_fits(int64_t N, int64_t n0)
 }
 
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
-                          const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
+                          int32_t grid_sites, const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
                           int32_t map_N, int cus, hipStream_t st, hipEvent_t *ev)
 {
     if (nlist <= 0) return hipSuccess;
@@ -2825,9 +2825,9 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
     // (few partly filled edge buffers) down to 256 of a small one (more waves in
     // flight): zone 1 at L = 16 (150000 sites) 3.78 / 3.23 / 3.08 ms for 1000
     // samples with 256 / 1024 / 2048, zones 1-7 (2000 sites) 0.46 / 0.57 / 0.62
-    const int64_t per_wg = std::max<int64_t>(256, std::min<int64_t>(2048, max_sites / 16 / 256 * 256));
-    const int32_t bx_hook = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (max_sites + per_wg - 1) / per_wg)));
-    const int32_t bx_site = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (max_sites + 1023) / 1024)));
+    const int64_t per_wg = std::max<int64_t>(256, std::min<int64_t>(2048, grid_sites / 16 / 256 * 256));
+    const int32_t bx_hook = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (grid_sites + per_wg - 1) / per_wg)));
+    const int32_t bx_site = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(1024, (grid_sites + 1023) / 1024)));
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], st);
     };
@@ -2853,8 +2853,8 @@ hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nli
         if (e != hipSuccess) return e;
         const uint32_t words = std::min(kHookMapWords, ((static_cast<uint32_t>(map_N) - 1u) >> 5) + 1u + MAP_PAD);
         // a few workgroups per CU over all samples, of up to 1024 sites each
-        const int32_t nt = static_cast<int32_t>(std::max(64, std::min(1024, (max_sites + 63) / 64 * 64)));
-        const int32_t most = std::max(1, (max_sites + nt - 1) / nt);
+        const int32_t nt = static_cast<int32_t>(std::max(64, std::min(1024, (grid_sites + 63) / 64 * 64)));
+        const int32_t most = std::max(1, (grid_sites + nt - 1) / nt);
         const int32_t bx = std::max(1, std::min(most, 4 * cus / nlist));
         hipLaunchKernelGGL(k, dim3(static_cast<uint32_t>(bx) * slots8), dim3(static_cast<uint32_t>(nt)), words * 4u, st, desc, list,
                            nlist, bx, words, tabs, ws, state);

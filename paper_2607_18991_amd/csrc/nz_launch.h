@@ -27,7 +27,8 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
                        NzState *state, bool by_xcd, int32_t max_nb, hipStream_t st);
 
 // Bulk connected components for the samples listed in list[0..nlist), whose
-// prefill lists hold max_sites sites at most.
+// prefill lists hold max_sites sites at most.  The grids are sized for lists of
+// grid_sites: longer ones take more passes.
 // smax: also the largest cluster of each smax-mode sample's prefilled state.
 // wrap: the listed samples are periodic first-wrap samples (64-bit entries).
 // periodic: the listed samples have periodic coordinates (all or none of them).
@@ -36,7 +37,7 @@ hipError_t launch_keys(const NzSample *desc, const int32_t *list, int32_t first,
 // separate expand pass).
 bool hook_map_fits(int64_t N, int64_t n0);
 hipError_t launch_prefill(const NzSample *desc, const int32_t *list, int32_t nlist, int32_t max_sites,
-                          const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
+                          int32_t grid_sites, const NzOffset *tabs, uint8_t *ws, NzState *state, bool smax, bool wrap, bool periodic,
                           int32_t map_N, int cus, hipStream_t st, hipEvent_t *ev = nullptr);
 
 // out[0..w) += sum over the chunk's finished samples 0..nsamp-1 of their S_max windows.
