@@ -1245,13 +1245,14 @@ NZ_API int nz_last_batch_timing(double ms[6])
 // latency of labelling and sweep; a batch that also holds wider ones runs the two
 // groups side by side (the wide group on a second host thread and stream), so that
 // one group's sweep and host round trips overlap the other's keys and labelling.
-// Each group gets its own share of the workspace.  7 compact neighbourhoods,
-// prefilled, side by side / as one group: L = 16 x 1000 20.4 / 21.5 ms, L = 24 x 200
-// 33.3 / 34.2, L = 8 1.73 / 1.89; plain L = 16 40.3 / 40.4.
+// Each group gets its own share of the workspace.  7 compact neighbourhoods, side
+// by side / as one group: prefilled L = 16 x 1000 17.7 / 19.0 ms, L = 24 x 200
+// 31.0 / 32.2, L = 8 x 1000 1.41 / 1.44; plain, where zone 1's sweep is most of a
+// batch, it gives nothing: 33.7 / 33.5, 80.0 / 78.5 and 1.28 / 1.25.
 
 constexpr int64_t kSplitMinSamples = 256;   // on both sides
 // widest neighbourhood of the first group (L = 16, 7 compact x 1000, prefilled:
-// z <= 10 18.1 ms, 64 17.8, 130 17.8, 242 17.8, 340 18.2)
+// z <= 10 17.9 ms, 64 17.5, 130 17.5, 242 17.8, 340 18.2)
 constexpr int32_t kSplitZ = 64;
 
 struct SplitPlan {
