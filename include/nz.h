@@ -271,8 +271,9 @@ int nz_last_batch_job_stats(int64_t *serial, int64_t *prefilled, int32_t njobs);
 /* Phase timing of nz_sweep_batch with HIP events recorded on the caller's
  * stream around each group of launches.  nz_set_timing(1) turns it on for later
  * calls on the calling thread (0 turns it off).  nz_last_batch_timing fills
- * ms[0..5]: milliseconds in keys (with clearing), bulk connected components,
- * 0 (there is no separate sort pass), sweep, the whole call, and ms[5] = number of sweep launches. */
+ * ms[0..5]: milliseconds in keys (with clearing, without the wait of one group
+ * for the other's keys), bulk connected components, 0 (there is no separate sort
+ * pass), sweep, the whole call, and ms[5] = number of sweep launches. */
 int nz_set_timing(int enable);
 int nz_last_batch_timing(double ms[6]);
 

@@ -60,9 +60,10 @@ struct PrefillEvents {
     }
 };
 
-// Events bracketing the phases of one chunk (keys, prefill, sweep).
+// Events bracketing the phases of one chunk: clearing (0, 1), keys (2, 3), prefill
+// (3, 4), sweep (4, 5).  Between 1 and 2 a group may wait for the other's keys.
 struct PhaseEvents {
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    hipEvent_t ev[6] = {};
     bool ok = false;
     PhaseEvents()
     {
@@ -826,7 +827,9 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             };
             if (pe) HIP_TRY(hipEventRecord(pe->ev[0], st));
             HIP_TRY(nz::launch_clear(d_desc, nullptr, n, 0, ws, d_state, st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[1], st));
             if (turn) HIP_TRY(turn->before(st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[2], st));
             for (int32_t a = 0; a < np;) {
                 const Part &first = parts[order[a]];
                 const int cls = keys_class(first.s);
@@ -840,7 +843,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                 a = b;
             }
             if (turn) HIP_TRY(turn->after(st));
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[1], st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));
             std::vector<NzState> state(n);
             std::vector<uint8_t> level(n, 0);   // in-chunk backoffs of every sample
             if (nlist > 0) {
@@ -914,7 +917,7 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
                     lists.push_back(std::move(again));
                 }
             }
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[2], st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[4], st));
 
             {
                 // The LDS residencies are accepted where the state they name fits a
@@ -943,17 +946,20 @@ int run_batch(const nz_job *jobs, int32_t njobs, uint8_t *ws, size_t ws_bytes, i
             if (smax)
                 HIP_TRY(nz::launch_winsum(d_desc, d_state, n, static_cast<int32_t>(smax->win_hi - smax->win_lo), ws,
                                           smax->d_out, st));
-            if (pe) HIP_TRY(hipEventRecord(pe->ev[3], st));
+            if (pe) HIP_TRY(hipEventRecord(pe->ev[5], st));
 
             // ---- read back and schedule the redo of unfinished samples
             HIP_TRY(hipMemcpyAsync(state.data(), d_state, n * sizeof(NzState), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
             lists.clear();
             if (pe) {
-                for (int k = 0; k < 3; ++k) {
+                // (g_ms[2]: the sweep orders its own blocks, there is no sort pass)
+                constexpr int phase[5] = {0, -1, 0, 1, 3};
+                for (int k = 0; k < 5; ++k) {
+                    if (phase[k] < 0) continue;
                     float ms = 0.0f;
                     HIP_TRY(hipEventElapsedTime(&ms, pe->ev[k], pe->ev[k + 1]));
-                    g_ms[k < 2 ? k : 3] += ms;   // ([2]: the sweep orders its own blocks, there is no sort pass)
+                    g_ms[phase[k]] += ms;
                 }
                 g_ms[5] += 1.0;
             }

@@ -2,7 +2,8 @@
 // host code (compiled without its kernels) so that the host side can be tested
 // without a GPU: device memory is host memory, copies are memcpy, and a launch is
 // only recorded, with the dynamic LDS it asks for and the limit its function has
-// at that moment.  A launch of the sweep marks every sample of its queue as done.
+// at that moment.  Streams have clocks: a launch takes a millisecond, waiting for an
+// event a second, and events hold their stream's time.  A launch of the sweep marks every sample of its queue as done.
 // Allocations of the host code are counted and can be made to fail.
 #include <hip/hip_runtime.h>
 #include <malloc.h>
@@ -35,6 +36,8 @@ std::map<const void *, std::string> &names()
 }
 std::map<const void *, size_t> g_limits;
 std::map<void *, size_t> g_blocks;
+std::map<hipStream_t, float> g_clock;
+std::map<hipEvent_t, float> g_events;
 std::vector<Launch> g_launches;
 int64_t g_mallocs = 0, g_frees = 0, g_streams = 0;
 void *g_bad_stream = nullptr;   // copies on it fail
@@ -137,6 +140,7 @@ FAKE hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t l
     std::lock_guard<std::mutex> g(g_lock);
     const std::string &name = names()[f];
     const auto it = g_limits.find(f);
+    g_clock[st] += 1.0f;
     g_launches.push_back({name, lds, it == g_limits.end() ? 65536 : it->second, st});
     if (name.find("nz_sweep_kernel") != std::string::npos) {
         const NzSweepArgs &a = *static_cast<const NzSweepArgs *>(args[0]);
@@ -227,18 +231,30 @@ FAKE hipError_t hipStreamCreateWithFlags(hipStream_t *st, unsigned)
     return hipSuccess;
 }
 FAKE hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-FAKE hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+FAKE hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t, unsigned)
+{
+    std::lock_guard<std::mutex> g(g_lock);
+    g_clock[st] += 1000.0f;
+    return hipSuccess;
+}
 FAKE hipError_t hipEventCreate(hipEvent_t *e)
 {
-    *e = reinterpret_cast<hipEvent_t>(static_cast<uintptr_t>(0x2000));
+    static std::atomic<uintptr_t> next{0x2000};
+    *e = reinterpret_cast<hipEvent_t>(next++);
     return hipSuccess;
 }
 FAKE hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 FAKE hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-FAKE hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-FAKE hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-FAKE hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t)
+FAKE hipError_t hipEventRecord(hipEvent_t e, hipStream_t st)
 {
-    *ms = 0.0f;
+    std::lock_guard<std::mutex> g(g_lock);
+    g_events[e] = g_clock[st];
+    return hipSuccess;
+}
+FAKE hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+FAKE hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)
+{
+    std::lock_guard<std::mutex> g(g_lock);
+    *ms = g_events[b] - g_events[a];
     return hipSuccess;
 }

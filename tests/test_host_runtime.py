@@ -267,3 +267,27 @@ def test_the_static_buffer_holds_one_sample_of_L36(lib, mask):
     assert lib.nz_sweep_batch_static(arr, n, _ptr(out), None, None, None, None) == 0, lib.nz_last_error()
     arr[0].L = 37
     assert lib.nz_sweep_batch_static(arr, n, _ptr(out), None, None, None, None) == nz.NZ_EWORKSPACE
+
+
+def test_the_keys_phase_holds_no_wait_for_the_other_group(lib):
+    """The second group's keys wait for the first one's: that time is in the whole call,
+    not in the milliseconds of the keys."""
+    from paper_2607_18991_amd import nz
+
+    arr, n = nz.make_jobs([dict(L=6, zone_mask=m, seed=1, nsamples=300) for m in (0x01, 0x7F)])
+    need = ctypes.c_size_t()
+    assert lib.nz_batch_workspace_bytes(arr, n, None, ctypes.byref(need)) == 0
+    ws, space = aligned(need.value)
+    out = np.zeros(600, dtype=np.int32)
+    ms = (ctypes.c_double * 6)()
+    lib.nz_set_timing(1)
+    try:
+        assert lib.nz_sweep_batch(arr, n, ws, need.value, _ptr(out), None, None, None, ctypes.c_void_p(0x77)) == 0
+        assert lib.nz_last_batch_timing(ms) == 0
+    finally:
+        lib.nz_set_timing(0)
+    keys, labelling, sort, sweep, _, launches = list(ms)
+    assert launches == 2
+    # per group: clearing and one keys launch, nothing to label, one sweep
+    assert (keys, labelling, sort, sweep) == (4.0, 0.0, 0.0, 2.0)
+    del space
